@@ -17,6 +17,16 @@ constexpr int kWave = 64;
 __device__ __forceinline__ uint32_t f2u(float x) { return __float_as_uint(x); }
 __device__ __forceinline__ float u2f(uint32_t x) { return __uint_as_float(x); }
 
+// Largest magnitude of four floats (as two instructions: fmaxf of fabsf also quiets signaling NaNs, which costs two
+// more).  With a NaN among them the result is unspecified.
+__device__ __forceinline__ float max_abs4(const float (&x)[4])
+{
+    float m;
+    asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(m) : "v"(x[0]), "v"(x[1]), "v"(x[2]));
+    asm("v_max_f32 %0, %1, |%2|" : "=v"(m) : "v"(m), "v"(x[3]));
+    return m;
+}
+
 // ---------------------------------------------------------------- rounding draws
 //
 // One 24-bit uniform integer per coordinate.  Per bucket the 64-bit mixer below turns
@@ -436,43 +446,136 @@ __device__ __forceinline__ bool table_round_up(uint32_t u, double lo, double hi,
     return up;
 }
 
-// Level|sign bytes of four coordinates whose first has in-bucket index idx0 (+ k0), for the bucket whose edges
-// e_t = l_t * ||v|| lie in LDS (e1 = edges[1]).  Called by whole waves: the first-bin route is chosen per wave.
-__device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_t counter0, uint32_t k1,
-                                                        const double *edges, double e1, uint32_t s, bool dead)
+// Level|sign bytes of four coordinates from their level indices (one per byte) and the coordinates (signs kept where
+// the level is not zero; a level is below 128).
+__device__ __forceinline__ uint32_t join_signs(const float (&xs)[4], uint32_t levels)
 {
-    const float xs[4] = {x.x, x.y, x.z, x.w};
-    const float big = fmaxf(fmaxf(fabsf(xs[0]), fabsf(xs[1])), fmaxf(fabsf(xs[2]), fabsf(xs[3])));
-    uint32_t levels = 0;
-    if (!dead) {
-        if (__all(!((double)big >= e1))) {          // every coordinate of every lane below the first level
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t u = draw24((counter0 + (uint32_t)c) * kRngC1, k1);
-                const double a = (double)fabsf(xs[c]);
-                levels |= (table_round_up(u, 0.0, e1, a) ? 1u : 0u) << (8 * c);
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t u = draw24((counter0 + (uint32_t)c) * kRngC1, k1);
-                const double a = (double)fabsf(xs[c]);
-                uint32_t j = 0;
-                for (uint32_t t = 1; t <= s + 1u; ++t)
-                    j += edges[t] <= a ? 1u : 0u;   // the levels increase: the count is the largest index
-                if (j <= s) {
-                    j += table_round_up(u, edges[j], edges[j + 1u], a) ? 1u : 0u;
-                }
-                levels |= j << (8 * c);
-            }
-        }
-    }
-    // sign bytes of the four coordinates, kept where the level is not zero (a level is below 128)
     const uint32_t v01 = __builtin_amdgcn_perm(f2u(xs[1]), f2u(xs[0]), 0x0c0c0703u);
     const uint32_t v23 = __builtin_amdgcn_perm(f2u(xs[3]), f2u(xs[2]), 0x0c0c0703u);
     const uint32_t sg = __builtin_amdgcn_perm(v23, v01, 0x05040100u);
     const uint32_t nz7 = (levels + 0x7f7f7f7fu) & 0x80808080u;
     return (sg & nz7) | levels;
+}
+
+// A bucket's level table, in LDS, filled by fill_table_bins.
+struct TableBins {
+    double edge[16];   // e_t = l_t * ||v||, exact
+    float2 bin[16];    // bin j: (E_j, w_j) = fp32 roundings of e_j and (e_{j+1} - e_j) 2^-24; the top level's: never up
+    float thr[16];     // thr[t], t >= 1: the smallest fp32 value at or above e_t (a >= thr[t] iff a >= e_t for fp32 a);
+                       // thr[0]: 1 if every w_j is far from the subnormals, so that the fp32 test below may be used
+};
+
+// Called by the first 16 threads of a team (t = thread in team) before a team barrier.  thr[0] is a vote among the 16
+// lanes of that DPP row.
+__device__ __forceinline__ void fill_table_bins(TableBins &B, const LevelTable &T, float norm, uint32_t s, uint32_t t)
+{
+    const double e = (double)T.lev[t] * (double)norm, next = (double)T.lev[min(t + 1u, 15u)] * (double)norm;
+    const float lo = (float)e;
+    const float w = t <= s ? (float)((next - e) * 0x1p-24) : 0.0f;
+    const uint64_t far = __ballot(t > s || w >= 0x1p-100f);
+    const uint32_t row = (threadIdx.x & (kWave - 1)) & ~(uint32_t)(kRow - 1);
+    B.edge[t] = e;
+    B.bin[t] = float2{t <= s ? lo : 0x1.fffffep127f, w};
+    B.thr[t] = t ? ((double)lo < e ? u2f(f2u(lo) + 1u) : lo) : ((uint16_t)(far >> row) == 0xffffu ? 1.0f : 0.0f);
+}
+
+// Level|sign bytes of four coordinates (in-bucket index of the first = counter0 - k0) by the fp64 rule.  Called by
+// whole waves: the first-bin route is chosen per wave.
+__device__ __forceinline__ uint32_t quantize_table_vec4_exact(const float4 &x, uint32_t counter0, uint32_t k1,
+                                                              const double *edges, double e1, uint32_t s)
+{
+    const float xs[4] = {x.x, x.y, x.z, x.w};
+    const float big = fmaxf(fmaxf(fabsf(xs[0]), fabsf(xs[1])), fmaxf(fabsf(xs[2]), fabsf(xs[3])));
+    uint32_t levels = 0;
+    if (__all(!((double)big >= e1))) {          // every coordinate of every lane below the first level
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const uint32_t u = draw24((counter0 + (uint32_t)c) * kRngC1, k1);
+            const double a = (double)fabsf(xs[c]);
+            levels |= (table_round_up(u, 0.0, e1, a) ? 1u : 0u) << (8 * c);
+        }
+    } else {
+#pragma unroll 1
+        for (int c = 0; c < 4; ++c) {
+            const float xc = c == 0 ? xs[0] : c == 1 ? xs[1] : c == 2 ? xs[2] : xs[3];
+            const uint32_t u = draw24((counter0 + (uint32_t)c) * kRngC1, k1);
+            const double a = (double)fabsf(xc);
+            uint32_t j = 0;
+            for (uint32_t t = 1; t <= s + 1u; ++t)
+                j += edges[t] <= a ? 1u : 0u;   // the levels increase: the count is the largest index
+            if (j <= s)
+                j += table_round_up(u, edges[j], edges[j + 1u], a) ? 1u : 0u;
+            levels |= j << (8 * c);
+        }
+    }
+    return join_signs(xs, levels);
+}
+
+// The same in fp32 arithmetic that knows its own error.  The bin is exact (thr).  With x = fl(a - E_j) and
+// t = fma(u, w_j, -x) the sign of t is the decision of the real-number rule unless |t| <= 2^-21 a: each of E_j, w_j and
+// x carries a relative error of at most 2^-24, so t is off by at most 2^-24 (u w_j + |a - E_j| + e_j) before its own
+// rounding, which keeps the sign; where u w_j < 2 a that is at most 2^-22 a, and where u w_j >= 2 a, t is at least a.
+// A row of the wave in which some coordinate is that close (a bin of relative width r: one coordinate in r 2^20) sets
+// `redo` and is to be decided again by the fp64 rule, as is every row of a bucket whose bins reach the subnormals
+// (thr[0] = 0: the caller's business).
+// What it is for: the kernels around it are bound by vector issue, and the fp64 rule is twice as long.  QSGDinf at 4 bits,
+// eight gradients of 25.6 M coordinates, quantize + pack + unpack: 350 us with the fp64 rule throughout, 270 us with this.
+struct TableRule {
+    const TableBins *bins;
+    float thr1, w0;      // first threshold, first bin's width
+    float thr_lane;      // lane l of a wave holds thr[l mod 16] (teams of a wave or more)
+    uint32_t s;
+};
+
+template <int TEAM>
+__device__ __forceinline__ TableRule make_table_rule(const TableBins &B, uint32_t s)
+{
+    return TableRule{&B, team_uniform_f32<TEAM>(B.thr[1]), team_uniform_f32<TEAM>(B.bin[0].y), B.thr[threadIdx.x & 15u], s};
+}
+
+template <int TEAM>
+__device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_t x0, uint32_t k1, const TableRule &R,
+                                                        bool &redo)
+{
+    const float xs[4] = {x.x, x.y, x.z, x.w};
+    float u[4], t[4], near = 0x1p127f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+        u[c] = (float)draw24(x0 + (uint32_t)c * kRngC1, k1);
+    uint32_t levels = 0;
+    if (__all(max_abs4(xs) < R.thr1)) {                          // every coordinate of every lane below the first level
+        uint32_t tb[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            t[c] = __builtin_fmaf(u[c], R.w0, -fabsf(xs[c]));
+            tb[c] = f2u(t[c]);
+            near = fminf(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
+        }
+        const uint32_t t01 = __builtin_amdgcn_perm(tb[1], tb[0], 0x0c0c0703u);
+        const uint32_t t23 = __builtin_amdgcn_perm(tb[3], tb[2], 0x0c0c0703u);
+        levels = (__builtin_amdgcn_perm(t23, t01, 0x05040100u) & 0x80808080u) >> 7;
+    } else {
+        uint32_t j[4] = {0, 0, 0, 0};
+        for (uint32_t l = 1; l <= R.s + 1u; ++l) {
+            float f;
+            if constexpr (TEAM >= (int)kWave)
+                f = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(R.thr_lane), (int)l));
+            else
+                f = R.bins->thr[l];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                j[c] += fabsf(xs[c]) >= f ? 1u : 0u;
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float2 b = R.bins->bin[j[c]];
+            t[c] = __builtin_fmaf(u[c], b.y, b.x - fabsf(xs[c]));
+            near = fminf(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
+            levels |= (j[c] + (t[c] < 0.0f ? 1u : 0u)) << (8 * c);
+        }
+    }
+    redo = __any(!(near > 0.0f));
+    return join_signs(xs, levels);
 }
 
 }  // namespace nuq

@@ -760,8 +760,8 @@ __device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &
                                                             const LevelTable &T, uint64_t b, bool active, uint64_t base,
                                                             uint32_t nbk, uint32_t tid, uint32_t *qb32, uint32_t *scratch)
 {
-    __shared__ double edges_all[TeamGeom<TEAM>::kTeamsPerWG][16];
-    double *edges = edges_all[threadIdx.x / TEAM];
+    __shared__ TableBins bins_all[TeamGeom<TEAM>::kTeamsPerWG];
+    TableBins &bins = bins_all[threadIdx.x / TEAM];
     const float *vb = W.v + base;
     const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
     float4 x[VPT];
@@ -797,16 +797,31 @@ __device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &
     }
     const bool dead = !(nrm > 0.0f) || !finite;
     if (tid < 16u)
-        edges[tid] = (double)T.lev[tid] * (double)nrm;
+        fill_table_bins(bins, T, nrm, P.s, tid);
     team_barrier<TEAM>();
-    const double e1 = edges[1];
     const BucketKey key = bucket_key(W.seed, b);
+    const TableRule R = make_table_rule<TEAM>(bins, P.s);
+    const bool all_exact = !dead && bins.thr[0] == 0.0f;
+    uint32_t redo = 0;                                     // rows to be decided again by the fp64 rule
+    const uint32_t x0 = (key.k0 + 4u * tid) * kRngC1;      // row i starts 4 * TEAM * i coordinates further on
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
         if ((uint32_t)i < P.rows) {
-            const uint32_t vi = (uint32_t)i * TEAM + tid;
-            qb32[vi] = quantize_table_vec4(x[i], key.k0 + 4u * vi, key.k1, edges, e1, P.s, dead);
+            bool again;
+            const uint32_t q =
+                quantize_table_vec4<TEAM>(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, R, again);
+            qb32[(uint32_t)i * TEAM + tid] = dead ? 0u : q;
+            redo |= (again ? 1u : 0u) << i;
         }
+    }
+    if (__any(all_exact))
+        redo = (1u << P.rows) - 1u;
+    while (redo) {                                         // uniform over the wave; the coordinates are loaded again
+        const uint32_t vi = (uint32_t)__builtin_ctz(redo) * TEAM + tid;
+        redo &= redo - 1u;
+        const uint32_t q = quantize_table_vec4_exact(load_vec4(vb, vi, nbk, aligned), key.k0 + 4u * vi, key.k1,
+                                                     bins.edge, bins.edge[1], P.s);
+        qb32[vi] = dead ? 0u : q;
     }
 }
 

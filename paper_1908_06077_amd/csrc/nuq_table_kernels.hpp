@@ -38,11 +38,11 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_bucket_norms_linf(Encod
 template <int TEAM, int VPT>
 __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize_table(EncodeParams P, EncodeBatch Wk, LevelTable T)
 {
-    __shared__ double edges_all[TeamGeom<TEAM>::kTeamsPerWG][16];
+    __shared__ TableBins bins_all[TeamGeom<TEAM>::kTeamsPerWG];
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
     const uint32_t team = threadIdx.x / TEAM;
-    double *edges = edges_all[team];
+    TableBins &bins = bins_all[team];
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + team;
     const bool active = b < P.nb;
     const uint64_t base = active ? b * P.bucket : 0;
@@ -54,17 +54,22 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize_table(EncodePa
     const float nf = active ? W.norms_in[b] : 0.0f;
     const bool dead = !(nf > 0.0f) || !(nf < __builtin_huge_valf());
     if (tid < 16u)
-        edges[tid] = (double)T.lev[tid] * (double)nf;
+        fill_table_bins(bins, T, nf, P.s, tid);
     team_barrier<TEAM>();
-    const double e1 = edges[1];
     const BucketKey key = bucket_key(W.seed, b);
+    const TableRule R = make_table_rule<TEAM>(bins, P.s);
+    const bool exact = __any(!dead && bins.thr[0] == 0.0f);
 #pragma unroll 1
     for (uint32_t i = 0; i < P.rows; ++i) {
         const uint32_t vi = i * TEAM + tid;
         const uint32_t e0 = 4u * vi;
         const bool mine = e0 < nbk;                     // lanes beyond the bucket's end run along with zeros
         const float4 x = mine ? load_vec4(vb, vi, nbk, aligned) : float4{0.f, 0.f, 0.f, 0.f};
-        const uint32_t packed = quantize_table_vec4(x, key.k0 + e0, key.k1, edges, e1, P.s, dead);
+        bool again;
+        uint32_t packed = quantize_table_vec4<TEAM>(x, (key.k0 + e0) * kRngC1, key.k1, R, again);
+        if (exact || again)
+            packed = quantize_table_vec4_exact(x, key.k0 + e0, key.k1, bins.edge, bins.edge[1], P.s);
+        packed = dead ? 0u : packed;
         if (mine) {
             if (qaligned && e0 + 3u < nbk) {
                 reinterpret_cast<uint32_t *>(qb)[vi] = packed;

@@ -1,0 +1,66 @@
+"""The level-table quantizer's fp32 rule where it can go wrong, bit for bit against the oracle's real-number rule:
+coordinates planted on, one unit above and one unit below their own rounding threshold (the rule must notice that it
+cannot tell and hand them to the fp64 rule), coordinates on the levels themselves, buckets whose bins reach the subnormals
+(fp64 rule throughout), and level tables whose lowest bins are tiny.  One size per shape of thread team, with short last
+buckets."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import gpu_util
+    return gpu_util
+
+
+CASES = [
+    # (d, bucket, kind, s, p, norm)
+    (3_001, 512, "uniform", 3, 0.0, 1.0),
+    (3_001, 300, "exp", 7, 0.3, 3e-7),
+    (9_001, 2048, "exp", 14, 0.05, 2.5),
+    (9_001, 1000, "uniform", 14, 0.0, 7e33),
+    (30_001, 8192, "uniform", 3, 0.0, 0.37),
+    (30_001, 8192, "exp", 14, 0.01, 1e-20),
+    (40_001, 16384, "exp", 1, 0.9, 1.0),
+    (70_001, 32768, "uniform", 6, 0.0, 1e-3),
+    (9_001, 2048, "uniform", 3, 0.0, 1e-36),
+    (3_001, 512, "exp", 4, 0.3, 1e-40),
+]
+
+
+@pytest.mark.parametrize("d,n,kind,s,p,norm", CASES)
+def test_planted_near_ties(g, d, n, kind, s, p, norm):
+    nuq = g.nuq
+    lev = workloads.level_table(kind, s, p) if kind == "uniform" else [0.0] + [float(np.float32(p ** (s + 1 - j))) for j in range(1, s + 2)]
+    rng = np.random.default_rng(d + n + s)
+    seed, B = int(rng.integers(1 << 60)), oracle.num_buckets(d, n)
+    N = np.float32(norm)
+    u = oracle.rng_fill(seed, d, n).astype(np.float64)
+    e = np.array(lev, dtype=np.float32).astype(np.float64) * float(N)
+    j = rng.integers(0, s + 1, d)
+    tie = (e[j] + u * (e[j + 1] - e[j]) * 2.0 ** -24).astype(np.float32)
+    v = np.where(rng.random(d) < 0.1, e[j].astype(np.float32), tie)
+    ulp = rng.integers(-1, 2, d)
+    v = np.where(ulp > 0, np.nextafter(v, np.float32(np.inf)), np.where(ulp < 0, np.nextafter(v, np.float32(0)), v))
+    v = (np.minimum(v, N) * rng.choice([-1.0, 1.0], d)).astype(np.float32)
+    v[::n] = N                                        # the maximum norm of every bucket is N
+    norms_np = np.full(B, N, dtype=np.float32)
+    want = oracle.quantize_table(v, n, lev, seed, norms_np)
+    vt = torch.from_numpy(v).to(g.DEV)
+    q = torch.full((d,), 0x7F, dtype=torch.uint8, device=g.DEV)
+    nuq.nuq_quantize_table(vt, n, lev, seed, torch.from_numpy(norms_np).to(g.DEV), q)
+    np.testing.assert_array_equal(q.cpu().numpy(), want)
+    # the fused front (its rows are decided in registers, the doubtful ones again from memory), as fixed-width codes
+    b = 5
+    norms = torch.empty(B, dtype=torch.float32, device=g.DEV)
+    packed = torch.full((nuq.nuq_fixed_words(d, n, b),), -1, dtype=torch.int32, device=g.DEV)
+    nuq.nuq_quantize_pack_fixed_table_batch([vt], n, lev, nuq.NORM_LINF, b, [seed], [norms], [packed])
+    np.testing.assert_array_equal(norms.cpu().numpy(), norms_np)
+    np.testing.assert_array_equal(g.u32(packed), oracle.pack_fixed(want, n, s, b))
+    assert nuq.nuq_last_error_flags() == 0
