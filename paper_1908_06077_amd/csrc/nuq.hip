@@ -352,6 +352,17 @@ int pack_fixed_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t buc
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
+        if (b == 4 || b == 8) {             // codes go from registers to memory
+            dim3 grid;
+            if (!bucket_grid<TEAM>(P.nb, K, grid))
+                return (int)NUQ_EINVAL;
+            ScopedTiming timing(MODE == 1 ? NUQ_T_ENCODE : NUQ_T_QUANTIZE_ENCODE, st);
+            if (b == 4)
+                hipLaunchKernelGGL((k_pack_fixed_direct<TEAM, VPT, MODE, 4>), grid, dim3(G::kWG), 0, st, P, Wk, F, T);
+            else
+                hipLaunchKernelGGL((k_pack_fixed_direct<TEAM, VPT, MODE, 8>), grid, dim3(G::kWG), 0, st, P, Wk, F, T);
+            return check_launch();
+        }
         P.lds_words = fixed_lds_words(P.rows, TEAM, F.wpb);
         const size_t lds_bytes = (size_t)P.lds_words * 4 * G::kTeamsPerWG;
         if (lds_bytes > 160 * 1024)

@@ -683,11 +683,11 @@ __host__ __device__ inline uint32_t team_lds_words(uint32_t rows, uint32_t team,
 }
 
 // Front of the fused kernels: the bucket's coordinates into registers (v is read once), its norm (written to
-// norms_out), the quantizer, level|sign bytes into the team's LDS words qb32[rows * TEAM].
-template <int TEAM, int VPT>
-__device__ __forceinline__ void front_quantize_to_lds(const EncodeParams &P, const EncodeWorker &W, uint64_t b,
-                                                      bool active, uint64_t base, uint32_t nbk, uint32_t tid,
-                                                      uint32_t *qb32, uint32_t *scratch)
+// norms_out), the quantizer; put(i, word) takes the level|sign bytes of the thread's row i < P.rows (coordinates
+// 4 * (i * TEAM + tid) .. + 3), rows in ascending order.
+template <int TEAM, int VPT, class Put>
+__device__ __forceinline__ void front_quantize(const EncodeParams &P, const EncodeWorker &W, uint64_t b, bool active,
+                                               uint64_t base, uint32_t nbk, uint32_t tid, uint32_t *scratch, Put put)
 {
     const float *vb = W.v + base;
     const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
@@ -724,22 +724,33 @@ __device__ __forceinline__ void front_quantize_to_lds(const EncodeParams &P, con
     const uint32_t x0 = (key.k0 + 4u * tid) * kRngC1;      // row i starts 4 * TEAM * i coordinates further on
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
-        if ((uint32_t)i < P.rows) {
-            const uint32_t vi = (uint32_t)i * TEAM + tid;
-            qb32[vi] = B.dead ? 0u : quantize_vec4(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, B);
-        }
+        if ((uint32_t)i < P.rows)
+            put(i, B.dead ? 0u : quantize_vec4(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, B));
     }
 }
 
-// Front of the kernels that start from level|sign bytes: q_in into the team's LDS words.
-template <int TEAM>
-__device__ __forceinline__ void front_bytes_to_lds(const EncodeParams &P, const EncodeWorker &W, uint64_t base,
-                                                   uint32_t nbk, uint32_t tid, uint32_t *qb32)
+// The same with the bytes into the team's LDS words qb32[rows * TEAM].
+template <int TEAM, int VPT>
+__device__ __forceinline__ void front_quantize_to_lds(const EncodeParams &P, const EncodeWorker &W, uint64_t b,
+                                                      bool active, uint64_t base, uint32_t nbk, uint32_t tid,
+                                                      uint32_t *qb32, uint32_t *scratch)
+{
+    front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, scratch,
+                              [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
+}
+
+// Front of the kernels that start from level|sign bytes: put(i, word) as for front_quantize, the bytes from q_in.
+template <int TEAM, int VPT, class Put>
+__device__ __forceinline__ void front_bytes(const EncodeParams &P, const EncodeWorker &W, uint64_t base, uint32_t nbk,
+                                            uint32_t tid, Put put)
 {
     const uint8_t *qg = W.q_in + base;
     const bool aligned = (reinterpret_cast<uintptr_t>(qg) & 3u) == 0;
-    for (uint32_t i = 0; i < P.rows; ++i) {
-        const uint32_t vi = i * TEAM + tid;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        if ((uint32_t)i >= P.rows)
+            break;
+        const uint32_t vi = (uint32_t)i * TEAM + tid;
         const uint32_t e0 = 4u * vi;
         uint32_t word = 0;
         if (aligned && e0 + 3u < nbk) {
@@ -749,16 +760,25 @@ __device__ __forceinline__ void front_bytes_to_lds(const EncodeParams &P, const 
                 if (e0 + c < nbk)
                     word |= (uint32_t)qg[e0 + c] << (8u * c);
         }
-        qb32[vi] = word;
+        put(i, word);
     }
 }
 
-// Front of the fused kernels for an arbitrary level table T and the norm P.norm_linf selects: as
-// front_quantize_to_lds, with quantize_table_vec4 on the bucket's edges l_t * ||v|| (kept in LDS).
 template <int TEAM, int VPT>
-__device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &P, const EncodeWorker &W,
-                                                            const LevelTable &T, uint64_t b, bool active, uint64_t base,
-                                                            uint32_t nbk, uint32_t tid, uint32_t *qb32, uint32_t *scratch)
+__device__ __forceinline__ void front_bytes_to_lds(const EncodeParams &P, const EncodeWorker &W, uint64_t base,
+                                                   uint32_t nbk, uint32_t tid, uint32_t *qb32)
+{
+    front_bytes<TEAM, VPT>(P, W, base, nbk, tid,
+                           [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
+}
+
+// Front of the fused kernels for an arbitrary level table T and the norm P.norm_linf selects: as front_quantize, with
+// quantize_table_vec4 on the bucket's bins (kept in LDS).  put may be called a second time for a row (a row decided
+// again): the last call counts.
+template <int TEAM, int VPT, class Put>
+__device__ __forceinline__ void front_quantize_table(const EncodeParams &P, const EncodeWorker &W, const LevelTable &T,
+                                                     uint64_t b, bool active, uint64_t base, uint32_t nbk,
+                                                     uint32_t tid, uint32_t *scratch, Put put)
 {
     __shared__ TableBins bins_all[TeamGeom<TEAM>::kTeamsPerWG];
     TableBins &bins = bins_all[threadIdx.x / TEAM];
@@ -810,19 +830,29 @@ __device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &
             bool again;
             const uint32_t q =
                 quantize_table_vec4<TEAM>(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, R, again);
-            qb32[(uint32_t)i * TEAM + tid] = dead ? 0u : q;
+            put(i, dead ? 0u : q);
             redo |= (again ? 1u : 0u) << i;
         }
     }
     if (__any(all_exact))
         redo = (1u << P.rows) - 1u;
     while (redo) {                                         // uniform over the wave; the coordinates are loaded again
-        const uint32_t vi = (uint32_t)__builtin_ctz(redo) * TEAM + tid;
+        const int i = __builtin_ctz(redo);
         redo &= redo - 1u;
+        const uint32_t vi = (uint32_t)i * TEAM + tid;
         const uint32_t q = quantize_table_vec4_exact(load_vec4(vb, vi, nbk, aligned), key.k0 + 4u * vi, key.k1,
                                                      bins.edge, bins.edge[1], P.s);
-        qb32[vi] = dead ? 0u : q;
+        put(i, dead ? 0u : q);
     }
+}
+
+template <int TEAM, int VPT>
+__device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &P, const EncodeWorker &W,
+                                                            const LevelTable &T, uint64_t b, bool active, uint64_t base,
+                                                            uint32_t nbk, uint32_t tid, uint32_t *qb32, uint32_t *scratch)
+{
+    front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, scratch,
+                                    [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
 }
 
 // MODE 0: fused norms + quantize + encode from v.  MODE 1: encode from level/sign bytes.  MODE 2: as 0 for the level
@@ -859,7 +889,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
     } else if constexpr (MODE == 0) {
         front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch);
     } else {
-        front_bytes_to_lds<TEAM>(P, W, base, nbk, tid, qb32);
+        front_bytes_to_lds<TEAM, VPT>(P, W, base, nbk, tid, qb32);
     }
     __syncthreads();
     encode_from_lds<TEAM, VPT>(P, W, active, b, qb32, out, rec, erc_lut, tail_lut, sync_l, blk, run_off, scratch);

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_pack_fixed(EncodeParams
     else if constexpr (MODE == 0)
         front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch);
     else
-        front_bytes_to_lds<TEAM>(P, W, base, nbk, tid, qb32);
+        front_bytes_to_lds<TEAM, VPT>(P, W, base, nbk, tid, qb32);
     __syncthreads();
 
     // Each thread packs a contiguous chunk of rows * 4 coordinates.  Codes are shifted into a 64-bit register and
@@ -80,6 +80,72 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_pack_fixed(EncodeParams
         uint32_t *dst = W.words + b * F.wpb;
         for (uint32_t i = tid; i < F.wpb; i += TEAM)
             dst[i] = field[i];
+    }
+}
+
+// ---- 4 and 8 bits: no LDS phase ----------------------------------------------------------------------------------
+// At these widths the four coordinates that a thread holds of a row are a whole piece of the field: at 8 bits its word,
+// at 4 bits half a word whose other half is its neighbour's.  So the codes go from registers to memory: 4 bytes per lane
+// and row, whole 256-byte runs per wave (at 4 bits two rows share an instruction: even lanes store their pair's word of
+// the first row, odd lanes that of the second).  Through LDS (k_pack_fixed: bytes out, contiguous chunks in, field OR-ed
+// together, field out, two barriers) the same codes cost 8 instructions per coordinate more.  Eight gradients of 25.6 M
+// coordinates at 4 bits: QSGDinf (bound by vector issue) 269 -> 226 us with the unpack; the main scheme's pack stays at
+// 147 us = 6.3 TB/s, what a bare kernel that reads as much and writes an eighth of it reaches.
+
+// The four level|sign bytes of a word as four 4-bit codes (sign << 3 | level, level <= 7), the first on top.
+__device__ __forceinline__ uint32_t nibble_codes(uint32_t bytes)
+{
+    const uint32_t n = ((bytes >> 4) & 0x08080808u) | (bytes & 0x07070707u);
+    const uint32_t hi = __builtin_amdgcn_udot4(n, 0x00000110u, 0u, false);      // n0 << 4 | n1
+    return __builtin_amdgcn_udot4(n, 0x01100000u, hi << 8, false);              // ... | n2 << 4 | n3
+}
+
+// MODE as k_pack_fixed; B = 4 or 8.
+template <int TEAM, int VPT, int MODE, int B>
+__global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_pack_fixed_direct(EncodeParams P, EncodeBatch Wk, FixedParams F,
+                                                                           LevelTable T)
+{
+    static_assert(B == 4 || B == 8, "codes of a thread's row must be whole halfwords");
+    __shared__ __align__(8) uint32_t scratch_all[TeamGeom<TEAM>::kTeamsPerWG][64];
+    const EncodeWorker &W = Wk.w[blockIdx.y];
+    const uint32_t tid = threadIdx.x % TEAM;
+    const uint32_t team = team_uniform_u32<TEAM>(threadIdx.x / TEAM);
+    uint32_t *scratch = scratch_all[team];
+    const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + team;
+    const bool active = b < P.nb;
+    const uint64_t base = active ? b * P.bucket : 0;
+    const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
+    uint32_t *const dst = W.words + (active ? b : 0) * F.wpb;
+    const uint32_t words = active ? F.wpb : 0u;             // words of the field that exist
+    const uint32_t odd = tid & 1u;
+    uint32_t codes[B == 4 ? VPT : 1] = {};
+    auto put = [&](int i, uint32_t bytes) {
+        if constexpr (B == 8) {
+            const uint32_t w = (uint32_t)i * TEAM + tid;
+            if (w < words)
+                dst[w] = __builtin_bswap32(bytes);          // level|sign bytes are the codes; the first one goes on top
+        } else {
+            codes[i] = nibble_codes(bytes);
+        }
+    };
+    if constexpr (MODE == 2)
+        front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, scratch, put);
+    else if constexpr (MODE == 0)
+        front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, scratch, put);
+    else
+        front_bytes<TEAM, VPT>(P, W, base, nbk, tid, put);
+    if constexpr (B == 4) {
+#pragma unroll
+        for (int i = 0; i < VPT; i += 2) {
+            if ((uint32_t)i < P.rows) {
+                const uint32_t own = codes[i] | (codes[i + 1] << 16);
+                const uint32_t other = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xf, 0xf, true);   // lane ^ 1
+                const uint32_t word = odd ? (other & 0xffff0000u) | (own >> 16) : (own << 16) | (other & 0xffffu);
+                const uint32_t w = ((uint32_t)(i + (int)odd) * TEAM + tid) >> 1;
+                if (w < words)
+                    dst[w] = word;
+            }
+        }
     }
 }
 

@@ -274,7 +274,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_emit(EncodePara
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
     __shared__ uint32_t enc[256];
     huffman_byte_table<TeamGeom<TEAM>::kWG>(H, enc);
-    front_bytes_to_lds<TEAM>(P, W, base, nbk, tid, qb32);
+    front_bytes_to_lds<TEAM, VPT>(P, W, base, nbk, tid, qb32);
     __syncthreads();
 
     const uint32_t total = huffman_from_lds<TEAM>(P, enc, qb32, field, sync_l, scratch, nbk, tid);
