@@ -928,7 +928,28 @@ static int unpack_accumulate_fixed_any(uint32_t K, const float *const *norms, co
     P.scale = scale;
     P.accumulate = accumulate;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool wide = bucket % 32u == 0 && (reinterpret_cast<uintptr_t>(out) & 15u) == 0;
+    const bool aligned_out = (reinterpret_cast<uintptr_t>(out) & 15u) == 0;
+    if ((b == 4u || b == 8u) && bucket % (32u / b) == 0 && aligned_out) {
+        // whole words per bucket, and the value tables of the buckets a workgroup can touch fit in 16 KB
+        const uint32_t span = unpack_direct_coords(b);
+        const uint64_t nb = nuq_num_buckets(d, bucket);
+        const bool tiled = span % bucket == 0 || bucket % span == 0;
+        const uint64_t tabs = std::min<uint64_t>(nb, tiled ? std::max(1u, span / bucket) : span / bucket + 2u);
+        const uint64_t lut_bytes = tabs * K * fixed_lut_entries(b) * sizeof(double);
+        const uint64_t blocks = (d + span - 1) / span;
+        if (lut_bytes <= 16384u) {
+            if (blocks > 0x7fffffffull)
+                return NUQ_EINVAL;
+            P.lut_tabs = (uint32_t)tabs;
+            const bool one = bucket % (b == 4u ? 512u : 256u) == 0;
+            auto kern = b == 4u ? (one ? k_unpack_accumulate_fixed_direct<4, true> : k_unpack_accumulate_fixed_direct<4, false>)
+                                : (one ? k_unpack_accumulate_fixed_direct<8, true> : k_unpack_accumulate_fixed_direct<8, false>);
+            ScopedTiming timing(NUQ_T_DECODE, st);
+            hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(256), (uint32_t)lut_bytes, st, P);
+            return check_launch();
+        }
+    }
+    const bool wide = bucket % 32u == 0 && aligned_out;
     const uint64_t threads = wide ? (d + 31) / 32 : d;
     const uint64_t blocks = (threads + 255) / 256;
     if (blocks > 0x7fffffffull)
@@ -956,11 +977,12 @@ static int unpack_accumulate_fixed_any(uint32_t K, const float *const *norms, co
     } while (0)
         switch (b) {
         case 3: NUQ_LAUNCH_UNPACK(3); break;
-        case 4: NUQ_LAUNCH_UNPACK(4); break;
         case 5: NUQ_LAUNCH_UNPACK(5); break;
         case 6: NUQ_LAUNCH_UNPACK(6); break;
         case 7: NUQ_LAUNCH_UNPACK(7); break;
-        default: NUQ_LAUNCH_UNPACK(8); break;
+        // the tables of 4- and 8-bit codes did not fit above, and this kernel's workgroups touch no fewer buckets
+        case 4: hipLaunchKernelGGL((k_unpack_accumulate_fixed32<4, false>), grid, dim3(256), 0, st, P); break;
+        default: hipLaunchKernelGGL((k_unpack_accumulate_fixed32<8, false>), grid, dim3(256), 0, st, P); break;
         }
 #undef NUQ_LAUNCH_UNPACK
     }

@@ -181,7 +181,7 @@ __device__ __forceinline__ double fixed_level_value(const UnpackParams &P, doubl
 // of every worker's field (one contiguous load per worker, coalesced over the wave), and the workgroup's 8192 results
 // go through LDS so that the stores are whole lines too.
 //
-// kLut: the value of every code, norm * sign * 2^(level - 1 - s) in fp64 (0 for level 0 and for codes that are not
+// kLut (at 4 and 8 bits k_unpack_accumulate_fixed_direct is the variant with tables): the value of every code, norm * sign * 2^(level - 1 - s) in fp64 (0 for level 0 and for codes that are not
 // valid), is tabulated in LDS once per (bucket the workgroup touches, worker); a code then costs a bit-field extract,
 // an LDS read and an fp64 add instead of the exponent arithmetic.  A table of 16 entries is 128 bytes = all 32 banks
 // once, so lanes that read one table never conflict whatever their codes.  Codes wider than 5 bits index 32 entries
@@ -257,11 +257,6 @@ __global__ __launch_bounds__(256) void k_unpack_accumulate_fixed32(UnpackParams 
             double nrm = 0.0;
             if constexpr (!kLut)
                 nrm = (double)P.norms[k][bk];
-            if constexpr (kLut && 32 % B == 0) {
-#pragma unroll
-                for (int t = 0; t < B; ++t)
-                    bad |= fixed_word_invalid<B>(w[t], P.s);
-            }
 #pragma unroll
             for (int c = 0; c < 32; ++c) {
                 // code c occupies bits [c*B, c*B + B) of the B words, most significant bit first
@@ -272,10 +267,8 @@ __global__ __launch_bounds__(256) void k_unpack_accumulate_fixed32(UnpackParams 
                 else
                     code = ((w[wi] << (off + B - 32)) | (w[wi + 1 < B ? wi + 1 : wi] >> (64 - off - B))) & ((1u << B) - 1u);
                 if constexpr (kLut) {
-                    if constexpr (32 % B != 0) {
-                        const uint32_t level = code & kLevelMask;
-                        bad |= level > P.s + 1u || code == (1u << (B - 1));
-                    }
+                    const uint32_t level = code & kLevelMask;
+                    bad |= level > P.s + 1u || code == (1u << (B - 1));
                     sum[c] += tab[k * kEntries + fixed_lut_index<B>(code)];
                 } else {
                     const uint32_t level = code & kLevelMask, neg = code >> (B - 1);
@@ -319,6 +312,122 @@ __global__ __launch_bounds__(256) void k_unpack_accumulate_fixed32(UnpackParams 
                 P.out[i + c] = P.accumulate ? P.out[i + c] + r[c] : r[c];
         }
     }
+}
+
+// ---- 4 and 8 bits: one word per worker and thread, whole lines out -----------------------------------------------
+// A thread's sums are of whole float4 groups that lie side by side over the wave, so the results leave in full lines
+// without a trip through LDS, and a thread holds 8 (4) fp64 sums instead of 32: eight waves per SIMD instead of three.
+// At 8 bits a word is four coordinates = one group.  At 4 bits it is eight, and a wave's 64 words are two rows of 64
+// groups: even lanes load the words of the first row, odd lanes those of the second, and a lane pair trades halves, after
+// which each lane holds the codes of its group of the first row (top half) and of the second.
+// K = 8, 25.6 M coordinates, 4 bits: 52 us with k_unpack_accumulate_fixed32 (bound by the loads in flight of three waves
+// per SIMD and by LDS), 39 us with this.
+constexpr uint32_t kUnpackIters = 4;
+constexpr uint32_t unpack_direct_coords(uint32_t b) { return kUnpackIters * 256u * (b == 4u ? 8u : 4u); }   // per workgroup
+
+// kOneBucket: what a wave handles at a time (512 or 256 coordinates) never crosses a bucket boundary.
+template <int B, bool kOneBucket>
+__global__ __launch_bounds__(256) void k_unpack_accumulate_fixed_direct(UnpackParams P)
+{
+    static_assert(B == 4 || B == 8, "a word is whole groups of four codes");
+    extern __shared__ __align__(128) double lut[];            // [lut_tabs][K][entries], as in k_unpack_accumulate_fixed32
+    constexpr uint32_t kEntries = fixed_lut_entries(B);
+    constexpr uint32_t kGroups = B == 4 ? 2u : 1u;            // float4 groups per lane and iteration
+    constexpr uint32_t kWaveCoords = 256u * kGroups;
+    const uint32_t lane = threadIdx.x & (kWave - 1u), wave = uniform_u32(threadIdx.x / kWave);
+    const uint64_t wg0 = (uint64_t)blockIdx.x * unpack_direct_coords(B);
+    auto bucket_of = [&](uint64_t i) { return P.d <= 0xffffffffull ? (uint64_t)((uint32_t)i / P.bucket) : i / P.bucket; };
+    const uint64_t bk_first = bucket_of(wg0);
+    {
+        const uint64_t nb = (P.d + P.bucket - 1) / P.bucket;
+        const uint32_t total = P.lut_tabs * P.K * kEntries;
+        for (uint32_t e = threadIdx.x; e < total; e += 256u) {
+            const uint32_t idx = e % kEntries, k = (e / kEntries) % P.K, tab = e / (kEntries * P.K);
+            const uint32_t level = B == 4 ? idx & 7u : idx & 15u, neg = B == 4 ? idx >> 3 : idx >> 4;
+            double val = 0.0;
+            if (bk_first + tab < nb && level >= 1u && level <= P.s + 1u) {
+                val = fixed_level_value(P, (double)P.norms[k][bk_first + tab], level);
+                val = neg ? -val : val;
+            }
+            lut[e] = val;
+        }
+        __syncthreads();
+    }
+    const uint32_t wsel = B == 4 ? (lane & 1u) * 32u + (lane >> 1) : lane;       // which of the wave's words this lane loads
+    const uint32_t swap = lane & 1u ? 0x05040100u : 0x03020706u;                 // halves of (other lane's, own)
+    const double sc = (double)P.scale;
+    bool bad = false;
+#pragma unroll 1
+    for (uint32_t it = 0; it < kUnpackIters; ++it) {
+        const uint64_t c_wave = wg0 + (uint64_t)(it * 4u + wave) * kWaveCoords;
+        if (c_wave >= P.d)
+            break;
+        const uint64_t c_word = c_wave + wsel * (32u / B);    // first coordinate of this lane's word
+        const bool live = c_word < P.d;
+        uint64_t word;
+        uint32_t tab[kGroups];                                // LDS index of the table of (bucket of group, worker 0)
+        if constexpr (kOneBucket) {
+            const uint64_t bk = bucket_of(c_wave);
+            word = bk * P.wpb + (uint32_t)(c_word - bk * P.bucket) / (32u / B);
+#pragma unroll
+            for (uint32_t g = 0; g < kGroups; ++g)
+                tab[g] = (uint32_t)(bk - bk_first) * P.K * kEntries;
+        } else {
+            const uint64_t bk = bucket_of(c_word);
+            word = bk * P.wpb + (uint32_t)(c_word - bk * P.bucket) / (32u / B);
+#pragma unroll
+            for (uint32_t g = 0; g < kGroups; ++g)            // (a group beyond the end: any table inside)
+                tab[g] = (uint32_t)(bucket_of(min(c_wave + 256u * g + 4u * lane, P.d - 1u)) - bk_first) * P.K * kEntries;
+        }
+        double sum[4 * kGroups];
+#pragma unroll
+        for (uint32_t c = 0; c < 4u * kGroups; ++c)
+            sum[c] = 0.0;
+        for (uint32_t k0 = 0; k0 < P.K; k0 += 8u) {
+            uint32_t w[8];
+#pragma unroll
+            for (uint32_t q = 0; q < 8u; ++q) {
+                w[q] = 0u;
+                if (k0 + q < P.K && live)
+                    w[q] = P.packed[k0 + q][word];
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < 8u; ++q) {
+                if (k0 + q >= P.K)                            // uniform
+                    break;
+                bad |= fixed_word_invalid<B>(w[q], P.s);
+                uint32_t x = w[q];
+                if constexpr (B == 4)
+                    x = __builtin_amdgcn_perm((uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true), x, swap);
+#pragma unroll
+                for (uint32_t c = 0; c < 4u * kGroups; ++c) {
+                    const uint32_t code = (x >> (32u - B - c * B)) & ((1u << B) - 1u);
+                    sum[c] += lut[tab[c / 4u] + (k0 + q) * kEntries + fixed_lut_index<B>(code)];
+                }
+            }
+        }
+#pragma unroll
+        for (uint32_t g = 0; g < kGroups; ++g) {
+            const uint64_t i = c_wave + 256u * g + 4u * lane;
+            float4 o{(float)(sc * sum[4 * g]), (float)(sc * sum[4 * g + 1]), (float)(sc * sum[4 * g + 2]),
+                     (float)(sc * sum[4 * g + 3])};
+            if (i + 3u < P.d) {
+                float4 *const dst = reinterpret_cast<float4 *>(P.out + i);
+                if (P.accumulate) {
+                    const float4 prev = *dst;
+                    *dst = float4{o.x + prev.x, o.y + prev.y, o.z + prev.z, o.w + prev.w};
+                } else {
+                    store_once4(dst, o);
+                }
+            } else {
+                const float r[4] = {o.x, o.y, o.z, o.w};
+                for (uint32_t c = 0; c < 4u && i + c < P.d; ++c)
+                    P.out[i + c] = P.accumulate ? P.out[i + c] + r[c] : r[c];
+            }
+        }
+    }
+    if (bad)
+        atomicOr(P.flags, kFlagMalformed);
 }
 
 // Any bucket size: one coordinate per thread.
