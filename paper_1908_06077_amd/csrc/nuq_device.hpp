@@ -52,7 +52,7 @@ __device__ __forceinline__ BucketKey bucket_key(uint64_t seed, uint64_t bucket_i
 // x = (k0 + index) * C1 on entry.
 __device__ __forceinline__ uint32_t draw24(uint32_t x, uint32_t k1)
 {
-    x = x ^ (x >> 15) ^ k1;
+    x = __builtin_amdgcn_bitop3_b32(x, x >> 15, k1, 0x96);   // x ^ (x >> 15) ^ k1 in one instruction
     x *= kRngC2;
     x ^= x >> 16;
     return x >> 8;

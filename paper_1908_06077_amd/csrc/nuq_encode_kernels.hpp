@@ -68,10 +68,16 @@ struct TeamGeom {
 // staged bit strings, lengths and messages, which the next kernel reads, out of the caches.  Used by teams of a
 // wave or more (measured: 172 -> 164 us on 8192-coordinate buckets, 3 % on 16384); quarter-wave teams, whose loads
 // are 256-byte pieces, lose 5 % with it and keep plain loads.
-__device__ __forceinline__ float4 load_once4(const float4 *p)
+// Both loads take any 4-byte aligned address: the hardware does not ask for more, only the C++ types do.
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load_once4(const float *p)
 {
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    const f32x4 r = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(p));
+    const f32x4_any r = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(p));
+    return float4{r.x, r.y, r.z, r.w};
+}
+__device__ __forceinline__ float4 load4(const float *p)
+{
+    const f32x4_any r = *reinterpret_cast<const f32x4_any *>(p);
     return float4{r.x, r.y, r.z, r.w};
 }
 
@@ -84,24 +90,70 @@ __device__ __forceinline__ void store_once4(float4 *p, float4 v)
 }
 
 // Load the four coordinates of vector `vi` of a bucket of `nbk` coordinates starting at `vb`.
-__device__ __forceinline__ float4 load_vec4(const float *vb, uint32_t vi, uint32_t nbk, bool aligned)
+__device__ __forceinline__ float4 load_vec4(const float *vb, uint32_t vi, uint32_t nbk)
 {
     const uint32_t e0 = 4u * vi;
-    if (aligned && e0 + 3u < nbk)
-        return reinterpret_cast<const float4 *>(vb)[vi];
-    float4 r;
-    r.x = e0 + 0u < nbk ? vb[e0 + 0u] : 0.0f;
-    r.y = e0 + 1u < nbk ? vb[e0 + 1u] : 0.0f;
-    r.z = e0 + 2u < nbk ? vb[e0 + 2u] : 0.0f;
-    r.w = e0 + 3u < nbk ? vb[e0 + 3u] : 0.0f;
+    if (e0 + 3u < nbk)
+        return load4(vb + e0);
+    float4 r{0.0f, 0.0f, 0.0f, 0.0f};
+    if (e0 < nbk) {
+        r.x = vb[e0];
+        r.y = e0 + 1u < nbk ? vb[e0 + 1u] : 0.0f;
+        r.z = e0 + 2u < nbk ? vb[e0 + 2u] : 0.0f;
+    }
     return r;
 }
 
-// Bucket norm from a per-row accessor.  fp32 partial sums (four accumulators per thread),
-// fp64 across the team; if the fp32 result could have lost range (tiny or huge sums) the
-// whole sum is redone in fp64.  Every thread of the team returns the same value.
+// A bucket's rows into registers.  wg_base: the workgroup's first bucket (uniform), lane_off: coordinates from there to
+// the team's bucket.  The addresses of a full bucket are a uniform base per row (scalar registers; the empty asm keeps
+// the compiler from folding the row into the lanes' 64-bit addresses, two instructions per row and lane) plus one 32-bit
+// lane offset.
+template <int TEAM, int VPT>
+__device__ __forceinline__ void load_rows(float4 (&x)[VPT], const float *wg_base, uint32_t lane_off, uint32_t nbk,
+                                          uint32_t rows, uint32_t tid)
+{
+    if (__all(nbk == (uint32_t)VPT * TEAM * 4u)) {       // full buckets that fill every row
+        const uint32_t off = 4u * (lane_off + 4u * tid);                           // bytes, below 2^18
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            const char *row = reinterpret_cast<const char *>(wg_base + i * (4 * TEAM));
+            if constexpr (TEAM >= 64) {
+                asm("" : "+s"(row));
+                x[i] = load_once4(reinterpret_cast<const float *>(row + off));
+            } else {
+                x[i] = load4(reinterpret_cast<const float *>(row + off));
+            }
+        }
+    } else {
+        const float *vb = wg_base + lane_off;
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            x[i] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+            if ((uint32_t)i < rows)
+                x[i] = load_vec4(vb, (uint32_t)i * TEAM + tid, nbk);
+        }
+    }
+}
+
+// sqrt(t) in fp64, correctly rounded, for t in [2^-80, 2^100]: what sqrt() does without its scaling for extreme arguments.
+__device__ __forceinline__ double sqrt_mid(double t)
+{
+    const double y = __builtin_amdgcn_rsq(t);
+    double g = t * y, h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, t), h, g);
+    return __builtin_fma(__builtin_fma(-g, g, t), h, g);
+}
+
+// Bucket norm from a per-row accessor.  fp32 partial sums (four accumulators per thread), fp64 across the team; if the
+// fp32 result could have lost range (tiny or huge sums) the whole sum is redone in fp64.  Every thread of the team
+// returns the same value.  A team of several waves leaves the fp64 part to its first wave (the others wait): done by
+// every wave for itself, as it was, it was 1.5 of the encoder's 26 vector instructions per coordinate.
+// lds: TEAM floats and scratch: 16 doubles of LDS (teams of several waves), free until the second barrier inside.
 template <int TEAM, int VPT, class Row>
-__device__ __forceinline__ float team_norm(Row row, double *scratch)
+__device__ __forceinline__ float team_norm(Row row, float *lds, double *scratch)
 {
     float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
 #pragma unroll
@@ -112,8 +164,33 @@ __device__ __forceinline__ float team_norm(Row row, double *scratch)
         a2 = __builtin_fmaf(x.z, x.z, a2);
         a3 = __builtin_fmaf(x.w, x.w, a3);
     }
-    double tot = team_sum_f64<TEAM>((double)((a0 + a1) + (a2 + a3)), scratch);
-    if (!(tot >= 0x1p-80 && tot <= 0x1p100)) {   // also catches NaN
+    const float part = (a0 + a1) + (a2 + a3);
+    double tot;
+    float norm;
+    bool fine;
+    if constexpr (TEAM > kWave) {
+        const uint32_t tid = threadIdx.x % TEAM;
+        lds[tid] = part;
+        __syncthreads();
+        if (tid < (uint32_t)kWave) {
+            tot = (double)lds[tid];
+#pragma unroll
+            for (int w = 1; w < TEAM / kWave; ++w)
+                tot += (double)lds[tid + w * kWave];
+            tot = wave_sum_f64(tot);
+            fine = tot >= 0x1p-80 && tot <= 0x1p100;
+            if (tid == 0)
+                reinterpret_cast<float *>(scratch)[0] = fine ? (float)sqrt_mid(tot) : -1.0f;
+        }
+        __syncthreads();
+        norm = uniform_f32(reinterpret_cast<const float *>(scratch)[0]);
+        fine = norm >= 0.0f;
+    } else {
+        tot = team_sum_f64<TEAM>((double)part, scratch);
+        fine = tot >= 0x1p-80 && tot <= 0x1p100;
+        norm = (float)sqrt_mid(tot);
+    }
+    if (!fine) {                 // (a NaN comes here too)
         double p = 0.0;
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
@@ -123,9 +200,9 @@ __device__ __forceinline__ float team_norm(Row row, double *scratch)
             p += (double)x.z * (double)x.z;
             p += (double)x.w * (double)x.w;
         }
-        tot = team_sum_f64<TEAM>(p, scratch);
+        norm = (float)sqrt(team_sum_f64<TEAM>(p, scratch));
     }
-    return (float)sqrt(tot);
+    return norm;
 }
 
 // ------------------------------------------------------------------ norms kernel
@@ -133,6 +210,7 @@ template <int TEAM, int VPT>
 __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_bucket_norms(EncodeParams P, EncodeBatch Wk)
 {
     __shared__ double scratch[16];
+    __shared__ float part[TEAM > kWave ? TEAM : 1];
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + threadIdx.x / TEAM;
@@ -140,11 +218,34 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_bucket_norms(EncodePara
     const uint64_t base = active ? b * P.bucket : 0;
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
     const float *vb = W.v + base;
-    const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
-    auto row = [&](int i) { return load_vec4(vb, (uint32_t)i * TEAM + tid, nbk, aligned); };
-    const float nrm = team_norm<TEAM, VPT>(row, scratch);
+    auto row = [&](int i) { return load_vec4(vb, (uint32_t)i * TEAM + tid, nbk); };
+    const float nrm = team_norm<TEAM, VPT>(row, part, scratch);
     if (active && tid == 0)
         W.norms_out[b] = nrm;
+}
+
+// Top bytes of four words, one per result byte.
+__device__ __forceinline__ uint32_t top_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
+{
+    const uint32_t w01 = __builtin_amdgcn_perm(w1, w0, 0x0c0c0703u);
+    const uint32_t w23 = __builtin_amdgcn_perm(w3, w2, 0x0c0c0703u);
+    return __builtin_amdgcn_perm(w23, w01, 0x05040100u);
+}
+__device__ __forceinline__ uint32_t top_bytes(const float (&x)[4])
+{
+    return top_bytes(f2u(x[0]), f2u(x[1]), f2u(x[2]), f2u(x[3]));
+}
+
+// Level of one coordinate (any magnitude) for the draw u: |v| is scaled into [ns, 2 ns) by replacing its exponent (its
+// distance to the lower end of its bin, divided by the bin's width in units of c, is then a - ns for every bin), bin index
+// from the difference of the bit patterns.  No branches.
+__device__ __forceinline__ uint32_t quantize_any(float x, float u, const BucketScale &B)
+{
+    const int diff = (int)((f2u(x) & 0x7fffffffu) - B.ns_bits);
+    const int m = diff >> 23;                          // bin: floor(log2(a / ns)), negative below the first level
+    const float a2 = u2f(B.ns_bits + ((uint32_t)diff & 0x007fffffu));
+    const float t = __builtin_fmaf(u, B.c, -(m < 0 ? fabsf(x) : a2 - B.ns));
+    return (uint32_t)min(max(m, -1) + 1 + (t < 0.0f ? 1 : 0), B.s + 1);   // m >= s: the top level, no draw
 }
 
 // Quantize the four coordinates of one vector; returns the four level|sign<<7 bytes.
@@ -153,61 +254,39 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_bucket_norms(EncodePara
 // Three routes, chosen per wave from the largest |v_i| of the vector over all lanes:
 //   below the first level (the usual case: |v_i| < 2^-s ||v||): the level is 0 or 1, "up" is the sign bit of
 //     t = fma(u, c, -|v|), and the bytes are assembled from the top bytes of v (sign) and t (up) with byte permutes;
-//   below twice the first level (s >= 1): bins [0, ns) and [ns, 2 ns) have the same width, so only the bin's lower end
-//     differs per coordinate;
-//   anything else: no branches; |v| is scaled into [ns, 2 ns) by replacing its exponent (its distance to the lower
-//     end of its bin, divided by the bin's width in units of c, is then a - ns for every bin), bin index from the
-//     difference of the bit patterns.
+//   below twice the first level (s >= 1): bins [0, ns) and [ns, 2 ns) have the same width, and u c < ns, so the level is
+//     the number of negative ones among t and t' = fma(u, c, ns - |v|): t is negative whenever |v| >= ns, t' never is
+//     when |v| < ns (ns - |v| is exact where it decides).  Without the selection of a bin per coordinate: 2.5 of 17
+//     instructions less;
+//   anything else: quantize_any.
 __device__ __forceinline__ uint32_t quantize_vec4(const float4 &x, uint32_t x0, uint32_t k1,
                                                   const BucketScale &B)
 {
     const float xs[4] = {x.x, x.y, x.z, x.w};   // already multiplied by B.prescale
-    const float big = fmaxf(fmaxf(fabsf(xs[0]), fabsf(xs[1])), fmaxf(fabsf(xs[2]), fabsf(xs[3])));
-    uint32_t u[4];
+    const float big = max_abs4(xs);
+    float u[4], t[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
-        u[c] = draw24(x0 + (uint32_t)c * kRngC1, k1);
-    if (__all(big < B.ns)) {
-        uint32_t tb[4];
+        u[c] = (float)draw24(x0 + (uint32_t)c * kRngC1, k1);
+    if (__all(big < B.ns2)) {
 #pragma unroll
         for (int c = 0; c < 4; ++c)
-            tb[c] = f2u(__builtin_fmaf((float)u[c], B.c, -fabsf(xs[c])));
-        // top bytes of t0..t3 and of v0..v3, one per result byte
-        const uint32_t t01 = __builtin_amdgcn_perm(tb[1], tb[0], 0x0c0c0703u);
-        const uint32_t t23 = __builtin_amdgcn_perm(tb[3], tb[2], 0x0c0c0703u);
-        const uint32_t v01 = __builtin_amdgcn_perm(f2u(xs[1]), f2u(xs[0]), 0x0c0c0703u);
-        const uint32_t v23 = __builtin_amdgcn_perm(f2u(xs[3]), f2u(xs[2]), 0x0c0c0703u);
-        const uint32_t up7 = __builtin_amdgcn_perm(t23, t01, 0x05040100u) & 0x80808080u;   // bit 7 of byte c = up_c
-        const uint32_t sg = __builtin_amdgcn_perm(v23, v01, 0x05040100u);
-        return (sg & up7) | (up7 >> 7);
+            t[c] = __builtin_fmaf(u[c], B.c, -fabsf(xs[c]));
+        const uint32_t sg = top_bytes(xs), up7 = top_bytes(t) & 0x80808080u;   // bit 7 of byte c: coordinate c is not 0
+        uint32_t levels = up7 >> 7;
+        if (!__all(big < B.ns)) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                t[c] = __builtin_fmaf(u[c], B.c, B.ns - fabsf(xs[c]));
+            levels += (top_bytes(t) >> 7) & 0x01010101u;
+        }
+        return (sg & up7) | levels;
     }
     uint32_t levels = 0;
-    if (B.s >= 1 && __all(big < B.ns2)) {
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float a = fabsf(xs[c]);
-            const float over = a - B.ns;                       // exact when it is used (ns <= a < 2 ns)
-            const bool low = over < 0.0f;
-            const float t = __builtin_fmaf((float)u[c], B.c, -(low ? a : over));
-            levels |= ((low ? 0u : 1u) + (t < 0.0f ? 1u : 0u)) << (8 * c);
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int diff = (int)((f2u(xs[c]) & 0x7fffffffu) - B.ns_bits);
-            const int m = diff >> 23;                          // bin: floor(log2(a / ns)), negative below the first level
-            const float a2 = u2f(B.ns_bits + ((uint32_t)diff & 0x007fffffu));
-            const float t = __builtin_fmaf((float)u[c], B.c, -(m < 0 ? fabsf(xs[c]) : a2 - B.ns));
-            const int j = min(max(m, -1) + 1 + (t < 0.0f ? 1 : 0), B.s + 1);   // m >= s: the top level, no draw
-            levels |= (uint32_t)j << (8 * c);
-        }
-    }
-    // sign bytes of the four coordinates, kept where the level is not zero (a level is below 128)
-    const uint32_t v01 = __builtin_amdgcn_perm(f2u(xs[1]), f2u(xs[0]), 0x0c0c0703u);
-    const uint32_t v23 = __builtin_amdgcn_perm(f2u(xs[3]), f2u(xs[2]), 0x0c0c0703u);
-    const uint32_t sg = __builtin_amdgcn_perm(v23, v01, 0x05040100u);
-    const uint32_t nz7 = (levels + 0x7f7f7f7fu) & 0x80808080u;
-    return (sg & nz7) | levels;
+    for (int c = 0; c < 4; ++c)
+        levels |= quantize_any(xs[c], u[c], B) << (8 * c);
+    return join_signs(xs, levels);
 }
 
 // --------------------------------------------------------------- quantize kernel
@@ -223,7 +302,6 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
     const uint32_t nbk = (uint32_t)min((uint64_t)P.bucket, P.d - base);
     const float *vb = W.v + base;
     uint8_t *qb = W.q_out + base;
-    const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
     const bool qaligned = (reinterpret_cast<uintptr_t>(qb) & 3u) == 0;
     const BucketScale B = make_scale(team_uniform_f32<TEAM>(W.norms_in[b]), (int)P.s);
     const BucketKey key = bucket_key(W.seed, b);
@@ -233,7 +311,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
         const uint32_t e0 = 4u * vi;
         if (e0 >= nbk)
             break;
-        float4 x = load_vec4(vb, vi, nbk, aligned);
+        float4 x = load_vec4(vb, vi, nbk);
         if (B.prescale != 1.0f) {
             x.x *= B.prescale;
             x.y *= B.prescale;
@@ -684,26 +762,18 @@ __host__ __device__ inline uint32_t team_lds_words(uint32_t rows, uint32_t team,
 
 // Front of the fused kernels: the bucket's coordinates into registers (v is read once), its norm (written to
 // norms_out), the quantizer; put(i, word) takes the level|sign bytes of the thread's row i < P.rows (coordinates
-// 4 * (i * TEAM + tid) .. + 3), rows in ascending order.
+// 4 * (i * TEAM + tid) .. + 3), rows in ascending order.  lds: TEAM words per team that put may be the next to write.
 template <int TEAM, int VPT, class Put>
 __device__ __forceinline__ void front_quantize(const EncodeParams &P, const EncodeWorker &W, uint64_t b, bool active,
-                                               uint64_t base, uint32_t nbk, uint32_t tid, uint32_t *scratch, Put put)
+                                               uint64_t base, uint32_t nbk, uint32_t tid, uint32_t *lds,
+                                               uint32_t *scratch, Put put)
 {
-    const float *vb = W.v + base;
-    const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
     float4 x[VPT];
-    if (aligned && nbk == (uint32_t)VPT * TEAM * 4u) {   // a full bucket that fills every row: plain vector loads
-#pragma unroll
-        for (int i = 0; i < VPT; ++i)
-            x[i] = TEAM >= 64 ? load_once4(reinterpret_cast<const float4 *>(vb) + ((uint32_t)i * TEAM + tid))
-                              : reinterpret_cast<const float4 *>(vb)[(uint32_t)i * TEAM + tid];
-    } else {
-#pragma unroll
-        for (int i = 0; i < VPT; ++i)
-            x[i] = load_vec4(vb, (uint32_t)i * TEAM + tid, nbk, aligned);
-    }
+    const uint64_t wg_base = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG * P.bucket;
+    load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid);
     auto row = [&](int i) { return x[i]; };
-    const float nrm = team_uniform_f32<TEAM>(team_norm<TEAM, VPT>(row, reinterpret_cast<double *>(scratch + 32)));
+    const float nrm = team_uniform_f32<TEAM>(
+        team_norm<TEAM, VPT>(row, reinterpret_cast<float *>(lds), reinterpret_cast<double *>(scratch + 32)));
     const bool finite = nrm < __builtin_huge_valf();   // false for NaN too
     if (active && tid == 0) {
         W.norms_out[b] = nrm;
@@ -735,7 +805,7 @@ __device__ __forceinline__ void front_quantize_to_lds(const EncodeParams &P, con
                                                       bool active, uint64_t base, uint32_t nbk, uint32_t tid,
                                                       uint32_t *qb32, uint32_t *scratch)
 {
-    front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, scratch,
+    front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch,
                               [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
 }
 
@@ -778,23 +848,14 @@ __device__ __forceinline__ void front_bytes_to_lds(const EncodeParams &P, const 
 template <int TEAM, int VPT, class Put>
 __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, const EncodeWorker &W, const LevelTable &T,
                                                      uint64_t b, bool active, uint64_t base, uint32_t nbk,
-                                                     uint32_t tid, uint32_t *scratch, Put put)
+                                                     uint32_t tid, uint32_t *lds, uint32_t *scratch, Put put)
 {
     __shared__ TableBins bins_all[TeamGeom<TEAM>::kTeamsPerWG];
     TableBins &bins = bins_all[threadIdx.x / TEAM];
     const float *vb = W.v + base;
-    const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
     float4 x[VPT];
-    if (aligned && nbk == (uint32_t)VPT * TEAM * 4u) {   // a full bucket that fills every row (as in the main front)
-#pragma unroll
-        for (int i = 0; i < VPT; ++i)
-            x[i] = TEAM >= 64 ? load_once4(reinterpret_cast<const float4 *>(vb) + ((uint32_t)i * TEAM + tid))
-                              : reinterpret_cast<const float4 *>(vb)[(uint32_t)i * TEAM + tid];
-    } else {
-#pragma unroll
-        for (int i = 0; i < VPT; ++i)
-            x[i] = load_vec4(vb, (uint32_t)i * TEAM + tid, nbk, aligned);
-    }
+    const uint64_t wg_base = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG * P.bucket;
+    load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid);
     float nrm;
     if (P.norm_linf) {
         uint32_t m = 0;
@@ -806,7 +867,7 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
         nrm = u2f(team_max_u32<TEAM>(m, scratch));
     } else {
         auto row = [&](int i) { return x[i]; };
-        nrm = team_norm<TEAM, VPT>(row, reinterpret_cast<double *>(scratch + 32));
+        nrm = team_norm<TEAM, VPT>(row, reinterpret_cast<float *>(lds), reinterpret_cast<double *>(scratch + 32));
     }
     nrm = team_uniform_f32<TEAM>(nrm);
     const bool finite = nrm < __builtin_huge_valf();   // false for NaN too
@@ -840,7 +901,7 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
         const int i = __builtin_ctz(redo);
         redo &= redo - 1u;
         const uint32_t vi = (uint32_t)i * TEAM + tid;
-        const uint32_t q = quantize_table_vec4_exact(load_vec4(vb, vi, nbk, aligned), key.k0 + 4u * vi, key.k1,
+        const uint32_t q = quantize_table_vec4_exact(load_vec4(vb, vi, nbk), key.k0 + 4u * vi, key.k1,
                                                      bins.edge, bins.edge[1], P.s);
         put(i, dead ? 0u : q);
     }
@@ -851,7 +912,7 @@ __device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &
                                                             const LevelTable &T, uint64_t b, bool active, uint64_t base,
                                                             uint32_t nbk, uint32_t tid, uint32_t *qb32, uint32_t *scratch)
 {
-    front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, scratch,
+    front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, qb32, scratch,
                                     [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
 }
 

@@ -21,11 +21,10 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_bucket_norms_linf(Encod
     const uint64_t base = active ? b * P.bucket : 0;
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
     const float *vb = W.v + base;
-    const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
     uint32_t m = 0;
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
-        const float4 x = load_vec4(vb, (uint32_t)i * TEAM + tid, nbk, aligned);
+        const float4 x = load_vec4(vb, (uint32_t)i * TEAM + tid, nbk);
         m = max(max(m, f2u(x.x) & 0x7fffffffu), f2u(x.y) & 0x7fffffffu);
         m = max(max(m, f2u(x.z) & 0x7fffffffu), f2u(x.w) & 0x7fffffffu);
     }
@@ -49,7 +48,6 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize_table(EncodePa
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
     const float *vb = W.v + base;
     uint8_t *qb = W.q_out + base;
-    const bool aligned = (reinterpret_cast<uintptr_t>(vb) & 15u) == 0;
     const bool qaligned = (reinterpret_cast<uintptr_t>(qb) & 3u) == 0;
     const float nf = active ? W.norms_in[b] : 0.0f;
     const bool dead = !(nf > 0.0f) || !(nf < __builtin_huge_valf());
@@ -64,7 +62,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize_table(EncodePa
         const uint32_t vi = i * TEAM + tid;
         const uint32_t e0 = 4u * vi;
         const bool mine = e0 < nbk;                     // lanes beyond the bucket's end run along with zeros
-        const float4 x = mine ? load_vec4(vb, vi, nbk, aligned) : float4{0.f, 0.f, 0.f, 0.f};
+        const float4 x = mine ? load_vec4(vb, vi, nbk) : float4{0.f, 0.f, 0.f, 0.f};
         bool again;
         uint32_t packed = quantize_table_vec4<TEAM>(x, (key.k0 + e0) * kRngC1, key.k1, R, again);
         if (exact || again)
