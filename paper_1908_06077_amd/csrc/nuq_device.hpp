@@ -27,6 +27,18 @@ __device__ __forceinline__ float max_abs4(const float (&x)[4])
     return m;
 }
 
+// Top bytes of four words, one per result byte.
+__device__ __forceinline__ uint32_t top_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
+{
+    const uint32_t w01 = __builtin_amdgcn_perm(w1, w0, 0x0c0c0703u);
+    const uint32_t w23 = __builtin_amdgcn_perm(w3, w2, 0x0c0c0703u);
+    return __builtin_amdgcn_perm(w23, w01, 0x05040100u);
+}
+__device__ __forceinline__ uint32_t top_bytes(const float (&x)[4])
+{
+    return top_bytes(f2u(x[0]), f2u(x[1]), f2u(x[2]), f2u(x[3]));
+}
+
 // ---------------------------------------------------------------- rounding draws
 //
 // One 24-bit uniform integer per coordinate.  Per bucket the 64-bit mixer below turns
@@ -278,8 +290,9 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v)
     return v;
 }
 
-// Exclusive prefix sum over the team in thread order; `total` receives the team sum.
-template <int TEAM>
+// Exclusive prefix sum over the team in thread order; `total` receives the team sum.  kFence = false: no thread can still
+// be reading what `scratch` held before (a barrier lies between).
+template <int TEAM, bool kFence = true>
 __device__ __forceinline__ uint32_t team_exclusive_sum(uint32_t v, uint32_t *scratch /* TEAM/64 */,
                                                        uint32_t &total)
 {
@@ -300,7 +313,8 @@ __device__ __forceinline__ uint32_t team_exclusive_sum(uint32_t v, uint32_t *scr
     } else {
         constexpr int NW = TEAM / kWave;
         const int wave = (threadIdx.x % TEAM) / kWave;
-        __syncthreads();
+        if constexpr (kFence)
+            __syncthreads();
         if (lane == kWave - 1)
             scratch[wave] = inc;
         __syncthreads();
@@ -446,17 +460,6 @@ __device__ __forceinline__ bool table_round_up(uint32_t u, double lo, double hi,
     return up;
 }
 
-// Level|sign bytes of four coordinates from their level indices (one per byte) and the coordinates (signs kept where
-// the level is not zero; a level is below 128).
-__device__ __forceinline__ uint32_t join_signs(const float (&xs)[4], uint32_t levels)
-{
-    const uint32_t v01 = __builtin_amdgcn_perm(f2u(xs[1]), f2u(xs[0]), 0x0c0c0703u);
-    const uint32_t v23 = __builtin_amdgcn_perm(f2u(xs[3]), f2u(xs[2]), 0x0c0c0703u);
-    const uint32_t sg = __builtin_amdgcn_perm(v23, v01, 0x05040100u);
-    const uint32_t nz7 = (levels + 0x7f7f7f7fu) & 0x80808080u;
-    return (sg & nz7) | levels;
-}
-
 // A bucket's level table, in LDS, filled by fill_table_bins.
 struct TableBins {
     double edge[16];   // e_t = l_t * ||v||, exact
@@ -479,10 +482,11 @@ __device__ __forceinline__ void fill_table_bins(TableBins &B, const LevelTable &
     B.thr[t] = t ? ((double)lo < e ? u2f(f2u(lo) + 1u) : lo) : ((uint16_t)(far >> row) == 0xffffu ? 1.0f : 0.0f);
 }
 
-// Level|sign bytes of four coordinates (in-bucket index of the first = counter0 - k0) by the fp64 rule.  Called by
+// Bytes (format F) of four coordinates (in-bucket index of the first = counter0 - k0) by the fp64 rule.  Called by
 // whole waves: the first-bin route is chosen per wave.
+template <class F>
 __device__ __forceinline__ uint32_t quantize_table_vec4_exact(const float4 &x, uint32_t counter0, uint32_t k1,
-                                                              const double *edges, double e1, uint32_t s)
+                                                              const double *edges, double e1, uint32_t s, const F &fmt)
 {
     const float xs[4] = {x.x, x.y, x.z, x.w};
     const float big = fmaxf(fmaxf(fabsf(xs[0]), fabsf(xs[1])), fmaxf(fabsf(xs[2]), fabsf(xs[3])));
@@ -508,7 +512,7 @@ __device__ __forceinline__ uint32_t quantize_table_vec4_exact(const float4 &x, u
             levels |= j << (8 * c);
         }
     }
-    return join_signs(xs, levels);
+    return fmt.any(top_bytes(xs), levels);
 }
 
 // The same in fp32 arithmetic that knows its own error.  The bin is exact (thr).  With x = fl(a - E_j) and
@@ -533,49 +537,44 @@ __device__ __forceinline__ TableRule make_table_rule(const TableBins &B, uint32_
     return TableRule{&B, team_uniform_f32<TEAM>(B.thr[1]), team_uniform_f32<TEAM>(B.bin[0].y), B.thr[threadIdx.x & 15u], s};
 }
 
-template <int TEAM>
+template <int TEAM, class F>
 __device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_t x0, uint32_t k1, const TableRule &R,
-                                                        bool &redo)
+                                                        const F &fmt, bool &redo)
 {
     const float xs[4] = {x.x, x.y, x.z, x.w};
     float u[4], t[4], near = 0x1p127f;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         u[c] = (float)draw24(x0 + (uint32_t)c * kRngC1, k1);
-    uint32_t levels = 0;
     if (__all(max_abs4(xs) < R.thr1)) {                          // every coordinate of every lane below the first level
-        uint32_t tb[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             t[c] = __builtin_fmaf(u[c], R.w0, -fabsf(xs[c]));
-            tb[c] = f2u(t[c]);
             near = fminf(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
         }
-        const uint32_t t01 = __builtin_amdgcn_perm(tb[1], tb[0], 0x0c0c0703u);
-        const uint32_t t23 = __builtin_amdgcn_perm(tb[3], tb[2], 0x0c0c0703u);
-        levels = (__builtin_amdgcn_perm(t23, t01, 0x05040100u) & 0x80808080u) >> 7;
-    } else {
-        uint32_t j[4] = {0, 0, 0, 0};
-        for (uint32_t l = 1; l <= R.s + 1u; ++l) {
-            float f;
-            if constexpr (TEAM >= (int)kWave)
-                f = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(R.thr_lane), (int)l));
-            else
-                f = R.bins->thr[l];
+        redo = __any(!(near > 0.0f));
+        return fmt.first(top_bytes(xs), top_bytes(t));
+    }
+    uint32_t levels = 0, j[4] = {0, 0, 0, 0};
+    for (uint32_t l = 1; l <= R.s + 1u; ++l) {
+        float f;
+        if constexpr (TEAM >= (int)kWave)
+            f = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(R.thr_lane), (int)l));
+        else
+            f = R.bins->thr[l];
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                j[c] += fabsf(xs[c]) >= f ? 1u : 0u;
-        }
+        for (int c = 0; c < 4; ++c)
+            j[c] += fabsf(xs[c]) >= f ? 1u : 0u;
+    }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const float2 b = R.bins->bin[j[c]];
-            t[c] = __builtin_fmaf(u[c], b.y, b.x - fabsf(xs[c]));
-            near = fminf(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
-            levels |= (j[c] + (t[c] < 0.0f ? 1u : 0u)) << (8 * c);
-        }
+    for (int c = 0; c < 4; ++c) {
+        const float2 b = R.bins->bin[j[c]];
+        t[c] = __builtin_fmaf(u[c], b.y, b.x - fabsf(xs[c]));
+        near = fminf(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
+        levels |= (j[c] + (t[c] < 0.0f ? 1u : 0u)) << (8 * c);
     }
     redo = __any(!(near > 0.0f));
-    return join_signs(xs, levels);
+    return fmt.any(top_bytes(xs), levels);
 }
 
 }  // namespace nuq

@@ -48,7 +48,7 @@ struct EncodeParams {
     uint32_t nblk;         // ERC messages: blocks per bucket = ceil(bucket / 2048)
     uint32_t slot_words;   // staging words per bucket
     uint32_t rows;         // ceil(bucket / (4*TEAM))
-    uint32_t lds_words;    // LDS words per team
+    uint32_t lds_words;    // LDS words per team (kernels that do not work theirs out)
     uint32_t rec_cap;      // nonzeros of a bucket whose indices fit the team's LDS list
     uint32_t out_cap;      // words of a bucket's bit string that fit the team's LDS buffer
     uint64_t nb_stride;    // nb rounded up to a multiple of 4: stride between workers in lens
@@ -224,18 +224,6 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_bucket_norms(EncodePara
         W.norms_out[b] = nrm;
 }
 
-// Top bytes of four words, one per result byte.
-__device__ __forceinline__ uint32_t top_bytes(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3)
-{
-    const uint32_t w01 = __builtin_amdgcn_perm(w1, w0, 0x0c0c0703u);
-    const uint32_t w23 = __builtin_amdgcn_perm(w3, w2, 0x0c0c0703u);
-    return __builtin_amdgcn_perm(w23, w01, 0x05040100u);
-}
-__device__ __forceinline__ uint32_t top_bytes(const float (&x)[4])
-{
-    return top_bytes(f2u(x[0]), f2u(x[1]), f2u(x[2]), f2u(x[3]));
-}
-
 // Level of one coordinate (any magnitude) for the draw u: |v| is scaled into [ns, 2 ns) by replacing its exponent (its
 // distance to the lower end of its bin, divided by the bin's width in units of c, is then a - ns for every bin), bin index
 // from the difference of the bit patterns.  No branches.
@@ -248,19 +236,58 @@ __device__ __forceinline__ uint32_t quantize_any(float x, float u, const BucketS
     return (uint32_t)min(max(m, -1) + 1 + (t < 0.0f ? 1 : 0), B.s + 1);   // m >= s: the top level, no draw
 }
 
-// Quantize the four coordinates of one vector; returns the four level|sign<<7 bytes.
+// How a quantized coordinate is handed on, four to a word.  sg: four sign bytes (top bytes of the coordinates), tb: four
+// bytes whose bit 7 says "not zero", tb2: four bytes whose bit 7 says "level 2", levels: four level indices.
+//
+// PlainBytes: level index | sign << 7, the byte of nuq_quantize (0 for a zero).
+struct PlainBytes {
+    __device__ __forceinline__ uint32_t first(uint32_t sg, uint32_t tb) const
+    {
+        const uint32_t up7 = tb & 0x80808080u;
+        return (sg & up7) | (up7 >> 7);
+    }
+    __device__ __forceinline__ uint32_t two(uint32_t sg, uint32_t tb, uint32_t tb2) const
+    {
+        const uint32_t up7 = tb & 0x80808080u;
+        return (sg & up7) | ((up7 >> 7) + ((tb2 >> 7) & 0x01010101u));
+    }
+    __device__ __forceinline__ uint32_t any(uint32_t sg, uint32_t levels) const
+    {
+        return (sg & ((levels + 0x7f7f7f7fu) & 0x80808080u)) | levels;
+    }
+};
+// FlagBytes, for the coding phase: bit 6 = not zero; the other bits only mean something where it is set: level index - 1
+// from bit 0, sign where sign_shift moves bit 7 to.  The nonzero mask is then one AND and one byte dot product per word.
+struct FlagBytes {
+    uint32_t sign_shift, sign_mask;
+    __device__ __forceinline__ uint32_t first(uint32_t sg, uint32_t tb) const
+    {
+        return ((sg >> sign_shift) & sign_mask) | ((tb >> 1) & 0x40404040u);
+    }
+    __device__ __forceinline__ uint32_t two(uint32_t sg, uint32_t tb, uint32_t tb2) const
+    {
+        return first(sg, tb) | ((tb2 >> 7) & 0x01010101u);
+    }
+    __device__ __forceinline__ uint32_t any(uint32_t sg, uint32_t levels) const
+    {
+        return ((sg >> sign_shift) & sign_mask) | (levels + 0x3f3f3f3fu);
+    }
+};
+
+// Quantize the four coordinates of one vector; returns the four bytes in format F.
 // x0 = (k0 + index of first coordinate) * C1.  The caller has applied B.prescale to x.
 //
 // Three routes, chosen per wave from the largest |v_i| of the vector over all lanes:
 //   below the first level (the usual case: |v_i| < 2^-s ||v||): the level is 0 or 1, "up" is the sign bit of
 //     t = fma(u, c, -|v|), and the bytes are assembled from the top bytes of v (sign) and t (up) with byte permutes;
-//   below twice the first level (s >= 1): bins [0, ns) and [ns, 2 ns) have the same width, and u c < ns, so the level is
+//   below twice the first level: bins [0, ns) and [ns, 2 ns) have the same width, and u c < ns, so the level is
 //     the number of negative ones among t and t' = fma(u, c, ns - |v|): t is negative whenever |v| >= ns, t' never is
 //     when |v| < ns (ns - |v| is exact where it decides).  Without the selection of a bin per coordinate: 2.5 of 17
 //     instructions less;
 //   anything else: quantize_any.
-__device__ __forceinline__ uint32_t quantize_vec4(const float4 &x, uint32_t x0, uint32_t k1,
-                                                  const BucketScale &B)
+template <class F>
+__device__ __forceinline__ uint32_t quantize_vec4(const float4 &x, uint32_t x0, uint32_t k1, const BucketScale &B,
+                                                  const F &fmt)
 {
     const float xs[4] = {x.x, x.y, x.z, x.w};   // already multiplied by B.prescale
     const float big = max_abs4(xs);
@@ -272,21 +299,19 @@ __device__ __forceinline__ uint32_t quantize_vec4(const float4 &x, uint32_t x0, 
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             t[c] = __builtin_fmaf(u[c], B.c, -fabsf(xs[c]));
-        const uint32_t sg = top_bytes(xs), up7 = top_bytes(t) & 0x80808080u;   // bit 7 of byte c: coordinate c is not 0
-        uint32_t levels = up7 >> 7;
-        if (!__all(big < B.ns)) {
+        const uint32_t sg = top_bytes(xs), tb = top_bytes(t);
+        if (__all(big < B.ns))
+            return fmt.first(sg, tb);
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                t[c] = __builtin_fmaf(u[c], B.c, B.ns - fabsf(xs[c]));
-            levels += (top_bytes(t) >> 7) & 0x01010101u;
-        }
-        return (sg & up7) | levels;
+        for (int c = 0; c < 4; ++c)
+            t[c] = __builtin_fmaf(u[c], B.c, B.ns - fabsf(xs[c]));
+        return fmt.two(sg, tb, top_bytes(t));
     }
     uint32_t levels = 0;
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         levels |= quantize_any(xs[c], u[c], B) << (8 * c);
-    return join_signs(xs, levels);
+    return fmt.any(top_bytes(xs), levels);
 }
 
 // --------------------------------------------------------------- quantize kernel
@@ -318,7 +343,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
             x.z *= B.prescale;
             x.w *= B.prescale;
         }
-        const uint32_t packed = B.dead ? 0u : quantize_vec4(x, (key.k0 + e0) * kRngC1, key.k1, B);
+        const uint32_t packed = B.dead ? 0u : quantize_vec4(x, (key.k0 + e0) * kRngC1, key.k1, B, PlainBytes{});
         if (qaligned && e0 + 3u < nbk) {
             reinterpret_cast<uint32_t *>(qb)[vi] = packed;
         } else {
@@ -330,21 +355,27 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
 
 // ----------------------------------------------------------------- coding phase
 //
-// On entry the team's level/sign bytes are in LDS (qb32, bytes at or beyond the bucket's
-// length are zero) and a barrier has been passed.  Produces the bucket's bit string in
-// LDS `out`, copies it to the bucket's staging slot, writes its bit length and its sync
-// entries.  Every thread of the workgroup must call it (it contains barriers).
+// On entry the team's bytes (FlagBytes) are in LDS (qb32, bytes at or beyond the bucket's length say "zero") and a
+// barrier has been passed.  Produces the bucket's bit string in LDS, copies it to the bucket's staging slot, writes its
+// bit length and its index entries.  Every thread of the workgroup must call it (it contains barriers).
 //
-// Steps: (1) every thread finds the nonzeros of its contiguous chunk and the team compacts
-// their indices into `rec` (a prefix sum gives the ranks); (2) the records are dealt out evenly,
-// a thread takes a contiguous run of them, looks up gap and level codes in a 256-entry table
-// and sums their lengths; a second prefix sum gives every run its bit offset; (3) the same
-// runs are walked again to OR the record bits into `out`.
+// Steps: (1) every thread finds the nonzeros of its contiguous chunk and the team compacts their indices into `rec` (a
+// prefix sum gives the ranks); (2) the records are dealt out evenly, a thread takes a contiguous run of them, looks up
+// their codes and sums their lengths; a second prefix sum gives every run its bit offset; (3) the run's records, kept in
+// registers, are OR-ed into the bit string.
+//
+// LDS bounds the number of buckets in flight on a CU, and a bucket's worst case (every coordinate nonzero at the longest
+// level code) is four to ten times what gradients produce.  So the team's index list and bit-string buffer hold `rec_cap`
+// nonzeros and `out_cap` words, sized for the usual case, and a bucket that exceeds one of them takes a slower way:
+//   nonzeros fit, bits fit  : as above
+//   nonzeros fit, bits don't: the same, but records are OR-ed into the (zeroed) staging slot in global memory
+//   nonzeros don't fit      : code_unlisted
+//
+// The kernel is bound by vector issue, so what counts here is instructions per record and per coordinate.
 
-// Code table for N < 256, built at compile time: code (right-aligned) | length << 16; entry 0 repeats entry 1.
-// A workgroup copies it to LDS once instead of computing it.
-struct ErcTable {
-    uint32_t v[256];
+// ERC of N (Alg. 2): groups binary(N), binary(bits(N) - 1), ... while the value is at least 2, last computed first, one 0.
+struct ErcWord {
+    uint32_t code, len;
 };
 constexpr uint32_t bit_width_c(uint32_t x)
 {
@@ -355,47 +386,139 @@ constexpr uint32_t bit_width_c(uint32_t x)
     }
     return w;
 }
-constexpr ErcTable make_erc_table()
+constexpr ErcWord erc_c(uint32_t N)
 {
-    ErcTable t{};
+    uint32_t code = 0, len = 0;
+    for (uint32_t g = N; g >= 2u; g = bit_width_c(g) - 1u) {
+        code |= g << len;
+        len += bit_width_c(g);
+    }
+    return ErcWord{code << 1, len + 1u};
+}
+
+// 512 words of code tables per workgroup, built at compile time and copied to LDS.
+//
+// Large teams (buckets above 2048, one coordinate in ten nonzero or fewer: gaps of any size): 256 entries by gap (code |
+// length << 16; entry 0 is not used) and 256 by byte: sign and level code, | their length << 16.
+// Small teams (a coordinate in four nonzero: gaps below 32 but for one in 10^4): the whole record, code | length << 27,
+// by byte and gap: 5 bits of gap, 3 of level, sign where levels are at most 8 (s <= 7), else 4 bits of gap, 4 of level.
+struct CodeTables {
+    uint32_t large[512], small[2][512];
+};
+constexpr CodeTables make_code_tables()
+{
+    CodeTables t{};
     for (uint32_t i = 0; i < 256u; ++i) {
-        const uint32_t N = i ? i : 1u;
-        // Alg. 2: groups binary(N), binary(bits(N) - 1), ... while the value is at least 2, last computed first, one 0
-        uint32_t code = 0, len = 0;
-        for (uint32_t g = N; g >= 2u; g = bit_width_c(g) - 1u) {
-            code |= g << len;
-            len += bit_width_c(g);
+        const ErcWord g = erc_c(i ? i : 1u), l = erc_c((i & 15u) + 1u);
+        t.large[i] = g.code | (g.len << 16);
+        t.large[256u + i] = ((i >> 7) << l.len) | l.code | ((l.len + 1u) << 16);
+    }
+    for (uint32_t v = 0; v < 2u; ++v)
+        for (uint32_t i = 0; i < 512u; ++i) {
+            const uint32_t gbits = v ? 4u : 5u, lbits = v ? 4u : 3u;
+            const uint32_t gap = i & ((1u << gbits) - 1u), x = i >> gbits;
+            const ErcWord g = erc_c(gap ? gap : 1u), l = erc_c((x & ((1u << lbits) - 1u)) + 1u);
+            const uint32_t tail = ((x >> lbits) << l.len) | l.code;
+            t.small[v][i] = (g.code << (l.len + 1u)) | tail | ((g.len + l.len + 1u) << 27);
         }
-        t.v[i] = (code << 1) | ((len + 1u) << 16);
-    }
     return t;
 }
-__device__ const ErcTable kErcTable = make_erc_table();
+__device__ const CodeTables kCodeTables = make_code_tables();
 
-// Table for the tail of a record, indexed by the level|sign byte (level in bits 0..6, 1..15; sign in bit 7): the
-// sign bit followed by the level's code, right-aligned, | their length << 16.
-constexpr ErcTable make_tail_table()
-{
-    const ErcTable erc = make_erc_table();
-    ErcTable t{};
-    for (uint32_t i = 0; i < 256u; ++i) {
-        const uint32_t e = erc.v[i & 15u], code = e & 0xffffu, len = e >> 16;
-        t.v[i] = ((i >> 7) << len) | code | ((len + 1u) << 16);
-    }
-    return t;
-}
-__device__ const ErcTable kTailTable = make_tail_table();
+template <int TEAM>
+constexpr bool kSmallTeam = TEAM <= kWave;
 
-// erc_lut[N] for N < 256: code (right-aligned) | length << 16.
-__device__ __forceinline__ uint32_t erc_lookup(const uint32_t *erc_lut, uint32_t N, uint32_t &len)
+// The byte format of the coding phase for the level count s.
+template <int TEAM>
+__device__ __forceinline__ FlagBytes flag_bytes(uint32_t s)
 {
-    if (N < 256u) {
-        const uint32_t e = erc_lut[N];
-        len = e >> 16;
-        return e & 0xffffu;
-    }
-    return erc_code(N, len);
+    if constexpr (kSmallTeam<TEAM>)
+        return s <= 7u ? FlagBytes{4u, 0x08080808u} : FlagBytes{3u, 0x10101010u};
+    else
+        return FlagBytes{0u, 0x80808080u};
 }
+
+template <int TEAM>
+__device__ __forceinline__ void load_code_tables(uint32_t *tables, uint32_t s)
+{
+    const uint32_t *src = kSmallTeam<TEAM> ? kCodeTables.small[s <= 7u ? 0 : 1] : kCodeTables.large;
+    if (threadIdx.x < 256u) {
+        tables[threadIdx.x] = src[threadIdx.x];
+        tables[256u + threadIdx.x] = src[256u + threadIdx.x];
+    }
+}
+
+// A record's bits (right-aligned) and length from its gap and byte.
+struct LargeRecords {
+    const uint32_t *tables;
+    __device__ __forceinline__ uint32_t operator()(uint32_t gap, uint32_t byte, uint32_t &len) const
+    {
+        uint32_t lg, cg;
+        if (gap < 256u) {
+            const uint32_t e = tables[gap];
+            lg = e >> 16;
+            cg = e & 0xffffu;
+        } else {
+            cg = erc_code(gap, lg);
+        }
+        const uint32_t tl = tables[256u + byte];
+        len = lg + (tl >> 16);
+        return (cg << (tl >> 16)) | (tl & 0xffffu);
+    }
+};
+// In one word (code | length << 27): a bucket of a small team has at most 2048 coordinates, so a record at most
+// 18 + 1 + 7 = 26 bits.
+struct SmallRecords {
+    const uint32_t *at;      // the table's entry for byte 0 (the "not zero" bit, 64, is part of every byte looked up)
+    uint32_t gap_bits;       // 5 (levels up to 8) or 4
+    __device__ __forceinline__ uint32_t packed(uint32_t gap, uint32_t byte) const
+    {
+        if (__builtin_expect(gap < (1u << gap_bits), 1))
+            return at[(byte << gap_bits) | gap];
+        const uint32_t lbits = 8u - gap_bits, x = byte & 0x1fu;
+        uint32_t lg, ll;
+        const uint32_t cg = erc_code(gap, lg), cl = erc_code((x & ((1u << lbits) - 1u)) + 1u, ll);
+        return (((cg << 1) | (x >> lbits)) << ll) | cl | ((lg + ll + 1u) << 27);
+    }
+    __device__ __forceinline__ uint32_t operator()(uint32_t gap, uint32_t byte, uint32_t &len) const
+    {
+        const uint32_t r = packed(gap, byte);
+        len = r >> 27;
+        return r & 0x7ffffffu;
+    }
+};
+template <int TEAM>
+__device__ __forceinline__ auto make_records(const uint32_t *tables, uint32_t s)
+{
+    if constexpr (kSmallTeam<TEAM>)
+        return SmallRecords{tables - (s <= 7u ? 64 << 5 : 64 << 4), s <= 7u ? 5u : 4u};
+    else
+        return LargeRecords{tables};
+}
+
+// A thread's records, consecutive in the bit string, are shifted into a 64-bit register and leave it 32 bits at a time (a
+// record is at most 31 bits, so at most 31 + 31 bits are pending), OR-ed into zeroed words because a thread's first and
+// last word are shared with its neighbours.  Bits that have left stay in the register, above the pending ones, until they
+// are shifted out: nothing reads them.
+struct BitWriter {
+    uint32_t wi, fill;
+    uint64_t acc;
+    __device__ __forceinline__ explicit BitWriter(uint32_t bit) : wi(bit >> 5), fill(bit & 31u), acc(0) {}
+    __device__ __forceinline__ void put(uint32_t *dst, uint32_t bits, uint32_t len)
+    {
+        acc = (acc << len) | bits;
+        fill += len;
+        if (fill >= 32u) {
+            fill -= 32u;
+            atomicOr(&dst[wi++], __builtin_amdgcn_alignbit((uint32_t)(acc >> 32), (uint32_t)acc, fill));
+        }
+    }
+    __device__ __forceinline__ void flush(uint32_t *dst)
+    {
+        if (fill)
+            atomicOr(&dst[wi], (uint32_t)(acc << (32u - fill)));
+    }
+};
 
 // Orders a team's LDS traffic between the phases of the coding pass.  A team of one wave needs no hardware barrier
 // (its lanes run in lockstep and its LDS operations complete in order), only the wait and a fence for the
@@ -411,362 +534,425 @@ __device__ __forceinline__ void team_barrier()
     }
 }
 
-// LDS is what bounds the number of buckets in flight on a CU, and a bucket's worst case (every coordinate
-// nonzero at the longest level code) is four to ten times what gradients produce.  So the team's index list and
-// bit-string buffer hold `rec_cap` nonzeros and `out_cap` words, sized for the usual case, and a bucket that
-// exceeds one of them takes a slower way around it:
-//   nonzeros fit, bits fit  : compacted index list, balanced record runs, bit string assembled in LDS
-//   nonzeros fit, bits don't: the same, but records are OR-ed into the (zeroed) staging slot in global memory
-//   nonzeros don't fit      : every thread codes the records of its own chunk; the bit string is assembled in LDS
-//                             over the list's and the buffer's words together if it fits there, else in the slot
-template <int TEAM, int VPT>
-__device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
-                                                const uint32_t *qb32, uint32_t *out, uint16_t *rec,
-                                                const uint32_t *erc_lut, const uint32_t *tail_lut, uint32_t *sync_l,
-                                                uint32_t *blk, uint32_t *run_off, uint32_t *scratch)
+// A team's LDS, in 32-bit words.
+struct TeamLds {
+    uint32_t *qb32;        // rows * TEAM: bytes
+    uint16_t *rec;         // rec_cap indices ...
+    uint32_t *out;         // ... then out_cap words of bit string; 16-byte aligned
+    uint32_t *sync_l;      // nsync
+    uint32_t *blk;         // nblk + 1: records before each block of the index
+    uint32_t *run_off;     // TEAM (large teams): bit offset of every thread's run
+    uint32_t *scratch;     // 64
+    const uint32_t *tables;
+};
+
+// What a thread knows of its bucket after step (1).
+struct Chunk {
+    uint64_t nz;           // mask of its chunk's nonzeros
+    uint32_t base;         // in-bucket index of the chunk's first coordinate
+    uint32_t rank0;        // records before the chunk
+    uint32_t nnz;          // records of the bucket
+};
+
+// Bit length and, with 16-byte stores, the bit string from LDS (zero up to a multiple of four words) to the bucket's slot.
+template <int TEAM>
+__device__ __forceinline__ void store_bucket(const EncodeParams &P, uint64_t b, uint32_t *slot, const uint32_t *out,
+                                             uint32_t nwords, uint32_t total, uint32_t tid)
+{
+    for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
+        *reinterpret_cast<uint4 *>(slot + i) = *reinterpret_cast<const uint4 *>(out + i);
+    if (tid == 0)
+        P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
+}
+
+// Buckets with more nonzeros than the list holds: every thread codes the records of its own chunk, in two passes; the bit
+// string is assembled over the list's and the buffer's words together (the two regions are adjacent: three quarters of the
+// worst case for large buckets) if it fits there, else in the slot in global memory.
+template <int TEAM>
+__device__ __forceinline__ void code_unlisted(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+                                              const TeamLds &L, const Chunk &C, uint32_t *slot)
 {
     const uint32_t tid = threadIdx.x % TEAM;
-    const uint32_t rows = P.rows;
-    const uint32_t base = tid * rows * 4u;
-    const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(qb32);
-
-    // (1) nonzero mask of this thread's chunk (rows <= VPT <= 16 words: two 32-bit halves), ranks, compaction
-    static_assert(VPT <= 16, "the chunk's mask is 64 bits");
-    uint32_t nz_lo = 0, nz_hi = 0;
-#pragma unroll
-    for (int w = 0; w < VPT; ++w) {
-        if ((uint32_t)w < rows) {
-            const uint32_t word = qb32[tid * rows + (uint32_t)w];
-            // bit 0 of every byte whose low seven bits (the level) are not all zero, then the four bits side by side
-            const uint32_t t = (((word & 0x7f7f7f7fu) + 0x7f7f7f7fu) >> 7) & 0x01010101u;
-            const uint32_t nib = __builtin_amdgcn_udot4(t, 0x08040201u, 0u, false);
-            if (w < 8)
-                nz_lo |= nib << (4 * w);
-            else
-                nz_hi |= nib << (4 * (w - 8));
-        }
-    }
-    const uint64_t nz = ((uint64_t)nz_hi << 32) | nz_lo;
-    uint32_t nnz;
-    uint32_t rank = team_exclusive_sum<TEAM>((uint32_t)(__popc(nz_lo) + __popc(nz_hi)), scratch, nnz);
-    const uint32_t rank0 = rank;                   // records before this thread's chunk
-    const bool listed = nnz <= P.rec_cap;          // uniform over the team
-    if (P.nsync) {
-        // blk[t] = records before block t of the decoder index: the thread whose chunk holds the block's first
-        // coordinate counts its own nonzeros below it (every block starts inside exactly one chunk)
-        constexpr uint32_t kBlock = 1u << kSyncBlockShift;
-        const uint32_t c = (base + kBlock - 1u) & ~(kBlock - 1u);
-        const uint32_t t = c >> kSyncBlockShift;
-        if (c < base + rows * 4u && t < P.nblk) {
-            const uint32_t sh = c - base;                                    // < 64
-            const uint64_t below = sh ? nz & (~0ull >> (64u - sh)) : 0ull;
-            blk[t] = rank0 + (uint32_t)__popcll((unsigned long long)below);
-        }
-        if (tid == 0)
-            blk[P.nblk] = nnz;
-    }
-    int before_chunk = -1;                         // last nonzero before this thread's chunk (unlisted buckets)
-    if (listed) {
-        auto list = [&](uint32_t m, uint32_t at) {
-            while (m) {
-                const uint32_t k = (uint32_t)__builtin_ctz(m);
-                m &= m - 1u;
-                rec[rank++] = (uint16_t)(at + k);
-            }
-        };
-        list(nz_lo, base);
-        if constexpr (VPT > 8)
-            list(nz_hi, base + 32u);
-    } else {
-        const int last = nz ? (int)base + 63 - __clzll((long long)nz) : -1;
-        before_chunk = team_exclusive_max<TEAM>(last, -1, reinterpret_cast<int *>(scratch + 16));
-    }
-    team_barrier<TEAM>();
-
-    // The records this thread codes, in index order: f(index, previous nonzero's index, level|sign byte).
-    const uint32_t per = (nnz + TEAM - 1u) / TEAM;
-    const uint32_t r0 = min(tid * per, nnz), r1 = min(r0 + per, nnz);
+    const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
+    const auto record = make_records<TEAM>(L.tables, P.s);
+    const int last = C.nz ? (int)C.base + 63 - __clzll((long long)C.nz) : -1;
+    const int before = team_exclusive_max<TEAM>(last, -1, reinterpret_cast<int *>(L.scratch + 16));
     auto for_my_records = [&](auto &&f) {
-        if (listed) {
-            int p = r0 ? (int)rec[r0 - 1u] : -1;
-            for (uint32_t r = r0; r < r1; ++r) {
-                const int e = (int)rec[r];
-                f(e, p, (uint32_t)qbytes[e]);
-                p = e;
-            }
-        } else {
-            int p = before_chunk;
-            uint64_t m = nz;
-            while (m) {
-                const int e = (int)base + __ffsll((unsigned long long)m) - 1;
-                m &= m - 1;
-                f(e, p, (uint32_t)qbytes[e]);
-                p = e;
-            }
-        }
-    };
-
-    // A record's bits (right-aligned) and length: ERC(gap), then sign and ERC(level) from the tail table.
-    auto make_record = [&](int e, int p, uint32_t byte, uint32_t &len) {
-        uint32_t lg;
-        const uint32_t cg = erc_lookup(erc_lut, (uint32_t)(e - p), lg);
-        const uint32_t tl = tail_lut[byte];
-        len = lg + (tl >> 16);
-        return (cg << (tl >> 16)) | (tl & 0xffffu);
-    };
-
-    // (2) lengths of this thread's records.  The first kKept records of a run from the list stay in registers
-    // for the third pass (a run is nnz / TEAM records: two or three for gradients in large buckets, eight where
-    // a quarter of a 512-coordinate bucket is nonzero).
-    constexpr uint32_t kKept = TEAM <= 64 ? 8 : 4;
-    uint32_t kept_bits[kKept], kept_len[kKept];
-    int kept_e[kKept];
-    uint32_t bits = 0;
-    if (listed) {
-        int p = r0 ? (int)rec[r0 - 1u] : -1;
-#pragma unroll
-        for (uint32_t i = 0; i < kKept; ++i) {
-            kept_len[i] = 0;
-            kept_bits[i] = 0;
-            kept_e[i] = p;
-            if (r0 + i < r1) {
-                const int e = (int)rec[r0 + i];
-                kept_bits[i] = make_record(e, p, (uint32_t)qbytes[e], kept_len[i]);
-                kept_e[i] = e;
-                bits += kept_len[i];
-                p = e;
-            }
-        }
-        for (uint32_t r = r0 + kKept; r < r1; ++r) {
-            const int e = (int)rec[r];
+        int p = before;
+        uint64_t m = C.nz;
+        while (m) {
+            const int e = (int)C.base + __ffsll((unsigned long long)m) - 1;
+            m &= m - 1;
             uint32_t len;
-            make_record(e, p, (uint32_t)qbytes[e], len);
-            bits += len;
+            const uint32_t bits = record((uint32_t)(e - p), (uint32_t)qbytes[e], len);
+            f(e, bits, len);
             p = e;
         }
-    } else {
-        for_my_records([&](int e, int p, uint32_t byte) {
-            uint32_t len;
-            make_record(e, p, byte, len);
-            bits += len;
-        });
-    }
+    };
+    uint32_t bits = 0;
+    for_my_records([&](int, uint32_t, uint32_t len) { bits += len; });
     uint32_t total;
-    const uint32_t off0 = team_exclusive_sum<TEAM>(bits, scratch + 32, total);
+    const uint32_t off0 = team_exclusive_sum<TEAM>(bits, L.scratch + 32, total);
     const uint32_t nwords = (total + 31u) >> 5;
-    // An unlisted bucket does not use the index list, so its bit string may spread over the list's LDS as well
-    // (the two regions are adjacent): three quarters of the worst case for large buckets.
-    uint32_t *const obuf = listed ? out : reinterpret_cast<uint32_t *>(rec);
-    const uint32_t ocap = listed ? P.out_cap : (P.rec_cap + 1u) / 2u + P.out_cap;
-    const bool in_lds = nwords <= ocap;                          // uniform over the team
-    const uint64_t gb = (uint64_t)blockIdx.y * P.nb + b;         // bucket index over the whole batch
-    uint32_t *slot = P.staging + (active ? gb : 0) * P.slot_words;
+    uint32_t *const obuf = reinterpret_cast<uint32_t *>(L.rec);
+    const bool in_lds = nwords <= (uint32_t)(L.out - obuf) + P.out_cap;          // uniform over the team
     if (in_lds) {
-        for (uint32_t i = tid; i < nwords; i += TEAM)
-            obuf[i] = 0u;
+        for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
+            *reinterpret_cast<uint4 *>(obuf + i) = uint4{0u, 0u, 0u, 0u};
     } else if (active) {
         for (uint32_t i = tid; i < nwords; i += TEAM)
             slot[i] = 0u;
         __threadfence();       // the zeros are in place before any record is OR-ed over them
     }
-    // Decoder index: entry i = (block t, piece g) describes record blk[t] + floor(g n_t / pieces) of the bucket.
+    // index entries: their record numbers go to LDS (bit 31: a block without records), an entry past the last record is the
+    // bucket's length, and whoever emits such a record writes the entry
     uint32_t *const sg = W.sync + (active ? b : 0) * P.nsync;
     const uint32_t pmask = (1u << P.pieces_shift) - 1u;
-    // Small teams (a wave or less: short runs, few entries) let the thread that owns a listed record write its entry
-    // from the lengths it holds in registers; large teams look the record up from the entry's side.
-    constexpr bool kOwnerWrites = TEAM <= (int)kWave;
-    const bool targets_to_lds = !listed || kOwnerWrites;
-    if (listed && !kOwnerWrites)
-        run_off[tid] = off0;              // where this thread's run of records starts in the bit string
-    if (targets_to_lds) {
-        // the entries' record numbers go to LDS (bit 31: a block without records); an entry past the last record is
-        // the bucket's length.  Unlisted records: whoever emits such a record writes the entry (below)
-        for (uint32_t i = tid; i < P.nsync; i += TEAM) {
-            const uint32_t f = blk[i >> P.pieces_shift], n = blk[(i >> P.pieces_shift) + 1u] - f;
-            const uint32_t r = f + (((i & pmask) * n) >> P.pieces_shift);
-            if (r >= nnz && active)
-                sg[i] = total;
-            sync_l[i] = r | (n ? 0u : 0x80000000u);
-        }
+    for (uint32_t i = tid; i < P.nsync; i += TEAM) {
+        const uint32_t f = L.blk[i >> P.pieces_shift], n = L.blk[(i >> P.pieces_shift) + 1u] - f;
+        const uint32_t r = f + (((i & pmask) * n) >> P.pieces_shift);
+        if (r >= C.nnz && active)
+            sg[i] = total;
+        L.sync_l[i] = r | (n ? 0u : 0x80000000u);
     }
     team_barrier<TEAM>();
-    if (listed && kOwnerWrites) {
-        // this thread's run is records [r0, r1), the first at bit off0: the entries that point into it (their record
-        // numbers are sorted) are found by bisection, a record's offset is the sum of the lengths before it in the run
-        if (r0 < r1 && P.nsync) {
-            uint32_t lo = 0, hi = P.nsync;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if ((sync_l[mid] & 0x7fffffffu) < r0)
-                    lo = mid + 1u;
-                else
-                    hi = mid;
-            }
-            for (uint32_t cur = lo; cur < P.nsync; ++cur) {
-                const uint32_t tg = sync_l[cur], r = tg & 0x7fffffffu;
-                if (r >= r1)
+    auto emit_all = [&](uint32_t *dst) {
+        uint32_t t = off0, rno = C.rank0, cur = 0, hi = P.nsync;
+        while (cur < hi) {                       // first entry at or after this thread's first record (they are sorted)
+            const uint32_t mid = (cur + hi) >> 1;
+            if ((L.sync_l[mid] & 0x7fffffffu) < rno)
+                cur = mid + 1u;
+            else
+                hi = mid;
+        }
+        BitWriter w(off0);
+        for_my_records([&](int e, uint32_t rbits, uint32_t len) {
+            while (cur < P.nsync) {
+                const uint32_t tg = L.sync_l[cur];
+                if ((tg & 0x7fffffffu) != rno)
                     break;
-                uint32_t pos = off0;
-#pragma unroll
-                for (uint32_t i = 0; i < kKept; ++i)
-                    pos += r0 + i < r ? kept_len[i] : 0u;
-                for (uint32_t q = r0 + kKept; q < r; ++q) {      // (a run longer than the records kept in registers)
-                    const int e = (int)rec[q];
-                    uint32_t len;
-                    make_record(e, (int)rec[q - 1u], (uint32_t)qbytes[e], len);
-                    pos += len;
-                }
-                const uint32_t rel = (tg >> 31) ? 0u : (uint32_t)rec[r] - ((cur >> P.pieces_shift) << kSyncBlockShift);
+                const uint32_t rel = (tg >> 31) ? 0u : (uint32_t)e - ((cur >> P.pieces_shift) << kSyncBlockShift);
                 if (active)
-                    sg[cur] = pos | (rel << 21);
+                    sg[cur] = t | (rel << 21);
+                ++cur;
             }
-        }
-    } else if (listed) {
-        // the run that holds the record starts at run_off[owner]; the lengths of the records before it in that run
-        // are looked up again (a run is nnz / TEAM records)
-        for (uint32_t i = tid; i < P.nsync; i += TEAM) {
-            const uint32_t t = i >> P.pieces_shift;
-            const uint32_t f = blk[t], n = blk[t + 1u] - f;
-            const uint32_t r = f + (((i & pmask) * n) >> P.pieces_shift);
-            uint32_t entry = total;
-            if (r < nnz) {
-                const uint32_t owner = r / per;
-                uint32_t q0 = owner * per;
-                uint32_t pos = run_off[owner];
-                int p = q0 ? (int)rec[q0 - 1u] : -1;
-                for (; q0 < r; ++q0) {
-                    const int e = (int)rec[q0];
-                    uint32_t len;
-                    make_record(e, p, (uint32_t)qbytes[e], len);
-                    pos += len;
-                    p = e;
-                }
-                entry = pos | ((n ? (uint32_t)rec[r] - (t << kSyncBlockShift) : 0u) << 21);
-            }
-            if (active)
-                sg[i] = entry;
-        }
-    }
-
-    // (3) emit.  A thread's records are consecutive in the bit string: they are shifted into a 64-bit register and
-    // leave it 32 bits at a time (a record is at most 31 bits, so at most 31 + 31 bits are pending), OR-ed into the
-    // zeroed words because a thread's first and last word are shared with its neighbours.
-    {
-        uint32_t t = off0, wi = off0 >> 5, fill = off0 & 31u;
-        uint64_t acc = 0;
-        // unlisted records: the index entries that point at this thread's records (their numbers are sorted)
-        uint32_t cur = P.nsync, rno = rank0;
-        if (!listed && P.nsync) {
-            uint32_t lo = 0, hi = P.nsync;
-            while (lo < hi) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if ((sync_l[mid] & 0x7fffffffu) < rank0)
-                    lo = mid + 1u;
-                else
-                    hi = mid;
-            }
-            cur = lo;
-        }
-        auto emit = [&](uint32_t *dst, int e, int p, uint32_t bitsrec, uint32_t len) {
-            (void)p;
-            if (!listed) {
-                while (cur < P.nsync) {
-                    const uint32_t tg = sync_l[cur];
-                    if ((tg & 0x7fffffffu) != rno)
-                        break;
-                    const uint32_t rel = (tg >> 31) ? 0u : (uint32_t)e - ((cur >> P.pieces_shift) << kSyncBlockShift);
-                    if (active)
-                        sg[cur] = t | (rel << 21);
-                    ++cur;
-                }
-                ++rno;
-            }
-            acc = (acc << len) | bitsrec;
-            fill += len;
+            ++rno;
             t += len;
-            if (fill >= 32u) {
-                fill -= 32u;
-                atomicOr(&dst[wi++], (uint32_t)(acc >> fill));
-                acc &= (1ull << fill) - 1ull;
-            }
-        };
-        auto flush = [&](uint32_t *dst) {
-            if (fill && t != off0)
-                atomicOr(&dst[wi], (uint32_t)(acc << (32u - fill)));
-        };
-        auto emit_all = [&](uint32_t *dst) {
-            if (listed) {
-                int p = r0 ? (int)rec[r0 - 1u] : -1;
-#pragma unroll
-                for (uint32_t i = 0; i < kKept; ++i) {
-                    if (kept_len[i])
-                        emit(dst, kept_e[i], p, kept_bits[i], kept_len[i]);
-                    p = kept_e[i];
-                }
-                for (uint32_t r = r0 + kKept; r < r1; ++r) {
-                    const int e = (int)rec[r];
-                    uint32_t len;
-                    const uint32_t bitsrec = make_record(e, p, (uint32_t)qbytes[e], len);
-                    emit(dst, e, p, bitsrec, len);
-                    p = e;
-                }
-            } else {
-                for_my_records([&](int e, int p, uint32_t byte) {
-                    uint32_t len;
-                    const uint32_t bitsrec = make_record(e, p, byte, len);
-                    emit(dst, e, p, bitsrec, len);
-                });
-            }
-        };
-        if (in_lds) {
-            emit_all(obuf);
-            flush(obuf);
-        } else if (active) {
-            emit_all(slot);
-            flush(slot);
-        }
-    }
+            w.put(dst, rbits, len);
+        });
+        if (C.nz)
+            w.flush(dst);
+    };
+    if (in_lds)
+        emit_all(obuf);
+    else if (active)
+        emit_all(slot);
     team_barrier<TEAM>();
     if (active) {
         if (in_lds)
-            for (uint32_t i = tid; i < nwords; i += TEAM)
-                slot[i] = obuf[i];
-        if (tid == 0)
+            store_bucket<TEAM>(P, b, slot, obuf, nwords, total, tid);
+        else if (tid == 0)
             P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
     }
 }
 
-// What a team's LDS holds of a bucket's nonzero list and bit string: everything for small buckets, a quarter
-// of the worst case for large ones (about four times what a Gaussian gradient produces).
+// Steps (2) and (3), teams of several waves: two or three records per thread.  The records' table entries, four of them
+// kept; the index entries are looked up from the entry's side (the run that holds the record starts at run_off[owner]; the
+// lengths of the records before it in that run are looked up again).
+template <int TEAM>
+__device__ __forceinline__ void code_listed_large(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+                                                  const TeamLds &L, uint32_t nnz, uint32_t *slot)
+{
+    const uint32_t tid = threadIdx.x % TEAM;
+    const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
+    const LargeRecords record{L.tables};
+    const uint32_t per = (nnz + TEAM - 1u) / TEAM;
+    const uint32_t r0 = min(tid * per, nnz), r1 = min(r0 + per, nnz);
+    constexpr uint32_t kKept = 4;
+    uint32_t kept_bits[kKept], kept_len[kKept], bits = 0;
+    int p = r0 ? (int)L.rec[r0 - 1u] : -1;
+#pragma unroll
+    for (uint32_t i = 0; i < kKept; ++i) {
+        kept_len[i] = 0;
+        kept_bits[i] = 0;
+        if (r0 + i < r1) {
+            const int e = (int)L.rec[r0 + i];
+            kept_bits[i] = record((uint32_t)(e - p), (uint32_t)qbytes[e], kept_len[i]);
+            bits += kept_len[i];
+            p = e;
+        }
+    }
+    const int p_kept = p;
+    for (uint32_t r = r0 + kKept; r < r1; ++r) {
+        const int e = (int)L.rec[r];
+        uint32_t len;
+        record((uint32_t)(e - p), (uint32_t)qbytes[e], len);
+        bits += len;
+        p = e;
+    }
+    uint32_t total;
+    const uint32_t off0 = team_exclusive_sum<TEAM, false>(bits, L.scratch + 16, total);
+    const uint32_t nwords = (total + 31u) >> 5;
+    const bool in_lds = nwords <= P.out_cap;                     // uniform over the team (the buffer was cleared before)
+    if (P.nsync)
+        L.run_off[tid] = off0;
+    if (!in_lds) {
+        if (active) {
+            for (uint32_t i = tid; i < nwords; i += TEAM)
+                slot[i] = 0u;
+            __threadfence();   // the zeros are in place before any record is OR-ed over them
+        }
+        team_barrier<TEAM>();
+    }
+    auto emit_all = [&](uint32_t *dst) {
+        BitWriter w(off0);
+#pragma unroll
+        for (uint32_t i = 0; i < kKept; ++i)
+            if (kept_len[i])
+                w.put(dst, kept_bits[i], kept_len[i]);
+        int q = p_kept;
+        for (uint32_t r = r0 + kKept; r < r1; ++r) {
+            const int e = (int)L.rec[r];
+            uint32_t len;
+            const uint32_t rb = record((uint32_t)(e - q), (uint32_t)qbytes[e], len);
+            w.put(dst, rb, len);
+            q = e;
+        }
+        if (r0 < r1)
+            w.flush(dst);
+    };
+    if (in_lds)
+        emit_all(L.out);
+    else if (active)
+        emit_all(slot);
+    team_barrier<TEAM>();
+    uint32_t *const sg = W.sync + (active ? b : 0) * P.nsync;
+    const uint32_t pmask = (1u << P.pieces_shift) - 1u;
+    for (uint32_t i = tid; i < P.nsync; i += TEAM) {
+        const uint32_t t = i >> P.pieces_shift;
+        const uint32_t f = L.blk[t], n = L.blk[t + 1u] - f;
+        const uint32_t r = f + (((i & pmask) * n) >> P.pieces_shift);
+        uint32_t entry = total;
+        if (r < nnz) {
+            const uint32_t owner = r / per;
+            uint32_t q0 = owner * per, pos = L.run_off[owner];
+            int q = q0 ? (int)L.rec[q0 - 1u] : -1;
+            for (; q0 < r; ++q0) {
+                const int e = (int)L.rec[q0];
+                uint32_t len;
+                record((uint32_t)(e - q), (uint32_t)qbytes[e], len);
+                pos += len;
+                q = e;
+            }
+            entry = pos | ((n ? (uint32_t)L.rec[r] - (t << kSyncBlockShift) : 0u) << 21);
+        }
+        if (active)
+            sg[i] = entry;
+    }
+    if (active) {
+        if (in_lds)
+            store_bucket<TEAM>(P, b, slot, L.out, nwords, total, tid);
+        else if (tid == 0)
+            P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
+    }
+}
+
+// Steps (2) and (3), teams of a wave or less: around ten records per thread, each looked up once and kept as one word.
+// A bucket is one block of the index and has at most one entry per thread.  While records are emitted, a record's place in
+// the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 26 bits), so the thread
+// of entry i reads its record's index before and its offset after.
+template <int TEAM>
+__device__ __forceinline__ void code_listed_small(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+                                                  const TeamLds &L, uint32_t nnz, uint32_t *slot)
+{
+    const uint32_t tid = threadIdx.x % TEAM;
+    const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
+    const auto record = make_records<TEAM>(L.tables, P.s);
+    const uint32_t per = (nnz + TEAM - 1u) / TEAM;
+    const uint32_t r0 = min(tid * per, nnz), r1 = min(r0 + per, nnz);
+    constexpr uint32_t kKept = 12;
+    uint32_t kept[kKept], bits = 0;
+    uint16_t *const run = L.rec + r0;
+    const uint32_t n = r1 - r0;
+    int p = r0 ? (int)run[-1] : -1;
+#pragma unroll
+    for (uint32_t i = 0; i < kKept; ++i) {
+        kept[i] = 0;
+        if (i < n) {
+            const int e = (int)run[i];
+            kept[i] = record.packed((uint32_t)(e - p), (uint32_t)qbytes[e]);
+            bits += kept[i] >> 27;
+            p = e;
+        }
+    }
+    const int p_kept = p;
+    for (uint32_t i = kKept; i < n; ++i) {
+        const int e = (int)run[i];
+        bits += record.packed((uint32_t)(e - p), (uint32_t)qbytes[e]) >> 27;
+        p = e;
+    }
+    uint32_t total;
+    const uint32_t off0 = team_exclusive_sum<TEAM>(bits, nullptr, total);
+    const uint32_t nwords = (total + 31u) >> 5;
+    const bool in_lds = nwords <= P.out_cap;                     // uniform over the team
+    const bool entry = tid < P.nsync && nnz;
+    const uint32_t r_entry = (tid * nnz) >> P.pieces_shift;      // < nnz for an entry
+    const uint32_t e_entry = entry ? (uint32_t)L.rec[r_entry] : 0u;
+    if (in_lds) {
+        for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
+            *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
+    } else if (active) {
+        for (uint32_t i = tid; i < nwords; i += TEAM)
+            slot[i] = 0u;
+        __threadfence();       // the zeros are in place before any record is OR-ed over them
+    }
+    team_barrier<TEAM>();
+    auto emit_all = [&](uint32_t *dst) {
+        BitWriter w(off0);
+        uint32_t t = off0;
+#pragma unroll
+        for (uint32_t i = 0; i < kKept; ++i)
+            if (kept[i]) {
+                run[i] = (uint16_t)t;
+                const uint32_t len = kept[i] >> 27;
+                t += len;
+                w.put(dst, kept[i] & 0x7ffffffu, len);
+            }
+        int q = p_kept;
+        for (uint32_t i = kKept; i < n; ++i) {
+            const int e = (int)run[i];
+            uint32_t len;
+            const uint32_t rb = record((uint32_t)(e - q), (uint32_t)qbytes[e], len);
+            run[i] = (uint16_t)t;
+            t += len;
+            w.put(dst, rb, len);
+            q = e;
+        }
+        if (n)
+            w.flush(dst);
+    };
+    if (in_lds)
+        emit_all(L.out);
+    else if (active)
+        emit_all(slot);
+    team_barrier<TEAM>();
+    if (active) {
+        if (tid < P.nsync)
+            W.sync[b * P.nsync + tid] = entry ? (uint32_t)L.rec[r_entry] | (e_entry << 21) : 0u;
+        if (in_lds)
+            store_bucket<TEAM>(P, b, slot, L.out, nwords, total, tid);
+        else if (tid == 0)
+            P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
+    }
+}
+
+template <int TEAM, int VPT>
+__device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+                                                const TeamLds &L)
+{
+    const uint32_t tid = threadIdx.x % TEAM;
+    const uint32_t rows = P.rows;
+    Chunk C;
+    C.base = tid * rows * 4u;
+
+    // (1) nonzero mask of this thread's chunk (rows <= VPT <= 16 words: two 32-bit halves), ranks, compaction.  The mask of
+    // two words is the byte dot products of their flags with 1, 2, 4, 8 and 16, 32, 64, 128, shifted left by 6.
+    static_assert(VPT % 8 == 0 && VPT <= 16, "the chunk's mask is 64 bits");
+    uint32_t half[2] = {0, 0};
+#pragma unroll
+    for (int w = 0; w < VPT; w += 2) {
+        if ((uint32_t)w < rows) {
+            const uint32_t *q = L.qb32 + tid * rows + (uint32_t)w;
+            uint32_t m = __builtin_amdgcn_udot4(q[0] & 0x40404040u, 0x08040201u, 0u, false);
+            if ((uint32_t)w + 1u < rows)
+                m = __builtin_amdgcn_udot4(q[1] & 0x40404040u, 0x80402010u, m, false);
+            half[w / 8] |= (w % 8 == 0 ? m >> 6 : m << (4 * (w % 8) - 6));
+        }
+    }
+    C.nz = ((uint64_t)half[1] << 32) | half[0];
+    C.rank0 = team_exclusive_sum<TEAM, false>((uint32_t)(__popc(half[0]) + __popc(half[1])), L.scratch, C.nnz);
+    const bool listed = C.nnz <= P.rec_cap;        // uniform over the team
+    if (P.nsync && (!kSmallTeam<TEAM> || !listed)) {
+        // blk[t] = records before block t of the decoder index: the thread whose chunk holds the block's first
+        // coordinate counts its own nonzeros below it (every block starts inside exactly one chunk)
+        constexpr uint32_t kBlock = 1u << kSyncBlockShift;
+        const uint32_t c = (C.base + kBlock - 1u) & ~(kBlock - 1u);
+        const uint32_t t = c >> kSyncBlockShift;
+        if (c < C.base + rows * 4u && t < P.nblk) {
+            const uint32_t sh = c - C.base;                                  // < 64
+            const uint64_t below = sh ? C.nz & (~0ull >> (64u - sh)) : 0ull;
+            L.blk[t] = C.rank0 + (uint32_t)__popcll((unsigned long long)below);
+        }
+        if (tid == 0)
+            L.blk[P.nblk] = C.nnz;
+    }
+    const uint64_t gb = (uint64_t)blockIdx.y * P.nb + b;         // bucket index over the whole batch
+    uint32_t *const slot = P.staging + (active ? gb : 0) * P.slot_words;
+    if (listed) {
+        uint16_t *r = L.rec + C.rank0;
+        auto list = [&](uint32_t m, uint32_t at) {
+            while (m) {
+                *r++ = (uint16_t)(at + (uint32_t)__builtin_ctz(m));
+                m &= m - 1u;
+            }
+        };
+        list(half[0], C.base);
+        if constexpr (VPT > 8)
+            list(half[1], C.base + 32u);
+        if constexpr (!kSmallTeam<TEAM>)
+            for (uint32_t i = 4u * tid; i < P.out_cap; i += 4u * TEAM)
+                *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
+        team_barrier<TEAM>();
+        if constexpr (kSmallTeam<TEAM>)
+            code_listed_small<TEAM>(P, W, active, b, L, C.nnz, slot);
+        else
+            code_listed_large<TEAM>(P, W, active, b, L, C.nnz, slot);
+    } else {
+        team_barrier<TEAM>();
+        code_unlisted<TEAM>(P, W, active, b, L, C, slot);
+    }
+}
+
+// What a team's LDS holds of a bucket's nonzero list and bit string.  Large buckets: a quarter of the worst case (about
+// four times what a Gaussian gradient produces).  Up to 512 coordinates: five nonzeros in eight (gradients: one in four),
+// which lets five workgroups of 16 buckets share a CU.
 __host__ __device__ inline uint32_t team_rec_cap(uint32_t bucket)
 {
     const uint32_t quarter = bucket / 4u;
-    return bucket <= 1024u ? bucket : (quarter > 1024u ? quarter : 1024u);
+    return bucket <= 512u ? (bucket * 5u / 8u + 7u) & ~7u : bucket <= 1024u ? bucket : (quarter > 1024u ? quarter : 1024u);
 }
-__host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words)
+__host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words)       // a multiple of 4, like slot_words
 {
-    const uint32_t quarter = slot_words / 4u;
+    const uint32_t quarter = (slot_words / 4u + 3u) & ~3u;
     return slot_words <= 256u ? slot_words : (quarter > 256u ? quarter : 256u);
 }
 
-// LDS carve-up per team (in 32-bit words): [qb32: rows*TEAM][rec: rec_cap/2 (u16 per listed nonzero)]
-// [out: out_cap + 1][sync: nsync][blk: nblk + 1][run_off: TEAM][scratch: 64 (16 uints, 16 ints, 16 uints, 8 doubles)];
-// the workgroup's two 256-entry code tables follow the last team.
-__host__ __device__ inline uint32_t team_lds_words(uint32_t rows, uint32_t team, uint32_t rec_cap, uint32_t out_cap,
+// Offsets of a team's LDS regions (see TeamLds), in words; `words` in all, a multiple of 4.  The workgroup's code tables
+// follow the last team.
+struct TeamLdsMap {
+    uint32_t rec, out, sync, blk, run_off, scratch, words;
+};
+__host__ __device__ inline TeamLdsMap team_lds_map(uint32_t rows, uint32_t team, uint32_t rec_cap, uint32_t out_cap,
                                                    uint32_t nsync, uint32_t nblk)
 {
-    uint32_t w = rows * team + (rec_cap + 1u) / 2u + out_cap + 1u + nsync + nblk + 1u + team;
-    w = (w + 1u) & ~1u;   // keep the scratch 8-byte aligned
-    return w + 64u;
+    TeamLdsMap m;
+    m.rec = rows * team;
+    m.out = m.rec + (((rec_cap + 1u) / 2u + 3u) & ~3u);
+    m.sync = m.out + out_cap;
+    m.blk = m.sync + nsync;
+    m.run_off = m.blk + nblk + 1u;
+    m.scratch = (m.run_off + (team > (uint32_t)kWave ? team : 0u) + 1u) & ~1u;      // 8-byte aligned
+    m.words = (m.scratch + (team > (uint32_t)kWave ? 64u : 0u) + 3u) & ~3u;         // small teams need no scratch
+    return m;
 }
 
 // Front of the fused kernels: the bucket's coordinates into registers (v is read once), its norm (written to
-// norms_out), the quantizer; put(i, word) takes the level|sign bytes of the thread's row i < P.rows (coordinates
+// norms_out), the quantizer; put(i, word) takes the bytes (format F) of the thread's row i < P.rows (coordinates
 // 4 * (i * TEAM + tid) .. + 3), rows in ascending order.  lds: TEAM words per team that put may be the next to write.
-template <int TEAM, int VPT, class Put>
+template <int TEAM, int VPT, class F, class Put>
 __device__ __forceinline__ void front_quantize(const EncodeParams &P, const EncodeWorker &W, uint64_t b, bool active,
                                                uint64_t base, uint32_t nbk, uint32_t tid, uint32_t *lds,
-                                               uint32_t *scratch, Put put)
+                                               uint32_t *scratch, const F &fmt, Put put)
 {
     float4 x[VPT];
     const uint64_t wg_base = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG * P.bucket;
@@ -795,17 +981,17 @@ __device__ __forceinline__ void front_quantize(const EncodeParams &P, const Enco
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
         if ((uint32_t)i < P.rows)
-            put(i, B.dead ? 0u : quantize_vec4(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, B));
+            put(i, B.dead ? 0u : quantize_vec4(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, B, fmt));
     }
 }
 
 // The same with the bytes into the team's LDS words qb32[rows * TEAM].
-template <int TEAM, int VPT>
+template <int TEAM, int VPT, class F>
 __device__ __forceinline__ void front_quantize_to_lds(const EncodeParams &P, const EncodeWorker &W, uint64_t b,
                                                       bool active, uint64_t base, uint32_t nbk, uint32_t tid,
-                                                      uint32_t *qb32, uint32_t *scratch)
+                                                      uint32_t *qb32, uint32_t *scratch, const F &fmt)
 {
-    front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch,
+    front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, fmt,
                               [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
 }
 
@@ -845,10 +1031,10 @@ __device__ __forceinline__ void front_bytes_to_lds(const EncodeParams &P, const 
 // Front of the fused kernels for an arbitrary level table T and the norm P.norm_linf selects: as front_quantize, with
 // quantize_table_vec4 on the bucket's bins (kept in LDS).  put may be called a second time for a row (a row decided
 // again): the last call counts.
-template <int TEAM, int VPT, class Put>
+template <int TEAM, int VPT, class F, class Put>
 __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, const EncodeWorker &W, const LevelTable &T,
                                                      uint64_t b, bool active, uint64_t base, uint32_t nbk,
-                                                     uint32_t tid, uint32_t *lds, uint32_t *scratch, Put put)
+                                                     uint32_t tid, uint32_t *lds, uint32_t *scratch, const F &fmt, Put put)
 {
     __shared__ TableBins bins_all[TeamGeom<TEAM>::kTeamsPerWG];
     TableBins &bins = bins_all[threadIdx.x / TEAM];
@@ -890,7 +1076,7 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
         if ((uint32_t)i < P.rows) {
             bool again;
             const uint32_t q =
-                quantize_table_vec4<TEAM>(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, R, again);
+                quantize_table_vec4<TEAM>(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, R, fmt, again);
             put(i, dead ? 0u : q);
             redo |= (again ? 1u : 0u) << i;
         }
@@ -902,17 +1088,18 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
         redo &= redo - 1u;
         const uint32_t vi = (uint32_t)i * TEAM + tid;
         const uint32_t q = quantize_table_vec4_exact(load_vec4(vb, vi, nbk), key.k0 + 4u * vi, key.k1,
-                                                     bins.edge, bins.edge[1], P.s);
+                                                     bins.edge, bins.edge[1], P.s, fmt);
         put(i, dead ? 0u : q);
     }
 }
 
-template <int TEAM, int VPT>
+template <int TEAM, int VPT, class F>
 __device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &P, const EncodeWorker &W,
                                                             const LevelTable &T, uint64_t b, bool active, uint64_t base,
-                                                            uint32_t nbk, uint32_t tid, uint32_t *qb32, uint32_t *scratch)
+                                                            uint32_t nbk, uint32_t tid, uint32_t *qb32, uint32_t *scratch,
+                                                            const F &fmt)
 {
-    front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, qb32, scratch,
+    front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, qb32, scratch, fmt,
                                     [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
 }
 
@@ -925,35 +1112,30 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
     const uint32_t team = team_uniform_u32<TEAM>(threadIdx.x / TEAM);   // a scalar unless a wave holds four teams
-    uint32_t *lds = smem + team * P.lds_words;
-    uint32_t *qb32 = lds;
-    uint16_t *rec = reinterpret_cast<uint16_t *>(qb32 + P.rows * TEAM);
-    uint32_t *out = qb32 + P.rows * TEAM + (P.rec_cap + 1u) / 2u;
-    uint32_t *sync_l = out + P.out_cap + 1u;
-    uint32_t *blk = sync_l + P.nsync;
-    uint32_t *run_off = blk + P.nblk + 1u;
-    uint32_t *scratch = lds + P.lds_words - 64u;
-    uint32_t *erc_lut = smem + TeamGeom<TEAM>::kTeamsPerWG * P.lds_words;
-    uint32_t *tail_lut = erc_lut + 256;
-    if (threadIdx.x < 256u) {
-        erc_lut[threadIdx.x] = kErcTable.v[threadIdx.x];
-        tail_lut[threadIdx.x] = kTailTable.v[threadIdx.x];
-    }
+    const TeamLdsMap map = team_lds_map(P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk);
+    uint32_t *const lds = smem + team * map.words;
+    uint32_t *const tables = smem + TeamGeom<TEAM>::kTeamsPerWG * map.words;
+    const TeamLds L{lds, reinterpret_cast<uint16_t *>(lds + map.rec), lds + map.out, lds + map.sync, lds + map.blk,
+                    lds + map.run_off, lds + map.scratch, tables};
+    load_code_tables<TEAM>(tables, P.s);
 
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + team;
     const bool active = b < P.nb;
     const uint64_t base = active ? b * P.bucket : 0;
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
 
+    const FlagBytes fmt = flag_bytes<TEAM>(P.s);
     if constexpr (MODE == 2) {
-        front_quantize_table_to_lds<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, qb32, scratch);
+        front_quantize_table_to_lds<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, L.qb32, L.scratch, fmt);
     } else if constexpr (MODE == 0) {
-        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch);
+        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, L.qb32, L.scratch, fmt);
     } else {
-        front_bytes_to_lds<TEAM, VPT>(P, W, base, nbk, tid, qb32);
+        front_bytes<TEAM, VPT>(P, W, base, nbk, tid, [&](int i, uint32_t w) {
+            L.qb32[(uint32_t)i * TEAM + tid] = fmt.any(w, w & 0x7f7f7f7fu);
+        });
     }
     __syncthreads();
-    encode_from_lds<TEAM, VPT>(P, W, active, b, qb32, out, rec, erc_lut, tail_lut, sync_l, blk, run_off, scratch);
+    encode_from_lds<TEAM, VPT>(P, W, active, b, L);
 }
 
 // ------------------------------------------------- offsets and gather of the slots

@@ -64,9 +64,9 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize_table(EncodePa
         const bool mine = e0 < nbk;                     // lanes beyond the bucket's end run along with zeros
         const float4 x = mine ? load_vec4(vb, vi, nbk) : float4{0.f, 0.f, 0.f, 0.f};
         bool again;
-        uint32_t packed = quantize_table_vec4<TEAM>(x, (key.k0 + e0) * kRngC1, key.k1, R, again);
+        uint32_t packed = quantize_table_vec4<TEAM>(x, (key.k0 + e0) * kRngC1, key.k1, R, PlainBytes{}, again);
         if (exact || again)
-            packed = quantize_table_vec4_exact(x, key.k0 + e0, key.k1, bins.edge, bins.edge[1], P.s);
+            packed = quantize_table_vec4_exact(x, key.k0 + e0, key.k1, bins.edge, bins.edge[1], P.s, PlainBytes{});
         packed = dead ? 0u : packed;
         if (mine) {
             if (qaligned && e0 + 3u < nbk) {

@@ -1,0 +1,52 @@
+"""ENCODE from crafted level|sign bytes at the edges of the coding phase, bit for bit against the oracle: one to sixteen
+rows per thread, the byte format on both sides of s = 7, gaps on both sides of the table's range, more records per thread
+than are kept in registers, exactly as many nonzeros as the index list holds and one more, bit strings on both sides of the
+buffer's size."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import gpu_util
+    return gpu_util
+
+
+@pytest.mark.parametrize("s", [3, 7, 8, 14])
+@pytest.mark.parametrize("n,S", [(512, 128), (512, 64), (500, 256), (60, 64), (64, 0), (1, 0), (17, 64), (2048, 64),
+                                 (1000, 128), (1021, 1024), (2049, 256), (8192, 256), (5000, 64), (16384, 128),
+                                 (20001, 512), (32768, 1024)])
+def test_crafted_bytes(g, n, S, s):
+    nuq = g.nuq
+    rng = np.random.default_rng(n * 16 + s)
+    cap = (n * 5 // 8 + 7) & ~7 if n <= 512 else n if n <= 1024 else max(n // 4, 1024)     # indices the list holds
+    counts = [n, min(n, cap), min(n, cap + 1), max(n // 4, 1), max(n // 15, 1), max(n // 40, 1), 1, 0, n // 2, n]
+    d = len(counts) * n - min(5, n - 1)
+    q = np.zeros(d, dtype=np.uint8)
+    for b, c in enumerate(counts):
+        lo, hi = b * n, min(d, (b + 1) * n)
+        at = rng.choice(hi - lo, size=min(c, hi - lo), replace=False)
+        lev = rng.integers(1, s + 2, size=at.size) if b % 3 else np.where(rng.random(at.size) < 0.9, 1, s + 1)
+        q[lo + at] = (lev | (rng.integers(0, 2, size=at.size) << 7)).astype(np.uint8)
+    if n >= 64:                                    # gaps of 15, 16, 31, 32, 33 and the largest there is
+        q[6 * n:7 * n] = 0
+        at = np.cumsum([1, 15, 16])
+        q[6 * n + at] = 1
+        if n >= 256:
+            q[6 * n + at[-1] + np.cumsum([31, 32, 33])] = s + 1
+        q[7 * n - 1] = 0x81
+    m = g.alloc_message(d, n, s, S)
+    nuq.nuq_encode(torch.from_numpy(q).to(g.DEV), n, s, S, m.bit_off, m.words, m.sync if nuq.nuq_num_sync(n, S) else None,
+                   g.workspace(d, n, s))
+    assert nuq.nuq_last_error_flags() == 0
+    bo, words, sync = oracle.encode(q, n, s, S)
+    np.testing.assert_array_equal(g.u64(m.bit_off), bo)
+    np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
+    assert not g.u32(m.words)[words.size:].any()
+    if sync.size:
+        np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
