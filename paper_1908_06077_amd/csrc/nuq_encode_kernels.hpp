@@ -64,17 +64,8 @@ struct TeamGeom {
     static constexpr int kTeamsPerWG = kWG / TEAM;
 };
 
-// A 16-byte load of data that is read once (gradients): non-temporal, so that the stream does not push the
-// staged bit strings, lengths and messages, which the next kernel reads, out of the caches.  Used by teams of a
-// wave or more (measured: 172 -> 164 us on 8192-coordinate buckets, 3 % on 16384); quarter-wave teams, whose loads
-// are 256-byte pieces, lose 5 % with it and keep plain loads.
-// Both loads take any 4-byte aligned address: the hardware does not ask for more, only the C++ types do.
+// A 16-byte load from any 4-byte aligned address: the hardware does not ask for more, only the C++ types do.
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ float4 load_once4(const float *p)
-{
-    const f32x4_any r = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any *>(p));
-    return float4{r.x, r.y, r.z, r.w};
-}
 __device__ __forceinline__ float4 load4(const float *p)
 {
     const f32x4_any r = *reinterpret_cast<const f32x4_any *>(p);
@@ -104,10 +95,15 @@ __device__ __forceinline__ float4 load_vec4(const float *vb, uint32_t vi, uint32
     return r;
 }
 
-// A bucket's rows into registers.  wg_base: the workgroup's first bucket (uniform), lane_off: coordinates from there to
+// A bucket's rows into registers.  Gradients are read once, so teams of a wave or more load them non-temporally: the
+// stream then does not push the staged bit strings, lengths and messages, which the next kernel reads, out of the caches
+// (172 -> 164 us on 8192-coordinate buckets, 3 % on 16384); quarter-wave teams, whose loads are 256-byte pieces, lose 5 %
+// with that and keep plain loads.  wg_base: the workgroup's first bucket (uniform), lane_off: coordinates from there to
 // the team's bucket.  The addresses of a full bucket are a uniform base per row (scalar registers; the empty asm keeps
 // the compiler from folding the row into the lanes' 64-bit addresses, two instructions per row and lane) plus one 32-bit
-// lane offset.
+// lane offset (in the global address space by type: behind the asm the compiler would have to assume a generic pointer).
+typedef const __attribute__((address_space(1))) char *GlobalBytes;
+typedef const __attribute__((address_space(1))) f32x4_any *GlobalFloat4;
 template <int TEAM, int VPT>
 __device__ __forceinline__ void load_rows(float4 (&x)[VPT], const float *wg_base, uint32_t lane_off, uint32_t nbk,
                                           uint32_t rows, uint32_t tid)
@@ -116,12 +112,14 @@ __device__ __forceinline__ void load_rows(float4 (&x)[VPT], const float *wg_base
         const uint32_t off = 4u * (lane_off + 4u * tid);                           // bytes, below 2^18
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
-            const char *row = reinterpret_cast<const char *>(wg_base + i * (4 * TEAM));
+            GlobalBytes row = (GlobalBytes)wg_base + i * (16 * TEAM);
             if constexpr (TEAM >= 64) {
                 asm("" : "+s"(row));
-                x[i] = load_once4(reinterpret_cast<const float *>(row + off));
+                const f32x4_any r = __builtin_nontemporal_load((GlobalFloat4)(row + off));
+                x[i] = float4{r.x, r.y, r.z, r.w};
             } else {
-                x[i] = load4(reinterpret_cast<const float *>(row + off));
+                const f32x4_any r = *(GlobalFloat4)(row + off);
+                x[i] = float4{r.x, r.y, r.z, r.w};
             }
         }
     } else {
@@ -438,15 +436,27 @@ __device__ __forceinline__ FlagBytes flag_bytes(uint32_t s)
         return FlagBytes{0u, 0x80808080u};
 }
 
+// The tables' way into LDS, in two halves: requested before the gradient's loads, stored when those are under way (a wait
+// for the tables before they are requested would start every workgroup with an idle round trip).
 template <int TEAM>
-__device__ __forceinline__ void load_code_tables(uint32_t *tables, uint32_t s)
-{
-    const uint32_t *src = kSmallTeam<TEAM> ? kCodeTables.small[s <= 7u ? 0 : 1] : kCodeTables.large;
-    if (threadIdx.x < 256u) {
-        tables[threadIdx.x] = src[threadIdx.x];
-        tables[256u + threadIdx.x] = src[256u + threadIdx.x];
+struct TableCopy {
+    uint32_t lo = 0, hi = 0;
+    __device__ __forceinline__ explicit TableCopy(uint32_t s)
+    {
+        const uint32_t *src = kSmallTeam<TEAM> ? kCodeTables.small[s <= 7u ? 0 : 1] : kCodeTables.large;
+        if (threadIdx.x < 256u) {
+            lo = src[threadIdx.x];
+            hi = src[256u + threadIdx.x];
+        }
     }
-}
+    __device__ __forceinline__ void store(uint32_t *tables) const
+    {
+        if (threadIdx.x < 256u) {
+            tables[threadIdx.x] = lo;
+            tables[256u + threadIdx.x] = hi;
+        }
+    }
+};
 
 // A record's bits (right-aligned) and length from its gap and byte.
 struct LargeRecords {
@@ -948,15 +958,17 @@ __host__ __device__ inline TeamLdsMap team_lds_map(uint32_t rows, uint32_t team,
 
 // Front of the fused kernels: the bucket's coordinates into registers (v is read once), its norm (written to
 // norms_out), the quantizer; put(i, word) takes the bytes (format F) of the thread's row i < P.rows (coordinates
-// 4 * (i * TEAM + tid) .. + 3), rows in ascending order.  lds: TEAM words per team that put may be the next to write.
-template <int TEAM, int VPT, class F, class Put>
+// 4 * (i * TEAM + tid) .. + 3), rows in ascending order; issued() is called once the loads are under way.  lds: TEAM words
+// per team that put may be the next to write.
+template <int TEAM, int VPT, class F, class Put, class Issued>
 __device__ __forceinline__ void front_quantize(const EncodeParams &P, const EncodeWorker &W, uint64_t b, bool active,
                                                uint64_t base, uint32_t nbk, uint32_t tid, uint32_t *lds,
-                                               uint32_t *scratch, const F &fmt, Put put)
+                                               uint32_t *scratch, const F &fmt, Put put, Issued issued)
 {
     float4 x[VPT];
     const uint64_t wg_base = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG * P.bucket;
     load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid);
+    issued();
     auto row = [&](int i) { return x[i]; };
     const float nrm = team_uniform_f32<TEAM>(
         team_norm<TEAM, VPT>(row, reinterpret_cast<float *>(lds), reinterpret_cast<double *>(scratch + 32)));
@@ -986,13 +998,14 @@ __device__ __forceinline__ void front_quantize(const EncodeParams &P, const Enco
 }
 
 // The same with the bytes into the team's LDS words qb32[rows * TEAM].
-template <int TEAM, int VPT, class F>
+template <int TEAM, int VPT, class F, class Issued>
 __device__ __forceinline__ void front_quantize_to_lds(const EncodeParams &P, const EncodeWorker &W, uint64_t b,
                                                       bool active, uint64_t base, uint32_t nbk, uint32_t tid,
-                                                      uint32_t *qb32, uint32_t *scratch, const F &fmt)
+                                                      uint32_t *qb32, uint32_t *scratch, const F &fmt,
+                                                      Issued issued)
 {
     front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, fmt,
-                              [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
+                              [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; }, issued);
 }
 
 // Front of the kernels that start from level|sign bytes: put(i, word) as for front_quantize, the bytes from q_in.
@@ -1031,10 +1044,11 @@ __device__ __forceinline__ void front_bytes_to_lds(const EncodeParams &P, const 
 // Front of the fused kernels for an arbitrary level table T and the norm P.norm_linf selects: as front_quantize, with
 // quantize_table_vec4 on the bucket's bins (kept in LDS).  put may be called a second time for a row (a row decided
 // again): the last call counts.
-template <int TEAM, int VPT, class F, class Put>
+template <int TEAM, int VPT, class F, class Put, class Issued>
 __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, const EncodeWorker &W, const LevelTable &T,
                                                      uint64_t b, bool active, uint64_t base, uint32_t nbk,
-                                                     uint32_t tid, uint32_t *lds, uint32_t *scratch, const F &fmt, Put put)
+                                                     uint32_t tid, uint32_t *lds, uint32_t *scratch, const F &fmt, Put put,
+                                                     Issued issued)
 {
     __shared__ TableBins bins_all[TeamGeom<TEAM>::kTeamsPerWG];
     TableBins &bins = bins_all[threadIdx.x / TEAM];
@@ -1042,6 +1056,7 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
     float4 x[VPT];
     const uint64_t wg_base = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG * P.bucket;
     load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid);
+    issued();
     float nrm;
     if (P.norm_linf) {
         uint32_t m = 0;
@@ -1093,14 +1108,14 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
     }
 }
 
-template <int TEAM, int VPT, class F>
+template <int TEAM, int VPT, class F, class Issued>
 __device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &P, const EncodeWorker &W,
                                                             const LevelTable &T, uint64_t b, bool active, uint64_t base,
                                                             uint32_t nbk, uint32_t tid, uint32_t *qb32, uint32_t *scratch,
-                                                            const F &fmt)
+                                                            const F &fmt, Issued issued)
 {
     front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, qb32, scratch, fmt,
-                                    [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; });
+                                    [&](int i, uint32_t word) { qb32[(uint32_t)i * TEAM + tid] = word; }, issued);
 }
 
 // MODE 0: fused norms + quantize + encode from v.  MODE 1: encode from level/sign bytes.  MODE 2: as 0 for the level
@@ -1117,7 +1132,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
     uint32_t *const tables = smem + TeamGeom<TEAM>::kTeamsPerWG * map.words;
     const TeamLds L{lds, reinterpret_cast<uint16_t *>(lds + map.rec), lds + map.out, lds + map.sync, lds + map.blk,
                     lds + map.run_off, lds + map.scratch, tables};
-    load_code_tables<TEAM>(tables, P.s);
+    const TableCopy<TEAM> copy(P.s);
 
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + team;
     const bool active = b < P.nb;
@@ -1125,11 +1140,13 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
 
     const FlagBytes fmt = flag_bytes<TEAM>(P.s);
+    auto loads_issued = [&] { copy.store(tables); };
     if constexpr (MODE == 2) {
-        front_quantize_table_to_lds<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, L.qb32, L.scratch, fmt);
+        front_quantize_table_to_lds<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, L.qb32, L.scratch, fmt, loads_issued);
     } else if constexpr (MODE == 0) {
-        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, L.qb32, L.scratch, fmt);
+        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, L.qb32, L.scratch, fmt, loads_issued);
     } else {
+        loads_issued();
         front_bytes<TEAM, VPT>(P, W, base, nbk, tid, [&](int i, uint32_t w) {
             L.qb32[(uint32_t)i * TEAM + tid] = fmt.any(w, w & 0x7f7f7f7fu);
         });

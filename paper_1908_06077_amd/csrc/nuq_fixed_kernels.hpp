@@ -43,9 +43,9 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_pack_fixed(EncodeParams
     for (uint32_t i = tid; i < F.wpb; i += TEAM)
         field[i] = 0u;
     if constexpr (MODE == 2)
-        front_quantize_table_to_lds<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, qb32, scratch, PlainBytes{});
+        front_quantize_table_to_lds<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, qb32, scratch, PlainBytes{}, [] {});
     else if constexpr (MODE == 0)
-        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, PlainBytes{});
+        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, PlainBytes{}, [] {});
     else
         front_bytes_to_lds<TEAM, VPT>(P, W, base, nbk, tid, qb32);
     __syncthreads();
@@ -130,9 +130,9 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_pack_fixed_direct(Encod
         }
     };
     if constexpr (MODE == 2)
-        front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, part, scratch, PlainBytes{}, put);
+        front_quantize_table<TEAM, VPT>(P, W, T, b, active, base, nbk, tid, part, scratch, PlainBytes{}, put, [] {});
     else if constexpr (MODE == 0)
-        front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, part, scratch, PlainBytes{}, put);
+        front_quantize<TEAM, VPT>(P, W, b, active, base, nbk, tid, part, scratch, PlainBytes{}, put, [] {});
     else
         front_bytes<TEAM, VPT>(P, W, base, nbk, tid, put);
     if constexpr (B == 4) {

@@ -239,7 +239,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
     __shared__ uint32_t enc[256];
     huffman_byte_table<TeamGeom<TEAM>::kWG>(H, enc);
-    front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, PlainBytes{});
+    front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, PlainBytes{}, [] {});
     __syncthreads();
     const uint32_t total = huffman_from_lds<TEAM>(P, enc, qb32, field, sync_l, scratch, nbk, tid);
     const uint32_t nwords = (total + 31u) >> 5;
