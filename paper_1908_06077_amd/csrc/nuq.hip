@@ -145,7 +145,7 @@ uint32_t slot_words_for(uint32_t bucket, uint32_t s)
 }
 
 struct Workspace {
-    uint32_t *lens;
+    uint32_t *units;
     uint64_t *chunk_sums;
     uint32_t *staging;
     uint64_t bytes;
@@ -158,7 +158,7 @@ Workspace carve(void *base, uint32_t K, uint64_t nb, uint32_t slot_words)
     uint64_t off = 0;
     Workspace w;
     char *p = static_cast<char *>(base);
-    w.lens = reinterpret_cast<uint32_t *>(p + off);
+    w.units = reinterpret_cast<uint32_t *>(p + off);
     off += up((uint64_t)K * ((nb + 3) & ~3ull) * 4);
     w.chunk_sums = reinterpret_cast<uint64_t *>(p + off);
     off += up((uint64_t)K * (nchunks + 1) * 8);
@@ -199,31 +199,50 @@ bool bucket_grid(uint64_t nb, uint32_t K, dim3 &grid)
     return true;
 }
 
-// Offsets and gather: lens and staging slots of K workers into their bit_off and words.
+// Offsets and gather: lengths and staging slots of K workers into their bit_off and words.
+template <uint32_t FB, uint32_t WG>
+int launch_finish_as(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, const uint64_t *prefix, uint64_t nchunks,
+                     uint32_t groups, uint32_t unit_shift, hipStream_t st)
+{
+    const uint64_t span = (uint64_t)FB * groups;
+    hipLaunchKernelGGL((k_finish<FB, WG>), dim3((uint32_t)((P.nb + span - 1) / span), K), dim3(WG), 0, st, P, Wk, prefix,
+                       nchunks, groups, unit_shift);
+    return check_launch();
+}
+
 int launch_finish(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, const Workspace &w, hipStream_t st)
 {
-    const uint64_t nb = P.nb;
-    const uint64_t nchunks = (nb + kChunk - 1) / kChunk;
+    // buckets per workgroup of the encoder
+    uint32_t unit_shift = 0;
+    (void)dispatch_team(P.bucket, [&](auto team_c, auto) {
+        unit_shift = log2u(TeamGeom<decltype(team_c)::value>::kTeamsPerWG);
+        return (int)NUQ_OK;
+    });
+    const uint64_t units = (P.nb + (1ull << unit_shift) - 1) >> unit_shift;
+    const uint64_t nchunks = (units + kChunk - 1) / kChunk;
     const uint64_t *prefix = nullptr;
-    if (nb > kDirectSumMax) {
-        hipLaunchKernelGGL(k_chunk_sums, dim3((uint32_t)nchunks, K), dim3(256), 0, st, w.lens, nb, P.nb_stride,
+    if (units > kDirectSumMax) {
+        hipLaunchKernelGGL(k_chunk_sums<false>, dim3((uint32_t)nchunks, K), dim3(256), 0, st, w.units, units, P.nb_stride,
                            nchunks, w.chunk_sums);
         hipLaunchKernelGGL(k_chunk_scan, dim3(K), dim3(256), 0, st, w.chunk_sums, nchunks);
         prefix = w.chunk_sums;
     }
-    const uint32_t fb = finish_buckets(P.bucket);
-    // groups of fb buckets per workgroup: one where there are few (every workgroup slot of the chip gets work), up
-    // to 8 where there are many (the sum of the lengths before a workgroup's first bucket is then paid once per 8)
-    const uint64_t ngroups = (nb + fb - 1) / fb;
-    const uint32_t per_wg = (uint32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, ngroups * K / 16384));
-    const dim3 fgrid((uint32_t)((ngroups + per_wg - 1) / per_wg), K);
-    if (fb == 64u && per_wg > 1u)        // many small groups: one wave per workgroup, four times the groups in flight
-        hipLaunchKernelGGL((k_finish<64, 64>), fgrid, dim3(64), 0, st, P, Wk, prefix, nchunks, per_wg);
-    else if (fb == 64u)
-        hipLaunchKernelGGL((k_finish<64, 256>), fgrid, dim3(256), 0, st, P, Wk, prefix, nchunks, per_wg);
-    else
-        hipLaunchKernelGGL((k_finish<16, 256>), fgrid, dim3(256), 0, st, P, Wk, prefix, nchunks, per_wg);
-    return check_launch();
+    // Buckets per workgroup: 4 where there are few buckets (1427 of 8192 coordinates: 11.2 us with 16, 4.2 with 4; 24960 of
+    // them: 9.2 with 16, 13.6 with 4, whose sums over the units before cost more than the copy), but at least a unit; 64
+    // small ones where that still gives a chip's worth of workgroups, so that there is something to copy.  Very many small
+    // buckets: one wave per workgroup (four times the groups in flight) and up to eight groups each (the sum before the
+    // first is paid once).
+    const uint64_t small_groups = (P.nb + 63) / 64 * K;
+    if (P.bucket <= 1024u && small_groups >= 2u * 16384u)
+        return launch_finish_as<64, 64>(P, Wk, K, prefix, nchunks, (uint32_t)std::min<uint64_t>(8, small_groups / 16384),
+                                        unit_shift, st);
+    if (P.bucket <= 1024u && small_groups >= 1024u)
+        return launch_finish_as<64, 256>(P, Wk, K, prefix, nchunks, 1, unit_shift, st);
+    if (unit_shift <= 2u && P.nb * K < 16u * 1024u)
+        return launch_finish_as<4, 256>(P, Wk, K, prefix, nchunks, 1, unit_shift, st);
+    return launch_finish_as<16, 256>(P, Wk, K, prefix, nchunks,
+                                     (uint32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, (P.nb + 15) / 16 * K / 16384)),
+                                     unit_shift, st);
 }
 
 // MODE 0: fused norms + quantize + ENCODE from v.  MODE 1: ENCODE from level/sign bytes.  MODE 2: as 0 with the
@@ -273,7 +292,7 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     P.pieces_shift = nsync ? sync_pieces_shift(bucket, sync_stride) : 0;
     P.nblk = sync_blocks(bucket);
     P.slot_words = slot_words;
-    P.lens = w.lens;
+    P.units = w.units;
     P.staging = w.staging;
     P.flags = flags;
     P.norm_linf = norm_kind == NUQ_NORM_LINF ? 1u : 0u;
@@ -411,7 +430,7 @@ bool huffman_tables(const uint8_t *lengths, uint32_t s, HuffmanCode &H)
 }
 
 struct HuffmanWorkspace {
-    uint32_t *lens;
+    uint32_t *units;       // bucket bit lengths
     uint64_t *chunk_sums;
     uint64_t bytes;
 };
@@ -421,7 +440,7 @@ HuffmanWorkspace carve_huffman(void *base, uint64_t nb)
     HuffmanWorkspace w{};
     const uint64_t nb_stride = (nb + 3) & ~3ull, nchunks = (nb + kChunk - 1) / kChunk;
     uint8_t *p = static_cast<uint8_t *>(base);
-    w.lens = reinterpret_cast<uint32_t *>(p);
+    w.units = reinterpret_cast<uint32_t *>(p);
     uint64_t off = (nb_stride * 4 + 15) & ~15ull;
     w.chunk_sums = reinterpret_cast<uint64_t *>(p + off);
     off += (nchunks + 1) * 8;
@@ -1112,7 +1131,7 @@ int nuq_encode_huffman(const uint8_t *q, uint64_t d, uint32_t bucket, uint32_t s
     P.s = s;
     P.sync_shift = nsync ? log2u(sync_stride) : 0;
     P.nsync = nsync;
-    P.lens = w.lens;
+    P.units = w.units;
     P.flags = flags;
     const uint64_t nchunks = (nb + kChunk - 1) / kChunk;
     return dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
@@ -1132,10 +1151,10 @@ int nuq_encode_huffman(const uint8_t *q, uint64_t d, uint32_t bucket, uint32_t s
         if (!bucket_grid<TEAM>(nb, 1, grid))
             return (int)NUQ_EINVAL;
         hipLaunchKernelGGL((k_huffman_lens<TEAM, VPT>), grid, dim3(G::kWG), 0, st, P, Wk, H);
-        hipLaunchKernelGGL(k_chunk_sums, dim3((uint32_t)nchunks, 1), dim3(256), 0, st, w.lens, nb, P.nb_stride, nchunks,
+        hipLaunchKernelGGL(k_chunk_sums<true>, dim3((uint32_t)nchunks, 1), dim3(256), 0, st, w.units, nb, P.nb_stride, nchunks,
                            w.chunk_sums);
         hipLaunchKernelGGL(k_chunk_scan, dim3(1), dim3(256), 0, st, w.chunk_sums, nchunks);
-        hipLaunchKernelGGL(k_bit_offsets, dim3((uint32_t)nchunks), dim3(256), 0, st, w.lens, nb, w.chunk_sums, bit_off);
+        hipLaunchKernelGGL(k_bit_offsets, dim3((uint32_t)nchunks), dim3(256), 0, st, w.units, nb, w.chunk_sums, bit_off);
         ScopedTiming timing(NUQ_T_ENCODE, st);
         hipLaunchKernelGGL(emit, grid, dim3(G::kWG), lds_bytes, st, P, Wk, H);
         return check_launch();
@@ -1203,7 +1222,7 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
     P.nsync = nsync;
     P.slot_words = slot_words;
     P.out_cap = slot_words;
-    P.lens = w.lens;
+    P.units = w.units;
     P.staging = w.staging;
     P.flags = flags;
     int rc = dispatch_team(bucket, [&](auto team_c, auto vpt_c) {

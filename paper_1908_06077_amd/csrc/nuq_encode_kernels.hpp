@@ -51,8 +51,8 @@ struct EncodeParams {
     uint32_t lds_words;    // LDS words per team (kernels that do not work theirs out)
     uint32_t rec_cap;      // nonzeros of a bucket whose indices fit the team's LDS list
     uint32_t out_cap;      // words of a bucket's bit string that fit the team's LDS buffer
-    uint64_t nb_stride;    // nb rounded up to a multiple of 4: stride between workers in lens
-    uint32_t *lens;        // [K * nb_stride] payload bits per bucket, worker-major
+    uint64_t nb_stride;    // nb rounded up to a multiple of 4: stride between workers in units
+    uint32_t *units;       // [K * nb_stride] words of bit string per workgroup of the encoder, worker-major (see k_finish)
     uint32_t *staging;     // [K * nb * slot_words]
     uint32_t *flags;
     uint32_t norm_linf;    // level-table mode: 0 = Euclidean norm, 1 = maximum norm
@@ -355,7 +355,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
 //
 // On entry the team's bytes (FlagBytes) are in LDS (qb32, bytes at or beyond the bucket's length say "zero") and a
 // barrier has been passed.  Produces the bucket's bit string in LDS, copies it to the bucket's staging slot, writes its
-// bit length and its index entries.  Every thread of the workgroup must call it (it contains barriers).
+// index entries.  Every thread of the workgroup must call it (it contains barriers).
 //
 // Steps: (1) every thread finds the nonzeros of its contiguous chunk and the team compacts their indices into `rec` (a
 // prefix sum gives the ranks); (2) the records are dealt out evenly, a thread takes a contiguous run of them, looks up
@@ -564,22 +564,43 @@ struct Chunk {
     uint32_t nnz;          // records of the bucket
 };
 
-// Bit length and, with 16-byte stores, the bit string from LDS (zero up to a multiple of four words) to the bucket's slot.
+// The bit string from LDS (zero up to a multiple of four words) to the bucket's slot, with 16-byte stores.
 template <int TEAM>
-__device__ __forceinline__ void store_bucket(const EncodeParams &P, uint64_t b, uint32_t *slot, const uint32_t *out,
-                                             uint32_t nwords, uint32_t total, uint32_t tid)
+__device__ __forceinline__ void store_bucket(uint32_t *slot, const uint32_t *out, uint32_t nwords, uint32_t tid)
 {
     for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
         *reinterpret_cast<uint4 *>(slot + i) = *reinterpret_cast<const uint4 *>(out + i);
-    if (tid == 0)
-        P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
+}
+
+// What k_finish needs to know of an encoder's workgroup: every bucket's bit length, left in the place of its offset, and
+// the words of all its buckets.  Called by all threads; total: bit length of the team's bucket.
+template <int TEAM>
+__device__ __forceinline__ void report_lengths(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+                                               uint32_t total)
+{
+    const uint32_t tid = threadIdx.x % TEAM;
+    if (active && tid == 0)
+        W.bit_off[b + 1] = total;
+    uint32_t words = active ? (total + 31u) >> 5 : 0u;
+    if constexpr (TeamGeom<TEAM>::kTeamsPerWG > 1) {
+        __shared__ uint32_t team_words[TeamGeom<TEAM>::kTeamsPerWG];
+        if (tid == 0)
+            team_words[threadIdx.x / TEAM] = words;
+        __syncthreads();
+        words = 0;
+#pragma unroll
+        for (int i = 0; i < TeamGeom<TEAM>::kTeamsPerWG; ++i)
+            words += team_words[i];
+    }
+    if (threadIdx.x == 0)
+        P.units[(uint64_t)blockIdx.y * P.nb_stride + blockIdx.x] = words;
 }
 
 // Buckets with more nonzeros than the list holds: every thread codes the records of its own chunk, in two passes; the bit
 // string is assembled over the list's and the buffer's words together (the two regions are adjacent: three quarters of the
 // worst case for large buckets) if it fits there, else in the slot in global memory.
 template <int TEAM>
-__device__ __forceinline__ void code_unlisted(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+__device__ __forceinline__ uint32_t code_unlisted(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
                                               const TeamLds &L, const Chunk &C, uint32_t *slot)
 {
     const uint32_t tid = threadIdx.x % TEAM;
@@ -658,19 +679,16 @@ __device__ __forceinline__ void code_unlisted(const EncodeParams &P, const Encod
     else if (active)
         emit_all(slot);
     team_barrier<TEAM>();
-    if (active) {
-        if (in_lds)
-            store_bucket<TEAM>(P, b, slot, obuf, nwords, total, tid);
-        else if (tid == 0)
-            P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
-    }
+    if (active && in_lds)
+        store_bucket<TEAM>(slot, obuf, nwords, tid);
+    return total;
 }
 
 // Steps (2) and (3), teams of several waves: two or three records per thread.  The records' table entries, four of them
 // kept; the index entries are looked up from the entry's side (the run that holds the record starts at run_off[owner]; the
 // lengths of the records before it in that run are looked up again).
 template <int TEAM>
-__device__ __forceinline__ void code_listed_large(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+__device__ __forceinline__ uint32_t code_listed_large(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
                                                   const TeamLds &L, uint32_t nnz, uint32_t *slot)
 {
     const uint32_t tid = threadIdx.x % TEAM;
@@ -759,12 +777,9 @@ __device__ __forceinline__ void code_listed_large(const EncodeParams &P, const E
         if (active)
             sg[i] = entry;
     }
-    if (active) {
-        if (in_lds)
-            store_bucket<TEAM>(P, b, slot, L.out, nwords, total, tid);
-        else if (tid == 0)
-            P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
-    }
+    if (active && in_lds)
+        store_bucket<TEAM>(slot, L.out, nwords, tid);
+    return total;
 }
 
 // Steps (2) and (3), teams of a wave or less: around ten records per thread, each looked up once and kept as one word.
@@ -772,7 +787,7 @@ __device__ __forceinline__ void code_listed_large(const EncodeParams &P, const E
 // the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 26 bits), so the thread
 // of entry i reads its record's index before and its offset after.
 template <int TEAM>
-__device__ __forceinline__ void code_listed_small(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+__device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
                                                   const TeamLds &L, uint32_t nnz, uint32_t *slot)
 {
     const uint32_t tid = threadIdx.x % TEAM;
@@ -850,14 +865,14 @@ __device__ __forceinline__ void code_listed_small(const EncodeParams &P, const E
         if (tid < P.nsync)
             W.sync[b * P.nsync + tid] = entry ? (uint32_t)L.rec[r_entry] | (e_entry << 21) : 0u;
         if (in_lds)
-            store_bucket<TEAM>(P, b, slot, L.out, nwords, total, tid);
-        else if (tid == 0)
-            P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
+            store_bucket<TEAM>(slot, L.out, nwords, tid);
     }
+    return total;
 }
 
+// Returns the bucket's bit length.
 template <int TEAM, int VPT>
-__device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
+__device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
                                                 const TeamLds &L)
 {
     const uint32_t tid = threadIdx.x % TEAM;
@@ -914,12 +929,12 @@ __device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const Enc
                 *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
         team_barrier<TEAM>();
         if constexpr (kSmallTeam<TEAM>)
-            code_listed_small<TEAM>(P, W, active, b, L, C.nnz, slot);
+            return code_listed_small<TEAM>(P, W, active, b, L, C.nnz, slot);
         else
-            code_listed_large<TEAM>(P, W, active, b, L, C.nnz, slot);
+            return code_listed_large<TEAM>(P, W, active, b, L, C.nnz, slot);
     } else {
         team_barrier<TEAM>();
-        code_unlisted<TEAM>(P, W, active, b, L, C, slot);
+        return code_unlisted<TEAM>(P, W, active, b, L, C, slot);
     }
 }
 
@@ -1152,21 +1167,22 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
         });
     }
     __syncthreads();
-    encode_from_lds<TEAM, VPT>(P, W, active, b, L);
+    report_lengths<TEAM>(P, W, active, b, encode_from_lds<TEAM, VPT>(P, W, active, b, L));
 }
 
 // ------------------------------------------------- offsets and gather of the slots
 //
 // wc_b = ceil(len_b / 32) words per bucket; start word of bucket b = sum of wc over the worker's
 // earlier buckets; bit_off[b+1] = 32 * start_b + len_b.  One "finish" kernel per batch: a
-// workgroup owns FB consecutive buckets of one worker (16, or 64 where buckets are small, so
-// that a workgroup still has a few thousand words to move), sums the word counts before them
-// (directly, or from per-chunk prefix sums when the worker has many buckets), writes their
-// offsets and copies their staging slots to their place in `words`, one word per thread at
-// a time, the word's bucket found by bisection.
+// workgroup owns FB consecutive buckets of one worker, sums the words before them, writes their offsets and copies their
+// staging slots to their place in `words`.
+//
+// The encoder leaves len_b in bit_off[b+1] and, per workgroup of its own (1, 4 or 16 buckets: a unit), the words of its
+// buckets in `units`: the words before a group are a sum over units, taken directly or, for more than 8192 units, from
+// per-chunk prefix sums.
 
-constexpr uint32_t kChunk = 1024;          // buckets per chunk of the two-level sum
-constexpr uint64_t kDirectSumMax = 8192;   // up to this many buckets every workgroup sums directly
+constexpr uint32_t kChunk = 1024;          // units per chunk of the two-level sum
+constexpr uint64_t kDirectSumMax = 8192;   // up to this many units every workgroup sums directly
 
 __device__ __forceinline__ uint64_t block_sum_u64(uint64_t x, uint64_t *scratch /* 4 */)
 {
@@ -1180,17 +1196,19 @@ __device__ __forceinline__ uint64_t block_sum_u64(uint64_t x, uint64_t *scratch 
     return scratch[0] + scratch[1] + scratch[2] + scratch[3];
 }
 
-// chunk_sums[k * (nchunks + 1) + c] = words of worker k's buckets [c*1024, (c+1)*1024)
-__global__ __launch_bounds__(256) void k_chunk_sums(const uint32_t *lens, uint64_t nb, uint64_t nb_stride,
+// chunk_sums[k * (nchunks + 1) + c] = words of worker k's units [c*1024, (c+1)*1024).  kBits: the n values are bit lengths
+// of buckets, not words.
+template <bool kBits>
+__global__ __launch_bounds__(256) void k_chunk_sums(const uint32_t *units, uint64_t n, uint64_t stride,
                                                     uint64_t nchunks, uint64_t *chunk_sums)
 {
     __shared__ uint64_t scratch[4];
-    const uint32_t *l = lens + (uint64_t)blockIdx.y * nb_stride;
+    const uint32_t *u = units + (uint64_t)blockIdx.y * stride;
     const uint64_t i0 = (uint64_t)blockIdx.x * kChunk;
     uint64_t s = 0;
     for (uint32_t k = threadIdx.x; k < kChunk; k += 256u)
-        if (i0 + k < nb)
-            s += (l[i0 + k] + 31u) >> 5;
+        if (i0 + k < n)
+            s += kBits ? (u[i0 + k] + 31u) >> 5 : u[i0 + k];
     s = block_sum_u64(s, scratch);
     if (threadIdx.x == 0)
         chunk_sums[(uint64_t)blockIdx.y * (nchunks + 1) + blockIdx.x] = s;
@@ -1230,98 +1248,127 @@ __global__ __launch_bounds__(256) void k_chunk_scan(uint64_t *chunk_sums, uint64
     }
 }
 
-// Buckets per workgroup of k_finish.
-__host__ __device__ inline uint32_t finish_buckets(uint32_t bucket) { return bucket <= 1024u ? 64u : 16u; }
-
-// grid (ceil(nb / FB), K), FB = 16 or 64.  chunk_prefix == nullptr: sum the lengths of all earlier buckets directly.
+// grid (ceil(nb / (FB * groups)), K), FB = 4, 16 or 64 buckets per group, a multiple of the unit (2^unit_shift buckets).
+// chunk_prefix == nullptr: sum the units before the group directly.
+//
+// What bounds it is latency: a chain of dependent loads (lengths, then the strings they locate, and the units before the
+// group), each a round trip, in a kernel of a few microseconds.  So the lengths and the units are requested together, the
+// strings as soon as the lengths are there (their place in the slots does not depend on the sum), and everything moves in
+// pieces of four words (a bucket's last piece may be shorter; any 4-byte aligned address takes a 16-byte store), each
+// found by one bisection.
 template <uint32_t FB, uint32_t WG>
 __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, const uint64_t *chunk_prefix,
-                                                uint64_t nchunks, uint32_t groups)
+                                                uint64_t nchunks, uint32_t groups, uint32_t unit_shift)
 {
-    static_assert(FB == 16 || FB == 64, "one wave scans the workgroup's word counts");
+    static_assert(FB == 4 || FB == 16 || FB == 64, "one wave scans the group's word counts");
     static_assert(WG == 64 || WG == 256, "block_sum_u64 adds four waves");
     __shared__ uint64_t scratch[4];
     __shared__ uint32_t wstart[FB + 1];   // first word of each bucket, relative to the group's first
-    __shared__ uint32_t skip[FB];
+    __shared__ uint32_t pstart[FB + 1];   // first piece of each bucket
     const EncodeWorker &W = Wk.w[blockIdx.y];
-    const uint32_t *__restrict__ lens = P.lens + (uint64_t)blockIdx.y * P.nb_stride;
+    const uint32_t *__restrict__ units = P.units + (uint64_t)blockIdx.y * P.nb_stride;
     const uint32_t tid = threadIdx.x;
+    auto load_len = [&](uint64_t b0) {
+        return tid < FB && b0 + tid < P.nb ? (uint32_t)W.bit_off[b0 + tid + 1] : 0u;
+    };
 
     // A workgroup takes `groups` consecutive groups of FB buckets: the words before its first bucket are summed once
     // (from the chunk's start), after that the running total carries over from group to group.
     uint64_t b_first = (uint64_t)blockIdx.x * groups * FB;
+    uint32_t my_len = load_len(b_first);
+    const uint64_t u_first = b_first >> unit_shift;
     uint64_t lo = 0, base = 0;
     if (chunk_prefix) {
-        const uint64_t c = b_first / kChunk;
+        const uint64_t c = u_first / kChunk;
         lo = c * kChunk;
         base = chunk_prefix[(uint64_t)blockIdx.y * (nchunks + 1) + c];
     }
-    uint32_t part = 0;     // < 2^32: at most 8192 lengths of < 2^21 bits each are summed here
+    uint32_t part = 0;     // < 2^32: at most 8192 units of at most 2^16 words are summed here
     {
-        // lo and b_first are multiples of 16, so the range splits into aligned groups of four lengths
-        const uint4 *__restrict__ l4 = reinterpret_cast<const uint4 *>(lens + lo);
-        const uint32_t n4 = (uint32_t)((b_first - lo) >> 2);
+        const uint4 *__restrict__ u4 = reinterpret_cast<const uint4 *>(units + lo);
+        const uint32_t n = (uint32_t)(u_first - lo), n4 = n >> 2;
 #pragma unroll 4
         for (uint32_t i = tid; i < n4; i += WG) {
-            const uint4 v = l4[i];
-            part += ((v.x + 31u) >> 5) + ((v.y + 31u) >> 5) + ((v.z + 31u) >> 5) + ((v.w + 31u) >> 5);
+            const uint4 v = u4[i];
+            part += v.x + v.y + v.z + v.w;
         }
+        if (tid < (n & 3u))
+            part += units[lo + 4u * n4 + tid];
     }
-    if constexpr (WG == 64u) {            // one wave
-        uint64_t x = part;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1)
-            x += __shfl_xor((unsigned long long)x, off, kWave);
-        base += x;
-    } else {
-        base += block_sum_u64(part, scratch);
-    }
+    bool summed = false;
 
     for (uint32_t g = 0; g < groups && b_first < P.nb; ++g, b_first += FB) {
-        uint32_t my_len = 0;
-        if (tid < FB && b_first + tid < P.nb)
-            my_len = lens[b_first + tid];
-        if (tid < kWave) {                      // the first wave: inclusive scan of the word counts
-            uint32_t inc = tid < FB ? (my_len + 31u) >> 5 : 0u;
-#pragma unroll
-            for (int off = 1; off < (int)FB; off <<= 1) {
-                const uint32_t t = (uint32_t)__shfl_up((int)inc, off, kWave);
-                if ((int)tid >= off)
-                    inc += t;
+        if (tid < kWave) {                      // the first wave: inclusive scans of the word and piece counts
+            const uint32_t words = (my_len + 31u) >> 5;
+            const uint32_t wi = wave_inclusive_sum(words), pi = wave_inclusive_sum((words + 3u) >> 2);
+            if (tid < FB) {
+                wstart[tid + 1] = wi;
+                pstart[tid + 1] = pi;
             }
-            if (tid < FB)
-                wstart[tid + 1] = inc;
             if (tid == 0)
-                wstart[0] = 0;
+                wstart[0] = pstart[0] = 0;
         }
         __syncthreads();
+        const uint32_t len = my_len;
+        if (g + 1u < groups)
+            my_len = load_len(b_first + FB);
+        const uint32_t total = pstart[FB];
+        const uint32_t *__restrict__ staging = P.staging + ((uint64_t)blockIdx.y * P.nb + b_first) * P.slot_words;
+        constexpr uint32_t kFlight = 4;         // pieces per thread under way at once
+        for (uint32_t p0 = tid; !summed || p0 < total; p0 += kFlight * WG) {
+            uint4 x[kFlight];
+            uint32_t bkt[kFlight], at[kFlight];
+#pragma unroll
+            for (uint32_t q = 0; q < kFlight; ++q) {
+                const uint32_t p = p0 + q * WG;
+                uint32_t j = 0;
+#pragma unroll
+                for (uint32_t step = FB / 2; step >= 1; step >>= 1)
+                    j += (pstart[j + step] <= p) ? step : 0u;
+                bkt[q] = j;
+                at[q] = 4u * (p - pstart[j]);
+                if (p < total)
+                    x[q] = *reinterpret_cast<const uint4 *>(staging + (uint64_t)j * P.slot_words + at[q]);
+            }
+            if (!summed) {                      // (once, with the first pieces under way)
+                if constexpr (WG == 64u) {
+                    uint64_t y = part;
+#pragma unroll
+                    for (int off = 32; off >= 1; off >>= 1)
+                        y += __shfl_xor((unsigned long long)y, off, kWave);
+                    base += y;
+                } else {
+                    base += block_sum_u64(part, scratch);
+                }
+                summed = true;
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < kFlight; ++q) {
+                const uint32_t end = wstart[bkt[q] + 1u], w = wstart[bkt[q]] + at[q];
+                if (p0 + q * WG < total && base + end <= W.words_cap) {
+                    uint32_t *dst = W.words + base + w;
+                    typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+                    if (w + 4u <= end) {
+                        *reinterpret_cast<u32x4_any *>(dst) = u32x4_any{x[q].x, x[q].y, x[q].z, x[q].w};
+                    } else {
+                        dst[0] = x[q].x;
+                        if (w + 1u < end)
+                            dst[1] = x[q].y;
+                        if (w + 2u < end)
+                            dst[2] = x[q].z;
+                    }
+                }
+            }
+        }
         if (tid < FB && b_first + tid < P.nb) {
-            const uint64_t start = base + wstart[tid];
-            W.bit_off[b_first + tid + 1] = 32ull * start + my_len;
+            W.bit_off[b_first + tid + 1] = 32ull * (base + wstart[tid]) + len;
             if (b_first + tid == 0)
                 W.bit_off[0] = 0;
-            const bool over = base + wstart[tid + 1] > W.words_cap;
-            skip[tid] = over;
-            if (over && my_len)
+            if (base + wstart[tid + 1] > W.words_cap && len)
                 atomicOr(P.flags, kFlagCapacity);
         }
-        __syncthreads();
-
-        // copy the staging slots: word w of the group's run belongs to the bucket found by bisection
-        const uint32_t total = wstart[FB];
-        const uint32_t *__restrict__ staging = P.staging + ((uint64_t)blockIdx.y * P.nb + b_first) * P.slot_words;
-        uint32_t *__restrict__ dst = W.words + base;
-#pragma unroll 4
-        for (uint32_t w = tid; w < total; w += WG) {
-            uint32_t j = 0;
-#pragma unroll
-            for (uint32_t step = FB / 2; step >= 1; step >>= 1)
-                j += (wstart[j + step] <= w) ? step : 0u;
-            if (!skip[j])
-                dst[w] = staging[(uint64_t)j * P.slot_words + (w - wstart[j])];
-        }
-        base += total;
-        __syncthreads();          // wstart and skip are read to the end before the next group overwrites them
+        base += wstart[FB];
+        __syncthreads();          // the group's starts are read to the end before the next group overwrites them
     }
 }
 

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_lens(EncodePara
     uint32_t total;
     team_exclusive_sum<TEAM>(bits, scratch_all[team], total);
     if (active && tid == 0)
-        P.lens[b] = total;
+        P.units[b] = total;                 // (bits here: k_chunk_sums and k_bit_offsets of this path take bits)
 }
 
 // bit_off from lens: one workgroup per chunk of 1024 buckets, chunk_prefix[c] = words before the chunk.
@@ -219,7 +219,7 @@ __device__ __forceinline__ uint32_t huffman_from_lds(const EncodeParams &P, cons
 }
 
 // Norms + quantizer + Huffman coding of one bucket per team, v read once, all workers in one launch (blockIdx.y): the
-// bit string goes to the bucket's staging slot and its length to lens; k_finish turns those into bit_off and words as
+// bit string goes to the bucket's staging slot and its length to report_lengths; k_finish turns those into bit_off and words as
 // for the ERC strings.
 template <int TEAM, int VPT>
 __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodeParams P, EncodeBatch Wk, HuffmanCode H)
@@ -251,9 +251,8 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
         uint32_t *sg = W.sync + b * P.nsync;
         for (uint32_t i = tid; i < P.nsync; i += TEAM)
             sg[i] = sync_l[i];
-        if (tid == 0)
-            P.lens[(uint64_t)blockIdx.y * P.nb_stride + b] = total;
     }
+    report_lengths<TEAM>(P, W, active, b, total);
 }
 
 template <int TEAM, int VPT>
