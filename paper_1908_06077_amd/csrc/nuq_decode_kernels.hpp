@@ -253,12 +253,13 @@ struct WalkWords {
     __device__ __forceinline__ uint32_t operator[](uint32_t i) const { return p[i]; }
 };
 
-// Word sources for the parser.  at(q) returns word q - 1 of the unit's frame (word 0 holds its bit 0); what it
-// returns for a word that does not exist is never looked at.
+// Word sources for the parser.  at(q) returns word q - 1 of the unit's frame (word 0 holds its bit 0), after(m) is
+// at(~m + 2); what they return for a word that does not exist is never looked at.
 struct GlobalWords {
     const uint32_t *p;
     uint32_t last;      // highest readable word index
     __device__ __forceinline__ uint32_t at(uint32_t q) const { return p[min(max(q, 1u) - 1u, last)]; }
+    __device__ __forceinline__ uint32_t after(int m) const { return at(~(uint32_t)m + 2u); }
 };
 
 // Words staged in LDS.  `p` points one word before the frame; the staging area is padded at both ends so
@@ -266,32 +267,37 @@ struct GlobalWords {
 struct StagedWords {
     const uint32_t *p;
     __device__ __forceinline__ uint32_t at(uint32_t q) const { return p[q]; }
+    // at(~m + 2): one multiply-add from the down-counting word index to the address (the compiler makes it a shift and a
+    // subtraction); |m| < 2^23 and p is below 2^23 bytes of LDS
+    __device__ __forceinline__ uint32_t after(int m) const
+    {
+        typedef const __attribute__((address_space(3))) uint32_t *LdsWords;
+        const LdsWords p2 = (LdsWords)p + 1;
+        uint32_t a;
+        asm("v_mad_i32_i24 %0, %1, -4, %2" : "=v"(a) : "v"(m), "v"((uint32_t)(uintptr_t)p2));
+        return *(LdsWords)(uintptr_t)a;
+    }
 };
 
 // ---- gap code table --------------------------------------------------------------------
-// Entry for the next seven stream bits p (MSB first):
-//   bits  0..4   length of the whole code (its first two groups fix it)
-//   bits  5..9   width of the last group of a three-group code (5..16), 0 for a code complete within the
-//                seven bits; that group ends one bit before the code does
-//   bits 10..13  value of a code complete within the seven bits (1..15), else 0
-// so that value = field2 + bitfield(window, 33 - length, width) for every code of up to three groups.
+// Entry for the next seven stream bits p (MSB first); the first two groups of a code of up to three groups fix its length
+// and the width of its last group:
+//   bits 0..4   31 - length (length <= 23).  A window rotated right by that many bits has the gap code and the sign bit of
+//               its record in its low bits and the level code on top.
+//   bits 5..9   width of the last group (2..16), whose value is the gap; 0 for the code "0" (gap 1)
 __device__ __forceinline__ uint32_t gap_table_entry(uint32_t p)
 {
     const uint32_t w = p << 25;
     uint32_t N, len;
     erc_decode_bits(w, N, len);
-    if (len <= 7u)
-        return len | (N << 10);
-    const uint32_t k2 = (w >> 30) + 1u;                         // second group's width (3 or 4)
-    const uint32_t g2 = (w >> (30u - k2)) & ((1u << k2) - 1u);  // second group = last group's width - 1
-    const uint32_t a = 2u + k2, v = g2 + 1u;
-    return (a + v + 1u) | (v << 5);
-}
-
-// value of the gap code at the top of window w, given its table entry
-__device__ __forceinline__ uint32_t gap_value(uint32_t w, uint32_t e)
-{
-    return (e >> 10) + __builtin_amdgcn_ubfe(w, 33u - (e & 31u), (e >> 5) & 31u);
+    uint32_t width = len == 1u ? 0u : len == 3u ? 2u : len - 3u;    // codes that end within the seven bits
+    if (len > 7u) {
+        const uint32_t k2 = (w >> 30) + 1u;                         // second group's width (3 or 4)
+        const uint32_t g2 = (w >> (30u - k2)) & ((1u << k2) - 1u);  // second group = last group's width - 1
+        width = g2 + 1u;
+        len = 2u + k2 + width + 1u;
+    }
+    return (31u - len) | (width << 5);
 }
 
 // Parse the records in bits [bit_lo, bit_hi) of a unit's frame and add their values into the tile.
@@ -315,33 +321,47 @@ __device__ __forceinline__ uint32_t level_table_entry(uint32_t p, uint32_t smax)
 // nine, and an LDS read takes ~64, so the loop is kept short (format checks are folded into two running values
 // and tested once) and is arranged around its one carried dependency, the bit position.  It is
 // software-pipelined by hand so that the two LDS reads on that chain are covered by other work:
-//   chain 1 : the 32-bit window at the position from two adjacent words through one funnel shift (position + 31
-//             is the loop variable: its word index names the second word of the pair, its complement is the
-//             shift); the table read for the gap code is issued.  The two words and the one after them are
-//             held in registers: a record is at most 31 bits (gap code <= 23, sign, level code <= 7), so the
-//             pair moves on by one word at most, and the word that then enters was requested an iteration
+//   chain 1 : the 32-bit window at the position from two adjacent words through one funnel shift (the loop variable
+//             counts down from ~(position + 31): it is the shift as it stands, and its word index names the second
+//             word of the pair); the table read for the gap code is issued.  The two words and the one after
+//             them are held in registers: a record is at most 31 bits (gap code <= 23, sign, level code <= 7),
+//             so the pair moves on by one word at most, and the word that then enters was requested an iteration
 //             ago: no read of stream words is on the chain
 //   cover   : level and value of the previous record (its level table entry was requested an iteration ago), its
 //             add into the tile
-//   chain 2 : gap code's length from the entry; the level table read is issued (nothing on the chain waits for
-//             it); level code's length from a byte permute on its first three bits (the code is at most seven
-//             bits: 0 | 1x0 | 101yy0 | 111yyy0); next position; the pair moves on if the position's word index
-//             did, and the word after the pair is requested
-//   cover   : this record's gap value and index, loop control
+//   chain 2 : the window is rotated by the gap entry, which leaves the level code on top, the sign in bit 0 and the
+//             gap code above it; the level table read is issued (nothing on the chain waits for it); what is left of
+//             the next position from a byte permute on the level code's first three bits (the code is at most seven
+//             bits: 0 | 1x0 | 101yy0 | 111yyy0); the pair moves on if the position's word index did, and the word
+//             after the pair is requested
+//   cover   : this record's gap (the low bits of the rotated window) and place in the tile, loop control
+// 27 vector and LDS instructions per record (31 with the position counting up and the gap's value cut out of the
+// window): 4 x 1.56 G coordinates in buckets of 512, a quarter of them nonzero, 2.83 -> 2.74 ms; 8 x 25.6 M in buckets of
+// 8192 40.3 -> 39.3 us.
 //
 // kTable: the value of level j is wnorm * lev[j] (an arbitrary level sequence, lev in LDS) instead of
 // wnorm * 2^j (wnorm = ||v|| * 2^(-1-s)); both are exact in fp64.
 // Where a decoded value goes.  TileSink: the fp64 tile in LDS that sums the workers (at0 = address of the
 // bucket's index 0).  DirectSink: a single message has nothing to sum: fp32(scale * value), the same rounding the
 // tile's output stage applies to a sum of one term, stored or added straight into the output.
+// A sink counts places in units of its own (kUnit = log2 units per coordinate), so that the parser's running index is the
+// address: place(i) of in-bucket index i, add(place, value).
 struct TileSink {
-    double *at0;
-    __device__ __forceinline__ void add(uint32_t idx, double v) const { atomicAdd(at0 + idx, v); }
+    double *tile;
+    uint32_t origin;                               // byte offset of the bucket's index 0 (modulo 2^32)
+    static constexpr uint32_t kUnit = 3;
+    __device__ __forceinline__ uint32_t place(uint32_t i) const { return origin + (i << kUnit); }
+    __device__ __forceinline__ void add(uint32_t at, double v) const
+    {
+        atomicAdd(reinterpret_cast<double *>(reinterpret_cast<char *>(tile) + at), v);
+    }
 };
 template <int UPDATE>
 struct DirectSink {
     float *at0;
     double scale;
+    static constexpr uint32_t kUnit = 0;
+    __device__ __forceinline__ uint32_t place(uint32_t i) const { return i; }
     __device__ __forceinline__ void add(uint32_t idx, double v) const
     {
         const float r = (float)(scale * v);
@@ -357,78 +377,77 @@ __device__ __forceinline__ void decode_unit_fast(const Words &words, const uint1
                                                  const float *lev, uint32_t bit_lo, uint32_t bit_hi, int forced,
                                                  uint32_t idx_hi, double wnorm, const Sink &sink, bool &bad)
 {
-    uint32_t p31 = bit_lo + 31u;
-    const uint32_t end31 = bit_hi + 31u;
-    if (p31 >= end31) {
-        bad |= p31 != end31;
+    if (bit_lo >= bit_hi) {
+        bad |= bit_lo != bit_hi;
         return;
     }
-    uint32_t q = p31 >> 5;
-    uint32_t hi = words.at(q), lo = words.at(q + 1u), nx = words.at(q + 2u);
-    int prev = -1;
+    int n = (int)~(bit_lo + 31u);                // counts down; its word index m = n >> 5 = ~(word of position + 31)
+    const int end = (int)~(bit_hi + 31u);
+    int m = n >> 5;
+    uint32_t hi = words.at(~(uint32_t)m), lo = words.at(~(uint32_t)m + 1u), nx = words.after(m);
+    const uint32_t place_last = sink.place(idx_hi - 1u);
+    uint32_t at, at_raw;            // place of the record, clamped to the last one and before that: once the latter has
+                                    // passed the last place it stays beyond it, so its last value tells
     uint32_t w, e;                  // window, gap entry
-    uint32_t idx, w2, e2;           // what an iteration leaves for the first cover step of the next: index, window
-                                    // at the sign bit, level entry (in flight)
-    uint32_t last_i = 0;            // index before clamping: non-decreasing, so the last one tells if any was too big
+    uint32_t y, e2;                 // rotated window; level entry (in flight)
     uint32_t min_j = 1;             // smallest table entry met: 0 marks a level code the message cannot hold
+    // ||v|| * l_j = (||v|| * 2^(-1-s)) * 2^j, exact in fp64: j is added to the exponent (never subnormal: an fp32 norm
+    // times a power of two down to 2^-15); zero, infinity and NaN stay what they are
+    const uint64_t wbits = (uint64_t)__double_as_longlong(wnorm) & 0x7fffffffffffffffull;
+    const uint32_t whi = (uint32_t)(wbits >> 32), wlo = (uint32_t)wbits;
+    const uint32_t binade = whi - 0x00100000u < 0x7fe00000u ? 0x00100000u : 0u;
 
     auto chain1 = [&]() {
-        w = __builtin_amdgcn_alignbit(hi, lo, ~p31);
+        w = __builtin_amdgcn_alignbit(hi, lo, (uint32_t)n);
         e = lut[w >> 25];
     };
     auto chain2 = [&]() {
-        const uint32_t lg = e & 31u;
-        w2 = w << lg;                            // sign bit on top, level code below
-        e2 = lut_level[(w2 >> 24) & 0x7fu];
-        const uint32_t sel = ((w2 >> 28) & 7u) | 0x0c0c0c00u;
-        const uint32_t lj1 = __builtin_amdgcn_perm(0x08040704u, 0x02020202u, sel);   // sign bit + level code
-        p31 += lg + lj1;                         // by 31 at most
-        const uint32_t qn = p31 >> 5;
-        const bool moved = qn != q;
+        y = __builtin_amdgcn_alignbit(w, w, e);
+        e2 = lut_level[y >> 25];
+        // selector: the level code's first three bits, three bytes of ones above; bytes: -(32 + length of the level code)
+        const uint32_t sel = __builtin_amdgcn_alignbit(0x01a1a1a0u, y, 29u);
+        const uint32_t t = __builtin_amdgcn_perm(0xd9dddaddu, 0xdfdfdfdfu, sel);
+        n = (int)((uint32_t)n + (e & 31u) + t);  // by 31 at most
+        const int mn = n >> 5;
+        const bool moved = mn != m;
         hi = moved ? lo : hi;
         lo = moved ? nx : lo;
-        q = qn;
-        nx = words.at(qn + 2u);
+        m = mn;
+        nx = words.after(mn);
     };
-    auto cover_index = [&]() {
-        uint32_t i = (uint32_t)(prev + (int)gap_value(w, e));
-        if (forced >= 0) {                       // entered through a sync entry: its index replaces the first gap
-            i = (uint32_t)forced;
-            forced = -1;
-        }
-        last_i = i;
-        idx = min(i, idx_hi - 1u);
-        prev = (int)idx;
-    };
+    auto gap = [&]() { return max(__builtin_amdgcn_ubfe(y, 2u, e >> 5), 1u); };
     auto cover_value = [&]() {
         const uint32_t j = e2;
         min_j = min(min_j, j);
-        // ||v|| * l_j = (||v|| * 2^(-1-s)) * 2^j, exact in fp64; the sign goes into the top bit
-        double mag;
-        if constexpr (kTable)
-            mag = wnorm * (double)lev[j];
-        else
-            mag = ldexp(wnorm, (int)j);
-        const uint32_t mh = (uint32_t)((uint64_t)__double_as_longlong(mag) >> 32);
-        const uint32_t vh = (mh & 0x7fffffffu) | (w2 & 0x80000000u);
-        const uint64_t vb = ((uint64_t)vh << 32) | (uint32_t)__double_as_longlong(mag);
-        sink.add(idx, __longlong_as_double((long long)vb));
+        uint32_t mh, ml;
+        if constexpr (kTable) {
+            const uint64_t mag = (uint64_t)__double_as_longlong(wnorm * (double)lev[j]) & 0x7fffffffffffffffull;
+            mh = (uint32_t)(mag >> 32);
+            ml = (uint32_t)mag;
+        } else {
+            mh = __umul24(j, binade) + whi;
+            ml = wlo;
+        }
+        sink.add(at, __longlong_as_double((long long)(((uint64_t)((y << 31) | mh) << 32) | ml)));
     };
 
     chain1();
     chain2();
-    cover_index();
-    while (p31 < end31) {
+    // (entered through a sync entry: its index replaces the first gap)
+    at_raw = sink.place(forced >= 0 ? (uint32_t)forced : gap() - 1u);
+    at = min(at_raw, place_last);
+    while (n > end) {
         chain1();
         __builtin_amdgcn_sched_barrier(0);
         cover_value();
         __builtin_amdgcn_sched_barrier(0);
         chain2();
         __builtin_amdgcn_sched_barrier(0);
-        cover_index();
+        at_raw = at + (gap() << Sink::kUnit);
+        at = min(at_raw, place_last);
     }
     cover_value();
-    bad |= (p31 != end31) | (last_i >= idx_hi) | (min_j == 0u);
+    bad |= (n != end) | (at_raw > place_last) | (min_j == 0u);
 }
 
 // Where a tile lies.  Everything here is uniform over the workgroup.
@@ -651,9 +670,9 @@ __global__ __launch_bounds__(kDecodeWG, 4) void k_decode_accumulate(DecodeParams
         }
         return U;
     };
-    // address of in-bucket index 0 of bucket bi of the tile (never dereferenced outside the tile)
+    // in-bucket index 0 of bucket bi of the tile, in bytes from the tile's start
     auto tile_origin = [&](const TileGeom &G, uint32_t bi) {
-        return partial ? tile - (int)G.in_lo : tile + bi * P.bucket;
+        return 8u * (partial ? 0u - G.in_lo : bi * P.bucket);
     };
     const uint32_t last_len = (uint32_t)(P.d - last_bucket * P.bucket);     // coordinates of the last bucket
     auto parse_planned = [&](const TileGeom &G, uint32_t bi, uint32_t g, const uint32_t *buf, const PackedPlan &Q,
@@ -661,7 +680,7 @@ __global__ __launch_bounds__(kDecodeWG, 4) void k_decode_accumulate(DecodeParams
         const uint32_t nbk = G.b0 + bi == last_bucket ? last_len : P.bucket;
         const uint32_t idx_hi = P.nsync ? min(nbk, ((g >> P.pieces_shift) + 1u) << kSyncBlockShift) : nbk;
         decode_unit_fast<kTable>(StagedWords{buf + (Q.where & 0xFFFu)}, lut, lut_level, lev, Q.bits & 0xFFFFu, Q.bits >> 16,
-                         (int)(Q.where >> 16) - 1, idx_hi, (double)Q.norm * wscale, TileSink{tile_origin(G, bi)}, bad);
+                         (int)(Q.where >> 16) - 1, idx_hi, (double)Q.norm * wscale, TileSink{tile, tile_origin(G, bi)}, bad);
     };
     // Any unit, from scratch: units beyond the planned ones and units whose words were not staged.
     auto slow_unit = [&](const TileGeom &G, const uint32_t *buf, uint32_t k, uint32_t bi, uint32_t g, bool report,
@@ -676,7 +695,7 @@ __global__ __launch_bounds__(kDecodeWG, 4) void k_decode_accumulate(DecodeParams
         else if (X.kind == 2)
             decode_unit_fast<kTable>(GlobalWords{P.words[k] + X.first_word, X.nwords - 1u}, lut, lut_level, lev, X.bit_lo, X.bit_hi,
                              X.forced,
-                             X.idx_hi, (double)X.norm * wscale, TileSink{tile_origin(G, bi)}, bad);
+                             X.idx_hi, (double)X.norm * wscale, TileSink{tile, tile_origin(G, bi)}, bad);
     };
     // Tiles of a large bucket without a sync index: every tile parses the bucket from its first record in
     // global memory and keeps what lands inside.
@@ -1124,7 +1143,7 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
                 if (R.bit_lo < S0.bit0 || R.bit_hi > S0.bit0 + (S0.nwords << 5)) {
                     bad = true;
                 } else {
-                    const TileSink sink{partial ? tile - (int)G0.in_lo : tile + sbi * P.bucket};
+                    const TileSink sink{tile, 8u * (partial ? 0u - G0.in_lo : sbi * P.bucket)};
                     if (S0.nwords <= stream_stride)
                         codec.parse(StagedWords{stage + my_stream * stream_stride}, R, S0.bit0, M0.norm, sink, bad);
                     else {                            // the part did not fit the staging area: words from global memory

@@ -882,7 +882,7 @@ struct HuffmanWaveCodec {
             const uint32_t sym = symbol ? entry & 15u : 0u, L = entry >> 4;
             bad |= symbol && !L;
             const uint32_t bits = zc + (symbol ? L + (sym ? 1u : 0u) : 0u);
-            const uint32_t at = R.c_lo + i + zc;
+            const uint32_t at = sink.place(R.c_lo + i + zc);
             i += zc + (symbol ? 1u : 0u);
             p31 += max(bits, 1u);                              // (a prefix that is no codeword still moves on)
             const uint32_t qn = p31 >> 5;

@@ -1,0 +1,107 @@
+"""DECODE of crafted level|sign bytes at the edges of the record parser, bit for bit against exact sums: gaps on both sides
+of every code length, all level codes, runs of every length modulo a word, norms that are zero, infinite or no number, odd
+tile ends, and parameters that are updated in place (full tiles, ragged ones, unaligned ones)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import gpu_util
+    return gpu_util
+
+
+def _bytes(rng, d, n, s, sparse):
+    """One worker's bytes: gaps drawn around the powers of two below 2^15, levels uniform."""
+    q = np.zeros(d, dtype=np.uint8)
+    edges = np.array([1, 2, 3, 4, 5, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64, 127, 128, 255, 256, 511, 512, 1023, 4095, 16383])
+    at = -1
+    while True:
+        at += int(rng.choice(edges[edges < n][: len(edges) if sparse else 9])) if n > 1 else 1
+        if at >= d:
+            break
+        q[at] = rng.integers(1, s + 2) | (int(rng.integers(0, 2)) << 7)
+    return q
+
+
+def _message(g, q, n, s, S, norms):
+    nuq, d = g.nuq, q.size
+    m = g.alloc_message(d, n, s, S)
+    nuq.nuq_encode(torch.from_numpy(q).to(g.DEV), n, s, S, m.bit_off, m.words, m.sync if nuq.nuq_num_sync(n, S) else None,
+                   g.workspace(d, n, s))
+    m.norms.copy_(torch.from_numpy(norms))
+    return m
+
+
+def _value(q, n, s, norms):
+    lev = (q & 0x7f).astype(np.int64)
+    v = np.repeat(norms.astype(np.float64), n)[: q.size]
+    with np.errstate(invalid="ignore"):
+        v = np.where(lev > 0, np.ldexp(v, lev - 1 - s), 0.0)
+    return np.where(q & 0x80, -v, v)
+
+
+@pytest.mark.parametrize("s", [1, 3, 7, 14])
+@pytest.mark.parametrize("n,S,K", [(8192, 256, 8), (8192, 256, 1), (512, 128, 4), (512, 128, 1), (1000, 128, 3), (16384, 128, 4),
+                                   (4096, 256, 2), (20001, 512, 5), (17, 64, 2), (512, 0, 3), (8192, 64, 8), (2048, 0, 1)])
+def test_crafted_records(g, n, S, K, s):
+    nuq = g.nuq
+    rng = np.random.default_rng(n + 64 * s + K)
+    d = max(3 * n + n // 3, 9000)
+    nb = -(-d // n)
+    qs = [_bytes(rng, d, n, s, sparse=k % 2 == 1) for k in range(K)]
+    norms = [np.exp2(rng.uniform(-3, 3, nb)).astype(np.float32) for _ in range(K)]
+    norms[0][0] = 0.0
+    msgs = [_message(g, q, n, s, S, v) for q, v in zip(qs, norms)]
+    want = sum(_value(q, n, s, v) for q, v in zip(qs, norms))          # exact in fp64: spans far below 2^29
+    out = torch.full((d,), 7.0, device=g.DEV)
+    nuq.nuq_decode_accumulate(msgs, d, n, s, S, 0.5, False, out)
+    assert nuq.nuq_last_error_flags() == 0
+    np.testing.assert_array_equal(out.cpu().numpy(), (0.5 * want).astype(np.float32))
+    # added to what is there, at an aligned and at an odd address
+    for shift in (0, 1):
+        flat = torch.arange(d + 1, dtype=torch.float32, device=g.DEV)
+        prior = flat[shift:shift + d].cpu().numpy()
+        nuq.nuq_decode_accumulate(msgs, d, n, s, S, 0.5, True, flat[shift:shift + d])
+        np.testing.assert_array_equal(flat[shift:shift + d].cpu().numpy(), (0.5 * want).astype(np.float32) + prior)
+
+
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, -2.0, 2.0 ** -149])
+@pytest.mark.parametrize("n,S,K", [(8192, 256, 2), (512, 128, 1)])
+def test_unusual_norms(g, n, S, K, bad):
+    """A received norm is taken as its magnitude (the sign is the record's), whatever it is."""
+    nuq = g.nuq
+    rng = np.random.default_rng(5)
+    d, s = 3 * n, 3
+    qs = [_bytes(rng, d, n, s, sparse=True) for _ in range(K)]
+    norms = [np.ones(3, dtype=np.float32) for _ in range(K)]
+    norms[0][1] = bad
+    msgs = [_message(g, q, n, s, S, v) for q, v in zip(qs, norms)]
+    out = torch.empty(d, device=g.DEV)
+    nuq.nuq_decode_accumulate(msgs, d, n, s, S, 1.0, False, out)
+    want = sum(_value(q, n, s, np.abs(v)) for q, v in zip(qs, norms)).astype(np.float32)
+    np.testing.assert_array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,S,K,d,shift", [(8192, 256, 8, 8192 * 3 + 5, 0), (512, 128, 4, 512 * 40 + 7, 0), (512, 128, 4, 512 * 40, 1),
+                                           (16384, 256, 4, 16384 * 2 + 3000, 0), (1000, 128, 3, 9001, 0)])
+def test_momentum_tiles(g, n, S, K, d, shift):
+    nuq = g.nuq
+    rng = np.random.default_rng(d)
+    s, nb = 3, -(-d // n)
+    qs = [_bytes(rng, d, n, s, sparse=False) for _ in range(K)]
+    norms = [np.exp2(rng.uniform(-3, 3, nb)).astype(np.float32) for _ in range(K)]
+    msgs = [_message(g, q, n, s, S, v) for q, v in zip(qs, norms)]
+    scale = float(np.float32(1.0 / K))
+    gd = (scale * sum(_value(q, n, s, v) for q, v in zip(qs, norms))).astype(np.float32).astype(np.float64)
+    w0, y0 = rng.standard_normal((2, d)).astype(np.float32)
+    w, y = (torch.empty(d + shift, device=g.DEV)[shift:].copy_(torch.from_numpy(a)) for a in (w0, y0))
+    alpha, mu, l = 0.25, 0.5, 1.0
+    nuq.nuq_decode_momentum_step(msgs, d, n, s, S, scale, alpha, mu, l, w, y)
+    yl = w0.astype(np.float64) - l * alpha * gd
+    want = (w0.astype(np.float64) - alpha * gd) + mu * (yl - y0.astype(np.float64))
+    np.testing.assert_allclose(w.cpu().numpy(), want, rtol=2.0 ** -23, atol=2.0 ** -30)      # one rounding to fp32
+    np.testing.assert_allclose(y.cpu().numpy(), yl, rtol=2.0 ** -23, atol=2.0 ** -30)
