@@ -1159,6 +1159,11 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
         lds_fence();
         if (has1)
             store_words(W0);                              // (the parse of this tile is over: the staging area is free)
+        // The offsets of the tile after the next were requested with those words and have arrived: said here, since the
+        // compiler would otherwise wait for them where the round ends, behind the stores and so for the stores (the
+        // output's other path issues an unknown number of them).  4 x 1.56 G coordinates in buckets of 512 2.74 -> 2.68 ms,
+        // 8 x 25.6 M in buckets of 8192 39.3 -> 38.2 us.
+        asm volatile("" : "+v"(M2.bo0), "+v"(M2.bo1), "+v"(M2.e_lo), "+v"(M2.e_hi), "+v"(M2.norm));
         tile_output<UPDATE, TC, kWaveWG>(P, tile, G0.c_lo, G0.span, lane);
         if (!has1)
             break;
