@@ -83,10 +83,29 @@ __device__ __forceinline__ uint32_t xcd_tile(const DecodeParams &P, uint32_t v)
 //   kUpdateMomentum  (out, yl) <- momentum rule of Sec. 4.2 with g = r (out = w)
 constexpr int kUpdateWrite = 0, kUpdateAdd = 1, kUpdateMomentum = 2;
 
-// A full, 16-byte aligned tile of TC coordinates: every thread handles TC/4/kDecodeWG float4 groups, two at a time, with the
-// loads of the old values issued before the LDS reads so that their latencies overlap.
-template <int UPDATE, uint32_t TC, uint32_t WG = kDecodeWG>
-__device__ __forceinline__ void apply_full_tile(const DecodeParams &P, double *tile, float *o, float *y, uint32_t tid)
+// What the output stage of a full, 16-byte aligned tile of TC coordinates reads: the old parameters and y^l, TC / 4 / WG
+// float4 groups per thread.  A caller that has the registers requests them before it parses the tile.
+template <int UPDATE, uint32_t TC, uint32_t WG>
+struct OldValues {
+    static constexpr uint32_t kRows = TC / 4u / WG;
+    float4 w[UPDATE != kUpdateWrite ? kRows : 1], y[UPDATE == kUpdateMomentum ? kRows : 1];
+    __device__ __forceinline__ void request(const float *o, const float *yl, uint32_t tid)
+    {
+#pragma unroll
+        for (uint32_t r = 0; r < kRows; ++r) {
+            if constexpr (UPDATE != kUpdateWrite)
+                w[r] = reinterpret_cast<const float4 *>(o)[tid + r * WG];
+            if constexpr (UPDATE == kUpdateMomentum)
+                y[r] = reinterpret_cast<const float4 *>(yl)[tid + r * WG];
+        }
+    }
+};
+
+// A full tile's output.  kHave: `old` holds what request() loads; else it is loaded here, two groups at a time, with the
+// loads issued before the LDS reads so that their latencies overlap.
+template <int UPDATE, uint32_t TC, uint32_t WG, bool kHave>
+__device__ __forceinline__ void apply_full_tile(const DecodeParams &P, double *tile, float *o, float *y, uint32_t tid,
+                                                const OldValues<UPDATE, TC, WG> *old)
 {
     constexpr uint32_t kFull = TC / 4u / WG;                      // float4 groups per thread
     const double sc = (double)P.scale;
@@ -98,9 +117,9 @@ __device__ __forceinline__ void apply_full_tile(const DecodeParams &P, double *t
         for (uint32_t r = 0; r < 2u; ++r) {
             const uint32_t i = tid + (r0 + r) * WG;
             if constexpr (UPDATE != kUpdateWrite)
-                w[r] = reinterpret_cast<const float4 *>(o)[i];
+                w[r] = kHave ? old->w[r0 + r] : reinterpret_cast<const float4 *>(o)[i];
             if constexpr (UPDATE == kUpdateMomentum)
-                yv[r] = reinterpret_cast<const float4 *>(y)[i];
+                yv[r] = kHave ? old->y[r0 + r] : reinterpret_cast<const float4 *>(y)[i];
         }
 #pragma unroll
         for (uint32_t r = 0; r < 2u; ++r) {
@@ -157,15 +176,26 @@ __device__ __forceinline__ void apply4(const DecodeParams &P, float4 r, float4 *
 
 // Output stage of a tile: scale the sums, round to fp32, apply to the output (write, add, or momentum rule), and
 // leave the tile zeroed.  Called by all WG threads of the workgroup.
-template <int UPDATE, uint32_t TC, uint32_t WG>
-__device__ __forceinline__ void tile_output(const DecodeParams &P, double *tile, uint64_t c_lo, uint32_t span, uint32_t tid)
+template <int UPDATE>
+__device__ __forceinline__ float *update_yl(const DecodeParams &P, uint64_t c_lo)
 {
-    float *o = P.out + c_lo;
-    float *y = UPDATE == kUpdateMomentum ? P.yl + c_lo : o;      // (read only under kUpdateMomentum)
-    const bool vec = ((reinterpret_cast<uintptr_t>(o) | reinterpret_cast<uintptr_t>(y)) & 15u) == 0;
-    const uint32_t n4 = vec ? span >> 2 : 0u;
+    return UPDATE == kUpdateMomentum ? P.yl + c_lo : P.out + c_lo;   // (read only under kUpdateMomentum)
+}
+// float4 groups of a tile that starts at coordinate c_lo: 0 without 16-byte alignment.
+template <int UPDATE>
+__device__ __forceinline__ uint32_t tile_groups(const DecodeParams &P, uint64_t c_lo, uint32_t span)
+{
+    const uintptr_t both = reinterpret_cast<uintptr_t>(P.out + c_lo) | reinterpret_cast<uintptr_t>(update_yl<UPDATE>(P, c_lo));
+    return (both & 15u) == 0 ? span >> 2 : 0u;
+}
+template <int UPDATE, uint32_t TC, uint32_t WG, bool kHave = false>
+__device__ __forceinline__ void tile_output(const DecodeParams &P, double *tile, uint64_t c_lo, uint32_t span, uint32_t tid,
+                                            const OldValues<UPDATE, TC, WG> *old = nullptr)
+{
+    float *o = P.out + c_lo, *y = update_yl<UPDATE>(P, c_lo);
+    const uint32_t n4 = tile_groups<UPDATE>(P, c_lo, span);
     if (n4 == TC / 4u) {
-        apply_full_tile<UPDATE, TC, WG>(P, tile, o, y, tid);
+        apply_full_tile<UPDATE, TC, WG, kHave>(P, tile, o, y, tid, old);
     } else {
         const double sc = (double)P.scale;
         for (uint32_t i = tid; i < n4; i += WG) {
@@ -1090,14 +1120,8 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
         asm volatile("" ::: "memory");
     };
 
-    // ---- tables, cleared tile
-    for (uint32_t i = lane; i < TC / 2u; i += kWaveWG)
-        reinterpret_cast<double2 *>(tile)[i] = double2{0.0, 0.0};
-    codec.init(P, lane);
-    if (lane < 5u)
-        stage[lane ? kStageWords + lane : 0u] = 0u;                  // the pads
-
-    // ---- prologue: offsets of the first two tiles, words of the first
+    // ---- prologue: offsets of the first two tiles requested; tables and cleared tile while they are under way; words of
+    // the first tile
     bool bad = false;
     const uint32_t stride = gridDim.x;
     uint32_t t = blockIdx.x;                                          // < ntiles by the launch
@@ -1107,6 +1131,11 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
         G1 = tile_geom(P, xcd_tile(P, t + stride));
         M1 = load_meta(G1);
     }
+    for (uint32_t i = lane; i < TC / 2u; i += kWaveWG)
+        reinterpret_cast<double2 *>(tile)[i] = double2{0.0, 0.0};
+    codec.init(P, lane);
+    if (lane < 5u)
+        stage[lane ? kStageWords + lane : 0u] = 0u;                  // the pads
     StreamPart S0 = part_of(G0, M0, bad);
     uint32_t W0[kWordsPerLane];
     load_words(G0, S0, W0);
@@ -1131,6 +1160,12 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
             G2 = tile_geom(P, xcd_tile(P, t + 2u * stride));
             M2 = load_meta(G2);
         }
+        // the old parameters too (read two groups at a time in the tile's output they were four round trips: step with
+        // momentum on 4 x 11.7 M coordinates 118.8 -> 116.4 us)
+        OldValues<UPDATE, TC, kWaveWG> old;
+        if constexpr (UPDATE != kUpdateWrite)
+            if (tile_groups<UPDATE>(P, G0.c_lo, G0.span) == TC / 4u)
+                old.request(P.out + G0.c_lo, update_yl<UPDATE>(P, G0.c_lo), lane);
         lds_fence();
 
         // ---- this lane's piece of tile t
@@ -1164,7 +1199,7 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
         // output's other path issues an unknown number of them).  4 x 1.56 G coordinates in buckets of 512 2.74 -> 2.68 ms,
         // 8 x 25.6 M in buckets of 8192 39.3 -> 38.2 us.
         asm volatile("" : "+v"(M2.bo0), "+v"(M2.bo1), "+v"(M2.e_lo), "+v"(M2.e_hi), "+v"(M2.norm));
-        tile_output<UPDATE, TC, kWaveWG>(P, tile, G0.c_lo, G0.span, lane);
+        tile_output<UPDATE, TC, kWaveWG, true>(P, tile, G0.c_lo, G0.span, lane, &old);
         if (!has1)
             break;
         lds_fence();
