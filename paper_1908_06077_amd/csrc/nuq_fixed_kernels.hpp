@@ -182,11 +182,12 @@ __device__ __forceinline__ double fixed_level_value(const UnpackParams &P, doubl
 // of every worker's field (one contiguous load per worker, coalesced over the wave), and the workgroup's 8192 results
 // go through LDS so that the stores are whole lines too.
 //
-// kLut (at 4 and 8 bits k_unpack_accumulate_fixed_direct is the variant with tables): the value of every code, norm * sign * 2^(level - 1 - s) in fp64 (0 for level 0 and for codes that are not
-// valid), is tabulated in LDS once per (bucket the workgroup touches, worker); a code then costs a bit-field extract,
-// an LDS read and an fp64 add instead of the exponent arithmetic.  A table of 16 entries is 128 bytes = all 32 banks
-// once, so lanes that read one table never conflict whatever their codes.  Codes wider than 5 bits index 32 entries
-// by (sign, low four level bits): levels stop at 15.  `lut_tabs` tables per worker are laid out bucket-major.
+// kLut (3, 5, 6 and 7 bits; at 4 and 8 k_unpack_accumulate_fixed_direct is the variant with tables): the value of every
+// code, norm * sign * 2^(level - 1 - s) in fp64 (0 for level 0 and for codes that are not valid), is tabulated in LDS once
+// per (bucket the workgroup touches, worker); a code then costs a bit-field extract, an LDS read and an fp64 add instead of
+// the exponent arithmetic.  A table of 16 entries is 128 bytes = all 32 banks once, so lanes that read one table never
+// conflict whatever their codes.  Codes wider than 5 bits index 32 entries by (sign, low four level bits): levels stop at
+// 15.  `lut_tabs` tables per worker are laid out bucket-major.
 constexpr uint32_t fixed_lut_entries(uint32_t b) { return b <= 5u ? 1u << b : 32u; }
 
 template <int B>

@@ -219,8 +219,8 @@ __device__ __forceinline__ uint32_t huffman_from_lds(const EncodeParams &P, cons
 }
 
 // Norms + quantizer + Huffman coding of one bucket per team, v read once, all workers in one launch (blockIdx.y): the
-// bit string goes to the bucket's staging slot and its length to report_lengths; k_finish turns those into bit_off and words as
-// for the ERC strings.
+// bit string goes to the bucket's staging slot and its length where k_finish looks for it (report_lengths); that kernel
+// turns them into bit_off and words as for the ERC strings.
 template <int TEAM, int VPT>
 __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodeParams P, EncodeBatch Wk, HuffmanCode H)
 {
