@@ -521,7 +521,9 @@ __device__ __forceinline__ uint32_t quantize_table_vec4_exact(const float4 &x, u
 // rounding, which keeps the sign; where u w_j < 2 a that is at most 2^-22 a, and where u w_j >= 2 a, t is at least a.
 // A row of the wave in which some coordinate is that close (a bin of relative width r: one coordinate in r 2^20) sets
 // `redo` and is to be decided again by the fp64 rule, as is every row of a bucket whose bins reach the subnormals
-// (thr[0] = 0: the caller's business).
+// (thr[0] = 0: the caller's business).  So is a row with an infinite coordinate (above every level) or a NaN (no level),
+// which a finite norm may meet where the caller supplies it: their margin is a NaN, and `near` is a minimum that a NaN
+// goes through.
 // What it is for: the kernels around it are bound by vector issue, and the fp64 rule is twice as long.  QSGDinf at 4 bits,
 // eight gradients of 25.6 M coordinates, quantize + pack + unpack: 350 us with the fp64 rule throughout, 270 us with this.
 struct TableRule {
@@ -543,6 +545,9 @@ __device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_
 {
     const float xs[4] = {x.x, x.y, x.z, x.w};
     float u[4], t[4], near = 0x1p127f;
+    auto margin = [&](int c) {
+        near = __builtin_elementwise_minimum(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
+    };
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         u[c] = (float)draw24(x0 + (uint32_t)c * kRngC1, k1);
@@ -550,7 +555,7 @@ __device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             t[c] = __builtin_fmaf(u[c], R.w0, -fabsf(xs[c]));
-            near = fminf(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
+            margin(c);
         }
         redo = __any(!(near > 0.0f));
         return fmt.first(top_bytes(xs), top_bytes(t));
@@ -570,7 +575,7 @@ __device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_
     for (int c = 0; c < 4; ++c) {
         const float2 b = R.bins->bin[j[c]];
         t[c] = __builtin_fmaf(u[c], b.y, b.x - fabsf(xs[c]));
-        near = fminf(near, __builtin_fmaf(fabsf(xs[c]), -0x1p-21f, fabsf(t[c])));
+        margin(c);
         levels |= (j[c] + (t[c] < 0.0f ? 1u : 0u)) << (8 * c);
     }
     redo = __any(!(near > 0.0f));

@@ -64,3 +64,28 @@ def test_planted_near_ties(g, d, n, kind, s, p, norm):
     np.testing.assert_array_equal(norms.cpu().numpy(), norms_np)
     np.testing.assert_array_equal(g.u32(packed), oracle.pack_fixed(want, n, s, b))
     assert nuq.nuq_last_error_flags() == 0
+
+
+@pytest.mark.parametrize("n", [300, 512, 2048, 8192, 20000])
+@pytest.mark.parametrize("kind,s", [("uniform", 3), ("exp", 7), ("uniform", 14)])
+@pytest.mark.parametrize("scale", [0.01, 0.5])
+def test_infinite_and_nan_coordinates_under_a_finite_norm(g, n, kind, s, scale):
+    """A norm that the caller supplies need not see what the vector holds: an infinite coordinate takes the top level, a
+    NaN level 0.  Beside coordinates that all lie in the first bin and beside ones that do not."""
+    nuq, d = g.nuq, 3 * n + 17
+    lev = workloads.level_table(kind, s, 0.3)
+    rng = np.random.default_rng(n + s)
+    v = (rng.uniform(-1.0, 1.0, d) * scale * lev[1]).astype(np.float32)
+    if scale > 0.1:
+        v[::5] = rng.uniform(-1.0, 1.0, v[::5].size)
+    at = rng.permutation(d)[:48].reshape(6, 8)
+    for a, x in zip(at, (np.inf, -np.inf, np.nan, -np.nan, 0.0, 1.0)):
+        v[a] = x
+    v.view(np.uint32)[at[2][:4]] = 0x7FA00001                  # signaling
+    norms = np.ones(oracle.num_buckets(d, n), dtype=np.float32)
+    q = torch.full((d,), 0x7F, dtype=torch.uint8, device=g.DEV)
+    nuq.nuq_quantize_table(torch.from_numpy(v).to(g.DEV), n, lev, n, torch.from_numpy(norms).to(g.DEV), q)
+    want = oracle.quantize_table(v, n, lev, n, norms)
+    assert want[at[0]].min() == s + 1 and not want[at[2]].any()
+    np.testing.assert_array_equal(q.cpu().numpy(), want)
+    assert nuq.nuq_last_error_flags() == 0
