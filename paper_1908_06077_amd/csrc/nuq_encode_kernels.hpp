@@ -283,12 +283,17 @@ struct FlagBytes {
 //     when |v| < ns (ns - |v| is exact where it decides).  Without the selection of a bin per coordinate: 2.5 of 17
 //     instructions less;
 //   anything else: quantize_any.
-template <class F>
+//
+// kNaN: the coordinates may hold a NaN (a finite norm that the caller supplies need not see it; under the fused kernels'
+// own norm such a bucket is empty).  It must not choose the route: fmaxf drops every NaN, max_abs4 a signaling one in three
+// of its four places.  And its t and t' carry a sign bit each, which would be level 2 by the second route: ns - |v| is at
+// most ns, so the minimum of the two only moves a NaN, and t' is then not negative.
+template <bool kNaN = false, class F>
 __device__ __forceinline__ uint32_t quantize_vec4(const float4 &x, uint32_t x0, uint32_t k1, const BucketScale &B,
                                                   const F &fmt)
 {
     const float xs[4] = {x.x, x.y, x.z, x.w};   // already multiplied by B.prescale
-    const float big = max_abs4(xs);
+    const float big = kNaN ? fmaxf(fmaxf(fabsf(xs[0]), fabsf(xs[1])), fmaxf(fabsf(xs[2]), fabsf(xs[3]))) : max_abs4(xs);
     float u[4], t[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c)
@@ -301,8 +306,10 @@ __device__ __forceinline__ uint32_t quantize_vec4(const float4 &x, uint32_t x0, 
         if (__all(big < B.ns))
             return fmt.first(sg, tb);
 #pragma unroll
-        for (int c = 0; c < 4; ++c)
-            t[c] = __builtin_fmaf(u[c], B.c, B.ns - fabsf(xs[c]));
+        for (int c = 0; c < 4; ++c) {
+            const float below = B.ns - fabsf(xs[c]);
+            t[c] = __builtin_fmaf(u[c], B.c, kNaN ? fminf(below, B.ns) : below);
+        }
         return fmt.two(sg, tb, top_bytes(t));
     }
     uint32_t levels = 0;
@@ -341,7 +348,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
             x.z *= B.prescale;
             x.w *= B.prescale;
         }
-        const uint32_t packed = B.dead ? 0u : quantize_vec4(x, (key.k0 + e0) * kRngC1, key.k1, B, PlainBytes{});
+        const uint32_t packed = B.dead ? 0u : quantize_vec4<true>(x, (key.k0 + e0) * kRngC1, key.k1, B, PlainBytes{});
         if (qaligned && e0 + 3u < nbk) {
             reinterpret_cast<uint32_t *>(qb)[vi] = packed;
         } else {
