@@ -443,6 +443,27 @@ __device__ __forceinline__ FlagBytes flag_bytes(uint32_t s)
         return FlagBytes{0u, 0x80808080u};
 }
 
+// nuq_encode's bytes (level index, sign in bit 7) in that format.  A level above s + 1 is the caller's error; it is coded
+// modulo 16 (a multiple of 16 as 1), so that a record is never longer than one of level 15 and a receiver with fewer levels
+// sees a level that it does not have.  Where the format has three bits of level, levels 9 to 15 set bit 4 too, which
+// SmallRecords<true> looks at.
+template <int TEAM>
+__device__ __forceinline__ uint32_t flag_caller_bytes(const FlagBytes &fmt, uint32_t s, uint32_t w)
+{
+    const bool three_bits = kSmallTeam<TEAM> && s <= 7u;
+    uint32_t levels = w & 0x7f7f7f7fu, above = 0;
+    if (__builtin_expect((w & (three_bits ? 0x78787878u : 0x70707070u)) != 0u, 0)) {
+        const uint32_t nonzero = ((levels + 0x7f7f7f7fu) >> 7) & 0x01010101u;
+        levels &= 0x0f0f0f0fu;
+        levels |= nonzero & ~((levels + 0x7f7f7f7fu) >> 7);
+        if (three_bits) {
+            above = (levels & 0x08080808u) & ((levels & 0x07070707u) + 0x07070707u);       // 9 to 15
+            levels -= above;
+        }
+    }
+    return fmt.any(w, levels) | (above << 1);
+}
+
 // The tables' way into LDS, in two halves: requested before the gradient's loads, stored when those are under way (a wait
 // for the tables before they are requested would start every workgroup with an idle round trip).
 template <int TEAM>
@@ -485,16 +506,19 @@ struct LargeRecords {
 };
 // In one word (code | length << 27): a bucket of a small team has at most 2048 coordinates, so a record at most
 // 18 + 1 + 7 = 26 bits.
+// kCaller: the bytes are flag_caller_bytes'.
+template <bool kCaller>
 struct SmallRecords {
     const uint32_t *at;      // the table's entry for byte 0 (the "not zero" bit, 64, is part of every byte looked up)
     uint32_t gap_bits;       // 5 (levels up to 8) or 4
     __device__ __forceinline__ uint32_t packed(uint32_t gap, uint32_t byte) const
     {
-        if (__builtin_expect(gap < (1u << gap_bits), 1))
+        const uint32_t above = kCaller ? byte & (gap_bits == 5u ? 0x10u : 0u) : 0u;      // levels 9 to 15 beside 3 bits
+        if (__builtin_expect((gap | (above << 1)) < (1u << gap_bits), 1))
             return at[(byte << gap_bits) | gap];
-        const uint32_t lbits = 8u - gap_bits, x = byte & 0x1fu;
+        const uint32_t lbits = 8u - gap_bits, x = (byte & 0x1fu) ^ above;
         uint32_t lg, ll;
-        const uint32_t cg = erc_code(gap, lg), cl = erc_code((x & ((1u << lbits) - 1u)) + 1u, ll);
+        const uint32_t cg = erc_code(gap, lg), cl = erc_code((x & ((1u << lbits) - 1u)) + (above >> 1) + 1u, ll);
         return (((cg << 1) | (x >> lbits)) << ll) | cl | ((lg + ll + 1u) << 27);
     }
     __device__ __forceinline__ uint32_t operator()(uint32_t gap, uint32_t byte, uint32_t &len) const
@@ -504,11 +528,11 @@ struct SmallRecords {
         return r & 0x7ffffffu;
     }
 };
-template <int TEAM>
+template <int TEAM, bool kCaller>
 __device__ __forceinline__ auto make_records(const uint32_t *tables, uint32_t s)
 {
     if constexpr (kSmallTeam<TEAM>)
-        return SmallRecords{tables - (s <= 7u ? 64 << 5 : 64 << 4), s <= 7u ? 5u : 4u};
+        return SmallRecords<kCaller>{tables - (s <= 7u ? 64 << 5 : 64 << 4), s <= 7u ? 5u : 4u};
     else
         return LargeRecords{tables};
 }
@@ -606,13 +630,13 @@ __device__ __forceinline__ void report_lengths(const EncodeParams &P, const Enco
 // Buckets with more nonzeros than the list holds: every thread codes the records of its own chunk, in two passes; the bit
 // string is assembled over the list's and the buffer's words together (the two regions are adjacent: three quarters of the
 // worst case for large buckets) if it fits there, else in the slot in global memory.
-template <int TEAM>
+template <int TEAM, bool kCaller>
 __device__ __forceinline__ uint32_t code_unlisted(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
                                               const TeamLds &L, const Chunk &C, uint32_t *slot)
 {
     const uint32_t tid = threadIdx.x % TEAM;
     const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
-    const auto record = make_records<TEAM>(L.tables, P.s);
+    const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
     const int last = C.nz ? (int)C.base + 63 - __clzll((long long)C.nz) : -1;
     const int before = team_exclusive_max<TEAM>(last, -1, reinterpret_cast<int *>(L.scratch + 16));
     auto for_my_records = [&](auto &&f) {
@@ -793,13 +817,13 @@ __device__ __forceinline__ uint32_t code_listed_large(const EncodeParams &P, con
 // A bucket is one block of the index and has at most one entry per thread.  While records are emitted, a record's place in
 // the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 26 bits), so the thread
 // of entry i reads its record's index before and its offset after.
-template <int TEAM>
+template <int TEAM, bool kCaller>
 __device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
                                                   const TeamLds &L, uint32_t nnz, uint32_t *slot)
 {
     const uint32_t tid = threadIdx.x % TEAM;
     const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
-    const auto record = make_records<TEAM>(L.tables, P.s);
+    const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
     const uint32_t per = (nnz + TEAM - 1u) / TEAM;
     const uint32_t r0 = min(tid * per, nnz), r1 = min(r0 + per, nnz);
     constexpr uint32_t kKept = 12;
@@ -877,8 +901,8 @@ __device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, con
     return total;
 }
 
-// Returns the bucket's bit length.
-template <int TEAM, int VPT>
+// Returns the bucket's bit length.  kCaller: the bytes are flag_caller_bytes'.
+template <int TEAM, int VPT, bool kCaller>
 __device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
                                                 const TeamLds &L)
 {
@@ -936,12 +960,12 @@ __device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const
                 *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
         team_barrier<TEAM>();
         if constexpr (kSmallTeam<TEAM>)
-            return code_listed_small<TEAM>(P, W, active, b, L, C.nnz, slot);
+            return code_listed_small<TEAM, kCaller>(P, W, active, b, L, C.nnz, slot);
         else
             return code_listed_large<TEAM>(P, W, active, b, L, C.nnz, slot);
     } else {
         team_barrier<TEAM>();
-        return code_unlisted<TEAM>(P, W, active, b, L, C, slot);
+        return code_unlisted<TEAM, kCaller>(P, W, active, b, L, C, slot);
     }
 }
 
@@ -1170,11 +1194,11 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
     } else {
         loads_issued();
         front_bytes<TEAM, VPT>(P, W, base, nbk, tid, [&](int i, uint32_t w) {
-            L.qb32[(uint32_t)i * TEAM + tid] = fmt.any(w, w & 0x7f7f7f7fu);
+            L.qb32[(uint32_t)i * TEAM + tid] = flag_caller_bytes<TEAM>(fmt, P.s, w);
         });
     }
     __syncthreads();
-    report_lengths<TEAM>(P, W, active, b, encode_from_lds<TEAM, VPT>(P, W, active, b, L));
+    report_lengths<TEAM>(P, W, active, b, encode_from_lds<TEAM, VPT, MODE == 1>(P, W, active, b, L));
 }
 
 // ------------------------------------------------- offsets and gather of the slots

@@ -50,3 +50,32 @@ def test_crafted_bytes(g, n, S, s):
     assert not g.u32(m.words)[words.size:].any()
     if sync.size:
         np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
+
+
+@pytest.mark.parametrize("s,density", [(1, 0.04), (3, 0.04), (7, 0.04), (7, 0.9), (8, 0.3), (14, 0.9)])
+@pytest.mark.parametrize("n,S", [(500, 128), (512, 128), (2048, 256), (1000, 64), (8192, 256), (20001, 512)])
+def test_levels_above_the_top(g, n, S, s, density):
+    """A level index above s + 1 is the caller's error, but not one that turns into another valid message: the level is coded
+    modulo 16 (1 for a multiple of 16), no other record changes, and the decoder refuses a level it does not have."""
+    nuq = g.nuq
+    rng = np.random.default_rng(n + 100 * s)
+    d = 4 * n - 7
+    q = np.where(rng.random(d) < density, rng.integers(1, s + 2, d), 0)
+    bad = (q > 0) & (rng.random(d) < 0.2)
+    bad[rng.permutation(np.flatnonzero(q))[:24]] = True
+    q[bad] = rng.integers(s + 2, 128, np.count_nonzero(bad))
+    q[np.flatnonzero(bad)[:8]] = [9, 15, 16, 17, 64, 65, 112, 127]
+    coded = np.where((q > 0) & (q % 16 == 0), 1, q % 16)
+    sign = np.where(q > 0, rng.integers(0, 2, d) << 7, 0)
+    m = g.alloc_message(d, n, 14, S)
+    nuq.nuq_encode(torch.from_numpy((q | sign).astype(np.uint8)).to(g.DEV), n, s, S, m.bit_off, m.words, m.sync,
+                   g.workspace(d, n, s))
+    assert nuq.nuq_last_error_flags() == 0
+    bo, words, sync = oracle.encode((coded | sign).astype(np.uint8), n, 14, S)
+    np.testing.assert_array_equal(g.u64(m.bit_off), bo)
+    np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
+    np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
+    m.norms.fill_(1.0)
+    out = torch.empty(d, dtype=torch.float32, device=g.DEV)
+    nuq.nuq_decode_accumulate([m], d, n, s, S, 1.0, False, out)
+    assert nuq.nuq_last_error_flags() == (nuq.FLAG_MALFORMED if (coded > s + 1).any() else 0)
