@@ -92,10 +92,11 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_pack_fixed(EncodeParams
 // coordinates at 4 bits: QSGDinf (bound by vector issue) 269 -> 226 us with the unpack; the main scheme's pack stays at
 // 147 us = 6.3 TB/s, what a bare kernel that reads as much and writes an eighth of it reaches.
 
-// The four level|sign bytes of a word as four 4-bit codes (sign << 3 | level, level <= 7), the first on top.
+// The four level|sign bytes of a word as four 4-bit codes (sign << 3 | level), the first on top.  A level above 7 is the
+// caller's error; its bit 3 meets the sign's, so that 8 is the signed zero that a receiver refuses, as at the other widths.
 __device__ __forceinline__ uint32_t nibble_codes(uint32_t bytes)
 {
-    const uint32_t n = ((bytes >> 4) & 0x08080808u) | (bytes & 0x07070707u);
+    const uint32_t n = ((bytes >> 4) & 0x08080808u) | (bytes & 0x0f0f0f0fu);
     const uint32_t hi = __builtin_amdgcn_udot4(n, 0x00000110u, 0u, false);      // n0 << 4 | n1
     return __builtin_amdgcn_udot4(n, 0x01100000u, hi << 8, false);              // ... | n2 << 4 | n3
 }

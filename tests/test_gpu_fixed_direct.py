@@ -1,6 +1,8 @@
 """Fixed-width coding at 4 and 8 bits, where pack and unpack go between registers and memory without an LDS phase: sizes
 at the edges of that route, against the oracle as in test_gpu_fixed.py (packed words bit-exact, averages within the bar)."""
+import numpy as np
 import pytest
+import torch
 
 import test_gpu_fixed as fixed
 
@@ -31,3 +33,19 @@ def g():
 ])
 def test_sizes_at_the_edges(g, d, n, s, b, K, kind):
     fixed.test_pack_fused_pack_and_unpack_average(g, d, n, s, b, K, kind)
+
+
+@pytest.mark.parametrize("n", [64, 512, 2048, 8192, 20000])
+def test_levels_above_the_top(g, n):
+    """Level indices from 8 up do not fit four bits (the caller's error): bit 3 is OR-ed with the sign, as it is at the widths
+    that go through LDS."""
+    nuq, d = g.nuq, 2 * n + 40
+    rng = np.random.default_rng(n)
+    q = rng.integers(0, 16, d)
+    q |= np.where(q > 0, rng.integers(0, 2, d) << 7, 0)
+    packed = torch.full((nuq.nuq_fixed_words(d, n, 4),), -1, dtype=torch.int32, device=g.DEV)
+    nuq.nuq_pack_fixed(torch.from_numpy(q.astype(np.uint8)).to(g.DEV), n, 3, 4, packed)
+    codes = np.zeros(3 * n, dtype=np.uint32)
+    codes[:d] = ((q >> 4) & 8) | (q & 15)
+    want = (codes.reshape(-1, 8) << np.arange(28, -1, -4, dtype=np.uint32)).sum(axis=1, dtype=np.uint32)
+    np.testing.assert_array_equal(g.u32(packed), want)
