@@ -34,9 +34,8 @@ CASES = [
 ]
 
 
-@pytest.mark.parametrize("d,n,kind,s,p,norm", CASES)
-def test_planted_near_ties(g, d, n, kind, s, p, norm):
-    nuq = g.nuq
+def planted(d, n, kind, s, p, norm):
+    """Levels, seed, coordinates on or beside their own rounding threshold or on a level, norms (the maximum of each bucket)."""
     lev = workloads.level_table(kind, s, p) if kind == "uniform" else [0.0] + [float(np.float32(p ** (s + 1 - j))) for j in range(1, s + 2)]
     rng = np.random.default_rng(d + n + s)
     seed, B = int(rng.integers(1 << 60)), oracle.num_buckets(d, n)
@@ -51,6 +50,14 @@ def test_planted_near_ties(g, d, n, kind, s, p, norm):
     v = (np.minimum(v, N) * rng.choice([-1.0, 1.0], d)).astype(np.float32)
     v[::n] = N                                        # the maximum norm of every bucket is N
     norms_np = np.full(B, N, dtype=np.float32)
+    return lev, seed, v, norms_np
+
+
+@pytest.mark.parametrize("d,n,kind,s,p,norm", CASES)
+def test_planted_near_ties(g, d, n, kind, s, p, norm):
+    nuq = g.nuq
+    lev, seed, v, norms_np = planted(d, n, kind, s, p, norm)
+    B = norms_np.size
     want = oracle.quantize_table(v, n, lev, seed, norms_np)
     vt = torch.from_numpy(v).to(g.DEV)
     q = torch.full((d,), 0x7F, dtype=torch.uint8, device=g.DEV)
@@ -63,6 +70,33 @@ def test_planted_near_ties(g, d, n, kind, s, p, norm):
     nuq.nuq_quantize_pack_fixed_table_batch([vt], n, lev, nuq.NORM_LINF, b, [seed], [norms], [packed])
     np.testing.assert_array_equal(norms.cpu().numpy(), norms_np)
     np.testing.assert_array_equal(g.u32(packed), oracle.pack_fixed(want, n, s, b))
+    assert nuq.nuq_last_error_flags() == 0
+
+
+@pytest.mark.parametrize("d,n,kind,s,p,norm", CASES)
+def test_planted_near_ties_where_a_row_is_put_twice(g, d, n, kind, s, p, norm):
+    """The fused kernels that hand a row's bytes on before they know that it is decided again: fixed width at 4 bits (codes in
+    registers) and at 8 (words in memory), and the bit strings (bytes in the coding phase's format)."""
+    nuq = g.nuq
+    lev, seed, v, norms_np = planted(d, n, kind, s, p, norm)
+    want = oracle.quantize_table(v, n, lev, seed, norms_np)
+    vt = torch.from_numpy(v).to(g.DEV)
+    for b in (4, 8):
+        if s + 2 > 1 << (b - 1):
+            continue
+        norms = torch.empty(norms_np.size, dtype=torch.float32, device=g.DEV)
+        packed = torch.full((nuq.nuq_fixed_words(d, n, b),), -1, dtype=torch.int32, device=g.DEV)
+        nuq.nuq_quantize_pack_fixed_table_batch([vt], n, lev, nuq.NORM_LINF, b, [seed], [norms], [packed])
+        np.testing.assert_array_equal(norms.cpu().numpy(), norms_np)
+        np.testing.assert_array_equal(g.u32(packed), oracle.pack_fixed(want, n, s, b))
+    S = 128
+    m = g.alloc_message(d, n, s, S)
+    nuq.nuq_quantize_encode_table_batch([vt], n, lev, nuq.NORM_LINF, [seed], S, [m], g.workspace(d, n, s))
+    bo, words, sync = oracle.encode(want, n, s, S)
+    np.testing.assert_array_equal(m.norms.cpu().numpy(), norms_np)
+    np.testing.assert_array_equal(g.u64(m.bit_off), bo)
+    np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
+    np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
     assert nuq.nuq_last_error_flags() == 0
 
 
