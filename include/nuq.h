@@ -106,8 +106,7 @@ uint64_t nuq_workspace_bytes(uint64_t d, uint32_t bucket, uint32_t K);
 /* ---- step 1: bucket norms (Def. 1: r_i = |v_i| / ||v||) --------------------------- */
 
 /* norms[b] = sqrt(sum of v_i^2 over bucket b), rounded to fp32.
- * v: d floats, 4-byte aligned (16-byte alignment with bucket % 4 == 0 takes the
- * vector-load path).  norms: B floats. */
+ * v: d floats, 4-byte aligned.  norms: B floats. */
 int nuq_bucket_norms(const float *v, uint64_t d, uint32_t bucket, float *norms,
                      nuq_stream_t stream);
 
@@ -210,9 +209,9 @@ int nuq_bucket_norms_linf(const float *v, uint64_t d, uint32_t bucket, float *no
 
 /* nuq_quantize for the level sequence `levels`: with e_t = levels[t] * norms[b] and a = |v_i|,
  * j = largest t with e_t <= a (j = s+1: the top level), else j+1 iff
- * u * (e_{j+1} - e_j) < (a - e_j) * 2^24, evaluated as exactly that sequence of IEEE fp64 operations
- * (the products e_t are exact; the two differences and the product with u round to nearest), u the
- * 24-bit draw of nuq_quantize.  For levels[t] = 2^(t-1-s) nothing rounds and q equals nuq_quantize's.
+ * u * (e_{j+1} - e_j) < (a - e_j) * 2^24 over the real numbers (no rounding enters the decision), u the
+ * 24-bit draw of nuq_quantize.  For levels[t] = 2^(t-1-s) q equals nuq_quantize's.  An infinite
+ * coordinate takes the top level, a NaN level 0.
  * norms may come from nuq_bucket_norms or nuq_bucket_norms_linf; a zero or non-finite norm gives an
  * all-zero bucket.  q feeds nuq_encode unchanged (a level index is coded the same way whatever its
  * value). */

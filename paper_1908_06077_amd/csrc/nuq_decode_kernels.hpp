@@ -174,8 +174,6 @@ __device__ __forceinline__ void apply4(const DecodeParams &P, float4 r, float4 *
 }
 
 
-// Output stage of a tile: scale the sums, round to fp32, apply to the output (write, add, or momentum rule), and
-// leave the tile zeroed.  Called by all WG threads of the workgroup.
 template <int UPDATE>
 __device__ __forceinline__ float *update_yl(const DecodeParams &P, uint64_t c_lo)
 {
@@ -188,6 +186,8 @@ __device__ __forceinline__ uint32_t tile_groups(const DecodeParams &P, uint64_t 
     const uintptr_t both = reinterpret_cast<uintptr_t>(P.out + c_lo) | reinterpret_cast<uintptr_t>(update_yl<UPDATE>(P, c_lo));
     return (both & 15u) == 0 ? span >> 2 : 0u;
 }
+// Output stage of a tile: scale the sums, round to fp32, apply to the output (write, add, or momentum rule), and
+// leave the tile zeroed.  Called by all WG threads of the workgroup.  kHave: as apply_full_tile.
 template <int UPDATE, uint32_t TC, uint32_t WG, bool kHave = false>
 __device__ __forceinline__ void tile_output(const DecodeParams &P, double *tile, uint64_t c_lo, uint32_t span, uint32_t tid,
                                             const OldValues<UPDATE, TC, WG> *old = nullptr)
@@ -371,9 +371,9 @@ __device__ __forceinline__ uint32_t level_table_entry(uint32_t p, uint32_t smax)
 //
 // kTable: the value of level j is wnorm * lev[j] (an arbitrary level sequence, lev in LDS) instead of
 // wnorm * 2^j (wnorm = ||v|| * 2^(-1-s)); both are exact in fp64.
-// Where a decoded value goes.  TileSink: the fp64 tile in LDS that sums the workers (at0 = address of the
-// bucket's index 0).  DirectSink: a single message has nothing to sum: fp32(scale * value), the same rounding the
-// tile's output stage applies to a sum of one term, stored or added straight into the output.
+// Where a decoded value goes.  TileSink: the fp64 tile in LDS that sums the workers.  DirectSink: a single message has
+// nothing to sum: fp32(scale * value), the same rounding the tile's output stage applies to a sum of one term, stored or
+// added straight into the output (at0 = address of the bucket's index 0).
 // A sink counts places in units of its own (kUnit = log2 units per coordinate), so that the parser's running index is the
 // address: place(i) of in-bucket index i, add(place, value).
 struct TileSink {

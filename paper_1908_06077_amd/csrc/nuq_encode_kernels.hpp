@@ -133,7 +133,9 @@ __device__ __forceinline__ void load_rows(float4 (&x)[VPT], const float *wg_base
     }
 }
 
-// sqrt(t) in fp64, correctly rounded, for t in [2^-80, 2^100]: what sqrt() does without its scaling for extreme arguments.
+// sqrt(t) in fp64, correctly rounded, for t in [2^-80, 2^100], where nothing can overflow or become subnormal: the
+// hardware's reciprocal square root as the seed, one step of Goldschmidt's iteration for the pair (g, h) -> (sqrt t,
+// 1 / (2 sqrt t)), then two corrections by the residual t - g^2, which an fma gives exactly (Markstein).
 __device__ __forceinline__ double sqrt_mid(double t)
 {
     const double y = __builtin_amdgcn_rsq(t);
@@ -505,7 +507,8 @@ struct LargeRecords {
     }
 };
 // In one word (code | length << 27): a bucket of a small team has at most 2048 coordinates, so a record at most
-// 18 + 1 + 7 = 26 bits.
+// 19 + 1 + 7 = 27 bits (the last of 2048 coordinates alone, at level 15): exactly what the word has room for.
+static_assert(erc_c(2048u).len + 1u + erc_c(15u).len <= 27u, "a small team's record beside its length in 32 bits");
 // kCaller: the bytes are flag_caller_bytes'.
 template <bool kCaller>
 struct SmallRecords {
@@ -815,7 +818,7 @@ __device__ __forceinline__ uint32_t code_listed_large(const EncodeParams &P, con
 
 // Steps (2) and (3), teams of a wave or less: around ten records per thread, each looked up once and kept as one word.
 // A bucket is one block of the index and has at most one entry per thread.  While records are emitted, a record's place in
-// the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 26 bits), so the thread
+// the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 27 bits), so the thread
 // of entry i reads its record's index before and its offset after.
 template <int TEAM, bool kCaller>
 __device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
