@@ -483,7 +483,7 @@ __device__ __forceinline__ void fill_table_bins(TableBins &B, const LevelTable &
 }
 
 // Bytes (format F) of four coordinates (in-bucket index of the first = counter0 - k0) by the fp64 rule.  Called by
-// whole waves: the first-bin route is chosen per wave.
+// all of a wave's lanes whose bucket is not dead: the first-bin route is chosen for them together.
 template <class F>
 __device__ __forceinline__ uint32_t quantize_table_vec4_exact(const float4 &x, uint32_t counter0, uint32_t k1,
                                                               const double *edges, double e1, uint32_t s, const F &fmt)
@@ -523,7 +523,8 @@ __device__ __forceinline__ uint32_t quantize_table_vec4_exact(const float4 &x, u
 // `redo` and is to be decided again by the fp64 rule, as is every row of a bucket whose bins reach the subnormals
 // (thr[0] = 0: the caller's business).  So is a row with an infinite coordinate (above every level) or a NaN (no level),
 // which a finite norm may meet where the caller supplies it: their margin is a NaN, and `near` is a minimum that a NaN
-// goes through.
+// goes through.  Not for dead buckets (a zero norm makes every margin zero): the caller leaves those out, whole rows of
+// them are then skipped, and so are the rows of an all-zero layer.
 // What it is for: the kernels around it are bound by vector issue, and the fp64 rule is twice as long.  QSGDinf at 4 bits,
 // eight gradients of 25.6 M coordinates, quantize + pack + unpack: 350 us with the fp64 rule throughout, 270 us with this.
 struct TableRule {

@@ -1133,27 +1133,28 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
     const BucketKey key = bucket_key(W.seed, b);
     const TableRule R = make_table_rule<TEAM>(bins, P.s);
     const bool all_exact = !dead && bins.thr[0] == 0.0f;
-    uint32_t redo = 0;                                     // rows to be decided again by the fp64 rule
+    uint32_t redo = 0;                                     // rows to be decided again by the fp64 rule (none if dead)
     const uint32_t x0 = (key.k0 + 4u * tid) * kRngC1;      // row i starts 4 * TEAM * i coordinates further on
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
         if ((uint32_t)i < P.rows) {
-            bool again;
-            const uint32_t q =
-                quantize_table_vec4<TEAM>(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, R, fmt, again);
-            put(i, dead ? 0u : q);
+            bool again = false;
+            uint32_t q = 0;
+            if (!dead)
+                q = quantize_table_vec4<TEAM>(x[i], x0 + (uint32_t)i * (4u * TEAM * kRngC1), key.k1, R, fmt, again);
+            put(i, q);
             redo |= (again ? 1u : 0u) << i;
         }
     }
     if (__any(all_exact))
-        redo = (1u << P.rows) - 1u;
-    while (redo) {                                         // uniform over the wave; the coordinates are loaded again
+        redo = dead ? 0u : (1u << P.rows) - 1u;
+    while (redo) {                             // uniform over the wave's live lanes; the coordinates are loaded again
         const int i = __builtin_ctz(redo);
         redo &= redo - 1u;
         const uint32_t vi = (uint32_t)i * TEAM + tid;
         const uint32_t q = quantize_table_vec4_exact(load_vec4(vb, vi, nbk), key.k0 + 4u * vi, key.k1,
                                                      bins.edge, bins.edge[1], P.s, fmt);
-        put(i, dead ? 0u : q);
+        put(i, q);
     }
 }
 

@@ -63,11 +63,13 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize_table(EncodePa
         const uint32_t e0 = 4u * vi;
         const bool mine = e0 < nbk;                     // lanes beyond the bucket's end run along with zeros
         const float4 x = mine ? load_vec4(vb, vi, nbk) : float4{0.f, 0.f, 0.f, 0.f};
-        bool again;
-        uint32_t packed = quantize_table_vec4<TEAM>(x, (key.k0 + e0) * kRngC1, key.k1, R, PlainBytes{}, again);
-        if (exact || again)
-            packed = quantize_table_vec4_exact(x, key.k0 + e0, key.k1, bins.edge, bins.edge[1], P.s, PlainBytes{});
-        packed = dead ? 0u : packed;
+        uint32_t packed = 0;
+        if (!dead) {
+            bool again;
+            packed = quantize_table_vec4<TEAM>(x, (key.k0 + e0) * kRngC1, key.k1, R, PlainBytes{}, again);
+            if (exact || again)
+                packed = quantize_table_vec4_exact(x, key.k0 + e0, key.k1, bins.edge, bins.edge[1], P.s, PlainBytes{});
+        }
         if (mine) {
             if (qaligned && e0 + 3u < nbk) {
                 reinterpret_cast<uint32_t *>(qb)[vi] = packed;

@@ -123,3 +123,30 @@ def test_infinite_and_nan_coordinates_under_a_finite_norm(g, n, kind, s, scale):
     assert want[at[0]].min() == s + 1 and not want[at[2]].any()
     np.testing.assert_array_equal(q.cpu().numpy(), want)
     assert nuq.nuq_last_error_flags() == 0
+
+
+@pytest.mark.parametrize("n", [60, 512, 2048, 8192, 32768])
+@pytest.mark.parametrize("kind,s", [("uniform", 3), ("exp", 7)])
+def test_dead_buckets_beside_live_ones(g, n, kind, s):
+    """Buckets of zeros, and buckets whose norm is infinite or NaN, among buckets with planted near-ties (four to a wave where
+    buckets are small)."""
+    nuq, B = g.nuq, 23
+    d = B * n - n // 3
+    lev, seed, v, norms_np = planted(d, n, kind, s, 0.3, 0.7)
+    for b in (0, 3, 5, 8, 9, 10, 11, 13, 22):
+        v[b * n:(b + 1) * n] = 0.0
+        norms_np[b] = 0.0
+    vt = torch.from_numpy(v).to(g.DEV)
+    want = oracle.quantize_table(v, n, lev, seed, norms_np)
+    norms = torch.empty(B, dtype=torch.float32, device=g.DEV)
+    packed = torch.full((nuq.nuq_fixed_words(d, n, 5),), -1, dtype=torch.int32, device=g.DEV)
+    nuq.nuq_quantize_pack_fixed_table_batch([vt], n, lev, nuq.NORM_LINF, 5, [seed], [norms], [packed])
+    np.testing.assert_array_equal(norms.cpu().numpy(), norms_np)
+    np.testing.assert_array_equal(g.u32(packed), oracle.pack_fixed(want, n, s, 5))
+    assert nuq.nuq_last_error_flags() == 0
+    norms_np[[2, 12]], norms_np[14] = np.inf, np.nan
+    for b in (2, 12, 14):
+        want[b * n:(b + 1) * n] = 0
+    q = torch.full((d,), 0x7F, dtype=torch.uint8, device=g.DEV)
+    nuq.nuq_quantize_table(vt, n, lev, seed, torch.from_numpy(norms_np).to(g.DEV), q)
+    np.testing.assert_array_equal(q.cpu().numpy(), want)
