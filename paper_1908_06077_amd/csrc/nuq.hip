@@ -963,6 +963,8 @@ static int unpack_accumulate_fixed_any(uint32_t K, const float *const *norms, co
             const bool one = bucket % (b == 4u ? 512u : 256u) == 0;
             auto kern = b == 4u ? (one ? k_unpack_accumulate_fixed_direct<4, true> : k_unpack_accumulate_fixed_direct<4, false>)
                                 : (one ? k_unpack_accumulate_fixed_direct<8, true> : k_unpack_accumulate_fixed_direct<8, false>);
+            if (b == 8u && K <= 2u)
+                kern = one ? k_unpack_accumulate_fixed_direct<8, true, true> : k_unpack_accumulate_fixed_direct<8, false, true>;
             ScopedTiming timing(NUQ_T_DECODE, st);
             hipLaunchKernelGGL(kern, dim3((uint32_t)blocks), dim3(256), (uint32_t)lut_bytes, st, P);
             return check_launch();

@@ -328,8 +328,12 @@ __global__ __launch_bounds__(256) void k_unpack_accumulate_fixed32(UnpackParams 
 constexpr uint32_t kUnpackIters = 4;
 constexpr uint32_t unpack_direct_coords(uint32_t b) { return kUnpackIters * 256u * (b == 4u ? 8u : 4u); }   // per workgroup
 
-// kOneBucket: what a wave handles at a time (512 or 256 coordinates) never crosses a bucket boundary.
-template <int B, bool kOneBucket>
+// kOneBucket: what a wave handles at a time (512 or 256 coordinates) never crosses a bucket boundary.  kFew: one or two
+// workers, whose words of all iterations are requested at once: a wave with one or two words in flight is too little for
+// the memory.  8 bits, 40 M coordinates of one worker: 37.5 us in turn, 28.1 at once (k_unpack_accumulate_fixed32 31.4); of
+// two 43.1, 36.2 (40.3); three fill it (48.7 against 60.9).  4 bits move half as much and gain nothing (28.9 to 30.5 in
+// turn, 30.0 at once).
+template <int B, bool kOneBucket, bool kFew = false>
 __global__ __launch_bounds__(256) void k_unpack_accumulate_fixed_direct(UnpackParams P)
 {
     static_assert(B == 4 || B == 8, "a word is whole groups of four codes");
@@ -360,42 +364,68 @@ __global__ __launch_bounds__(256) void k_unpack_accumulate_fixed_direct(UnpackPa
     const uint32_t swap = lane & 1u ? 0x05040100u : 0x03020706u;                 // halves of (other lane's, own)
     const double sc = (double)P.scale;
     bool bad = false;
-#pragma unroll 1
+    auto first_of_wave = [&](uint32_t it) { return wg0 + (uint64_t)(it * 4u + wave) * kWaveCoords; };
+    auto first_of_word = [&](uint64_t c_wave) { return c_wave + wsel * (32u / B); };    // (of this lane's word)
+    // returns the word's index; tab: LDS index of the table of (bucket of group, worker 0)
+    auto place = [&](uint64_t c_wave, uint32_t (&tab)[kGroups]) {
+        const uint64_t c_word = first_of_word(c_wave);
+        const uint64_t bk = bucket_of(kOneBucket ? c_wave : c_word);
+#pragma unroll
+        for (uint32_t g = 0; g < kGroups; ++g)                // (a group beyond the end: any table inside)
+            tab[g] = (uint32_t)((kOneBucket ? bk : bucket_of(min(c_wave + 256u * g + 4u * lane, P.d - 1u))) - bk_first) * P.K *
+                     kEntries;
+        return bk * P.wpb + (uint32_t)(c_word - bk * P.bucket) / (32u / B);
+    };
+    uint32_t ahead[kFew ? kUnpackIters : 1][2], tabs[kFew ? kUnpackIters : 1][kGroups];
+    if constexpr (kFew) {
+#pragma unroll
+        for (uint32_t it = 0; it < kUnpackIters; ++it) {
+            const uint64_t c_wave = first_of_wave(it);
+            ahead[it][0] = ahead[it][1] = 0u;
+            if (c_wave < P.d) {
+                const uint64_t word = place(c_wave, tabs[it]);
+                if (first_of_word(c_wave) < P.d) {
+                    ahead[it][0] = P.packed[0][word];
+                    if (P.K > 1u)
+                        ahead[it][1] = P.packed[1][word];
+                }
+            }
+        }
+    }
+#pragma unroll(kFew ? kUnpackIters : 1)
     for (uint32_t it = 0; it < kUnpackIters; ++it) {
-        const uint64_t c_wave = wg0 + (uint64_t)(it * 4u + wave) * kWaveCoords;
+        const uint64_t c_wave = first_of_wave(it);
         if (c_wave >= P.d)
             break;
-        const uint64_t c_word = c_wave + wsel * (32u / B);    // first coordinate of this lane's word
-        const bool live = c_word < P.d;
-        uint64_t word;
-        uint32_t tab[kGroups];                                // LDS index of the table of (bucket of group, worker 0)
-        if constexpr (kOneBucket) {
-            const uint64_t bk = bucket_of(c_wave);
-            word = bk * P.wpb + (uint32_t)(c_word - bk * P.bucket) / (32u / B);
+        uint64_t word = 0;
+        uint32_t tab[kGroups];
+        if constexpr (kFew) {
 #pragma unroll
             for (uint32_t g = 0; g < kGroups; ++g)
-                tab[g] = (uint32_t)(bk - bk_first) * P.K * kEntries;
+                tab[g] = tabs[it][g];
         } else {
-            const uint64_t bk = bucket_of(c_word);
-            word = bk * P.wpb + (uint32_t)(c_word - bk * P.bucket) / (32u / B);
-#pragma unroll
-            for (uint32_t g = 0; g < kGroups; ++g)            // (a group beyond the end: any table inside)
-                tab[g] = (uint32_t)(bucket_of(min(c_wave + 256u * g + 4u * lane, P.d - 1u)) - bk_first) * P.K * kEntries;
+            word = place(c_wave, tab);
         }
+        const bool live = first_of_word(c_wave) < P.d;
         double sum[4 * kGroups];
 #pragma unroll
         for (uint32_t c = 0; c < 4u * kGroups; ++c)
             sum[c] = 0.0;
-        for (uint32_t k0 = 0; k0 < P.K; k0 += 8u) {
-            uint32_t w[8];
+        constexpr uint32_t kFlight = kFew ? 2u : 8u;
+        for (uint32_t k0 = 0; k0 < (kFew ? 1u : P.K); k0 += kFlight) {
+            uint32_t w[kFlight];
 #pragma unroll
-            for (uint32_t q = 0; q < 8u; ++q) {
-                w[q] = 0u;
-                if (k0 + q < P.K && live)
-                    w[q] = P.packed[k0 + q][word];
+            for (uint32_t q = 0; q < kFlight; ++q) {
+                if constexpr (kFew) {
+                    w[q] = ahead[it][q];
+                } else {
+                    w[q] = 0u;
+                    if (k0 + q < P.K && live)
+                        w[q] = P.packed[k0 + q][word];
+                }
             }
 #pragma unroll
-            for (uint32_t q = 0; q < 8u; ++q) {
+            for (uint32_t q = 0; q < kFlight; ++q) {
                 if (k0 + q >= P.K)                            // uniform
                     break;
                 bad |= fixed_word_invalid<B>(w[q], P.s);

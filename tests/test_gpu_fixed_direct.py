@@ -29,6 +29,10 @@ def g():
     (70_001, 4096, 14, 8, 17, "gauss"),
     (8_192 * 3 + 513, 8192, 3, 4, 2, "gauss"),   # the last wave holds one coordinate of its second row
     (33_000, 32768, 14, 8, 2, "mixed"),
+    (12_289, 8192, 6, 8, 1, "gauss"),     # one and two workers: all words of a wave requested at once
+    (4_096 * 2 + 769, 512, 6, 8, 2, "mixed"),
+    (30_001, 1000, 9, 8, 2, "mixed"),
+    (30_001, 1000, 9, 8, 1, "edges"),
     (1_022, 1022, 3, 4, 2, "mixed"),      # buckets that are not whole words: the other kernel unpacks
 ])
 def test_sizes_at_the_edges(g, d, n, s, b, K, kind):
