@@ -79,3 +79,30 @@ def test_levels_above_the_top(g, n, S, s, density):
     out = torch.empty(d, dtype=torch.float32, device=g.DEV)
     nuq.nuq_decode_accumulate([m], d, n, s, S, 1.0, False, out)
     assert nuq.nuq_last_error_flags() == (nuq.FLAG_MALFORMED if (coded > s + 1).any() else 0)
+
+
+@pytest.mark.parametrize("n,S", [(3000, 0), (3000, 64), (8192, 256), (16384, 128), (20000, 512), (32768, 1024)])
+def test_strings_of_one_window_and_of_two(g, n, S):
+    """Buckets without a zero, a string of exactly the words that the list's and the buffer's LDS hold, a word more, and the
+    longest."""
+    nuq, s = g.nuq, 14
+    rng = np.random.default_rng(n)
+    up4 = lambda x: (x + 3) & ~3
+    slot = up4((9 * n + 31) // 32)
+    cap = up4((max(n // 4, 1024) + 1) // 2) + max(up4(slot // 4), 256)
+    x = (32 * cap - 3 * n) // 6                                # records of 9 bits (level 15), the others take 3 (level 1)
+    d = 6 * n
+    q = np.ones(d, dtype=np.uint8)
+    for b, c in enumerate((x, x + 1, n, x + 6, x - 6, x)):
+        q[b * n + rng.permutation(n)[:c]] = 15
+    q |= (rng.integers(0, 2, d) << 7).astype(np.uint8)
+    m = g.alloc_message(d, n, s, S)
+    nuq.nuq_encode(torch.from_numpy(q).to(g.DEV), n, s, S, m.bit_off, m.words, m.sync if S else None, g.workspace(d, n, s))
+    assert nuq.nuq_last_error_flags() == 0
+    bo, words, sync = oracle.encode(q, n, s, S)
+    lens = (bo[1:].astype(np.int64) - (bo[:-1].astype(np.int64) + 31) // 32 * 32 + 31) // 32
+    assert lens[0] == cap and lens[1] == cap + 1
+    np.testing.assert_array_equal(g.u64(m.bit_off), bo)
+    np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
+    if S:
+        np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
