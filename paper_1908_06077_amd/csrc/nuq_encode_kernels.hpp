@@ -992,12 +992,16 @@ __device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const
 }
 
 // What a team's LDS holds of a bucket's nonzero list and bit string.  Large buckets: a quarter of the worst case (about
-// four times what a Gaussian gradient produces).  Up to 512 coordinates: five nonzeros in eight (gradients: one in four),
-// which lets five workgroups of 16 buckets share a CU.
+// four times what a Gaussian gradient produces).  257 to 512 coordinates: five nonzeros in eight (gradients: one in four),
+// which lets five workgroups of 16 buckets share a CU.  Up to 256: all of them, since eight workgroups, as many as there are
+// waves for, fit beside that (at most 272 words per team), and the smaller a bucket, the denser it is.  30 M coordinates, list
+// of five in eight -> whole list, s = 3: buckets of 64 141 -> 101 us, of 100 91 -> 84.
 __host__ __device__ inline uint32_t team_rec_cap(uint32_t bucket)
 {
     const uint32_t quarter = bucket / 4u;
-    return bucket <= 512u ? (bucket * 5u / 8u + 7u) & ~7u : bucket <= 1024u ? bucket : (quarter > 1024u ? quarter : 1024u);
+    if (bucket <= 1024u)
+        return bucket > 256u && bucket <= 512u ? (bucket * 5u / 8u + 7u) & ~7u : bucket;
+    return quarter > 1024u ? quarter : 1024u;
 }
 __host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words)       // a multiple of 4, like slot_words
 {
