@@ -370,7 +370,9 @@ __device__ __forceinline__ uint32_t level_table_entry(uint32_t p, uint32_t smax)
 // 8192 40.3 -> 39.3 us.
 //
 // kTable: the value of level j is wnorm * lev[j] (an arbitrary level sequence, lev in LDS) instead of
-// wnorm * 2^j (wnorm = ||v|| * 2^(-1-s)); both are exact in fp64.
+// wnorm * 2^j (wnorm = ||v|| * 2^(-1-s)); both are exact in fp64.  lev[j] is requested ahead of chain 1, whose own read then
+// covers it: LDS reads return in order, so behind that read it held up everything the window's entry was needed for (two
+// messages of 12 M coordinates, s = 10, stride 512: 241 -> 197 us; eight, s = 3: 38.7 -> 35.0).
 // Where a decoded value goes.  TileSink: the fp64 tile in LDS that sums the workers.  DirectSink: a single message has
 // nothing to sum: fp32(scale * value), the same rounding the tile's output stage applies to a sum of one term, stored or
 // added straight into the output (at0 = address of the bucket's index 0).
@@ -427,6 +429,13 @@ __device__ __forceinline__ void decode_unit_fast(const Words &words, const uint1
     const uint32_t whi = (uint32_t)(wbits >> 32), wlo = (uint32_t)wbits;
     const uint32_t binade = whi - 0x00100000u < 0x7fe00000u ? 0x00100000u : 0u;
 
+    float lj = 0.0f;                // kTable: lev[] of the level entry
+    auto level_value = [&]() {
+        if constexpr (kTable) {
+            lj = lev[e2];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
     auto chain1 = [&]() {
         w = __builtin_amdgcn_alignbit(hi, lo, (uint32_t)n);
         e = lut[w >> 25];
@@ -451,7 +460,7 @@ __device__ __forceinline__ void decode_unit_fast(const Words &words, const uint1
         min_j = min(min_j, j);
         uint32_t mh, ml;
         if constexpr (kTable) {
-            const uint64_t mag = (uint64_t)__double_as_longlong(wnorm * (double)lev[j]) & 0x7fffffffffffffffull;
+            const uint64_t mag = (uint64_t)__double_as_longlong(wnorm * (double)lj) & 0x7fffffffffffffffull;
             mh = (uint32_t)(mag >> 32);
             ml = (uint32_t)mag;
         } else {
@@ -467,6 +476,7 @@ __device__ __forceinline__ void decode_unit_fast(const Words &words, const uint1
     at_raw = sink.place(forced >= 0 ? (uint32_t)forced : gap() - 1u);
     at = min(at_raw, place_last);
     while (n > end) {
+        level_value();
         chain1();
         __builtin_amdgcn_sched_barrier(0);
         cover_value();
@@ -476,6 +486,7 @@ __device__ __forceinline__ void decode_unit_fast(const Words &words, const uint1
         at_raw = at + (gap() << Sink::kUnit);
         at = min(at_raw, place_last);
     }
+    level_value();
     cover_value();
     bad |= (n != end) | (at_raw > place_last) | (min_j == 0u);
 }
