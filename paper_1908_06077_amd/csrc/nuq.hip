@@ -803,6 +803,8 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     // One wave per workgroup where a tile holds at most 64 pieces and each stream's pieces fit the lanes that copy it
     // (every usual geometry with an index); the two-wave kernel takes the rest (no index, many workers, fine strides).
     const bool wave = nsync && max_streams <= 64u && P.segs_per_tile <= (1u << P.lanes_shift);
+    if (wave)
+        P.parts_shift = P.lanes_shift - log2u(P.segs_per_tile);
     uint32_t resident = decode_resident_workgroups(variant, wave);
     if (!resident)
         return NUQ_EHIP;
@@ -1372,8 +1374,7 @@ int nuq_decode_accumulate_huffman(uint32_t K, const float *const *norms, const u
     // the lanes that copy a stream's words parse its pieces: a piece per lane
     if (P.segs_per_tile > (1u << P.lanes_shift))
         return NUQ_EINVAL;
-    P.stream_cap = HuffmanWaveCodec::kWordsPerLane << P.lanes_shift;
-    P.stream_stride = max_streams >= 16u ? P.stream_cap - 1u : P.stream_cap;
+    P.parts_shift = P.lanes_shift - log2u(P.segs_per_tile);
     uint32_t *flags = flags_ptr();
     if (!flags)
         return NUQ_EHIP;

@@ -59,6 +59,7 @@ struct DecodeParams {
     uint32_t lanes_shift;       // log2 of the lanes that copy one stream's words
     uint32_t stream_cap;        // words the lanes of a stream carry = kWordsPerLane << lanes_shift
     uint32_t stream_stride;     // LDS words per stream: stream_cap, or stream_cap - 1 (odd) for tiles of many streams
+    uint32_t parts_shift;       // one-wave decoder: log2 of the lanes that load a piece's words
     float scale;
     float *yl;                  // kUpdateMomentum: y^l of the previous step, replaced by this step's
     double alpha, la, mu;       // kUpdateMomentum: step size, l * step size, momentum parameter
@@ -404,43 +405,40 @@ struct DirectSink {
     }
 };
 
-template <bool kTable, class Words, class Sink>
-__device__ __forceinline__ void decode_unit_fast(const Words &words, const uint16_t *lut, const uint8_t *lut_level,
-                                                 const float *lev, uint32_t bit_lo, uint32_t bit_hi, int forced,
-                                                 uint32_t idx_hi, double wnorm, const Sink &sink, bool &bad)
-{
-    if (bit_lo >= bit_hi) {
-        bad |= bit_lo != bit_hi;
-        return;
-    }
-    int n = (int)~(bit_lo + 31u);                // counts down; its word index m = n >> 5 = ~(word of position + 31)
-    const int end = (int)~(bit_hi + 31u);
-    int m = n >> 5;
-    uint32_t hi = words.at(~(uint32_t)m), lo = words.at(~(uint32_t)m + 1u), nx = words.after(m);
-    const uint32_t place_last = sink.place(idx_hi - 1u);
+template <bool kTable, class Sink>
+struct ErcParser {
+    const uint16_t *lut;
+    const uint8_t *lut_level;
+    const float *lev;
+    Sink sink;
+    double wnorm;
+    int n, end;                     // position (see above) and the unit's end in the same count
+    int m;                          // n >> 5 = ~(word of position + 31)
+    uint32_t hi, lo, nx;
+    uint32_t place_last;
     uint32_t at, at_raw;            // place of the record, clamped to the last one and before that: once the latter has
                                     // passed the last place it stays beyond it, so its last value tells
     uint32_t w, e;                  // window, gap entry
     uint32_t y, e2;                 // rotated window; level entry (in flight)
-    uint32_t min_j = 1;             // smallest table entry met: 0 marks a level code the message cannot hold
-    // ||v|| * l_j = (||v|| * 2^(-1-s)) * 2^j, exact in fp64: j is added to the exponent (never subnormal: an fp32 norm
-    // times a power of two down to 2^-15); zero, infinity and NaN stay what they are
-    const uint64_t wbits = (uint64_t)__double_as_longlong(wnorm) & 0x7fffffffffffffffull;
-    const uint32_t whi = (uint32_t)(wbits >> 32), wlo = (uint32_t)wbits;
-    const uint32_t binade = whi - 0x00100000u < 0x7fe00000u ? 0x00100000u : 0u;
+    uint32_t min_j;                 // smallest table entry met: 0 marks a level code the message cannot hold
+    float lj;                       // kTable: lev[] of the level entry
+    uint32_t whi, wlo, binade;
 
-    float lj = 0.0f;                // kTable: lev[] of the level entry
-    auto level_value = [&]() {
+    __device__ __forceinline__ void level_value()
+    {
         if constexpr (kTable) {
             lj = lev[e2];
             __builtin_amdgcn_sched_barrier(0);
         }
-    };
-    auto chain1 = [&]() {
+    }
+    __device__ __forceinline__ void chain1()
+    {
         w = __builtin_amdgcn_alignbit(hi, lo, (uint32_t)n);
         e = lut[w >> 25];
-    };
-    auto chain2 = [&]() {
+    }
+    template <class Words>
+    __device__ __forceinline__ void chain2(const Words &words)
+    {
         y = __builtin_amdgcn_alignbit(w, w, e);
         e2 = lut_level[y >> 25];
         // selector: the level code's first three bits, three bytes of ones above; bytes: -(32 + length of the level code)
@@ -453,9 +451,10 @@ __device__ __forceinline__ void decode_unit_fast(const Words &words, const uint1
         lo = moved ? nx : lo;
         m = mn;
         nx = words.after(mn);
-    };
-    auto gap = [&]() { return max(__builtin_amdgcn_ubfe(y, 2u, e >> 5), 1u); };
-    auto cover_value = [&]() {
+    }
+    __device__ __forceinline__ uint32_t gap() const { return max(__builtin_amdgcn_ubfe(y, 2u, e >> 5), 1u); }
+    __device__ __forceinline__ void cover_value()
+    {
         const uint32_t j = e2;
         min_j = min(min_j, j);
         uint32_t mh, ml;
@@ -468,27 +467,75 @@ __device__ __forceinline__ void decode_unit_fast(const Words &words, const uint1
             ml = wlo;
         }
         sink.add(at, __longlong_as_double((long long)(((uint64_t)((y << 31) | mh) << 32) | ml)));
-    };
+    }
+    template <class Words>
+    __device__ __forceinline__ void load(const Words &words)
+    {
+        m = n >> 5;
+        hi = words.at(~(uint32_t)m);
+        lo = words.at(~(uint32_t)m + 1u);
+        nx = words.after(m);
+    }
 
-    chain1();
-    chain2();
-    // (entered through a sync entry: its index replaces the first gap)
-    at_raw = sink.place(forced >= 0 ? (uint32_t)forced : gap() - 1u);
-    at = min(at_raw, place_last);
-    while (n > end) {
-        level_value();
+    // The first record of a unit that has one.
+    template <class Words>
+    __device__ __forceinline__ void start(const Words &words, uint32_t bit_lo, uint32_t bit_hi, int forced, uint32_t idx_hi)
+    {
+        n = (int)~(bit_lo + 31u);
+        end = (int)~(bit_hi + 31u);
+        load(words);
+        place_last = sink.place(idx_hi - 1u);
+        min_j = 1;
+        // ||v|| * l_j = (||v|| * 2^(-1-s)) * 2^j, exact in fp64: j is added to the exponent (never subnormal: an fp32 norm
+        // times a power of two down to 2^-15); zero, infinity and NaN stay what they are
+        const uint64_t wbits = (uint64_t)__double_as_longlong(wnorm) & 0x7fffffffffffffffull;
+        whi = (uint32_t)(wbits >> 32);
+        wlo = (uint32_t)wbits;
+        binade = whi - 0x00100000u < 0x7fe00000u ? 0x00100000u : 0u;
+        lj = 0.0f;
         chain1();
-        __builtin_amdgcn_sched_barrier(0);
-        cover_value();
-        __builtin_amdgcn_sched_barrier(0);
-        chain2();
-        __builtin_amdgcn_sched_barrier(0);
-        at_raw = at + (gap() << Sink::kUnit);
+        chain2(words);
+        // (entered through a sync entry: its index replaces the first gap)
+        at_raw = sink.place(forced >= 0 ? (uint32_t)forced : gap() - 1u);
         at = min(at_raw, place_last);
     }
-    level_value();
-    cover_value();
-    bad |= (n != end) | (at_raw > place_last) | (min_j == 0u);
+    // Records while the position is above `stop`.
+    template <class Words>
+    __device__ __forceinline__ void run(const Words &words, int stop)
+    {
+        while (n > stop) {
+            level_value();
+            chain1();
+            __builtin_amdgcn_sched_barrier(0);
+            cover_value();
+            __builtin_amdgcn_sched_barrier(0);
+            chain2(words);
+            __builtin_amdgcn_sched_barrier(0);
+            at_raw = at + (gap() << Sink::kUnit);
+            at = min(at_raw, place_last);
+        }
+    }
+    __device__ __forceinline__ void finish(bool &bad)
+    {
+        level_value();
+        cover_value();
+        bad |= (n != end) | (at_raw > place_last) | (min_j == 0u);
+    }
+};
+
+template <bool kTable, class Words, class Sink>
+__device__ __forceinline__ void decode_unit_fast(const Words &words, const uint16_t *lut, const uint8_t *lut_level,
+                                                 const float *lev, uint32_t bit_lo, uint32_t bit_hi, int forced,
+                                                 uint32_t idx_hi, double wnorm, const Sink &sink, bool &bad)
+{
+    if (bit_lo >= bit_hi) {
+        bad |= bit_lo != bit_hi;
+        return;
+    }
+    ErcParser<kTable, Sink> U{lut, lut_level, lev, sink, wnorm};
+    U.start(words, bit_lo, bit_hi, forced, idx_hi);
+    U.run(words, U.end);
+    U.finish(bad);
 }
 
 // Where a tile lies.  Everything here is uniform over the workgroup.
@@ -994,7 +1041,7 @@ struct WaveMeta {           // what a lane loads for its stream (bucket, worker)
 // The paper's ENCODE (App. A): records ERC(gap) | sign | ERC(level index), pieces of equal record count.
 template <bool kTable>
 struct ErcCodec {
-    static constexpr uint32_t kWordsPerLane = nuq::kWordsPerLane;
+    static constexpr uint32_t kRowWords = 13, kFewWords = 8;
     uint16_t *lut;          // LDS: 128 entries (gap_table_entry)
     uint8_t *lut_level;     // LDS: 128 entries (level_table_entry)
     float *lev;             // LDS: 16 level values (level-table variant), else nullptr
@@ -1040,46 +1087,66 @@ struct ErcCodec {
         }
         return true;
     }
-    template <class Words>
-    __device__ __forceinline__ void parse(const Words &words, const Range &R, uint32_t bit0, float norm,
-                                          const TileSink &sink, bool &bad) const
+    using Parser = ErcParser<kTable, TileSink>;
+    __device__ __forceinline__ Parser parser(float norm, const TileSink &sink) const
     {
-        const double wnorm = (double)norm * (kTable ? 1.0 : ldexp(1.0, -1 - (int)s));
-        decode_unit_fast<kTable>(words, lut, lut_level, lev, R.bit_lo - bit0, R.bit_hi - bit0, (int)R.forced, R.idx_hi,
-                                 wnorm, sink, bad);
+        return Parser{lut, lut_level, lev, sink, (double)norm * (kTable ? 1.0 : ldexp(1.0, -1 - (int)s))};
+    }
+    __device__ __forceinline__ void start(Parser &U, const StagedWords &words, const Range &R) const
+    {
+        U.start(words, R.bit_lo & 31u, R.bit_hi - (R.bit_lo & ~31u), (int)R.forced, R.idx_hi);
     }
     uint32_t s;
 };
 
 // The kernel's body is written once for every code of the level indices.  A Codec supplies
-//   kWordsPerLane                    staged words each lane carries (64 x that many per tile)
+//   kRowWords                        words of a lane's piece that are staged at a time
 //   init(P, lane)                    its tables, into LDS that the kernel handed it
 //   entries(sy, g, P, e_lo, e_hi)    the index entries that bound piece g of a bucket (sy = the bucket's entries)
-//   range(P, g, nbk, e_lo, e_hi, len, R, bad)   piece g's bit range and what else its parse needs; false = nothing to do
-//   parse(words, R, bit0, norm, sink, bad)      the parse proper, adding values into the tile
+//   range(P, g, nbk, e_lo, e_hi, len, R, bad)   piece g's bit range (R.bit_lo, R.bit_hi, from the bucket's first bit) and
+//                                    what else its parse needs; false = nothing to do
+//   Parser, parser(norm, sink), start(U, words, R), U.run(words, stop), U.finish(bad)   the parse proper, adding values into
+//                                    the tile; U.n, U.end: position and end as ~(bits from the row's first word + 31), so
+//                                    that they count down
+//
+// Words reach the parser through LDS, a row per lane: kRowWords words of the lane's piece at a time.  The first row of the
+// next tile's pieces is in flight while a tile is parsed; a piece with more words than a row (dense gradients, level tables
+// that leave most coordinates nonzero) gets the next row, also requested while the one before is parsed, until no lane of
+// the wave has words left.  A record may straddle two rows: a row's last word is the next one's first.  Copied stream by
+// stream into a fixed share of the staging area, as they were, a piece of more than eight words was read from global memory
+// record by record, which is what buckets of 256, eight workers' buckets of 512 or 1000 and dense level tables have: decode
+// of 4 x 16.8 M coordinates in buckets of 256 66 -> 44 us at stride 128, 113 -> 66 at 256, of 8 x 16.8 M in buckets of 1000
+// 66 -> 52; QSGDinf through ERC, 8 x 16.8 M, encode + decode 567 -> 436.  13 words: what eight workgroups per CU leave room for.
+// On gradients (six words per piece) the rows need fewer instructions than the copy did, no lane exchange and no clamped
+// addresses: 8 x 25.6 M in buckets of 8192 39.9 -> 36.4 us, 4 x 195 M in buckets of 512 337 -> 328.
 template <class Codec, int UPDATE, uint32_t TC>
 __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &codec)
 {
-    constexpr uint32_t kWordsPerLane = Codec::kWordsPerLane;
-    constexpr uint32_t kStageWords = kWave * kWordsPerLane;
+    constexpr uint32_t kRowWords = Codec::kRowWords, kFewWords = Codec::kFewWords;
     __shared__ __align__(16) double tile[TC];
-    __shared__ uint32_t stage[kStageWords + 5];       // words at [1, kStageWords]; pads as in k_decode_accumulate
+    // rows of kRowWords words per lane that loads for a piece, one more (odd: they then start in different banks) where that
+    // is even; the parser may read one word before a row and three behind it
+    static_assert(kRowWords % 2u == 1u, "the stride of rows that one lane loads");
+    __shared__ uint32_t stage[kWave * kRowWords + kWave / 2 + 4];
     const uint32_t lane = threadIdx.x;
     const bool partial = !P.buckets_per_tile;         // tiles are parts of one bucket
-    const uint32_t stream_stride = TC == kTileCoordsBig ? P.stream_cap : P.stream_stride;
     const uint64_t last_bucket = P.nb - 1u;
     const uint32_t last_len = (uint32_t)(P.d - last_bucket * P.bucket);
 
-    // this lane's stream (bucket in tile, worker) and piece of it; its pointers into that worker's arrays
-    const uint32_t lanes = 1u << P.lanes_shift;
-    const uint32_t my_stream = lane >> P.lanes_shift, my_sub = lane & (lanes - 1u);
+    // this lane's stream (bucket in tile, worker) and piece of it; its pointers into that worker's arrays.  Where a tile has
+    // half as many pieces as lanes or fewer, 2^parts_shift lanes load the words of a piece, the first of which parses it.
+    const uint32_t piece_lanes_shift = P.lanes_shift - P.parts_shift;
+    const uint32_t my_stream = lane >> P.lanes_shift;
+    const uint32_t my_sub = lane & ((1u << piece_lanes_shift) - 1u);
+    const uint32_t my_part = (lane >> piece_lanes_shift) & ((1u << P.parts_shift) - 1u);
     const uint32_t sk = my_stream % P.K, sbi = my_stream / P.K;
     const uint64_t *const pb = P.bit_off[sk];
     const float *const pn = P.norms[sk];
     const uint32_t *const ps = P.sync[sk];
     const uint32_t *const pw = P.words[sk];
     const uint64_t words_bits = P.words_bits[sk];
-    const uint32_t first_lane = lane & ~(lanes - 1u);
+    const uint32_t row_words = kRowWords << P.parts_shift, few_words = kFewWords << P.parts_shift;
+    uint32_t *const row = stage + 1u + ((my_stream << piece_lanes_shift) + my_sub) * (row_words | 1u);
 
     auto load_meta = [&](const TileGeom &G) {
         WaveMeta m;
@@ -1090,38 +1157,65 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
         codec.entries(ps + b * P.nsync, G.g0 + my_sub, P, m.e_lo, m.e_hi);
         return m;
     };
-    // the part of the lane's stream that the tile needs: from the entry of the tile's first piece to that of the
-    // piece after its last one (held by the stream's first and last lanes)
-    auto part_of = [&](const TileGeom &G, const WaveMeta &m, bool &bad) {
-        uint32_t e0 = 0, e1 = 0;
-        if (partial) {
-            const uint32_t pieces = G.g1 - G.g0;                      // >= 1 for a tile with coordinates
-            e0 = (uint32_t)__shfl((int)m.e_lo, (int)first_lane, kWave);
-            e1 = (uint32_t)__shfl((int)m.e_hi, (int)(first_lane + max(pieces, 1u) - 1u), kWave);
+    // the lane's piece of a tile (the pointer in the global address space by type: one of two, it would be taken for generic)
+    typedef const __attribute__((address_space(1))) uint32_t *GlobalWordsPtr;
+    struct Unit {
+        typename Codec::Range R;
+        GlobalWordsPtr src;         // the word that holds its first bit
+        uint32_t words;             // from there to its end; 0: nothing to do
+        uint32_t beyond;            // from there to the end of the message (at most 2^31)
+    };
+    auto words_left = [&](uint64_t first) { return (uint32_t)min((words_bits >> 5) - first, (uint64_t)1u << 31); };
+    auto make_unit = [&](const TileGeom &G, const WaveMeta &m, bool &bad) {
+        Unit U{};
+        if (my_stream < G.nstreams && my_sub < G.g1 - G.g0) {
+            // offsets that run backwards, leave the worker's words or span 2^21 bits or more: nothing is read from words[]
+            const uint64_t start = (m.bo0 + 31ull) & ~31ull;
+            const bool wrong = m.bo1 < m.bo0 || m.bo1 > words_bits ||
+                               (m.bo1 > start && m.bo1 - start > (uint64_t)kSyncOffMask);
+            const uint32_t len = m.bo1 > start && !wrong ? (uint32_t)(m.bo1 - start) : 0u;
+            bad |= wrong;
+            const uint32_t nbk = G.b0 + sbi == last_bucket ? last_len : P.bucket;
+            if (codec.range(P, G.g0 + my_sub, nbk, m.e_lo, m.e_hi, len, U.R, bad)) {
+                U.src = (GlobalWordsPtr)pw + (start >> 5) + (U.R.bit_lo >> 5);
+                U.beyond = words_left((start >> 5) + (U.R.bit_lo >> 5));
+                U.words = ((U.R.bit_hi + 31u) >> 5) - (U.R.bit_lo >> 5);
+            }
         }
-        bool wrong = false;
-        const StreamPart S = stream_part(P, G, m.bo0, m.bo1, e0, e1, words_bits, wrong);
-        bad |= wrong && my_stream < G.nstreams;                       // (a lane without a stream loaded any bucket's)
-        return S;
+        return U;
     };
-    auto load_words = [&](const TileGeom &G, const StreamPart &S, uint32_t (&w)[kWordsPerLane]) {
-        // lanes beyond the part's end load its last word again (nothing reads what they store); a lane without a
-        // stream, or a part without words, loads any readable word
-        const uint32_t cnt = my_stream < G.nstreams ? min(S.nwords, stream_stride) : 0u;
-        const uint32_t *src = cnt ? pw + S.first_word : P.flags;
-        const uint32_t last = max(cnt, 1u) - 1u;
+    // Words [first, first + row_words) of a unit, the first few_words of them or (`wide`, uniform) all: kFewWords or
+    // kRowWords in a run per lane, loaded whatever the unit's end (nothing looks beyond it).  A run that would leave the
+    // message is loaded from elsewhere instead, and word by word where it is stored: two ways to load into one set of
+    // registers would make the compiler wait for the loads where the ways join.
+    auto run_at = [&](uint32_t first, bool wide) { return first + (wide ? kRowWords : kFewWords) * my_part; };
+    auto load_row = [&](const Unit &U, uint32_t first, bool wide, uint32_t (&w)[kRowWords]) {
+        const uint32_t at = run_at(first, wide);
+        const bool inside = U.words > at && U.beyond >= at + kRowWords;
+        const GlobalWordsPtr src = inside ? U.src + at : (GlobalWordsPtr)kCodeTables.large;
 #pragma unroll
-        for (uint32_t i = 0; i < kWordsPerLane; ++i)
-            w[i] = src[min(my_sub + (i << P.lanes_shift), last)];
+        for (uint32_t i = 0; i < kFewWords; ++i)
+            w[i] = src[i];
+        if (wide)
+#pragma unroll
+            for (uint32_t i = kFewWords; i < kRowWords; ++i)
+                w[i] = src[i];
     };
-    auto store_words = [&](const uint32_t (&w)[kWordsPerLane]) {
-        const uint32_t base = 1u + my_stream * stream_stride + my_sub;
+    auto store_row = [&](const Unit &U, uint32_t first, bool wide, const uint32_t (&w)[kRowWords]) {
+        const uint32_t at = run_at(first, wide);
+        uint32_t *const r = row + (wide ? kRowWords : kFewWords) * my_part;
 #pragma unroll
-        for (uint32_t i = 0; i + 1u < kWordsPerLane; ++i)
-            stage[base + (i << P.lanes_shift)] = w[i];
-        constexpr uint32_t kLast = kWordsPerLane - 1u;                // an odd stride has no place for the very last word
-        if (TC == kTileCoordsBig || my_sub + (kLast << P.lanes_shift) < stream_stride)
-            stage[base + (kLast << P.lanes_shift)] = w[kLast];
+        for (uint32_t i = 0; i < kFewWords; ++i)
+            r[i] = w[i];
+        if (wide)
+#pragma unroll
+            for (uint32_t i = kFewWords; i < kRowWords; ++i)
+                r[i] = w[i];
+        if (__builtin_expect(U.words > at && U.beyond < at + kRowWords, 0)) {
+#pragma unroll 1
+            for (uint32_t i = 0; i < (wide ? kRowWords : kFewWords) && at + i < U.words; ++i)
+                r[i] = U.src[at + i];
+        }
     };
     // LDS traffic of one wave needs no hardware barrier: its operations complete in order.  (No memory fence here: a
     // fence also waits for every global load and store in flight, which is exactly what this kernel keeps in flight.)
@@ -1145,12 +1239,11 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
     for (uint32_t i = lane; i < TC / 2u; i += kWaveWG)
         reinterpret_cast<double2 *>(tile)[i] = double2{0.0, 0.0};
     codec.init(P, lane);
-    if (lane < 5u)
-        stage[lane ? kStageWords + lane : 0u] = 0u;                  // the pads
-    StreamPart S0 = part_of(G0, M0, bad);
-    uint32_t W0[kWordsPerLane];
-    load_words(G0, S0, W0);
-    store_words(W0);
+    Unit U0 = make_unit(G0, M0, bad);
+    uint32_t W0[kRowWords];
+    bool wide = __any(U0.words > few_words);
+    load_row(U0, 0u, wide, W0);
+    store_row(U0, 0u, wide, W0);
 
     // Order of a round, chosen for the one counter that tracks loads and stores alike and in issue order: the next
     // tile's words and the offsets of the tile after it are requested first, this tile is parsed (which takes longer
@@ -1160,12 +1253,13 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
     for (;;) {
         const bool has1 = t + stride < P.ntiles;                      // uniform
         const bool has2 = has1 && t + stride < P.ntiles - stride;
-        StreamPart S1 = S0;
+        Unit U1 = U0;
         TileGeom G2 = G1;
         WaveMeta M2 = M1;
         if (has1) {
-            S1 = part_of(G1, M1, bad);
-            load_words(G1, S1, W0);
+            U1 = make_unit(G1, M1, bad);
+            wide = __any(U1.words > few_words);
+            load_row(U1, 0u, wide, W0);
         }
         if (has2) {
             G2 = tile_geom(P, xcd_tile(P, t + 2u * stride));
@@ -1180,31 +1274,52 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
         lds_fence();
 
         // ---- this lane's piece of tile t
-        const uint32_t pieces = G0.g1 - G0.g0;
-        if (my_stream < G0.nstreams && my_sub < pieces) {
-            const uint32_t nbk = G0.b0 + sbi == last_bucket ? last_len : P.bucket;
-            typename Codec::Range R;
-            if (codec.range(P, G0.g0 + my_sub, nbk, M0.e_lo, M0.e_hi, S0.len, R, bad)) {
-                // (an index that is not monotone would leave the part of the stream that was copied)
-                if (R.bit_lo < S0.bit0 || R.bit_hi > S0.bit0 + (S0.nwords << 5)) {
-                    bad = true;
-                } else {
-                    const TileSink sink{tile, 8u * (partial ? 0u - G0.in_lo : sbi * P.bucket)};
-                    if (S0.nwords <= stream_stride)
-                        codec.parse(StagedWords{stage + my_stream * stream_stride}, R, S0.bit0, M0.norm, sink, bad);
-                    else {                            // the part did not fit the staging area: words from global memory
-                        codec.parse(GlobalWords{pw + S0.first_word, S0.nwords - 1u}, R, S0.bit0, M0.norm, sink, bad);
-                        // every load of this rare path has landed before the paths join again: otherwise the compiler,
-                        // which must assume the worst of the joined paths, waits for all memory traffic wherever the
-                        // usual path later touches a register that this one loaded into
-                        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+        {
+            const bool work = U0.words != 0u && my_part == 0u;
+            const TileSink sink{tile, 8u * (partial ? 0u - G0.in_lo : sbi * P.bucket)};
+            typename Codec::Parser parser = codec.parser(M0.norm, sink);
+            const StagedWords words{row - 1};
+            if (!__any(U0.words > row_words)) {
+                if (work) {
+                    codec.start(parser, words, U0.R);
+                    parser.run(words, parser.end);
+                    parser.finish(bad);
+                }
+            } else {
+                // a record needs its position's word and the next one: the last position that a row serves
+                const uint32_t step = row_words - 1u;                 // words by which a row moves on
+                const int row_end = (int)~(32u * step + 32u);
+                uint32_t first = step, w[kRowWords];
+                load_row(U0, first, true, w);
+                if (work) {
+                    codec.start(parser, words, U0.R);
+                    parser.run(words, max(parser.end, row_end));
+                }
+                while (__any(work && parser.n > parser.end)) {
+                    lds_fence();
+                    store_row(U0, first, true, w);
+                    lds_fence();
+                    first += step;
+                    if (__any(U0.words > first))
+                        load_row(U0, first, true, w);
+                    if (work && parser.n > parser.end) {
+                        parser.n += 32 * (int)step;
+                        parser.end += 32 * (int)step;
+                        parser.load(words);
+                        parser.run(words, max(parser.end, row_end));
                     }
                 }
+                if (work)
+                    parser.finish(bad);
+                // every load of this path has landed before the paths join again: otherwise the compiler, which must assume
+                // the worst of the joined paths, waits for all memory traffic wherever the other path later touches a
+                // register that this one loaded into
+                __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
             }
         }
         lds_fence();
         if (has1)
-            store_words(W0);                              // (the parse of this tile is over: the staging area is free)
+            store_row(U1, 0u, wide, W0);                  // (the parse of this tile is over: the staging area is free)
         // The offsets of the tile after the next were requested with those words and have arrived: said here, since the
         // compiler would otherwise wait for them where the round ends, behind the stores and so for the stores (the
         // output's other path issues an unknown number of them).  4 x 1.56 G coordinates in buckets of 512 2.74 -> 2.68 ms,
@@ -1219,7 +1334,7 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
         G1 = G2;
         M0 = M1;
         M1 = M2;
-        S0 = S1;
+        U0 = U1;
     }
     if (bad)
         atomicOr(P.flags, kFlagMalformed);

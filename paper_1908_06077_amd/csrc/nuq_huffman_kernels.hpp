@@ -797,8 +797,11 @@ __global__ __launch_bounds__(kHuffmanDirectWG) void k_huffman_decode_direct(Huff
 // zero bits, followed by one nonzero symbol when its codeword and sign still fit the 32-bit window: about as many
 // steps as the ERC parse has records.  With any other code a step is one symbol.
 struct HuffmanWaveCodec {
-    static constexpr uint32_t kWordsPerLane = 13;      // a tile's part of a string is ~75 words on gradient data; 13: eight workgroups per CU
-    uint8_t *lut8;          // LDS, 256 entries: symbol | length << 4 of the codeword the eight bits start with, else 0
+    static constexpr uint32_t kRowWords = 13, kFewWords = 11;      // gradient data: about ten words per piece of 256 coordinates; 13: eight workgroups per CU
+    // LDS, 256 entries: symbol | length << 4 of the codeword the eight bits start with, 0 where that is "0" for symbol 0, else
+    // kNoCodeword: no length, and a symbol that makes the parser move on by a bit
+    static constexpr uint32_t kNoCodeword = 0x0fu;
+    uint8_t *lut8;
     uint32_t *canon;        // LDS, 64 words: first[16], count[16], offset[16], sorted[16] of the canonical code
     const HuffmanCode *H;
     uint32_t s, sync_shift;
@@ -815,7 +818,7 @@ struct HuffmanWaveCodec {
             canon[48u + lane] = H->sorted[lane];
         }
         for (uint32_t p = lane; p < 256u; p += kWave) {
-            uint32_t entry = 0;
+            uint32_t entry = kNoCodeword;
             for (uint32_t L = 1; L <= 8u && L <= H->maxlen; ++L) {
                 const uint32_t idx = (p >> (8u - L)) - H->first[L];
                 if (idx < H->count[L]) {
@@ -823,7 +826,7 @@ struct HuffmanWaveCodec {
                     break;
                 }
             }
-            lut8[p] = (uint8_t)entry;
+            lut8[p] = (uint8_t)(entry == 0x10u ? 0u : entry);
         }
     }
     __device__ __forceinline__ void entries(const uint32_t *sy, uint32_t g, const DecodeParams &P, uint32_t &e_lo,
@@ -847,58 +850,90 @@ struct HuffmanWaveCodec {
         }
         return true;
     }
-    template <class Words>
-    __device__ __forceinline__ void parse(const Words &words, const Range &R, uint32_t bit0, float norm,
-                                          const TileSink &sink, bool &bad) const
-    {
-        const double wnorm = (double)norm * ldexp(1.0, -1 - (int)s);
-        const uint32_t maxlen = H->maxlen;
-        const bool zero_run = H->len[0] == 1u;        // symbol 0 is the codeword "0"
-        const uint32_t zcap = zero_run ? 30u - maxlen : 0u;   // zeros + codeword + sign: 31 bits of the window at most
-        uint32_t p31 = R.bit_lo - bit0 + 31u;
-        const uint32_t end31 = R.bit_hi - bit0 + 31u;
-        uint32_t q = p31 >> 5;
-        uint32_t hi = words.at(q), lo = words.at(q + 1u), nx = words.at(q + 2u);
-        uint32_t i = 0;
-        const bool long_codes = maxlen > 8u;                  // uniform: most codes have none
-        while (i < R.n && p31 < end31) {
-            const uint32_t w = __builtin_amdgcn_alignbit(hi, lo, ~p31);
-            const uint32_t z = zero_run ? (uint32_t)__clz((int)w) : 0u;       // 32 for an all-zero window
-            const uint32_t left = R.n - i;
-            const bool symbol = z <= zcap && z < left;       // a symbol that is not part of the zero run follows
-            const uint32_t zc = min(min(z, zcap), left);
-            const uint32_t w2 = w << zc;
-            uint32_t entry = lut8[w2 >> 24];
-            if (long_codes && symbol && !entry) {              // a codeword of nine bits or more, or none
-                for (uint32_t L = 9; L <= maxlen; ++L) {
-                    const uint32_t idx = (w2 >> (32u - L)) - canon[L];
-                    if (idx < canon[16u + L]) {
-                        entry = canon[48u + canon[32u + L] + idx] | (L << 4);
-                        break;
+    struct Parser {
+        const uint8_t *lut8;
+        const uint32_t *canon;
+        TileSink sink;
+        double wnorm;
+        uint32_t maxlen;
+        bool zero_run;              // symbol 0 is the codeword "0"
+        int n, end;                 // ~(bits from the row's first word + 31)
+        uint32_t hi, lo, nx;
+        uint32_t i, count, c_lo;    // coordinates done, of how many, the first one's index
+        bool wrong;                 // a prefix that is no codeword, or bits beyond the last coordinate
+        template <class Words>
+        __device__ __forceinline__ void load(const Words &words)
+        {
+            const uint32_t q = ~(uint32_t)n >> 5;
+            hi = words.at(q);
+            lo = words.at(q + 1u);
+            nx = words.at(q + 2u);
+        }
+        template <class Words>
+        __device__ __forceinline__ void run(const Words &words, int stop)
+        {
+            const uint32_t zcap = zero_run ? 30u - maxlen : 0u;   // zeros + codeword + sign: 31 bits of the window at most
+            const bool long_codes = maxlen > 8u;                  // uniform: most codes have none
+            uint32_t p31 = ~(uint32_t)n, q = p31 >> 5;
+            const uint32_t stop31 = ~(uint32_t)stop;
+            while (i < count && p31 < stop31) {
+                const uint32_t w = __builtin_amdgcn_alignbit(hi, lo, ~p31);
+                const uint32_t z = zero_run ? (uint32_t)__clz((int)w) : 0u;       // 32 for an all-zero window
+                const uint32_t left = count - i;
+                const bool symbol = z <= zcap && z < left;       // a symbol that is not part of the zero run follows
+                const uint32_t zc = min(min(z, zcap), left);
+                const uint32_t w2 = w << zc;
+                uint32_t entry = lut8[w2 >> 24];
+                if (long_codes && symbol && entry == kNoCodeword) {       // a codeword of nine bits or more, or none
+                    for (uint32_t L = 9; L <= maxlen; ++L) {
+                        const uint32_t idx = (w2 >> (32u - L)) - canon[L];
+                        if (idx < canon[16u + L]) {
+                            entry = canon[48u + canon[32u + L] + idx] | (L << 4);
+                            break;
+                        }
                     }
                 }
+                // everything below is straight-line: a step without a symbol adds nothing and moves on by its zeros
+                const uint32_t sym = symbol ? entry & 15u : 0u, L = entry >> 4;
+                wrong |= symbol && entry == kNoCodeword;                          // (and moves on by its one bit)
+                const uint32_t bits = zc + (symbol ? L + (sym ? 1u : 0u) : 0u);
+                const uint32_t at = sink.place(c_lo + i + zc);
+                i += zc + (symbol ? 1u : 0u);
+                p31 += bits;
+                const uint32_t qn = p31 >> 5;
+                const bool moved = qn != q;
+                hi = moved ? lo : hi;
+                lo = moved ? nx : lo;
+                q = qn;
+                nx = words.at(qn + 2u);
+                if (sym) {
+                    const double mag = ldexp(wnorm, (int)sym);
+                    const uint32_t neg = (w2 << L) & 0x80000000u;
+                    const uint64_t vb = (uint64_t)__double_as_longlong(mag) | ((uint64_t)neg << 32);
+                    sink.add(at, __longlong_as_double((long long)vb));
+                }
             }
-            // everything below is straight-line: a step without a symbol adds nothing and moves on by its zeros
-            const uint32_t sym = symbol ? entry & 15u : 0u, L = entry >> 4;
-            bad |= symbol && !L;
-            const uint32_t bits = zc + (symbol ? L + (sym ? 1u : 0u) : 0u);
-            const uint32_t at = sink.place(R.c_lo + i + zc);
-            i += zc + (symbol ? 1u : 0u);
-            p31 += max(bits, 1u);                              // (a prefix that is no codeword still moves on)
-            const uint32_t qn = p31 >> 5;
-            const bool moved = qn != q;
-            hi = moved ? lo : hi;
-            lo = moved ? nx : lo;
-            q = qn;
-            nx = words.at(qn + 2u);
-            if (sym) {
-                const double mag = ldexp(wnorm, (int)sym);
-                const uint32_t neg = (w2 << L) & 0x80000000u;
-                const uint64_t vb = (uint64_t)__double_as_longlong(mag) | ((uint64_t)neg << 32);
-                sink.add(at, __longlong_as_double((long long)vb));
+            n = (int)~p31;
+            if (i >= count && n != end) {
+                wrong = true;
+                n = end;                                          // (all coordinates done: no further row is asked for)
             }
         }
-        bad |= i != R.n || p31 != end31;
+        __device__ __forceinline__ void finish(bool &bad) const { bad |= wrong || i != count || n != end; }
+    };
+    __device__ __forceinline__ Parser parser(float norm, const TileSink &sink) const
+    {
+        return Parser{lut8, canon, sink, (double)norm * ldexp(1.0, -1 - (int)s), H->maxlen, H->len[0] == 1u};
+    }
+    __device__ __forceinline__ void start(Parser &U, const StagedWords &words, const Range &R) const
+    {
+        U.n = (int)~((R.bit_lo & 31u) + 31u);
+        U.end = (int)~(R.bit_hi - (R.bit_lo & ~31u) + 31u);
+        U.i = 0;
+        U.count = R.n;
+        U.c_lo = R.c_lo;
+        U.wrong = false;
+        U.load(words);
     }
 };
 

@@ -105,3 +105,56 @@ def test_momentum_tiles(g, n, S, K, d, shift):
     want = (w0.astype(np.float64) - alpha * gd) + mu * (yl - y0.astype(np.float64))
     np.testing.assert_allclose(w.cpu().numpy(), want, rtol=2.0 ** -23, atol=2.0 ** -30)      # one rounding to fp32
     np.testing.assert_allclose(y.cpu().numpy(), yl, rtol=2.0 ** -23, atol=2.0 ** -30)
+
+
+def _dense_bytes(rng, d, n, s, density):
+    """Bytes whose share of nonzeros differs from bucket to bucket around `density`, a bucket in four full, one empty."""
+    nb = -(-d // n)
+    share = np.clip(density * 2.0 ** rng.uniform(-1, 1, nb), 0, 1)
+    share[::4], share[1::8] = 1.0, 0.0
+    level = rng.integers(1, s + 2, d).astype(np.uint8) | (rng.integers(0, 2, d).astype(np.uint8) << 7)
+    return np.where(rng.random(d) < np.repeat(share, n)[:d], level, 0).astype(np.uint8)
+
+
+@pytest.mark.parametrize("density", [0.02, 0.25, 0.7])
+@pytest.mark.parametrize("n,S,K,s", [(8192, 256, 8, 3), (512, 128, 4, 3), (512, 256, 4, 7), (512, 512, 2, 14), (256, 256, 4, 3),
+                                     (256, 64, 3, 5), (1000, 256, 8, 3), (1024, 512, 3, 2), (16384, 512, 4, 7), (20000, 1024, 2, 14),
+                                     (64, 64, 2, 3)])
+def test_pieces_of_every_length(g, n, S, K, s, density):
+    """Pieces of less than a row of words to many rows, one to eight lanes loading a row, in messages that end with their last
+    word (the last piece's row would leave the message): the average, and the same through Huffman-coded levels."""
+    nuq = g.nuq
+    rng = np.random.default_rng(n + 7 * S + K)
+    d = 9 * n + n // 2 + 1
+    nb = -(-d // n)
+    qs = [_dense_bytes(rng, d, n, s, density) for _ in range(K)]
+    norms = [np.exp2(rng.uniform(-3, 3, nb)).astype(np.float32) for _ in range(K)]
+    want = (0.5 * sum(_value(q, n, s, v) for q, v in zip(qs, norms))).astype(np.float32)      # the sum is exact in fp64
+
+    def cut(m):        # the message's words alone, the next thing in memory something else
+        used = (int(m.bit_off[-1].item()) + 31) // 32
+        return nuq.Message(m.norms, m.bit_off, m.words[:used].clone(), m.sync)
+
+    msgs = [cut(_message(g, q, n, s, S, v)) for q, v in zip(qs, norms)]
+    out = torch.full((d,), 7.0, device=g.DEV)
+    nuq.nuq_decode_accumulate(msgs, d, n, s, S, 0.5, False, out)
+    assert nuq.nuq_last_error_flags() == 0
+    np.testing.assert_array_equal(out.cpu().numpy(), want)
+
+    nsync = nuq.nuq_huffman_num_sync(n, S)
+    if not nsync or -(-min(n, 2048) // S) > 64 // (max(1, 2048 // n) * K):
+        return                                     # no index, or more pieces in a tile than lanes: not taken
+    for code_s, hist in ((s, [1 << (s + 1 - j) for j in range(s + 2)]), (s, [1] * (s + 2))):     # "0" for level 0, and not
+        lengths = nuq.nuq_huffman_lengths(hist, code_s)
+        hm = []
+        for q, v in zip(qs, norms):
+            m = nuq.Message(torch.from_numpy(v).to(g.DEV), torch.empty(nb + 1, dtype=torch.int64, device=g.DEV),
+                            torch.zeros(nuq.nuq_huffman_max_words(d, n), dtype=torch.int32, device=g.DEV),
+                            torch.empty(max(1, nb * nsync), dtype=torch.int32, device=g.DEV))
+            ws = torch.empty(nuq.nuq_encode_huffman_workspace_bytes(d, n), dtype=torch.uint8, device=g.DEV)
+            nuq.nuq_encode_huffman(torch.from_numpy(q).to(g.DEV), n, s, S, lengths, m.bit_off, m.words, m.sync, ws)
+            hm.append(cut(m))
+        out.fill_(7.0)
+        nuq.nuq_decode_accumulate_huffman(hm, d, n, s, S, lengths, 0.5, False, out)
+        assert nuq.nuq_last_error_flags() == 0
+        np.testing.assert_array_equal(out.cpu().numpy(), want)
