@@ -1233,11 +1233,11 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
-        P.lds_words = ((P.rows * TEAM + P.out_cap + 1u + nsync + 1u) & ~1u) + 64u;
+        P.lds_words = ((P.rows * TEAM + P.out_cap + nsync + 3u) & ~3u) + 64u;       // 16-byte aligned teams and fields
         const size_t lds_bytes = (size_t)P.lds_words * 4 * G::kTeamsPerWG;
         if (lds_bytes > 160 * 1024)
             return (int)NUQ_EINVAL;
-        auto kern = k_huffman_fused<TEAM, VPT>;
+        auto kern = s <= 6u ? k_huffman_fused<TEAM, VPT, true> : k_huffman_fused<TEAM, VPT, false>;
         if (lds_bytes > 48 * 1024 &&
             hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds_bytes) != hipSuccess)

@@ -218,10 +218,110 @@ __device__ __forceinline__ uint32_t huffman_from_lds(const EncodeParams &P, cons
     return total;
 }
 
+// ---- levels up to 7 (s <= 6): two coordinates per table entry ------------------------------------------------------
+// A coordinate is then four bits, level | sign << 3, and two of them index a table of 256 entries: what both send (at most
+// 16 bits: codewords have at most s + 1 bits) | its length << 16.  A word of four coordinates is two reads and one push of
+// up to 32 bits, the same instructions whatever the levels are; byte by byte (huffman_from_lds) a wave went through the way
+// for words of zeros and through that for others for nearly every word, 14 instructions per coordinate.  Encode + decode:
+// 8 x 25.6 M coordinates at s = 3 252 -> 219 us, 4 x 16.8 M at s = 5 187 -> 154.  From s = 7 on a level has more than three
+// bits and huffman_from_lds stays.
+
+// Bytes level | sign << 3 (the sign of a zero means nothing).
+struct NibbleBytes {
+    __device__ __forceinline__ uint32_t any(uint32_t sg, uint32_t levels) const
+    {
+        return ((sg >> 4) & 0x08080808u) | levels;
+    }
+    __device__ __forceinline__ uint32_t first(uint32_t sg, uint32_t tb) const { return any(sg, (tb >> 7) & 0x01010101u); }
+    __device__ __forceinline__ uint32_t two(uint32_t sg, uint32_t tb, uint32_t tb2) const
+    {
+        return first(sg, tb) + ((tb2 >> 7) & 0x01010101u);
+    }
+};
+
+// The table's entry for this thread (256 of them), in two halves as TableCopy: its codewords requested before the gradient's
+// loads, the entry made and stored when those are under way.
+struct PairTable {
+    uint32_t len0, code0, len1, code1;
+    __device__ __forceinline__ explicit PairTable(const HuffmanCode &H)
+    {
+        const uint32_t l0 = threadIdx.x & 7u, l1 = (threadIdx.x >> 4) & 7u;
+        len0 = H.len[l0];
+        code0 = H.code[l0];
+        len1 = H.len[l1];
+        code1 = H.code[l1];
+    }
+    __device__ __forceinline__ void store(uint32_t *pairs) const
+    {
+        const uint32_t p = threadIdx.x;
+        if (p < 256u) {
+            const uint32_t s0 = (p & 7u) ? 1u : 0u, s1 = (p & 0x70u) ? 1u : 0u;        // a sign bit follows
+            const uint32_t c0 = (code0 << s0) | (s0 & (p >> 3)), c1 = (code1 << s1) | (s1 & (p >> 7));
+            pairs[p] = (c0 << (len1 + s1)) | c1 | ((len0 + s0 + len1 + s1) << 16);
+        }
+    }
+};
+
+// huffman_from_lds for such bytes and that table.  A thread's words are looked up once and kept (VPT of them).
+template <int TEAM, int VPT>
+__device__ __forceinline__ uint32_t huffman_pairs_from_lds(const EncodeParams &P, const uint32_t *pairs, const uint32_t *qb32,
+                                                           uint32_t *field, uint32_t *sync_l, uint32_t *scratch, uint32_t nbk,
+                                                           uint32_t tid)
+{
+    const uint32_t c0 = tid * P.rows * 4u;
+    const uint32_t *qw = qb32 + tid * P.rows;
+    // the index boundary (a multiple of the stride, 64 or more, so of four) inside this chunk of at most 64 coordinates
+    const uint32_t smask = (1u << P.sync_shift) - 1u;
+    const uint32_t cb = P.sync_shift ? (c0 + smask) & ~smask : ~0u;
+    const bool has_boundary = P.sync_shift && cb && cb < min(c0 + P.rows * 4u, nbk);
+    const uint32_t iw = (cb - c0) >> 2;
+    uint32_t code[VPT], len[VPT], bits = 0, before = 0;
+#pragma unroll
+    for (int i = 0; i < VPT; ++i) {
+        code[i] = len[i] = 0;
+        if ((uint32_t)i < P.rows) {
+            before = (uint32_t)i == iw ? bits : before;
+            const uint32_t c = c0 + 4u * (uint32_t)i, w = qw[i];
+            if (__all(c + 4u <= nbk)) {
+                const uint32_t t = w | (w >> 4);
+                const uint32_t e0 = pairs[t & 0xffu], e1 = pairs[(t >> 16) & 0xffu], l1 = e1 >> 16;
+                code[i] = ((e0 & 0xffffu) << l1) | (e1 & 0xffffu);
+                len[i] = (e0 >> 16) + l1;
+            } else {                                              // the bucket ends in some lane's word: one by one
+                const uint32_t zero = pairs[0] >> 17;             // length of level 0's codeword
+                for (uint32_t j = 0; j < 4u; ++j)
+                    if (c + j < nbk) {
+                        const uint32_t e = pairs[(w >> (8u * j)) & 15u], l = (e >> 16) - zero;
+                        code[i] = (code[i] << l) | ((e & 0xffffu) >> zero);
+                        len[i] += l;
+                    }
+            }
+            bits += len[i];
+        }
+    }
+    uint32_t total;
+    const uint32_t pos = team_exclusive_sum<TEAM>(bits, scratch, total);
+    const uint32_t nwords = (total + 31u) >> 5;
+    for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
+        *reinterpret_cast<uint4 *>(field + i) = uint4{0u, 0u, 0u, 0u};
+    for (uint32_t i = tid; i < P.nsync; i += TEAM)
+        sync_l[i] = total;                          // boundaries at or beyond the bucket's end
+    team_barrier<TEAM>();
+    BitWriter out(pos);                             // (at most 31 + 32 bits are pending)
+#pragma unroll
+    for (int i = 0; i < VPT; ++i)
+        if ((uint32_t)i < P.rows)
+            out.put(field, code[i], len[i]);
+    out.flush(field);
+    if (has_boundary)
+        sync_l[(cb >> P.sync_shift) - 1u] = pos + before;
+    return total;
+}
+
 // Norms + quantizer + Huffman coding of one bucket per team, v read once, all workers in one launch (blockIdx.y): the
 // bit string goes to the bucket's staging slot and its length where k_finish looks for it (report_lengths); that kernel
-// turns them into bit_off and words as for the ERC strings.
-template <int TEAM, int VPT>
+// turns them into bit_off and words as for the ERC strings.  kPairs: s <= 6.
+template <int TEAM, int VPT, bool kPairs>
 __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodeParams P, EncodeBatch Wk, HuffmanCode H)
 {
     extern __shared__ __align__(16) uint32_t smem[];
@@ -231,23 +331,29 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
     uint32_t *lds = smem + team * P.lds_words;
     uint32_t *qb32 = lds;
     uint32_t *field = qb32 + P.rows * TEAM;
-    uint32_t *sync_l = field + P.out_cap + 1u;
+    uint32_t *sync_l = field + P.out_cap;
     uint32_t *scratch = lds + P.lds_words - 64u;
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + team;
     const bool active = b < P.nb;
     const uint64_t base = active ? b * P.bucket : 0;
     const uint32_t nbk = active ? (uint32_t)min((uint64_t)P.bucket, P.d - base) : 0u;
     __shared__ uint32_t enc[256];
-    huffman_byte_table<TeamGeom<TEAM>::kWG>(H, enc);
-    front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, PlainBytes{}, [] {});
-    __syncthreads();
-    const uint32_t total = huffman_from_lds<TEAM>(P, enc, qb32, field, sync_l, scratch, nbk, tid);
-    const uint32_t nwords = (total + 31u) >> 5;
+    uint32_t total;
+    if constexpr (kPairs) {
+        const PairTable table(H);
+        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, NibbleBytes{},
+                                         [&] { table.store(enc); });
+        __syncthreads();
+        total = huffman_pairs_from_lds<TEAM, VPT>(P, enc, qb32, field, sync_l, scratch, nbk, tid);
+    } else {
+        huffman_byte_table<TeamGeom<TEAM>::kWG>(H, enc);
+        front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, PlainBytes{}, [] {});
+        __syncthreads();
+        total = huffman_from_lds<TEAM>(P, enc, qb32, field, sync_l, scratch, nbk, tid);
+    }
     team_barrier<TEAM>();
     if (active) {
-        uint32_t *slot = P.staging + ((uint64_t)blockIdx.y * P.nb + b) * P.slot_words;
-        for (uint32_t i = tid; i < nwords; i += TEAM)
-            slot[i] = field[i];
+        store_bucket<TEAM>(P.staging + ((uint64_t)blockIdx.y * P.nb + b) * P.slot_words, field, (total + 31u) >> 5, tid);
         uint32_t *sg = W.sync + b * P.nsync;
         for (uint32_t i = tid; i < P.nsync; i += TEAM)
             sg[i] = sync_l[i];

@@ -345,3 +345,28 @@ def test_config3_fused_decode_at_full_size(g):
             mag += np.abs(deq)
         diff = np.abs(out[c_lo:c_hi].cpu().numpy().astype(np.float64) - want * scale32)
         assert np.all(diff <= 1e-6 * mag * scale32 + 1e-45)
+
+
+@pytest.mark.parametrize("s", [1, 3, 6, 7])
+@pytest.mark.parametrize("d,n,S", [(8192 * 2 + 3, 8192, 256), (20001, 20000, 64), (4099, 1000, 128), (515, 512, 0), (6, 5, 0),
+                                   (3 * 1536 + 1, 1536, 64)])
+def test_fused_coding_with_long_codewords(g, d, n, S, s):
+    """The fused encoder on both sides of s = 6 (two coordinates per table entry, or one) with a code in which level 0 has
+    the longest codeword: words of up to 4 (s + 2) bits; buckets that end inside a word, and of no whole word."""
+    nuq = g.nuq
+    v = torch.from_numpy(make_vector("edges", d, n, np.random.default_rng(d + s))).to(g.DEV)
+    B, nsync, cap = nuq.nuq_num_buckets(d, n), nuq.nuq_huffman_num_sync(n, S), nuq.nuq_huffman_max_words(d, n)
+    lengths = nuq.nuq_huffman_lengths([2 ** j for j in range(s + 2)], s)
+    assert lengths[0] == s + 1
+    m = nuq.Message(torch.empty(B, dtype=torch.float32, device=g.DEV), torch.empty(B + 1, dtype=torch.int64, device=g.DEV),
+                    torch.zeros(cap, dtype=torch.int32, device=g.DEV),
+                    torch.full((max(1, B * nsync),), 0x55555555, dtype=torch.int32, device=g.DEV))
+    ws = torch.empty(nuq.nuq_encode_huffman_batch_workspace_bytes(1, d, n, s), dtype=torch.uint8, device=g.DEV)
+    nuq.nuq_quantize_encode_huffman_batch([v], n, s, [9], S, lengths, [m], ws)
+    q = oracle.quantize(v.cpu().numpy(), n, s, 9, m.norms.cpu().numpy())
+    bo, words, sync = oracle.encode_huffman(q, n, s, lengths, S)
+    np.testing.assert_array_equal(g.u64(m.bit_off), bo)
+    np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
+    assert not g.u32(m.words)[words.size:].any()
+    if sync.size:
+        np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
