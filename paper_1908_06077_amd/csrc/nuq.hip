@@ -169,18 +169,49 @@ Workspace carve(void *base, uint32_t K, uint64_t nb, uint32_t slot_words)
 }
 
 // Team shape per bucket size: (threads per bucket, float4 rows per thread).
-template <class F>
-int dispatch_team(uint32_t bucket, F &&f)
+//
+// dense: most coordinates are nonzero (s >= 6, or the maximum norm), and coding them outweighs all else.  Then a whole wave
+// per bucket of 513 to 1024 is better: s = 7 in buckets of 1000 135 us, 147 with half a wave.
+//
+// A team's fixed work (norm reduction, scale, key, scans, barriers) costs the encoder as much as a thousand coordinates per
+// wave, so a thread owns 16 coordinates or more: with 64 threads for buckets of 513 to 1024, 256 for up to 4096 and 1024
+// beyond 16384 (and their partial sums, see kNormParts), encode of 4 x 16.8 M coordinates took 86 us in buckets of 1024, 107 of
+// 700, 74 of 4096, 87 of 3000, 113 of 20000; with half of that 77, 85, 61, 70 and 77.  kPack: kernels that store what the
+// quantizer yields and do nothing else.  They are bound by memory and want more waves in flight: 4-bit packing and unpacking
+// in buckets of 4096 68 us with 256 threads, 73 with 128 (but with a level table, which is bound by issue, 108 and 96), in
+// buckets of 20000 78.7 with 1024, 80.5 with 512.
+enum class TeamUse { kCode, kPack, kPackTable };
+template <TeamUse kUse = TeamUse::kCode, class F>
+int dispatch_team(uint32_t bucket, bool dense, F &&f)
 {
-    if (bucket <= 512)   // four buckets per wave
-        return f(std::integral_constant<int, 16>{}, std::integral_constant<int, 8>{});
+    using std::integral_constant;
+    if (bucket <= 256)   // four buckets per wave
+        return f(integral_constant<int, 16>{}, integral_constant<int, 4>{});
+    if (bucket <= 512)
+        return f(integral_constant<int, 16>{}, integral_constant<int, 8>{});
+    if (bucket <= 1024 && dense)
+        return f(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+    if (bucket <= 1024)  // two
+        return f(integral_constant<int, 32>{}, integral_constant<int, 8>{});
     if (bucket <= 2048)
-        return f(std::integral_constant<int, 64>{}, std::integral_constant<int, 8>{});
+        return f(integral_constant<int, 64>{}, integral_constant<int, 8>{});
+    if (bucket <= 4096) {
+        if constexpr (kUse == TeamUse::kPack)
+            return f(integral_constant<int, 256>{}, integral_constant<int, 4>{});
+        else
+            return f(integral_constant<int, 128>{}, integral_constant<int, 8>{});
+    }
     if (bucket <= 8192)
-        return f(std::integral_constant<int, 256>{}, std::integral_constant<int, 8>{});
+        return f(integral_constant<int, 256>{}, integral_constant<int, 8>{});
     if (bucket <= 16384)
-        return f(std::integral_constant<int, 256>{}, std::integral_constant<int, 16>{});
-    return f(std::integral_constant<int, 1024>{}, std::integral_constant<int, 8>{});
+        return f(integral_constant<int, 256>{}, integral_constant<int, 16>{});
+    // (rows that no bucket of the size has are loaded too, see load_rows)
+    if constexpr (kUse == TeamUse::kCode)
+        return bucket <= 24576 ? f(integral_constant<int, 512>{}, integral_constant<int, 12>{})
+                               : f(integral_constant<int, 512>{}, integral_constant<int, 16>{});
+    else
+        return bucket <= 24576 ? f(integral_constant<int, 1024>{}, integral_constant<int, 6>{})
+                               : f(integral_constant<int, 1024>{}, integral_constant<int, 8>{});
 }
 
 int check_launch()
@@ -210,11 +241,11 @@ int launch_finish_as(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, c
     return check_launch();
 }
 
-int launch_finish(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, const Workspace &w, hipStream_t st)
+int launch_finish(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, const Workspace &w, bool dense, hipStream_t st)
 {
     // buckets per workgroup of the encoder
     uint32_t unit_shift = 0;
-    (void)dispatch_team(P.bucket, [&](auto team_c, auto) {
+    (void)dispatch_team(P.bucket, dense, [&](auto team_c, auto) {
         unit_shift = log2u(TeamGeom<decltype(team_c)::value>::kTeamsPerWG);
         return (int)NUQ_OK;
     });
@@ -296,7 +327,8 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     P.staging = w.staging;
     P.flags = flags;
     P.norm_linf = norm_kind == NUQ_NORM_LINF ? 1u : 0u;
-    int rc = dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    const bool dense = P.norm_linf || s >= 6u;
+    int rc = dispatch_team(bucket, dense, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -321,7 +353,7 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     if (rc != NUQ_OK)
         return rc;
 
-    return launch_finish(P, Wk, K, w, st);
+    return launch_finish(P, Wk, K, w, dense, st);
 }
 
 bool valid_fixed(uint32_t s, uint32_t b)
@@ -367,7 +399,7 @@ int pack_fixed_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t buc
     FixedParams F{};
     F.b = b;
     F.wpb = (bucket * b + 31u) / 32u;
-    return dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    return dispatch_team<MODE == 2 ? TeamUse::kPackTable : TeamUse::kPack>(bucket, false, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -540,7 +572,7 @@ int nuq_bucket_norms(const float *v, uint64_t d, uint32_t bucket, float *norms, 
     P.bucket = bucket;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         dim3 grid;
         if (!bucket_grid<TEAM>(P.nb, 1, grid))
@@ -567,7 +599,7 @@ int nuq_quantize(const float *v, uint64_t d, uint32_t bucket, uint32_t s, uint64
     P.s = s;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
         dim3 grid;
@@ -591,7 +623,7 @@ int nuq_bucket_norms_linf(const float *v, uint64_t d, uint32_t bucket, float *no
     P.bucket = bucket;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         dim3 grid;
         if (!bucket_grid<TEAM>(P.nb, 1, grid))
@@ -622,7 +654,7 @@ int nuq_quantize_table(const float *v, uint64_t d, uint32_t bucket, uint32_t s, 
     P.s = s;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
         dim3 grid;
@@ -1138,7 +1170,7 @@ int nuq_encode_huffman(const uint8_t *q, uint64_t d, uint32_t bucket, uint32_t s
     P.units = w.units;
     P.flags = flags;
     const uint64_t nchunks = (nb + kChunk - 1) / kChunk;
-    return dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -1229,7 +1261,7 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
     P.units = w.units;
     P.staging = w.staging;
     P.flags = flags;
-    int rc = dispatch_team(bucket, [&](auto team_c, auto vpt_c) {
+    int rc = dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -1251,7 +1283,7 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
     });
     if (rc != NUQ_OK)
         return rc;
-    return launch_finish(P, Wk, K, w, st);
+    return launch_finish(P, Wk, K, w, false, st);
 }
 
 int nuq_decode_huffman_batch(uint32_t K, const uint64_t *const *bit_off, const uint32_t *const *words,

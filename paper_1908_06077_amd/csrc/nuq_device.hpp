@@ -169,12 +169,18 @@ __device__ __forceinline__ bool erc_decode_window(uint32_t &win, int &avail, uin
 
 // ------------------------------------------------------- team reductions / scans
 //
-// TEAM threads (16, 64, 256 or 1024) own one bucket.  A workgroup holds max(256, TEAM) threads,
-// i.e. 16 teams of a quarter wave (a DPP row) each, 4 one-wave teams or a single multi-wave team.
+// TEAM threads (16, 32, 64, 128, 256, 512 or 1024) own one bucket.  A workgroup holds 16 teams of a quarter wave (a DPP row)
+// each, 8 of half a wave, 4 one-wave teams or a single multi-wave team.
 // Multi-wave variants use a small LDS scratch and __syncthreads(); every thread of the workgroup must
-// call them.  A quarter-wave team serves small buckets: the per-bucket work that a wave does once
-// (norm reduction, scale, hash key, scans) then serves four buckets at a time.
+// call them.  Teams of a quarter or half a wave serve small buckets: the per-bucket work that a wave does once
+// (norm reduction, scale, hash key, scans) then serves four or two buckets at a time.
 constexpr int kRow = 16;   // lanes of a DPP row
+
+// A bucket's norm is a sum of fp32 partial sums, one per thread, and so depends in its last bit on which coordinates share
+// a thread.  Teams of 32, 128 and 512 form the partial sums of twice as many threads (of 64, 256 and 1024: the norms that
+// messages of these bucket sizes have always carried): a thread's even rows are one of them, its odd rows another.
+template <int TEAM>
+constexpr int kNormParts = TEAM == 32 || TEAM == 128 || TEAM == 512 ? 2 : 1;
 
 // A value that is the same in every thread of a team, as a scalar when the team is at least a wave.
 template <int TEAM>
@@ -191,10 +197,11 @@ __device__ __forceinline__ float team_uniform_f32(float x)
     return u2f(team_uniform_u32<TEAM>(f2u(x)));
 }
 
-// The value lane 15 of each DPP row holds, in every lane of that row.
-__device__ __forceinline__ uint32_t row_last_u32(uint32_t x)
+// The value the last lane of each team of TEAM lanes (16 or 32) holds, in every lane of that team.
+template <int TEAM>
+__device__ __forceinline__ uint32_t team_last_u32(uint32_t x)
 {
-    return (uint32_t)__shfl((int)x, (int)((threadIdx.x & (kWave - 1)) | (kRow - 1)), kWave);
+    return (uint32_t)__shfl((int)x, (int)((threadIdx.x & (kWave - 1)) | (TEAM - 1)), kWave);
 }
 
 // Value of a wave-uniform quantity as a scalar (lets the compiler keep what derives from it in
@@ -234,47 +241,62 @@ __device__ __forceinline__ double wave_sum_f64(double x)
     return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
 }
 
-// Sum of x over each row of 16 lanes, returned in every lane of the row: four row shifts leave the total in the
-// row's last lane (the same summation order for every bucket), which is then handed to the others.
-__device__ __forceinline__ double row_sum_f64(double x)
+// Sums over teams of 16 or 32 lanes, in the team's last lane: four row shifts leave the total of a row in its last lane (the
+// same summation order for every bucket), a row broadcast adds the first row's to the second's.
+template <int TEAM>
+__device__ __forceinline__ double part_sum_f64(double x)
 {
-    auto step = [](double v, auto ctrl) {
+    auto step = [](double v, auto ctrl, auto row_mask, auto bound) {
         const uint64_t b = (uint64_t)__double_as_longlong(v);
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, decltype(ctrl)::value, 0xf, 0xf, true);
-        const uint32_t hi =
-            (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), decltype(ctrl)::value, 0xf, 0xf, true);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, decltype(ctrl)::value,
+                                                                  decltype(row_mask)::value, 0xf, decltype(bound)::value);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), decltype(ctrl)::value,
+                                                                  decltype(row_mask)::value, 0xf, decltype(bound)::value);
         return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
     };
     using std::integral_constant;
-    x = step(x, integral_constant<int, 0x111>{});
-    x = step(x, integral_constant<int, 0x112>{});
-    x = step(x, integral_constant<int, 0x114>{});
-    x = step(x, integral_constant<int, 0x118>{});
-    const uint64_t b = (uint64_t)__double_as_longlong(x);
-    const uint32_t lo = row_last_u32((uint32_t)b), hi = row_last_u32((uint32_t)(b >> 32));
-    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    using All = integral_constant<int, 0xf>;
+    x = step(x, integral_constant<int, 0x111>{}, All{}, integral_constant<bool, true>{});
+    x = step(x, integral_constant<int, 0x112>{}, All{}, integral_constant<bool, true>{});
+    x = step(x, integral_constant<int, 0x114>{}, All{}, integral_constant<bool, true>{});
+    x = step(x, integral_constant<int, 0x118>{}, All{}, integral_constant<bool, true>{});
+    if constexpr (TEAM == 32)
+        x = step(x, integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{}, integral_constant<bool, false>{});
+    return x;
 }
 
+// Sum of the team's kNormParts x TEAM values, in every lane, added in the order of a team of that many threads.  scratch: a
+// double per wave and part (teams of several waves).
 template <int TEAM>
-__device__ __forceinline__ double team_sum_f64(double x, double *scratch /* TEAM/64 doubles */)
+__device__ __forceinline__ double team_sum_f64(const double (&x)[kNormParts<TEAM>], double *scratch)
 {
-    if constexpr (TEAM == kRow)
-        return row_sum_f64(x);
-    x = wave_sum_f64(x);
-    if constexpr (TEAM > kWave) {
+    constexpr int kParts = kNormParts<TEAM>;
+    if constexpr (TEAM < kWave) {
+        double t = part_sum_f64<TEAM>(x[kParts - 1]);
+        if constexpr (kParts == 2)
+            t += part_sum_f64<TEAM>(x[0]);
+        const uint64_t b = (uint64_t)__double_as_longlong(t);
+        const uint32_t lo = team_last_u32<TEAM>((uint32_t)b), hi = team_last_u32<TEAM>((uint32_t)(b >> 32));
+        return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+    } else if constexpr (TEAM == kWave) {
+        return wave_sum_f64(x[0]);
+    } else {
         constexpr int NW = TEAM / kWave;
         const int wave = (threadIdx.x % TEAM) / kWave;
         __syncthreads();
-        if ((threadIdx.x & (kWave - 1)) == 0)
-            scratch[wave] = x;
+#pragma unroll
+        for (int h = 0; h < kParts; ++h) {
+            const double t = wave_sum_f64(x[h]);
+            if ((threadIdx.x & (kWave - 1)) == 0)
+                scratch[h * NW + wave] = t;
+        }
         __syncthreads();
         double t = 0.0;
 #pragma unroll
-        for (int w = 0; w < NW; ++w)
+        for (int w = 0; w < NW * kParts; ++w)
             t += scratch[w];
-        x = t;
+        return t;
     }
-    return x;
 }
 
 // Inclusive prefix sum across the 64 lanes of a wave with DPP moves: four row-shift steps scan
@@ -296,13 +318,15 @@ template <int TEAM, bool kFence = true>
 __device__ __forceinline__ uint32_t team_exclusive_sum(uint32_t v, uint32_t *scratch /* TEAM/64 */,
                                                        uint32_t &total)
 {
-    if constexpr (TEAM == kRow) {
+    if constexpr (TEAM < kWave) {
         uint32_t inc = v;
         inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xf, 0xf, true);   // row_shr:1
         inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xf, 0xf, true);   // row_shr:2
         inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xf, 0xf, true);   // row_shr:4
         inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xf, 0xf, true);   // row_shr:8
-        total = row_last_u32(inc);
+        if constexpr (TEAM == 32)
+            inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x142, 0xa, 0xf, false);  // row_bcast:15 -> rows 1, 3
+        total = team_last_u32<TEAM>(inc);
         return inc - v;
     }
     const int lane = threadIdx.x & (kWave - 1);
@@ -334,16 +358,16 @@ __device__ __forceinline__ uint32_t team_exclusive_sum(uint32_t v, uint32_t *scr
 template <int TEAM>
 __device__ __forceinline__ int team_exclusive_max(int v, int ident, int *scratch /* TEAM/64 */)
 {
-    if constexpr (TEAM == kRow) {
-        const int l = threadIdx.x & (kRow - 1);
+    if constexpr (TEAM < kWave) {
+        const int l = threadIdx.x & (TEAM - 1);
         int inc = v;
 #pragma unroll
-        for (int off = 1; off < kRow; off <<= 1) {
-            const int t = __shfl_up(inc, off, kRow);
+        for (int off = 1; off < TEAM; off <<= 1) {
+            const int t = __shfl_up(inc, off, TEAM);
             if (l >= off)
                 inc = max(inc, t);
         }
-        const int exc = __shfl_up(inc, 1, kRow);
+        const int exc = __shfl_up(inc, 1, TEAM);
         return l == 0 ? ident : exc;
     }
     const int lane = threadIdx.x & (kWave - 1);
@@ -393,7 +417,7 @@ __device__ __forceinline__ uint32_t team_max_u32(uint32_t x, uint32_t *scratch)
     for (int off = kLanes / 2; off >= 1; off >>= 1)
         x = max(x, (uint32_t)__shfl_xor((int)x, off, kWave));
     if constexpr (TEAM > kWave) {
-        const uint32_t wave = threadIdx.x / kWave;
+        const uint32_t wave = (threadIdx.x % TEAM) / kWave;
         __syncthreads();
         if ((threadIdx.x & (kWave - 1)) == 0)
             scratch[wave] = x;

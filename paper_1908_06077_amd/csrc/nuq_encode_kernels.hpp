@@ -60,7 +60,7 @@ struct EncodeParams {
 
 template <int TEAM>
 struct TeamGeom {
-    static constexpr int kWG = TEAM < 256 ? 256 : TEAM;
+    static constexpr int kWG = TEAM <= kWave ? 256 : TEAM;     // (barriers inside a team of several waves: it is alone)
     static constexpr int kTeamsPerWG = kWG / TEAM;
 };
 
@@ -122,7 +122,41 @@ __device__ __forceinline__ void load_rows(float4 (&x)[VPT], const float *wg_base
                 x[i] = float4{r.x, r.y, r.z, r.w};
             }
         }
-    } else {
+    } else if (__all(nbk >= 4u)) {
+        // Buckets that do not fill every row (their size, or the vector's end): addresses clamped to the last four
+        // coordinates, so that no load is predicated or branched around and all are under way together; what came from too
+        // far down is then shifted out, rows beyond the bucket size are cleared.  Predicated, as it was, a row's load was
+        // waited for before the next one was issued: encode of 4 x 16.8 M
+        // coordinates in buckets of 1000 (half a wave each) 107 -> 82 us, of 700 96 -> 85.
+        const uint32_t top = nbk - 4u;
+        auto first = [&](int i) { return 4u * ((uint32_t)i * TEAM + tid); };
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            const GlobalFloat4 at = (GlobalFloat4)((GlobalBytes)wg_base + 4u * (lane_off + min(first(i), top)));
+            f32x4_any r;
+            if constexpr (TEAM >= 64)
+                r = __builtin_nontemporal_load(at);
+            else
+                r = *at;
+            x[i] = float4{r.x, r.y, r.z, r.w};
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            const uint32_t over = first(i) - min(first(i), top);
+            if ((uint32_t)i >= rows) {
+                x[i] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+            } else if (__any(over != 0u)) {
+                const bool one = over & 1u, two = over & 2u, gone = over >= 4u;
+                const float4 t = x[i];
+                const float t0 = one ? t.y : t.x, t1 = one ? t.z : t.y, t2 = one ? t.w : t.z, t3 = one ? 0.0f : t.w;
+                x[i].x = gone ? 0.0f : two ? t2 : t0;
+                x[i].y = gone ? 0.0f : two ? t3 : t1;
+                x[i].z = gone || two ? 0.0f : t2;
+                x[i].w = gone || two ? 0.0f : t3;
+            }
+        }
+    } else {                                             // a bucket of fewer than four coordinates, or none, in the wave
         const float *vb = wg_base + lane_off;
 #pragma unroll
         for (int i = 0; i < VPT; ++i) {
@@ -151,31 +185,38 @@ __device__ __forceinline__ double sqrt_mid(double t)
 // fp32 result could have lost range (tiny or huge sums) the whole sum is redone in fp64.  Every thread of the team
 // returns the same value.  A team of several waves leaves the fp64 part to its first wave (the others wait): done by
 // every wave for itself, as it was, it was 1.5 of the encoder's 26 vector instructions per coordinate.
-// lds: TEAM floats and scratch: 16 doubles of LDS (teams of several waves), free until the second barrier inside.
+// lds: kNormParts x TEAM floats and scratch: 16 doubles of LDS (teams of several waves), free until the second barrier inside.
 template <int TEAM, int VPT, class Row>
 __device__ __forceinline__ float team_norm(Row row, float *lds, double *scratch)
 {
-    float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+    constexpr int kParts = kNormParts<TEAM>;
+    float part[kParts];
 #pragma unroll
-    for (int i = 0; i < VPT; ++i) {
-        const float4 x = row(i);
-        a0 = __builtin_fmaf(x.x, x.x, a0);
-        a1 = __builtin_fmaf(x.y, x.y, a1);
-        a2 = __builtin_fmaf(x.z, x.z, a2);
-        a3 = __builtin_fmaf(x.w, x.w, a3);
+    for (int h = 0; h < kParts; ++h) {
+        float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
+#pragma unroll
+        for (int i = h; i < VPT; i += kParts) {
+            const float4 x = row(i);
+            a0 = __builtin_fmaf(x.x, x.x, a0);
+            a1 = __builtin_fmaf(x.y, x.y, a1);
+            a2 = __builtin_fmaf(x.z, x.z, a2);
+            a3 = __builtin_fmaf(x.w, x.w, a3);
+        }
+        part[h] = (a0 + a1) + (a2 + a3);
     }
-    const float part = (a0 + a1) + (a2 + a3);
     double tot;
     float norm;
     bool fine;
     if constexpr (TEAM > kWave) {
         const uint32_t tid = threadIdx.x % TEAM;
-        lds[tid] = part;
+#pragma unroll
+        for (int h = 0; h < kParts; ++h)
+            lds[tid + h * TEAM] = part[h];
         __syncthreads();
         if (tid < (uint32_t)kWave) {
             tot = (double)lds[tid];
 #pragma unroll
-            for (int w = 1; w < TEAM / kWave; ++w)
+            for (int w = 1; w < kParts * TEAM / kWave; ++w)
                 tot += (double)lds[tid + w * kWave];
             tot = wave_sum_f64(tot);
             fine = tot >= 0x1p-80 && tot <= 0x1p100;
@@ -186,19 +227,27 @@ __device__ __forceinline__ float team_norm(Row row, float *lds, double *scratch)
         norm = uniform_f32(reinterpret_cast<const float *>(scratch)[0]);
         fine = norm >= 0.0f;
     } else {
-        tot = team_sum_f64<TEAM>((double)part, scratch);
+        double p[kParts];
+#pragma unroll
+        for (int h = 0; h < kParts; ++h)
+            p[h] = (double)part[h];
+        tot = team_sum_f64<TEAM>(p, scratch);
         fine = tot >= 0x1p-80 && tot <= 0x1p100;
         norm = (float)sqrt_mid(tot);
     }
     if (!fine) {                 // (a NaN comes here too)
-        double p = 0.0;
+        double p[kParts];
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-            const float4 x = row(i);
-            p += (double)x.x * (double)x.x;
-            p += (double)x.y * (double)x.y;
-            p += (double)x.z * (double)x.z;
-            p += (double)x.w * (double)x.w;
+        for (int h = 0; h < kParts; ++h) {
+            p[h] = 0.0;
+#pragma unroll
+            for (int i = h; i < VPT; i += kParts) {
+                const float4 x = row(i);
+                p[h] += (double)x.x * (double)x.x;
+                p[h] += (double)x.y * (double)x.y;
+                p[h] += (double)x.z * (double)x.z;
+                p[h] += (double)x.w * (double)x.w;
+            }
         }
         norm = (float)sqrt(team_sum_f64<TEAM>(p, scratch));
     }
@@ -210,7 +259,7 @@ template <int TEAM, int VPT>
 __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_bucket_norms(EncodeParams P, EncodeBatch Wk)
 {
     __shared__ double scratch[16];
-    __shared__ float part[TEAM > kWave ? TEAM : 1];
+    __shared__ float part[TEAM > kWave ? kNormParts<TEAM> * TEAM : 1];
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + threadIdx.x / TEAM;
@@ -470,21 +519,22 @@ __device__ __forceinline__ uint32_t flag_caller_bytes(const FlagBytes &fmt, uint
 // for the tables before they are requested would start every workgroup with an idle round trip).
 template <int TEAM>
 struct TableCopy {
-    uint32_t lo = 0, hi = 0;
+    static constexpr uint32_t kWG = TeamGeom<TEAM>::kWG, kPer = kWG < 256u ? 512u / kWG : 2u, kStep = 512u / kPer;
+    uint32_t words[kPer] = {};
     __device__ __forceinline__ explicit TableCopy(uint32_t s)
     {
         const uint32_t *src = kSmallTeam<TEAM> ? kCodeTables.small[s <= 7u ? 0 : 1] : kCodeTables.large;
-        if (threadIdx.x < 256u) {
-            lo = src[threadIdx.x];
-            hi = src[256u + threadIdx.x];
-        }
+        if (kWG == kStep || threadIdx.x < kStep)
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; ++i)
+                words[i] = src[threadIdx.x + i * kStep];
     }
     __device__ __forceinline__ void store(uint32_t *tables) const
     {
-        if (threadIdx.x < 256u) {
-            tables[threadIdx.x] = lo;
-            tables[256u + threadIdx.x] = hi;
-        }
+        if (kWG == kStep || threadIdx.x < kStep)
+#pragma unroll
+            for (uint32_t i = 0; i < kPer; ++i)
+                tables[threadIdx.x + i * kStep] = words[i];
     }
 };
 
@@ -848,21 +898,29 @@ __device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, con
     const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
     const uint32_t per = (nnz + TEAM - 1u) / TEAM;
     const uint32_t r0 = min(tid * per, nnz), r1 = min(r0 + per, nnz);
-    constexpr uint32_t kKept = 12;
-    uint32_t kept[kKept], bits = 0;
+    // The first twelve are what gradients have; twelve more are kept where some lane of the wave has them (up to 32 where
+    // most coordinates are nonzero; looked up again for the emission they cost twice), the rest looked up again.
+    constexpr uint32_t kUsual = 12, kKept = 2 * kUsual;
+    uint32_t kept[kKept] = {}, bits = 0;
     uint16_t *const run = L.rec + r0;
     const uint32_t n = r1 - r0;
+    const bool many = __any(n > kUsual);
     int p = r0 ? (int)run[-1] : -1;
-#pragma unroll
-    for (uint32_t i = 0; i < kKept; ++i) {
-        kept[i] = 0;
+    auto look_up = [&](uint32_t i) {
         if (i < n) {
             const int e = (int)run[i];
             kept[i] = record.packed((uint32_t)(e - p), (uint32_t)qbytes[e]);
             bits += kept[i] >> 27;
             p = e;
         }
-    }
+    };
+#pragma unroll
+    for (uint32_t i = 0; i < kUsual; ++i)
+        look_up(i);
+    if (many)
+#pragma unroll
+        for (uint32_t i = kUsual; i < kKept; ++i)
+            look_up(i);
     const int p_kept = p;
     for (uint32_t i = kKept; i < n; ++i) {
         const int e = (int)run[i];
@@ -888,14 +946,21 @@ __device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, con
     auto emit_all = [&](uint32_t *dst) {
         BitWriter w(off0);
         uint32_t t = off0;
-#pragma unroll
-        for (uint32_t i = 0; i < kKept; ++i)
+        auto emit = [&](uint32_t i) {
             if (kept[i]) {
                 run[i] = (uint16_t)t;
                 const uint32_t len = kept[i] >> 27;
                 t += len;
                 w.put(dst, kept[i] & 0x7ffffffu, len);
             }
+        };
+#pragma unroll
+        for (uint32_t i = 0; i < kUsual; ++i)
+            emit(i);
+        if (many)
+#pragma unroll
+            for (uint32_t i = kUsual; i < kKept; ++i)
+                emit(i);
         int q = p_kept;
         for (uint32_t i = kKept; i < n; ++i) {
             const int e = (int)run[i];
@@ -935,7 +1000,7 @@ __device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const
 
     // (1) nonzero mask of this thread's chunk (rows <= VPT <= 16 words: two 32-bit halves), ranks, compaction.  The mask of
     // two words is the byte dot products of their flags with 1, 2, 4, 8 and 16, 32, 64, 128, shifted left by 6.
-    static_assert(VPT % 8 == 0 && VPT <= 16, "the chunk's mask is 64 bits");
+    static_assert(VPT % 2 == 0 && VPT <= 16, "the chunk's mask is 64 bits, made of two words at a time");
     uint32_t half[2] = {0, 0};
 #pragma unroll
     for (int w = 0; w < VPT; w += 2) {

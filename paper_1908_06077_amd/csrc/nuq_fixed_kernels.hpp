@@ -108,7 +108,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_pack_fixed_direct(Encod
 {
     static_assert(B == 4 || B == 8, "codes of a thread's row must be whole halfwords");
     __shared__ __align__(8) uint32_t scratch_all[TeamGeom<TEAM>::kTeamsPerWG][64];
-    __shared__ uint32_t part[TEAM > kWave ? TEAM : 1];
+    __shared__ uint32_t part[TEAM > kWave ? kNormParts<TEAM> * TEAM : 1];
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
     const uint32_t team = team_uniform_u32<TEAM>(threadIdx.x / TEAM);

@@ -239,25 +239,33 @@ struct NibbleBytes {
     }
 };
 
-// The table's entry for this thread (256 of them), in two halves as TableCopy: its codewords requested before the gradient's
+// The table's entries for this thread (one of 256, or two), in two halves as TableCopy: its codewords requested before the gradient's
 // loads, the entry made and stored when those are under way.
+template <uint32_t WG>
 struct PairTable {
-    uint32_t len0, code0, len1, code1;
+    static constexpr uint32_t kPer = WG < 256u ? 256u / WG : 1u, kStep = 256u / kPer;
+    uint32_t len0, code0, len1[kPer], code1[kPer];        // the first coordinate's bits are the same for all of a thread's
     __device__ __forceinline__ explicit PairTable(const HuffmanCode &H)
     {
-        const uint32_t l0 = threadIdx.x & 7u, l1 = (threadIdx.x >> 4) & 7u;
-        len0 = H.len[l0];
-        code0 = H.code[l0];
-        len1 = H.len[l1];
-        code1 = H.code[l1];
+        len0 = H.len[threadIdx.x & 7u];
+        code0 = H.code[threadIdx.x & 7u];
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) {
+            const uint32_t level = ((threadIdx.x + i * kStep) >> 4) & 7u;
+            len1[i] = H.len[level];
+            code1[i] = H.code[level];
+        }
     }
     __device__ __forceinline__ void store(uint32_t *pairs) const
     {
-        const uint32_t p = threadIdx.x;
-        if (p < 256u) {
-            const uint32_t s0 = (p & 7u) ? 1u : 0u, s1 = (p & 0x70u) ? 1u : 0u;        // a sign bit follows
-            const uint32_t c0 = (code0 << s0) | (s0 & (p >> 3)), c1 = (code1 << s1) | (s1 & (p >> 7));
-            pairs[p] = (c0 << (len1 + s1)) | c1 | ((len0 + s0 + len1 + s1) << 16);
+#pragma unroll
+        for (uint32_t i = 0; i < kPer; ++i) {
+            const uint32_t p = threadIdx.x + i * kStep;
+            if (p < 256u) {
+                const uint32_t s0 = (p & 7u) ? 1u : 0u, s1 = (p & 0x70u) ? 1u : 0u;    // a sign bit follows
+                const uint32_t c0 = (code0 << s0) | (s0 & (p >> 3)), c1 = (code1[i] << s1) | (s1 & (p >> 7));
+                pairs[p] = (c0 << (len1[i] + s1)) | c1 | ((len0 + s0 + len1[i] + s1) << 16);
+            }
         }
     }
 };
@@ -340,7 +348,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
     __shared__ uint32_t enc[256];
     uint32_t total;
     if constexpr (kPairs) {
-        const PairTable table(H);
+        const PairTable<TeamGeom<TEAM>::kWG> table(H);
         front_quantize_to_lds<TEAM, VPT>(P, W, b, active, base, nbk, tid, qb32, scratch, NibbleBytes{},
                                          [&] { table.store(enc); });
         __syncthreads();
