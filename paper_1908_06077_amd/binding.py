@@ -1,4 +1,7 @@
-"""ctypes binding of the C ABI in include/nuq.h.  Argument marshalling only."""
+"""Binding of the C ABI in include/nuq.h.  Argument marshalling only.
+
+The calls of a training step, an exchange or a variance draw go through _nuq_calls (csrc/nuq_calls.cpp), which takes the plain
+case in C++; what it declines, and everything else, goes through the checks and ctypes calls below."""
 from __future__ import annotations
 
 import ctypes
@@ -77,6 +80,14 @@ for _name, (_res, _args) in _SIGNATURES.items():
     _fn.argtypes = _args
 
 
+if not os.path.exists(os.path.join(_HERE, "_nuq_calls.so")):
+    raise ImportError("_nuq_calls.so is not built: see libnuq.so above")
+from . import _nuq_calls as _calls  # noqa: E402
+
+_calls.bind(tuple(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in _calls.names()),
+            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+
+
 def library_path() -> str:
     return _LIB_PATH
 
@@ -129,10 +140,7 @@ def _sizes(d: int, bucket: int, sync_stride: int, huffman: bool = False) -> tupl
 
 def _message_arrays(messages, d: int, bucket: int, sync_stride: int, huffman: bool = False, norms: bool = True):
     """ctypes pointer arrays (norms, bit_off, words, words_len, sync) of K messages, every tensor checked against the
-    size that d, bucket and sync_stride imply.
-
-    A step on some ten thousand coordinates takes as long as its marshalling, so it is one pass over the messages and one
-    array type: 41 -> 35 us for encode and decode of four messages, a step on 4 x 65 537 coordinates 39.9 -> 36.4 us."""
+    size that d, bucket and sync_stride imply."""
     K = len(messages)
     B, nsync = _sizes(d, bucket, sync_stride, huffman)
     addresses = ctypes.c_uint64 * K                      # (one array type: addresses and lengths alike)
@@ -236,6 +244,9 @@ def nuq_quantize_encode_static(v: torch.Tensor, bucket: int, s: int, seed: int, 
 
 def nuq_quantize_encode_batch(vs: list[torch.Tensor], bucket: int, s: int, seeds: list[int], sync_stride: int,
                               messages: list["Message"], workspace: torch.Tensor) -> None:
+    code = _calls.quantize_encode_batch(vs, bucket, s, seeds, sync_stride, messages, workspace)
+    if code is not None:
+        return _check("nuq_quantize_encode_batch", code)
     K = len(vs)
     d = vs[0].numel()
     if any([v.numel() != d for v in vs]) or len(seeds) != K or len(messages) != K:
@@ -251,6 +262,9 @@ def nuq_quantize_encode_batch(vs: list[torch.Tensor], bucket: int, s: int, seeds
 
 def nuq_decode_accumulate(messages: list[Message], d: int, bucket: int, s: int, sync_stride: int, scale: float,
                           accumulate: bool, out: torch.Tensor) -> None:
+    code = _calls.decode_accumulate(messages, d, bucket, s, sync_stride, scale, accumulate, out)
+    if code is not None:
+        return _check("nuq_decode_accumulate", code)
     K = len(messages)
     norms, offs, words, lens, sync = _message_arrays(messages, d, bucket, sync_stride)
     if out.numel() != d:
@@ -289,6 +303,9 @@ NORM_L2, NORM_LINF = 0, 1
 
 def nuq_quantize_encode_table_batch(vs: list[torch.Tensor], bucket: int, levels, norm_kind: int, seeds: list[int],
                                     sync_stride: int, messages: list["Message"], workspace: torch.Tensor) -> None:
+    code = _calls.quantize_encode_table_batch(vs, bucket, levels, norm_kind, seeds, sync_stride, messages, workspace)
+    if code is not None:
+        return _check("nuq_quantize_encode_table_batch", code)
     K = len(vs)
     d = vs[0].numel()
     s = len(levels) - 2
@@ -306,6 +323,9 @@ def nuq_quantize_encode_table_batch(vs: list[torch.Tensor], bucket: int, levels,
 
 def nuq_decode_accumulate_table(messages: list[Message], d: int, bucket: int, levels, sync_stride: int, scale: float,
                                 accumulate: bool, out: torch.Tensor) -> None:
+    code = _calls.decode_accumulate_table(messages, d, bucket, levels, sync_stride, scale, accumulate, out)
+    if code is not None:
+        return _check("nuq_decode_accumulate_table", code)
     K = len(messages)
     s = len(levels) - 2
     norms, offs, words, lens, sync = _message_arrays(messages, d, bucket, sync_stride)
@@ -330,6 +350,9 @@ def nuq_pack_fixed(q: torch.Tensor, bucket: int, s: int, b: int, packed: torch.T
 
 def nuq_quantize_pack_fixed_batch(vs: list[torch.Tensor], bucket: int, s: int, b: int, seeds: list[int],
                                   norms: list[torch.Tensor], packed: list[torch.Tensor]) -> None:
+    code = _calls.quantize_pack_fixed_batch(vs, bucket, s, b, seeds, norms, packed)
+    if code is not None:
+        return _check("nuq_quantize_pack_fixed_batch", code)
     K = len(vs)
     d = vs[0].numel()
     if any(v.numel() != d for v in vs) or len(seeds) != K or len(norms) != K or len(packed) != K:
@@ -343,6 +366,9 @@ def nuq_quantize_pack_fixed_batch(vs: list[torch.Tensor], bucket: int, s: int, b
 
 def nuq_unpack_accumulate_fixed(norms: list[torch.Tensor], packed: list[torch.Tensor], d: int, bucket: int, s: int,
                                 b: int, scale: float, accumulate: bool, out: torch.Tensor) -> None:
+    code = _calls.unpack_accumulate_fixed(norms, packed, d, bucket, s, b, scale, accumulate, out)
+    if code is not None:
+        return _check("nuq_unpack_accumulate_fixed", code)
     K = len(norms)
     arr = lambda ts, dt: (ctypes.c_void_p * K)(*[_ptr(t, dt) for t in ts])
     if out.numel() != d:
@@ -354,6 +380,9 @@ def nuq_unpack_accumulate_fixed(norms: list[torch.Tensor], packed: list[torch.Te
 
 def nuq_quantize_pack_fixed_table_batch(vs: list[torch.Tensor], bucket: int, levels, norm_kind: int, b: int,
                                         seeds: list[int], norms: list[torch.Tensor], packed: list[torch.Tensor]) -> None:
+    code = _calls.quantize_pack_fixed_table_batch(vs, bucket, levels, norm_kind, b, seeds, norms, packed)
+    if code is not None:
+        return _check("nuq_quantize_pack_fixed_table_batch", code)
     K = len(vs)
     d = vs[0].numel()
     s = len(levels) - 2
@@ -370,6 +399,9 @@ def nuq_quantize_pack_fixed_table_batch(vs: list[torch.Tensor], bucket: int, lev
 
 def nuq_unpack_accumulate_fixed_table(norms: list[torch.Tensor], packed: list[torch.Tensor], d: int, bucket: int,
                                       levels, b: int, scale: float, accumulate: bool, out: torch.Tensor) -> None:
+    code = _calls.unpack_accumulate_fixed_table(norms, packed, d, bucket, levels, b, scale, accumulate, out)
+    if code is not None:
+        return _check("nuq_unpack_accumulate_fixed_table", code)
     K = len(norms)
     s = len(levels) - 2
     if out.numel() != d or len(packed) != K:
@@ -439,6 +471,9 @@ def nuq_encode_huffman_batch_workspace_bytes(K: int, d: int, bucket: int, s: int
 
 def nuq_quantize_encode_huffman_batch(vs: list[torch.Tensor], bucket: int, s: int, seeds: list[int], sync_stride: int,
                                       lengths, messages: list["Message"], workspace: torch.Tensor) -> None:
+    code = _calls.quantize_encode_huffman_batch(vs, bucket, s, seeds, sync_stride, lengths, messages, workspace)
+    if code is not None:
+        return _check("nuq_quantize_encode_huffman_batch", code)
     K = len(vs)
     d = vs[0].numel()
     if any(v.numel() != d for v in vs) or len(seeds) != K or len(messages) != K:
@@ -471,6 +506,9 @@ def nuq_decode_huffman_batch(messages: list[Message], d: int, bucket: int, s: in
 
 def nuq_decode_accumulate_huffman(messages: list[Message], d: int, bucket: int, s: int, sync_stride: int, lengths,
                                   scale: float, accumulate: bool, out: torch.Tensor) -> None:
+    code = _calls.decode_accumulate_huffman(messages, d, bucket, s, sync_stride, lengths, scale, accumulate, out)
+    if code is not None:
+        return _check("nuq_decode_accumulate_huffman", code)
     K = len(messages)
     norms, offs, words, lens, sync = _message_arrays(messages, d, bucket, sync_stride, huffman=True)
     if out.numel() != d:
@@ -508,6 +546,9 @@ def nuq_momentum_step(w: torch.Tensor, yl: torch.Tensor, g: torch.Tensor, alpha:
 
 def nuq_decode_momentum_step(messages: list[Message], d: int, bucket: int, s: int, sync_stride: int, scale: float,
                              alpha: float, mu: float, l: float, w: torch.Tensor, yl: torch.Tensor) -> None:
+    code = _calls.decode_momentum_step(messages, d, bucket, s, sync_stride, scale, alpha, mu, l, w, yl)
+    if code is not None:
+        return _check("nuq_decode_momentum_step", code)
     K = len(messages)
     norms, offs, words, lens, sync = _message_arrays(messages, d, bucket, sync_stride)
     if w.numel() != d or yl.numel() != d:
@@ -519,6 +560,9 @@ def nuq_decode_momentum_step(messages: list[Message], d: int, bucket: int, s: in
 
 
 def nuq_moments_accumulate(g: torch.Tensor, total: torch.Tensor, total_sq: torch.Tensor) -> None:
+    code = _calls.moments_accumulate(g, total, total_sq)
+    if code is not None:
+        return _check("nuq_moments_accumulate", code)
     d = g.numel()
     if total.numel() != d or total_sq.numel() != d:
         raise ValueError("the moment sums hold d doubles each")

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <mutex>
 #include <type_traits>
@@ -49,11 +50,20 @@ void *static_workspace_ptr()
 // Sticky error flags, one word per device (each device holds its own copy of the symbol).
 __device__ uint32_t g_flags;
 
+// Their address on the current device, looked up once per device and kept (a symbol does not move).
 uint32_t *flags_ptr()
 {
-    void *p = nullptr;
-    if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_flags)) != hipSuccess)
+    static std::atomic<void *> ptrs[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0)
         return nullptr;
+    void *p = dev < 64 ? ptrs[dev].load(std::memory_order_relaxed) : nullptr;
+    if (!p) {
+        if (hipGetSymbolAddress(&p, HIP_SYMBOL(g_flags)) != hipSuccess)
+            return nullptr;
+        if (dev < 64)
+            ptrs[dev].store(p, std::memory_order_relaxed);
+    }
     return static_cast<uint32_t *>(p);
 }
 
