@@ -782,6 +782,22 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     if (momentum && levels)
         return NUQ_EINVAL;
     if (K == 1 && !levels && !momentum && (nsync || bucket <= 512)) {
+        if (!accumulate && nsync && bucket >= kOneMinBucket) {
+            // One message, written: up to 64 pieces per wave, as many blocks of 2048 coordinates (whole buckets below that)
+            // as 16 KB of bytes hold, less three that the first float4 group may begin before the first of them; fewer where
+            // that would leave less than a thousand waves (1 M coordinates: 14.3 us with eight blocks each, 8.0 with one).
+            constexpr uint64_t kOneWaves = 1024;
+            const uint32_t span = std::min(bucket, 1u << kSyncBlockShift);
+            const uint64_t nblocks = P.nb * (P.nseg >> P.pieces_shift);
+            P.segs_per_tile = (uint32_t)std::min<uint64_t>(
+                std::min(64u >> P.pieces_shift, (kOneCoords - (bucket % 4u ? 3u : 0u)) / span), (nblocks + kOneWaves) / kOneWaves);
+            const uint64_t wgs = (nblocks + P.segs_per_tile - 1) / P.segs_per_tile;
+            if (wgs > 0x7fffffffull)
+                return NUQ_EINVAL;
+            ScopedTiming timing(NUQ_T_DECODE, static_cast<hipStream_t>(stream));
+            hipLaunchKernelGGL(k_decode_one, dim3((uint32_t)wgs), dim3(kWave), 0, static_cast<hipStream_t>(stream), P);
+            return check_launch();
+        }
         // one message: a lane per (bucket, sync segment), values stored directly (k_decode_single)
         const uint64_t wgs = (P.nb * P.nseg + kSingleWG - 1) / kSingleWG;
         if (wgs > 0x7fffffffull)

@@ -383,6 +383,7 @@ struct TileSink {
     double *tile;
     uint32_t origin;                               // byte offset of the bucket's index 0 (modulo 2^32)
     static constexpr uint32_t kUnit = 3;
+    static constexpr bool kCodes = false;
     __device__ __forceinline__ uint32_t place(uint32_t i) const { return origin + (i << kUnit); }
     __device__ __forceinline__ void add(uint32_t at, double v) const
     {
@@ -394,6 +395,7 @@ struct DirectSink {
     float *at0;
     double scale;
     static constexpr uint32_t kUnit = 0;
+    static constexpr bool kCodes = false;
     __device__ __forceinline__ uint32_t place(uint32_t i) const { return i; }
     __device__ __forceinline__ void add(uint32_t idx, double v) const
     {
@@ -403,6 +405,20 @@ struct DirectSink {
         else
             at0[idx] = r;
     }
+};
+
+// CodeSink: the record's level and sign as a byte in LDS, level | sign << 4 (sign: bit 0 of y).
+struct CodeSink {
+    uint8_t *codes;
+    uint32_t origin;                               // place of the bucket's index 0 (modulo 2^32)
+    static constexpr uint32_t kUnit = 0;
+    static constexpr bool kCodes = true;
+    __device__ __forceinline__ uint32_t place(uint32_t i) const { return origin + i; }
+    __device__ __forceinline__ void put(uint32_t at, uint32_t y, uint32_t level) const
+    {
+        codes[at] = (uint8_t)(((y & 1u) << 4) | level);
+    }
+    __device__ __forceinline__ void add(uint32_t, double) const {}
 };
 
 template <bool kTable, class Sink>
@@ -457,6 +473,10 @@ struct ErcParser {
     {
         const uint32_t j = e2;
         min_j = min(min_j, j);
+        if constexpr (Sink::kCodes) {
+            sink.put(at, y, j);
+            return;
+        }
         uint32_t mh, ml;
         if constexpr (kTable) {
             const uint64_t mag = (uint64_t)__double_as_longlong(wnorm * (double)lj) & 0x7fffffffffffffffull;
@@ -1467,6 +1487,135 @@ __global__ __launch_bounds__(kSingleWG) void k_decode_single(DecodeParams P)
         else
             decode_unit_fast<false>(GlobalWords{src, nw - 1u}, lut, lut_level, nullptr, rel_lo, rel_hi, forced, idx_hi,
                                     wnorm, sink, bad);
+    }
+    if (bad)
+        atomicOr(P.flags, kFlagMalformed);
+}
+
+// The write mode for buckets of 512 coordinates or more.  A wave takes up to 64 pieces, 8 blocks of 2048 coordinates (or as
+// many whole small buckets), as bytes in 16 KB of LDS: the parser stores a record's level and sign, and the blocks are then
+// written out in order, each byte looked up in a table of its bucket's 32 values, fp32(scale * value).  Every line of the
+// result is written once.  Against clearing it first and scattering into it (k_decode_single, which smaller buckets and the
+// add keep): 200 M coordinates in buckets of 8192 260 -> 153 us, of 512 374 -> 261; 16.8 M at s = 7 in buckets of 4096 123 ->
+// 55; 1 M 11.1 -> 8.0.
+constexpr uint32_t kOneCoords = 16384;
+constexpr uint32_t kOneMinBucket = 512;
+
+__global__ __launch_bounds__(kWave) void k_decode_one(DecodeParams P)
+{
+    __shared__ __align__(16) uint8_t codes[kOneCoords];
+    __shared__ uint32_t rows[kWave * kSingleRow];
+    __shared__ float values[32];
+    __shared__ uint16_t lut[128];
+    __shared__ uint8_t lut_level[128];
+    const uint32_t lane = threadIdx.x;
+    // blocks of this workgroup: block t of all buckets, numbered bucket by bucket
+    const uint32_t pieces = 1u << P.pieces_shift, blocks = P.segs_per_tile;          // blocks per workgroup
+    const uint64_t per_bucket = P.nseg >> P.pieces_shift, nblocks = P.nb * per_bucket;
+    const uint64_t t0 = (uint64_t)blockIdx.x * blocks;
+
+    // ---- this lane's piece: metadata, then its words into the lane's LDS row
+    const uint64_t t = min(t0 + (lane >> P.pieces_shift), nblocks - 1u);             // (a lane without one loads and ignores)
+    const uint64_t b = t / per_bucket;
+    const uint32_t blk = (uint32_t)(t - b * per_bucket), g = (blk << P.pieces_shift) + (lane & (pieces - 1u));
+    bool work = (lane >> P.pieces_shift) < blocks && t0 + (lane >> P.pieces_shift) < nblocks;
+    const uint64_t bo0 = P.bit_off[0][b], bo1 = P.bit_off[0][b + 1];
+    const uint32_t *sy = P.sync[0] + b * P.nsync;
+    const uint32_t e0 = sy[g], e1 = sy[min(g + 1u, P.nseg - 1u)];
+    lut[lane] = (uint16_t)gap_table_entry(lane);
+    lut[lane + kWave] = (uint16_t)gap_table_entry(lane + kWave);
+    lut_level[lane] = (uint8_t)level_table_entry(lane, P.s + 1u);
+    lut_level[lane + kWave] = (uint8_t)level_table_entry(lane + kWave, P.s + 1u);
+    for (uint32_t i = lane; i < kOneCoords / 16u; i += kWave)
+        reinterpret_cast<uint4 *>(codes)[i] = uint4{0u, 0u, 0u, 0u};
+    const uint32_t nbk = (uint32_t)min((uint64_t)P.bucket, P.d - b * P.bucket);
+    const uint32_t idx_hi = min(nbk, (blk + 1u) << kSyncBlockShift);
+    const uint64_t start = (bo0 + 31ull) & ~31ull;
+    // offsets run forwards, stay inside the words received, and a bucket's bit string is below 2^21 bits
+    bool bad = work && (bo1 < bo0 || bo1 > P.words_bits[0] || (bo1 > start && bo1 - start > (uint64_t)kSyncOffMask));
+    const uint32_t len = bo1 > start && !bad ? (uint32_t)(bo1 - start) : 0u;
+    const uint32_t bit_lo = e0 & kSyncOffMask, bit_hi = g + 1u < P.nseg ? e1 & kSyncOffMask : len;
+    const uint32_t forced = (blk << kSyncBlockShift) + (e0 >> 21);
+    if (work && (bit_lo > bit_hi || bit_hi > len || (bit_hi > bit_lo && forced >= idx_hi))) {
+        bad = true;
+        work = false;
+    }
+    work = work && bit_hi > bit_lo;
+    const uint32_t w0 = bit_lo >> 5, nw = work ? ((bit_hi + 31u) >> 5) - w0 : 0u;
+    const uint32_t *src = P.words[0] + (start >> 5) + w0;
+    uint32_t *row = rows + lane * kSingleRow;
+    const bool staged = nw <= kSingleCap;
+    if (work && staged) {
+        for (uint32_t j0 = 0; j0 < nw; j0 += 8u) {                   // loads of a group in flight together
+            uint32_t x[8];
+#pragma unroll
+            for (uint32_t j = 0; j < 8u; ++j)
+                x[j] = src[min(j0 + j, nw - 1u)];
+#pragma unroll
+            for (uint32_t j = 0; j < 8u; ++j)
+                row[1u + j0 + j] = x[j];
+        }
+    }
+    __syncthreads();
+
+    // ---- records into the byte of their coordinate; the first coordinate's float4 group is byte 0 of `codes`
+    const uint64_t b_first = t0 / per_bucket;
+    const uint64_t c0 = b_first * P.bucket + ((t0 - b_first * per_bucket) << kSyncBlockShift), c_base = c0 & ~3ull;
+    if (work) {
+        const CodeSink sink{codes, (uint32_t)(b * P.bucket - c_base)};
+        if (staged)
+            decode_unit_fast<false>(StagedWords{row}, lut, lut_level, nullptr, bit_lo & 31u, bit_hi - (w0 << 5), (int)forced, idx_hi,
+                                    1.0, sink, bad);
+        else
+            decode_unit_fast<false>(GlobalWords{src, nw - 1u}, lut, lut_level, nullptr, bit_lo & 31u, bit_hi - (w0 << 5),
+                                    (int)forced, idx_hi, 1.0, sink, bad);
+    }
+
+    // ---- the blocks, one after the other
+    const bool vec = (reinterpret_cast<uintptr_t>(P.out) & 15u) == 0;
+    uint64_t bb = b_first;
+    uint32_t in_b = (uint32_t)(t0 - b_first * per_bucket);
+    for (uint32_t i = 0; i < blocks && t0 + i < nblocks; ++i) {
+        const uint64_t lo = bb * P.bucket + ((uint64_t)in_b << kSyncBlockShift);
+        const uint64_t hi = min(min(P.d, (bb + 1u) * P.bucket), lo + (1u << kSyncBlockShift));
+        __syncthreads();
+        if ((i == 0 || in_b == 0) && lane < 32u) {
+            const double mag = ldexp((double)P.norms[0][bb], (int)(lane & 15u) - 1 - (int)P.s);
+            const uint64_t bits = (uint64_t)__double_as_longlong(mag) & 0x7fffffffffffffffull;       // a norm is a magnitude
+            const double v = __longlong_as_double((long long)(bits | ((uint64_t)(lane >> 4) << 63)));
+            values[lane] = (lane & 15u) ? (float)((double)P.scale * v) : 0.0f;
+        }
+        __syncthreads();
+        if (lo < hi) {
+            const uint64_t up = vec ? min((lo + 3u) & ~3ull, hi) : hi, dn = vec ? max(hi & ~3ull, up) : hi;
+            for (uint64_t c = lo + lane; c < up; c += kWave)
+                P.out[c] = values[codes[c - c_base]];
+            const uint32_t groups = (uint32_t)(dn - up) >> 2, at = (uint32_t)(up - c_base) >> 2;
+            float4 *const o = reinterpret_cast<float4 *>(P.out + up);
+            const uint32_t *const q4 = reinterpret_cast<const uint32_t *>(codes) + at;
+            constexpr uint32_t kFlight = 2;
+            for (uint32_t i0 = lane; i0 < groups; i0 += kFlight * kWave) {
+                uint32_t q[kFlight];
+                float4 v[kFlight];
+#pragma unroll
+                for (uint32_t r = 0; r < kFlight; ++r)
+                    q[r] = q4[min(i0 + r * kWave, groups - 1u)];
+#pragma unroll
+                for (uint32_t r = 0; r < kFlight; ++r)
+                    v[r] = float4{values[q[r] & 0xffu], values[(q[r] >> 8) & 0xffu], values[(q[r] >> 16) & 0xffu],
+                                  values[q[r] >> 24]};
+#pragma unroll
+                for (uint32_t r = 0; r < kFlight; ++r)
+                    if (i0 + r * kWave < groups)
+                        store_once4(o + i0 + r * kWave, v[r]);
+            }
+            for (uint64_t c = dn + lane; c < hi; c += kWave)
+                P.out[c] = values[codes[c - c_base]];
+        }
+        if (++in_b == per_bucket) {
+            in_b = 0;
+            ++bb;
+        }
     }
     if (bad)
         atomicOr(P.flags, kFlagMalformed);

@@ -158,3 +158,25 @@ def test_pieces_of_every_length(g, n, S, K, s, density):
         nuq.nuq_decode_accumulate_huffman(hm, d, n, s, S, lengths, 0.5, False, out)
         assert nuq.nuq_last_error_flags() == 0
         np.testing.assert_array_equal(out.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("n,S,s,d", [(511, 64, 3, 511 * 9 + 1), (512, 64, 3, 512 * 70), (513, 512, 3, 513 * 70 + 2), (1000, 256, 7, 1), (1000, 256, 7, 40_003),
+                                     (2047, 1024, 14, 2047 * 40 + 5), (2049, 128, 3, 2049 * 30 + 2048), (4098, 256, 5, 4098 * 9 + 3),
+                                     (8192, 256, 3, 8192 * 700 + 77), (20001, 64, 3, 20001 * 3 + 2049), (32768, 1024, 1, 32768 * 5 + 4)])
+def test_one_message(g, n, S, s, d, shift):
+    """A single message written out: blocks per workgroup from one to the most that fit, odd bucket sizes (blocks that begin and
+    end inside a float4 group), a last bucket that ends inside a block and leaves others empty, an odd output address."""
+    nuq = g.nuq
+    rng = np.random.default_rng(d + n)
+    nb = -(-d // n)
+    q = _dense_bytes(rng, d, n, s, 0.1)
+    norms = np.exp2(rng.uniform(-140, 100, nb)).astype(np.float32)
+    msg = _message(g, q, n, s, S, norms)
+    flat = torch.full((d + 9,), 7.0, device=g.DEV)
+    nuq.nuq_decode_accumulate([msg], d, n, s, S, 0.3, False, flat[shift + 4:shift + 4 + d])
+    assert nuq.nuq_last_error_flags() == 0
+    got = flat.cpu().numpy()
+    want = (np.float64(np.float32(0.3)) * _value(q, n, s, norms)).astype(np.float32)
+    np.testing.assert_array_equal(got[shift + 4:shift + 4 + d].view(np.uint32), want.view(np.uint32))
+    assert (got[:shift + 4] == 7.0).all() and (got[shift + 4 + d:] == 7.0).all()
