@@ -180,3 +180,34 @@ def test_one_message(g, n, S, s, d, shift):
     want = (np.float64(np.float32(0.3)) * _value(q, n, s, norms)).astype(np.float32)
     np.testing.assert_array_equal(got[shift + 4:shift + 4 + d].view(np.uint32), want.view(np.uint32))
     assert (got[:shift + 4] == 7.0).all() and (got[shift + 4 + d:] == 7.0).all()
+
+
+@pytest.mark.parametrize("update", ["write", "add", "momentum"])
+@pytest.mark.parametrize("n,S,K,d", [(1000, 256, 2, 9000), (1000, 256, 2, 8009), (1001, 128, 3, 6006), (512, 512, 4, 512 * 17), (512, 256, 2, 512 * 16 + 259),
+                                     (256, 256, 2, 256 * 33 + 2), (2048, 512, 2, 2048 * 5 + 6), (1024, 512, 4, 1024 * 9), (20000, 256, 4, 40_004),
+                                     (4100, 256, 2, 8200)])
+def test_tiles_that_are_not_full(g, n, S, K, d, update):
+    """Tiles of 2048 and of 4096 coordinates that small buckets do not fill, of few or of no float4 groups, and both tile sizes'
+    lines: the result of each way of applying a tile."""
+    nuq = g.nuq
+    rng = np.random.default_rng(n + d)
+    s, nb = 3, -(-d // n)
+    qs = [_dense_bytes(rng, d, n, s, 0.2) for _ in range(K)]
+    norms = [np.exp2(rng.uniform(-3, 3, nb)).astype(np.float32) for _ in range(K)]
+    msgs = [_message(g, q, n, s, S, v) for q, v in zip(qs, norms)]
+    r = (0.5 * sum(_value(q, n, s, v) for q, v in zip(qs, norms))).astype(np.float32)
+    w0, y0 = rng.standard_normal((2, d + 8)).astype(np.float32)
+    w, y = torch.from_numpy(w0.copy()).to(g.DEV), torch.from_numpy(y0.copy()).to(g.DEV)
+    if update == "momentum":
+        nuq.nuq_decode_momentum_step(msgs, d, n, s, S, 0.5, 0.25, 0.5, 1.0, w[:d], y[:d])
+        g64 = r.astype(np.float64)
+        yl = w0[:d].astype(np.float64) - 0.25 * g64
+        want = (w0[:d].astype(np.float64) - 0.25 * g64) + 0.5 * (yl - y0[:d].astype(np.float64))
+        np.testing.assert_allclose(y.cpu().numpy()[:d], yl, rtol=2.0 ** -23, atol=2.0 ** -30)      # one rounding to fp32
+        np.testing.assert_allclose(w.cpu().numpy()[:d], want, rtol=2.0 ** -23, atol=2.0 ** -30)
+    else:
+        nuq.nuq_decode_accumulate(msgs, d, n, s, S, 0.5, update == "add", w[:d])
+        np.testing.assert_array_equal(w.cpu().numpy()[:d], r + w0[:d] if update == "add" else r)
+    np.testing.assert_array_equal(w.cpu().numpy()[d:], w0[d:])
+    np.testing.assert_array_equal(y.cpu().numpy()[d:], y0[d:])
+    assert nuq.nuq_last_error_flags() == 0
