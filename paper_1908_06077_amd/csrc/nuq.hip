@@ -814,7 +814,11 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     // Tiles of 4096 coordinates (32 KB of fp64, four workgroups per CU instead of eight) where the usual 2048 would
     // give the 64 parsing lanes at most 32 units: parts of large buckets of few workers.  The parse is bound by
     // instruction issue, so one full wave per SIMD gets through more records than two half-empty ones.
-    const bool big = nsync && bucket >= kTileCoordsBig && (K << P.pieces_shift) <= 32u;
+    // Small buckets: only where they fill the tile and 2048 coordinates have at most 16 units (4 x 16.8 M coordinates in buckets
+    // of 512 at stride 512 84 -> 78 us, two messages at 256 48 -> 44; with 32 units 50 -> 52).
+    const bool big = nsync && (bucket >= kTileCoordsBig ? (K << P.pieces_shift) <= 32u
+                                                        : kTileCoordsBig % bucket == 0 && kTileCoordsBig / bucket * K <= kMaxStreams &&
+                                                              (kTileCoords / bucket * K << P.pieces_shift) <= 16u);
     const uint32_t tile_coords = big ? kTileCoordsBig : kTileCoords;
     const uint32_t variant = 2u * ((levels ? 3u : 0u) + (momentum ? (uint32_t)kUpdateMomentum
                                                                   : accumulate ? (uint32_t)kUpdateAdd
@@ -828,7 +832,7 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     uint64_t ntiles;
     uint32_t max_streams;
     if (bucket <= kTileCoords) {
-        const uint32_t by_size = kTileCoords / bucket, by_streams = kMaxStreams / K;
+        const uint32_t by_size = tile_coords / bucket, by_streams = kMaxStreams / K;
         P.buckets_per_tile = by_size < by_streams ? by_size : by_streams;
         P.tiles_per_bucket = 1;
         P.tile_coords = P.buckets_per_tile * bucket;
