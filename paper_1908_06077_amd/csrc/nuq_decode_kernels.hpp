@@ -130,8 +130,10 @@ __device__ __forceinline__ void apply_full_tile(const DecodeParams &P, double *t
             double2 *src = reinterpret_cast<double2 *>(tile) + 2u * (tid + (r0 + r) * WG);
             a[r] = src[0];
             c[r] = src[1];
-            src[0] = double2{0.0, 0.0};
-            src[1] = double2{0.0, 0.0};
+            if (!kPart || tid + (r0 + r) * WG < n4) {         // (what follows the groups is the caller's, maybe another wave's)
+                src[0] = double2{0.0, 0.0};
+                src[1] = double2{0.0, 0.0};
+            }
         }
 #pragma unroll
         for (uint32_t r = 0; r < 2u; ++r) {
