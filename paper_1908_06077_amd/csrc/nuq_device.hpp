@@ -576,7 +576,8 @@ __device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_
 #pragma unroll
     for (int c = 0; c < 4; ++c)
         u[c] = (float)draw24(x0 + (uint32_t)c * kRngC1, k1);
-    if (__all(max_abs4(xs) < R.thr1)) {                          // every coordinate of every lane below the first level
+    const float big = max_abs4(xs);
+    if (__all(big < R.thr1)) {                                   // every coordinate of every lane below the first level
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             t[c] = __builtin_fmaf(u[c], R.w0, -fabsf(xs[c]));
@@ -592,6 +593,11 @@ __device__ __forceinline__ uint32_t quantize_table_vec4(const float4 &x, uint32_
             f = u2f((uint32_t)__builtin_amdgcn_readlane((int)f2u(R.thr_lane), (int)l));
         else
             f = R.bins->thr[l];
+        // No lane above this level, nor above the next (they increase).  2 % of QSGDinf and of s = 7 where the threshold is a
+        // scalar; teams of less than a wave read it from LDS, and lose 1 % with this.
+        if constexpr (TEAM >= (int)kWave)
+            if (!__any(big >= f))
+                break;
 #pragma unroll
         for (int c = 0; c < 4; ++c)
             j[c] += fabsf(xs[c]) >= f ? 1u : 0u;
