@@ -11,8 +11,8 @@
 // LDS capacity bounds the number of tiles in flight, a lone wave issues a dependent
 // instruction only every nine cycles or so, and a tile's life would mostly be spent waiting on
 // memory (offsets and sync entries first, then the words they point to) and on bookkeeping.  So
-// a workgroup is persistent, walks a strided sequence of tiles, and its two waves have
-// different jobs: the first parses tile t while the second prepares tile t+1 -- works out
+// a workgroup is persistent and walks a strided sequence of tiles.  In the kernel for any geometry
+// its two waves have different jobs: the first parses tile t while the second prepares tile t+1 -- works out
 // which words each unit needs, fetches them into registers, leaves a three-word plan per unit
 // in LDS -- and has the metadata loads of tile t+2 in flight.  When the parse is over the
 // fetched words go to the LDS staging area and both waves write tile t out and clear it.  The critical path of a tile is its
@@ -28,7 +28,7 @@ constexpr uint32_t kMaxWorkers = 32;
 constexpr uint32_t kDecodeWG = 128;        // threads per workgroup: a parsing wave and a preparing wave
 constexpr uint32_t kTileCoords = 2048;     // coordinates per tile (16 KB of fp64) ...
 constexpr uint32_t kTileCoordsBig = 4096;  // ... or, for few workers and large buckets, twice that (see the launcher)
-constexpr uint32_t kWordsPerLane = 8;      // staged words each lane of the preparing wave carries
+constexpr uint32_t kWordsPerLane = 8;      // staged words each lane of the two-wave kernel's preparing wave carries
 constexpr uint32_t kStageWords = kWave * kWordsPerLane;   // LDS words per staging buffer
 constexpr uint32_t kMaxStreams = 64;       // (bucket, worker) bit strings per tile
 constexpr uint32_t kPlanned = 2 * kWave;   // units of a tile that are planned ahead (two per preparing lane)
@@ -1014,14 +1014,12 @@ __global__ __launch_bounds__(kDecodeWG, 4) void k_decode_accumulate(DecodeParams
 }
 
 // ---- the tile decoder as one wave per workgroup --------------------------------------------------------------
-// For messages with a decoder index whose tiles hold at most 64 pieces, each stream's pieces within the lanes that copy
-// that stream (the usual geometries).  What bounds the two-wave kernel above on such tiles is neither the parse nor
+// For messages with a decoder index whose tiles hold at most 64 pieces (the usual geometries).  What bounds the two-wave kernel above on such tiles is neither the parse nor
 // memory but its own bookkeeping: the preparing wave works through several hundred mostly dependent instructions per
 // tile at a lone wave's pace (an instruction every nine cycles), sharing its SIMD's issue slots with the parsing waves,
 // and two barriers per tile keep the eight workgroups of a CU in step, so that all of them parse, and then all of them
-// write, at the same time.  Here one wave does everything for its tiles, in order and without barriers: the lanes
-// that copy a stream's words are the lanes that parse its pieces (so one set of offsets and index entries serves
-// both), the words of the next tile and the offsets of the tile after it are in flight in registers while this
+// write, at the same time.  Here one wave does everything for its tiles, in order and without barriers: a lane
+// loads the words that it parses (so one set of offsets and index entries serves both), the words of the next tile and the offsets of the tile after it are in flight in registers while this
 // tile is parsed and written (a wave per SIMD pair leaves 256 registers per lane), and the workgroups of a CU drift
 // apart, which spreads parse, LDS and store traffic over time.
 constexpr uint32_t kWaveWG = 64;
@@ -1094,7 +1092,7 @@ struct ErcCodec {
 };
 
 // The kernel's body is written once for every code of the level indices.  A Codec supplies
-//   kRowWords                        words of a lane's piece that are staged at a time
+//   kRowWords, kFewWords             words of a lane's piece that are staged at a time; where no lane has more than the latter
 //   init(P, lane)                    its tables, into LDS that the kernel handed it
 //   entries(sy, g, P, e_lo, e_hi)    the index entries that bound piece g of a bucket (sy = the bucket's entries)
 //   range(P, g, nbk, e_lo, e_hi, len, R, bad)   piece g's bit range (R.bit_lo, R.bit_hi, from the bucket's first bit) and
@@ -1110,7 +1108,7 @@ struct ErcCodec {
 // stream into a fixed share of the staging area, as they were, a piece of more than eight words was read from global memory
 // record by record, which is what buckets of 256, eight workers' buckets of 512 or 1000 and dense level tables have: decode
 // of 4 x 16.8 M coordinates in buckets of 256 66 -> 44 us at stride 128, 113 -> 66 at 256, of 8 x 16.8 M in buckets of 1000
-// 66 -> 52; QSGDinf through ERC, 8 x 16.8 M, encode + decode 567 -> 436.  13 words: what eight workgroups per CU leave room for.
+// 66 -> 52 (47 with partial tiles in one go); QSGDinf through ERC, 8 x 16.8 M, encode + decode 567 -> 436.  13 words: what eight workgroups per CU leave room for.
 // On gradients (six words per piece) the rows need fewer instructions than the copy did, no lane exchange and no clamped
 // addresses: 8 x 25.6 M in buckets of 8192 39.9 -> 36.4 us, 4 x 195 M in buckets of 512 337 -> 328.
 template <class Codec, int UPDATE, uint32_t TC>
