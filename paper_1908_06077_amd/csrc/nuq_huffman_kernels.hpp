@@ -964,12 +964,13 @@ struct HuffmanWaveCodec {
         }
         return true;
     }
-    // Two loops.  run_zeros, where symbol 0 is the codeword "0" and no codeword is longer than eight bits (what gradients
-    // give up to s = 7): a step is a run of zeros and the symbol that ends it, if it does; counts and index in the form of
-    // the ERC parser (position counting down, level added to the exponent, the add of a step under the next one's table
-    // read; about 30 vector instructions where run_any has 40 and as many scalar ones: encode + decode of 8 x 25.6 M coordinates
-    // at s = 3 264 -> 252 us, of 3 x 16.8 M at s = 5 218 -> 186).  run_any, one symbol per step or a zero run with a codeword
-    // from the canonical tables, for the others.
+    // Two loops.  run_short, where no codeword is longer than eight bits (every code up to s = 7): with kRuns (symbol 0 is the
+    // codeword "0") a step is a run of zeros and the symbol that ends it, if it does, else one symbol, of a bit or more; counts
+    // and index in the form of the ERC parser (position counting down, level added to the exponent, the add of a step under the
+    // next one's table read; with kRuns about 30 vector instructions where run_any has 40 and as many scalar ones).  Encode +
+    // decode of 8 x 25.6 M coordinates at s = 3 264 -> 252 us, of 3 x 16.8 M at s = 5 218 -> 186; without kRuns, s = 7, of 8 x
+    // 25.6 M 807 -> 708, of 3 x 16.8 M in buckets of 4096 352 -> 262, of 4 x 16.8 M in buckets of 512 424 -> 353.  run_any, one
+    // symbol per step or a zero run with a codeword from the canonical tables, for codes with longer words.
     struct Parser {
         const uint8_t *lut8;
         const uint32_t *canon;
@@ -992,13 +993,15 @@ struct HuffmanWaveCodec {
         template <class Words>
         __device__ __forceinline__ void run(const Words &words, int stop)
         {
-            if (zero_run && maxlen <= 8u)
-                run_zeros(words, stop);
-            else
+            if (maxlen > 8u)
                 run_any(words, stop);
+            else if (zero_run)
+                run_short<true>(words, stop);
+            else
+                run_short<false>(words, stop);
         }
-        template <class Words>
-        __device__ __forceinline__ void run_zeros(const Words &words, int stop)
+        template <bool kRuns, class Words>
+        __device__ __forceinline__ void run_short(const Words &words, int stop)
         {
             // zeros of a step: what is left of the piece's bits, and with a codeword and its sign 32 bits at most
             const uint32_t cap = 31u - maxlen;
@@ -1017,23 +1020,28 @@ struct HuffmanWaveCodec {
             };
             while (n > stop) {
                 const uint32_t w = __builtin_amdgcn_alignbit(hi, lo, (uint32_t)n);
-                uint32_t z;                                                        // all ones for an all-zero window
-                asm("v_ffbh_u32 %0, %1" : "=v"(z) : "v"(w));
                 const uint32_t left = (uint32_t)(n - end);                         // bits, >= 1
-                const uint32_t zc = min(min(z, left), cap), w2 = w << zc;
+                uint32_t zc = 0;
+                if constexpr (kRuns) {
+                    uint32_t z;                                                    // all ones for an all-zero window
+                    asm("v_ffbh_u32 %0, %1" : "=v"(z) : "v"(w));
+                    zc = min(min(z, left), cap);
+                }
+                const uint32_t w2 = w << zc;
                 uint32_t e = lut8[w2 >> 24];                                       // 0 for eight bits that start with a 0
                 __builtin_amdgcn_sched_barrier(0);
                 add_value();
                 __builtin_amdgcn_sched_barrier(0);
-                e = left > zc ? e : 0u;
+                if constexpr (kRuns)
+                    e = left > zc ? e : 0u;
                 sym = e & 15u;
                 const uint32_t L = e >> 4;
                 wrong |= e == kNoCodeword;
                 sign = w2 << L;
                 const uint32_t is = i + zc;
                 at = origin + (min(is, last) << TileSink::kUnit);
-                const uint32_t one = sym ? 1u : 0u;
-                i = is + one;
+                const uint32_t one = min(sym, 1u);
+                i = is + (kRuns ? one : 1u);
                 n = n - (int)zc - (int)L - (int)one;
                 const int mn = n >> 5;
                 const bool moved = mn != m;

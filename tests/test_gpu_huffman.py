@@ -370,3 +370,34 @@ def test_fused_coding_with_long_codewords(g, d, n, S, s):
     assert not g.u32(m.words)[words.size:].any()
     if sync.size:
         np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
+
+
+@pytest.mark.parametrize("s,hist", [(7, [2 ** j for j in range(9)]),         # level 0 has the codeword of eight bits
+                                    (7, [3, 2, 9, 4, 4, 3, 2, 1, 1]), (1, [1, 4, 2])])
+@pytest.mark.parametrize("d,n,S", [(8192 * 3 + 5, 8192, 256), (4099, 1000, 512), (3 * 512 + 1, 512, 128)])
+def test_fused_decode_one_symbol_per_step(g, d, n, S, s, hist):
+    """Messages whose code has no one-bit level 0 and no codeword above eight bits: pieces of several rows of words, of one
+    coordinate, and at the end of the message."""
+    nuq = g.nuq
+    K = 3
+    B, nsync, cap = nuq.nuq_num_buckets(d, n), nuq.nuq_huffman_num_sync(n, S), nuq.nuq_huffman_max_words(d, n)
+    lengths = nuq.nuq_huffman_lengths(hist, s)
+    assert lengths[0] > 1 and max(lengths) <= 8
+    vs = [torch.from_numpy(make_vector("edges" if k else "gauss", d, n, np.random.default_rng(d + s + k))).to(g.DEV)
+          for k in range(K)]
+    msgs = [nuq.Message(torch.empty(B, dtype=torch.float32, device=g.DEV), torch.empty(B + 1, dtype=torch.int64, device=g.DEV),
+                        torch.zeros(cap, dtype=torch.int32, device=g.DEV),
+                        torch.zeros(max(1, B * nsync), dtype=torch.int32, device=g.DEV)) for _ in range(K)]
+    ws = torch.empty(nuq.nuq_encode_huffman_batch_workspace_bytes(K, d, n, s), dtype=torch.uint8, device=g.DEV)
+    nuq.nuq_quantize_encode_huffman_batch(vs, n, s, [4, 5, 6], S, lengths, msgs, ws)
+    out = torch.empty(d, dtype=torch.float32, device=g.DEV)
+    nuq.nuq_decode_accumulate_huffman(msgs, d, n, s, S, lengths, 1.0 / K, False, out)
+    assert nuq.nuq_last_error_flags() == 0
+    want, mag = np.zeros(d), np.zeros(d)
+    for v, m, seed in zip(vs, msgs, [4, 5, 6]):
+        norms = m.norms.cpu().numpy()
+        deq = oracle.dequantize(oracle.quantize(v.cpu().numpy(), n, s, seed, norms), n, s, norms).astype(np.float64)
+        want += deq
+        mag += np.abs(deq)
+    scale = float(np.float32(1.0 / K))
+    assert np.all(np.abs(out.cpu().numpy().astype(np.float64) - want * scale) <= 1e-6 * mag * scale + 1e-45)
