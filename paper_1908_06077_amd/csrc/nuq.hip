@@ -782,7 +782,12 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     if (momentum && levels)
         return NUQ_EINVAL;
     if (K == 1 && !levels && !momentum && (nsync || bucket <= 512)) {
-        if (!accumulate && nsync && bucket >= kOneMinBucket) {
+        // Few values (s = 1, or s = 2 in large buckets: at most 2^s sqrt(bucket) of a bucket's coordinates are nonzero on average)
+        // into a result that stays in the 256 MB last-level cache between clearing and scattering go to k_decode_single: s = 1,
+        // 36.7 M coordinates in buckets of 8192 28.3 us (k_decode_one 32.8), of 512 41.1 (53.5), s = 2 in buckets of 16384 30.6
+        // (32.4), of 8192 33.7 (33.6); but 100 M at s = 1 98.9 (78.6).
+        const bool few = (s == 1 || (s == 2 && bucket >= 16384u)) && d >= (1ull << 23) && d < (1ull << 26);
+        if (!accumulate && nsync && bucket >= kOneMinBucket && !few) {
             // One message, written: up to 64 pieces per wave, as many blocks of 2048 coordinates (whole buckets below that)
             // as 16 KB of bytes hold, less three that the first float4 group may begin before the first of them; fewer where
             // that would leave less than a thousand waves (1 M coordinates: 14.3 us with eight blocks each, 8.0 with one).
@@ -814,10 +819,12 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     // Tiles of 4096 coordinates (32 KB of fp64, four workgroups per CU instead of eight) where the usual 2048 would
     // give the 64 parsing lanes at most 32 units: parts of large buckets of few workers.  The parse is bound by
     // instruction issue, so one full wave per SIMD gets through more records than two half-empty ones.
-    // Small buckets: only where they fill the tile and 2048 coordinates have at most 16 units (4 x 16.8 M coordinates in buckets
-    // of 512 at stride 512 84 -> 78 us, two messages at 256 48 -> 44; with 32 units 50 -> 52).
+    // Small buckets: only where they fill the tile, 2048 coordinates have at most 16 units (4 x 16.8 M coordinates in buckets
+    // of 512 at stride 512 84 -> 78 us, two messages at 256 48 -> 44; with 32 units 50 -> 52) and there is a tile for every CU
+    // (0.3 M coordinates, exponential levels at s = 7, both directions 65.8 -> 69.5 with tiles of 4096).
     const bool big = nsync && (bucket >= kTileCoordsBig ? (K << P.pieces_shift) <= 32u
                                                         : kTileCoordsBig % bucket == 0 && kTileCoordsBig / bucket * K <= kMaxStreams &&
+                                                              d >= 256ull * kTileCoordsBig &&
                                                               (kTileCoords / bucket * K << P.pieces_shift) <= 16u);
     const uint32_t tile_coords = big ? kTileCoordsBig : kTileCoords;
     const uint32_t variant = 2u * ((levels ? 3u : 0u) + (momentum ? (uint32_t)kUpdateMomentum
