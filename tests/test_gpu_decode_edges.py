@@ -163,7 +163,8 @@ def test_pieces_of_every_length(g, n, S, K, s, density):
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("n,S,s,d", [(511, 64, 3, 511 * 9 + 1), (512, 64, 3, 512 * 70), (513, 512, 3, 513 * 70 + 2), (1000, 256, 7, 1), (1000, 256, 7, 40_003),
                                      (2047, 1024, 14, 2047 * 40 + 5), (2049, 128, 3, 2049 * 30 + 2048), (4098, 256, 5, 4098 * 9 + 3),
-                                     (8192, 256, 3, 8192 * 700 + 77), (20001, 64, 3, 20001 * 3 + 2049), (32768, 1024, 1, 32768 * 5 + 4)])
+                                     (8192, 256, 3, 8192 * 700 + 77), (20001, 64, 3, 20001 * 3 + 2049), (32768, 1024, 1, 32768 * 5 + 4),
+                                     (8192, 256, 1, 8192 * 1024 - 1), (8192, 256, 1, 8192 * 1024 + 77)])
 def test_one_message(g, n, S, s, d, shift):
     """A single message written out: blocks per workgroup from one to the most that fit, odd bucket sizes (blocks that begin and
     end inside a float4 group), a last bucket that ends inside a block and leaves others empty, an odd output address."""
@@ -185,7 +186,7 @@ def test_one_message(g, n, S, s, d, shift):
 @pytest.mark.parametrize("update", ["write", "add", "momentum"])
 @pytest.mark.parametrize("n,S,K,d", [(1000, 256, 2, 9000), (1000, 256, 2, 8009), (1001, 128, 3, 6006), (512, 512, 4, 512 * 17), (512, 256, 2, 512 * 16 + 259),
                                      (256, 256, 2, 256 * 33 + 2), (2048, 512, 2, 2048 * 5 + 6), (1024, 512, 4, 1024 * 9), (20000, 256, 4, 40_004),
-                                     (4100, 256, 2, 8200)])
+                                     (4100, 256, 2, 8200), (512, 512, 4, 512 * 2050 + 2), (512, 256, 2, 512 * 2052 + 258)])
 def test_tiles_that_are_not_full(g, n, S, K, d, update):
     """Tiles of 2048 and of 4096 coordinates that small buckets do not fill, of few or of no float4 groups, and both tile sizes'
     lines: the result of each way of applying a tile."""
