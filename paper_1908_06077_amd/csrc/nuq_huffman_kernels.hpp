@@ -958,7 +958,8 @@ struct HuffmanWaveCodec {
         R.n = min(nbk - R.c_lo, 1u << sync_shift);
         R.bit_lo = e_lo & kSyncOffMask;
         R.bit_hi = g + 1u < P.nseg ? e_hi & kSyncOffMask : len;
-        if (R.bit_lo > R.bit_hi || R.bit_hi > len) {
+        // (a coordinate costs at least one bit: a piece without bits, as of a message that was never received, is malformed)
+        if (R.bit_lo >= R.bit_hi || R.bit_hi > len) {
             bad = true;
             return false;
         }

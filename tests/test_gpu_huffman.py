@@ -257,6 +257,38 @@ def test_malformed_messages_raise_the_flag(g):
                                [1, 1, 2, 3, 3], q)
 
 
+@pytest.mark.parametrize("cut", ["nothing received", "last bucket"])
+@pytest.mark.parametrize("n,s,S,K", [(1024, 3, 256, 1), (1024, 3, 256, 3), (8192, 3, 256, 2), (512, 7, 128, 2), (20000, 14, 512, 1)])
+def test_pieces_without_bits_raise_the_flag(g, n, s, S, K, cut):
+    """A worker's message whose offsets and index are all zero, and one whose last bucket ends at the word where it begins:
+    coordinates without a bit are malformed, wherever in its word the piece stands, and add nothing."""
+    nuq = g.nuq
+    rng = np.random.default_rng(n + K)
+    d = 3 * n + n // 2 + 1
+    nb = 4
+    qs = [np.where(rng.random(d) < 0.2, rng.integers(1, s + 2, d), 0).astype(np.uint8) for _ in range(K)]
+    lengths = nuq.nuq_huffman_lengths([1 << (s + 1 - j) for j in range(s + 2)], s)
+    dev = lambda a, dt: torch.from_numpy(a.view(dt)).to(g.DEV)
+    norms = torch.ones(nb, dtype=torch.float32, device=g.DEV)
+    msgs, want = [], np.zeros(d)
+    for k, q in enumerate(qs):
+        bo, words, sync = oracle.encode_huffman(q, n, s, lengths, S)
+        value = oracle.dequantize(q, n, s, np.ones(nb, np.float32)).astype(np.float64)
+        if k == K - 1:
+            if cut == "last bucket":
+                bo[-1] = (bo[-2] + np.uint64(31)) & ~np.uint64(31)
+                sync[-(sync.size // nb):] = 0
+                value[(nb - 1) * n:] = 0
+            else:
+                bo[:], sync[:], value[:] = 0, 0, 0
+        msgs.append(nuq.Message(norms, dev(bo, np.int64), dev(words, np.int32), dev(sync, np.int32)))
+        want += value
+    out = torch.full((d,), 7.0, device=g.DEV)
+    nuq.nuq_decode_accumulate_huffman(msgs, d, n, s, S, lengths, 1.0, False, out)
+    assert nuq.nuq_last_error_flags() == nuq.FLAG_MALFORMED
+    np.testing.assert_array_equal(out.cpu().numpy(), want.astype(np.float32))      # multiples of 2^(-1-s): exact
+
+
 def test_config3_worker_at_full_size(g):
     """One worker of config 3 at full size: code from its own histogram, message against the oracle on sampled
     buckets, decode gives the bytes back."""
