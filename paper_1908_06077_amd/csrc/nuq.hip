@@ -178,50 +178,98 @@ Workspace carve(void *base, uint32_t K, uint64_t nb, uint32_t slot_words)
     return w;
 }
 
-// Team shape per bucket size: (threads per bucket, float4 rows per thread).
-//
-// dense: most coordinates are nonzero (s >= 6, or the maximum norm), and coding them outweighs all else.  Then a whole wave
-// per bucket of 513 to 1024 is better: s = 7 in buckets of 1000 135 us, 147 with half a wave.
-//
-// A team's fixed work (norm reduction, scale, key, scans, barriers) costs the encoder as much as a thousand coordinates per
-// wave, so a thread owns 16 coordinates or more: with 64 threads for buckets of 513 to 1024, 256 for up to 4096 and 1024
-// beyond 16384 (and their partial sums, see kNormParts), encode of 4 x 16.8 M coordinates took 86 us in buckets of 1024, 107 of
-// 700, 74 of 4096, 87 of 3000, 113 of 20000; with half of that 77, 85, 61, 70 and 77.  kPack: kernels that store what the
-// quantizer yields and do nothing else.  They are bound by memory and want more waves in flight: 4-bit packing and unpacking
-// in buckets of 4096 68 us with 256 threads, 73 with 128 (but with a level table, which is bound by issue, 108 and 96), in
-// buckets of 20000 78.7 with 1024, 80.5 with 512.
-enum class TeamUse { kCode, kPack, kPackTable };
-template <TeamUse kUse = TeamUse::kCode, class F>
-int dispatch_team(uint32_t bucket, bool dense, F &&f)
+// What a kernel does with what the quantizer yields: codes it (kErc: main scheme, kErcOther: level tables, or bytes that the
+// caller gives; kHuffman), packs codes of a level table, or stores it (kStore; or has no quantizer).
+enum class TeamUse { kErc, kErcOther, kHuffman, kPackTable, kStore };
+
+// Team shape per bucket size: (threads per bucket, float4 rows per thread).  kNarrow: half the threads, twice the rows, where
+// narrow_teams<kUse> may ask for that.  Both form the same partial sums of a norm (kNormParts).  Rows that no bucket of the
+// size has are loaded too (load_rows), hence the shapes of 4, 6 and 12 rows: packing 2 x 24.6 M coordinates at 8 bits in
+// buckets of 10 000 takes 42.2 us with 12 rows, 46.2 with 16.
+template <TeamUse kUse, bool kNarrow, class F>
+int dispatch_team_as(uint32_t bucket, F &&f)
 {
     using std::integral_constant;
+    constexpr bool kNarrow4096 = kNarrow && kUse != TeamUse::kStore, kNarrow32768 = kNarrow4096 && kUse != TeamUse::kPackTable;
     if (bucket <= 256)   // four buckets per wave
         return f(integral_constant<int, 16>{}, integral_constant<int, 4>{});
     if (bucket <= 512)
         return f(integral_constant<int, 16>{}, integral_constant<int, 8>{});
-    if (bucket <= 1024 && dense)
-        return f(integral_constant<int, 64>{}, integral_constant<int, 4>{});
-    if (bucket <= 1024)  // two
-        return f(integral_constant<int, 32>{}, integral_constant<int, 8>{});
+    if (bucket <= 1024) {
+        if constexpr (kNarrow)
+            return f(integral_constant<int, 32>{}, integral_constant<int, 8>{});
+        else
+            return f(integral_constant<int, 64>{}, integral_constant<int, 4>{});
+    }
     if (bucket <= 2048)
         return f(integral_constant<int, 64>{}, integral_constant<int, 8>{});
     if (bucket <= 4096) {
-        if constexpr (kUse == TeamUse::kPack)
-            return f(integral_constant<int, 256>{}, integral_constant<int, 4>{});
-        else
+        if constexpr (kNarrow4096)
             return f(integral_constant<int, 128>{}, integral_constant<int, 8>{});
+        else
+            return f(integral_constant<int, 256>{}, integral_constant<int, 4>{});
     }
     if (bucket <= 8192)
         return f(integral_constant<int, 256>{}, integral_constant<int, 8>{});
+    if (bucket <= 12288)
+        return f(integral_constant<int, 256>{}, integral_constant<int, 12>{});
     if (bucket <= 16384)
         return f(integral_constant<int, 256>{}, integral_constant<int, 16>{});
-    // (rows that no bucket of the size has are loaded too, see load_rows)
-    if constexpr (kUse == TeamUse::kCode)
+    if constexpr (kNarrow32768)
         return bucket <= 24576 ? f(integral_constant<int, 512>{}, integral_constant<int, 12>{})
                                : f(integral_constant<int, 512>{}, integral_constant<int, 16>{});
     else
         return bucket <= 24576 ? f(integral_constant<int, 1024>{}, integral_constant<int, 6>{})
                                : f(integral_constant<int, 1024>{}, integral_constant<int, 8>{});
+}
+
+template <TeamUse kUse, class F>
+int dispatch_team(uint32_t bucket, bool narrow, F &&f)
+{
+    return narrow ? dispatch_team_as<kUse, true>(bucket, f) : dispatch_team_as<kUse, false>(bucket, f);
+}
+
+// Whether nb buckets of each of K workers take the narrow shapes.  A team's fixed work (norm reduction, scale, key, scans,
+// barriers) costs the fused encoders as much as a thousand coordinates per wave, so with half the waves per bucket a full chip
+// gets through more buckets; a chip that is not full waits for a single bucket instead, which then takes longer.  The line is a
+// number of buckets (wide against narrow in turn on the same gradients, some 2500 calls of random sizes):
+//   above 16384: as soon as there are more buckets than CUs (256).  2.1 M coordinates in 258 buckets 21.7 -> 17.5 us, 30 M in
+//     1500 of them 72 -> 48; 0.4 M in 27 buckets at s = 7 26.0 with 1024 threads, 32.0 with 512.  Huffman: from 1024 buckets
+//     up to 24576 coordinates (4.9 M 34.2 -> 30.8; 600 buckets 27 and 30), never above (14 M 58 and 64).
+//   2049 to 4096: from 2048 buckets of sparse levels (3390 buckets 18.3 -> 16.5 us, 1644 of them 14.5 and 15.3), 4096 of dense
+//     ones, 8192 with the maximum norm (4292 buckets, s = 6, 56 and 64); Huffman from 4096 (5118: 23.9 -> 22.8; 2152: 14.8 and
+//     15.1); packing with a level table from 8192 (8808: 31.4 -> 28.4; 6264: 35.7 and 36.9).
+//   513 to 1024: from 5120 buckets (8937 of 600 coordinates 18.6 -> 14.9 us, 5916 14.9 -> 13.0, 4222 of 513 15.4 and 17.4),
+//     where half a wave's rows waste less of a bucket (up to 832 coordinates: 28 % on 131 k buckets of 513) or levels are
+//     sparse (13 k of 1000 22.5 -> 20.4; dense, 95 k of 1024 at s = 5, 9 % slower), but not with many levels from a table or
+//     from bytes (55 k of 600, s = 14, 79 and 87); Huffman of more than 832 from 8192 (11 k of 1000 21.5 -> 20.9; 6.2 k of 1024
+//     6 % slower).  All others, memory-bound: up to 640 coordinates, five rows where a wave loads 768, from 8192 buckets (packing
+//     at 4 or 8 bits 15 % less on 50 k and more), up to 832 from 32768 (56 k of 700 9 % less, 17 k of 800 2 % more).
+// What these shapes cost where the chip is not full: nuq_quantize on 0.2 M coordinates in buckets of 1000 3.8 us with a wave, 6.0
+// with half; nuq_encode on 0.6 M in buckets of 3000 at s = 14 18.3 and 27.9; nuq_encode_huffman on 0.2 M in buckets of 1024 15.8
+// and 20.8.
+// Sparse: with the Euclidean norm a coordinate is norm / sqrt(bucket) on average, and with a first level l1 of three times that
+// or more about a quarter of the coordinates or less are nonzero.
+template <TeamUse kUse>
+bool narrow_teams(uint64_t nb, uint32_t K, uint32_t bucket, uint32_t s, bool linf = false, double l1 = 0.0)
+{
+    const uint64_t teams = nb * K;
+    const bool sparse = !linf && l1 * l1 * bucket >= 9.0;
+    if constexpr (kUse == TeamUse::kErc || kUse == TeamUse::kErcOther) {
+        if (bucket <= 1024u)
+            return teams >= 5120u && (bucket <= 832u || sparse) && (kUse == TeamUse::kErc || s <= 5u);
+        if (bucket <= 4096u)
+            return teams >= (sparse ? 2048u : linf ? 8192u : 4096u);
+        return teams > 256u;
+    } else if constexpr (kUse == TeamUse::kHuffman) {
+        if (bucket <= 1024u)
+            return teams >= (bucket <= 832u ? 5120u : 8192u);
+        return bucket <= 4096u ? teams >= 4096u : bucket <= 24576u && teams >= 1024u;
+    } else {
+        if (bucket <= 1024u)
+            return (bucket <= 640u && teams >= 8192u) || (bucket <= 832u && teams >= 32768u);
+        return kUse == TeamUse::kPackTable && bucket <= 4096u && teams >= 8192u;
+    }
 }
 
 int check_launch()
@@ -251,11 +299,11 @@ int launch_finish_as(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, c
     return check_launch();
 }
 
-int launch_finish(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, const Workspace &w, bool dense, hipStream_t st)
+int launch_finish(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, const Workspace &w, bool narrow, hipStream_t st)
 {
     // buckets per workgroup of the encoder
     uint32_t unit_shift = 0;
-    (void)dispatch_team(P.bucket, dense, [&](auto team_c, auto) {
+    (void)dispatch_team<TeamUse::kErc>(P.bucket, narrow, [&](auto team_c, auto) {
         unit_shift = log2u(TeamGeom<decltype(team_c)::value>::kTeamsPerWG);
         return (int)NUQ_OK;
     });
@@ -337,8 +385,10 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     P.staging = w.staging;
     P.flags = flags;
     P.norm_linf = norm_kind == NUQ_NORM_LINF ? 1u : 0u;
-    const bool dense = P.norm_linf || s >= 6u;
-    int rc = dispatch_team(bucket, dense, [&](auto team_c, auto vpt_c) {
+    constexpr TeamUse kUse = MODE == 0 ? TeamUse::kErc : TeamUse::kErcOther;
+    const double l1 = MODE == 2 ? (double)levels[1] : std::ldexp(1.0, -(int)s);
+    const bool narrow = narrow_teams<kUse>(nb, K, bucket, s, P.norm_linf, l1);
+    int rc = dispatch_team<kUse>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -363,7 +413,7 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     if (rc != NUQ_OK)
         return rc;
 
-    return launch_finish(P, Wk, K, w, dense, st);
+    return launch_finish(P, Wk, K, w, narrow, st);
 }
 
 bool valid_fixed(uint32_t s, uint32_t b)
@@ -409,7 +459,9 @@ int pack_fixed_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t buc
     FixedParams F{};
     F.b = b;
     F.wpb = (bucket * b + 31u) / 32u;
-    return dispatch_team<MODE == 2 ? TeamUse::kPackTable : TeamUse::kPack>(bucket, false, [&](auto team_c, auto vpt_c) {
+    constexpr TeamUse kUse = MODE == 2 ? TeamUse::kPackTable : TeamUse::kStore;
+    const bool narrow = narrow_teams<kUse>(P.nb, K, bucket, s);
+    return dispatch_team<kUse>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -582,7 +634,8 @@ int nuq_bucket_norms(const float *v, uint64_t d, uint32_t bucket, float *norms, 
     P.bucket = bucket;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
+    const bool narrow = narrow_teams<TeamUse::kStore>(P.nb, 1, bucket, 0);
+    return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         dim3 grid;
         if (!bucket_grid<TEAM>(P.nb, 1, grid))
@@ -609,7 +662,8 @@ int nuq_quantize(const float *v, uint64_t d, uint32_t bucket, uint32_t s, uint64
     P.s = s;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
+    const bool narrow = narrow_teams<TeamUse::kStore>(P.nb, 1, bucket, 0);
+    return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
         dim3 grid;
@@ -633,7 +687,8 @@ int nuq_bucket_norms_linf(const float *v, uint64_t d, uint32_t bucket, float *no
     P.bucket = bucket;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
+    const bool narrow = narrow_teams<TeamUse::kStore>(P.nb, 1, bucket, 0);
+    return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         dim3 grid;
         if (!bucket_grid<TEAM>(P.nb, 1, grid))
@@ -664,7 +719,8 @@ int nuq_quantize_table(const float *v, uint64_t d, uint32_t bucket, uint32_t s, 
     P.s = s;
     P.nb = nuq_num_buckets(d, bucket);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
+    const bool narrow = narrow_teams<TeamUse::kStore>(P.nb, 1, bucket, 0);
+    return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
         dim3 grid;
@@ -1207,7 +1263,8 @@ int nuq_encode_huffman(const uint8_t *q, uint64_t d, uint32_t bucket, uint32_t s
     P.units = w.units;
     P.flags = flags;
     const uint64_t nchunks = (nb + kChunk - 1) / kChunk;
-    return dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
+    const bool narrow = narrow_teams<TeamUse::kStore>(P.nb, 1, bucket, 0);
+    return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -1298,7 +1355,8 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
     P.units = w.units;
     P.staging = w.staging;
     P.flags = flags;
-    int rc = dispatch_team(bucket, false, [&](auto team_c, auto vpt_c) {
+    const bool narrow = narrow_teams<TeamUse::kHuffman>(nb, K, bucket, s);
+    int rc = dispatch_team<TeamUse::kHuffman>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
@@ -1320,7 +1378,7 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
     });
     if (rc != NUQ_OK)
         return rc;
-    return launch_finish(P, Wk, K, w, false, st);
+    return launch_finish(P, Wk, K, w, narrow, st);
 }
 
 int nuq_decode_huffman_batch(uint32_t K, const uint64_t *const *bit_off, const uint32_t *const *words,
