@@ -1219,7 +1219,7 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
         fill_table_bins(bins, T, nrm, P.s, tid);
     team_barrier<TEAM>();
     const BucketKey key = bucket_key(W.seed, b);
-    const TableRule R = make_table_rule<TEAM>(bins, P.s);
+    const TableRule R = make_table_rule<TEAM>(bins, P.s, P.s <= (P.norm_linf ? 3u : 7u));
     const bool all_exact = !dead && bins.thr[0] == 0.0f;
     uint32_t redo = 0;                                     // rows to be decided again by the fp64 rule (none if dead)
     const uint32_t x0 = (key.k0 + 4u * tid) * kRngC1;      // row i starts 4 * TEAM * i coordinates further on

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize_table(EncodePa
         fill_table_bins(bins, T, nf, P.s, tid);
     team_barrier<TEAM>();
     const BucketKey key = bucket_key(W.seed, b);
-    const TableRule R = make_table_rule<TEAM>(bins, P.s);
+    const TableRule R = make_table_rule<TEAM>(bins, P.s, P.s <= 7u);
     const bool exact = __any(!dead && bins.thr[0] == 0.0f);
 #pragma unroll 1
     for (uint32_t i = 0; i < P.rows; ++i) {

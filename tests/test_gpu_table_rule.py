@@ -150,3 +150,33 @@ def test_dead_buckets_beside_live_ones(g, n, kind, s):
     q = torch.full((d,), 0x7F, dtype=torch.uint8, device=g.DEV)
     nuq.nuq_quantize_table(vt, n, lev, seed, torch.from_numpy(norms_np).to(g.DEV), q)
     np.testing.assert_array_equal(q.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n", [1000, 2048, 8192])
+@pytest.mark.parametrize("s", [1, 2, 3, 4, 5, 6, 7, 8, 11, 12, 13, 14])
+def test_rows_that_end_at_every_level(g, s, n):
+    """Rows (a wave's 256 coordinates) whose largest coordinate is on, just above or just below each level in turn: both ways of
+    leaving out the levels that no coordinate of a row reaches, in the standalone quantizer and in the pack, either norm."""
+    nuq = g.nuq
+    rng = np.random.default_rng(s + n)
+    d = 5 * n + 3
+    for kind in ("uniform", "exp"):
+        lev = [0.0] + [float(np.float32(j / (s + 1) if kind == "uniform" else 0.4 ** (s + 1 - j))) for j in range(1, s + 2)]
+        table = np.array(lev, dtype=np.float32)
+        top = np.repeat(table[rng.integers(1, s + 2, -(-d // 256))], 256)[:d]
+        v = (top * rng.random(d)).astype(np.float32)
+        v[::256] = np.nextafter(top[::256], np.where(rng.random(v[::256].size) < 0.5, 0, 2).astype(np.float32))
+        v[128::256] = np.where(rng.random(v[128::256].size) < 0.5, top[128::256], v[128::256])
+        v = np.minimum(v, np.float32(1.0)) * rng.choice([-1.0, 1.0], d).astype(np.float32)
+        v[::n] = 1.0
+        vt = torch.from_numpy(v).to(g.DEV)
+        B = nuq.nuq_num_buckets(d, n)
+        norms, q = torch.empty(B, device=g.DEV), torch.empty(d, dtype=torch.uint8, device=g.DEV)
+        for norm in (nuq.NORM_LINF, nuq.NORM_L2):
+            packed = torch.zeros(nuq.nuq_fixed_words(d, n, 8), dtype=torch.int32, device=g.DEV)
+            nuq.nuq_quantize_pack_fixed_table_batch([vt], n, lev, norm, 8, [5], [norms], [packed])
+            want = oracle.quantize_table(v, n, table, 5, norms.cpu().numpy())
+            np.testing.assert_array_equal(g.u32(packed), oracle.pack_fixed(want, n, s, 8))
+            nuq.nuq_quantize_table(vt, n, lev, 5, norms, q)
+            np.testing.assert_array_equal(q.cpu().numpy(), want)
+    assert nuq.nuq_last_error_flags() == 0
