@@ -912,8 +912,9 @@ __global__ __launch_bounds__(kHuffmanDirectWG) void k_huffman_decode_direct(Huff
 // steps as the ERC parse has records.  With any other code a step is one symbol.
 struct HuffmanWaveCodec {
     static constexpr uint32_t kRowWords = 13, kFewWords = 11;      // gradient data: about ten words per piece of 256 coordinates; 13: eight workgroups per CU
-    // LDS, 256 entries: symbol | length << 4 of the codeword the eight bits start with, 0 where that is "0" for symbol 0, else
-    // kNoCodeword: no length, and a symbol that makes the parser move on by a bit
+    // LDS, 256 entries: symbol | length << 4 of the codeword the eight bits start with, 0 where that is "0" for symbol 0,
+    // kNoCodeword where it has nine bits or more (the code is complete, the host has seen to that: every prefix is of some
+    // codeword)
     static constexpr uint32_t kNoCodeword = 0x0fu;
     uint8_t *lut8;
     uint32_t *canon;        // LDS, 64 words: first[16], count[16], offset[16], sorted[16] of the canonical code
@@ -982,7 +983,6 @@ struct HuffmanWaveCodec {
         int n, end;                 // ~(bits from the row's first word + 31)
         uint32_t hi, lo, nx;
         uint32_t i, count, c_lo;    // coordinates done, of how many, the first one's index
-        bool wrong;                 // a prefix that is no codeword, or bits beyond the last coordinate
         template <class Words>
         __device__ __forceinline__ void load(const Words &words)
         {
@@ -1037,7 +1037,6 @@ struct HuffmanWaveCodec {
                     e = left > zc ? e : 0u;
                 sym = e & 15u;
                 const uint32_t L = e >> 4;
-                wrong |= e == kNoCodeword;
                 sign = w2 << L;
                 const uint32_t is = i + zc;
                 at = origin + (min(is, last) << TileSink::kUnit);
@@ -1057,7 +1056,6 @@ struct HuffmanWaveCodec {
         __device__ __forceinline__ void run_any(const Words &words, int stop)
         {
             const uint32_t zcap = zero_run ? 30u - maxlen : 0u;   // zeros + codeword + sign: 31 bits of the window at most
-            const bool long_codes = maxlen > 8u;                  // uniform: most codes have none
             uint32_t p31 = ~(uint32_t)n, q = p31 >> 5;
             const uint32_t stop31 = ~(uint32_t)stop;
             while (i < count && p31 < stop31) {
@@ -1068,7 +1066,7 @@ struct HuffmanWaveCodec {
                 const uint32_t zc = min(min(z, zcap), left);
                 const uint32_t w2 = w << zc;
                 uint32_t entry = lut8[w2 >> 24];
-                if (long_codes && symbol && entry == kNoCodeword) {       // a codeword of nine bits or more, or none
+                if (symbol && entry == kNoCodeword) {              // a codeword of nine bits or more
                     for (uint32_t L = 9; L <= maxlen; ++L) {
                         const uint32_t idx = (w2 >> (32u - L)) - canon[L];
                         if (idx < canon[16u + L]) {
@@ -1079,7 +1077,6 @@ struct HuffmanWaveCodec {
                 }
                 // everything below is straight-line: a step without a symbol adds nothing and moves on by its zeros
                 const uint32_t sym = symbol ? entry & 15u : 0u, L = entry >> 4;
-                wrong |= symbol && entry == kNoCodeword;                          // (and moves on by its one bit)
                 const uint32_t bits = zc + (symbol ? L + (sym ? 1u : 0u) : 0u);
                 const uint32_t at = sink.place(c_lo + i + zc);
                 i += zc + (symbol ? 1u : 0u);
@@ -1098,12 +1095,14 @@ struct HuffmanWaveCodec {
                 }
             }
             n = (int)~p31;
-            if (i >= count && n != end) {
-                wrong = true;
-                n = end;                                          // (all coordinates done: no further row is asked for)
+            // (the compiler would otherwise carry which of the two conditions ended the loop through every step, in scalar masks)
+            asm("" : "+v"(i));
+            if (i >= count && n != end) {                         // bits beyond the last coordinate: no further row is asked for
+                i = count + 1u;
+                n = end;
             }
         }
-        __device__ __forceinline__ void finish(bool &bad) const { bad |= wrong || i != count || n != end; }
+        __device__ __forceinline__ void finish(bool &bad) const { bad |= i != count || n != end; }
     };
     __device__ __forceinline__ Parser parser(float norm, const TileSink &sink) const
     {
@@ -1116,7 +1115,6 @@ struct HuffmanWaveCodec {
         U.i = 0;
         U.count = R.n;
         U.c_lo = R.c_lo;
-        U.wrong = false;
         U.load(words);
     }
 };
