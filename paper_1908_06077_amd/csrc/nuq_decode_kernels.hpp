@@ -115,6 +115,8 @@ __device__ __forceinline__ void apply_full_tile(const DecodeParams &P, double *t
     const double sc = (double)P.scale;
 #pragma unroll
     for (uint32_t r0 = 0; r0 < kFull; r0 += 2u) {
+        if (kPart && r0 == 2u && n4 <= 2u * WG)                       // (tiles of tiny buckets: a few groups in all)
+            break;
         float4 w[2], yv[2];
         double2 a[2], c[2];
 #pragma unroll

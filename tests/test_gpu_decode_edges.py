@@ -212,3 +212,30 @@ def test_tiles_that_are_not_full(g, n, S, K, d, update):
     np.testing.assert_array_equal(w.cpu().numpy()[d:], w0[d:])
     np.testing.assert_array_equal(y.cpu().numpy()[d:], y0[d:])
     assert nuq.nuq_last_error_flags() == 0
+
+
+@pytest.mark.parametrize("update", ["write", "add", "momentum"])
+@pytest.mark.parametrize("n,K,d", [(1, 1, 203), (1, 3, 1000), (1, 16, 67), (3, 5, 2005), (8, 4, 4100), (8, 16, 4104), (33, 8, 9002), (100, 16, 3000)])
+def test_tiles_of_few_groups(g, n, K, d, update):
+    """Tiles of a few coordinates up to a few float4 groups per lane (so many workers, or so small buckets, that a tile's bit
+    strings are its limit): none, one or both halves of the output stage."""
+    nuq = g.nuq
+    rng = np.random.default_rng(n + d)
+    s, S, nb = 3, 64, -(-d // n)
+    qs = [_dense_bytes(rng, d, n, s, 0.5) for _ in range(K)]
+    norms = [np.exp2(rng.uniform(-3, 3, nb)).astype(np.float32) for _ in range(K)]
+    msgs = [_message(g, q, n, s, S, v) for q, v in zip(qs, norms)]
+    r = (0.5 * sum(_value(q, n, s, v) for q, v in zip(qs, norms))).astype(np.float32)
+    w0, y0 = rng.standard_normal((2, d + 8)).astype(np.float32)
+    w, y = torch.from_numpy(w0.copy()).to(g.DEV), torch.from_numpy(y0.copy()).to(g.DEV)
+    if update == "momentum":
+        nuq.nuq_decode_momentum_step(msgs, d, n, s, S, 0.5, 0.25, 0.5, 1.0, w[:d], y[:d])
+        yl = w0[:d].astype(np.float64) - 0.25 * r.astype(np.float64)
+        np.testing.assert_allclose(y.cpu().numpy()[:d], yl, rtol=2.0 ** -23, atol=2.0 ** -30)      # one rounding to fp32
+        np.testing.assert_allclose(w.cpu().numpy()[:d], yl + 0.5 * (yl - y0[:d].astype(np.float64)), rtol=2.0 ** -23, atol=2.0 ** -30)
+    else:
+        nuq.nuq_decode_accumulate(msgs, d, n, s, S, 0.5, update == "add", w[:d])
+        np.testing.assert_array_equal(w.cpu().numpy()[:d], r + w0[:d] if update == "add" else r)
+    np.testing.assert_array_equal(w.cpu().numpy()[d:], w0[d:])
+    np.testing.assert_array_equal(y.cpu().numpy()[d:], y0[d:])
+    assert nuq.nuq_last_error_flags() == 0
