@@ -838,12 +838,17 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     if (momentum && levels)
         return NUQ_EINVAL;
     if (K == 1 && !levels && !momentum && (nsync || bucket <= 512)) {
-        // Few values (s = 1, or s = 2 in large buckets: at most 2^s sqrt(bucket) of a bucket's coordinates are nonzero on average)
-        // into a result that stays in the 256 MB last-level cache between clearing and scattering go to k_decode_single: s = 1,
-        // 36.7 M coordinates in buckets of 8192 28.3 us (k_decode_one 32.8), of 512 41.1 (53.5), s = 2 in buckets of 16384 30.6
-        // (32.4), of 8192 33.7 (33.6); but 100 M at s = 1 98.9 (78.6).
-        const bool few = (s == 1 || (s == 2 && bucket >= 16384u)) && d >= (1ull << 23) && d < (1ull << 26);
-        if (!accumulate && nsync && bucket >= kOneMinBucket && !few) {
+        // k_decode_one costs the parse and the result; k_decode_single clears the result and scatters the values, which costs
+        // little where they are few and the result stays in the 256 MB last-level cache in between.  With fewer than a coordinate
+        // in seven nonzero (0.8 x 2^s / sqrt(bucket) of them are, on average) it is faster from 2 M to 64 M coordinates: 27 M in
+        // buckets of 8192 at s = 3 17 %, 41 M of 10 000 at s = 1 38 %; below that launches weigh more, beyond it memory does (124 M of
+        // 1000 at s = 3 takes 1.6 times as long).  So it is where an index piece has much less than a stride's coordinates (a
+        // bucket just above a block or a power of two of strides: 44 M of 513 at stride 128 53 us and 93), and at stride 64, where
+        // a wave's 64 pieces are a fourth of what its bytes hold, below 4 M (5 % in the mean).
+        const uint32_t filled = nsync ? std::min(sync_stride, bucket) : 0u;
+        const bool one = d >= (1ull << 26) || (10ull * bucket >= 6ull * P.nseg * filled && (sync_stride > 64u || d >= (1ull << 22)) &&
+                                               (d < (1ull << 21) || bucket <= (32ull << (2u * s))));
+        if (!accumulate && nsync && bucket >= kOneMinBucket && one) {
             // One message, written: up to 64 pieces per wave, as many blocks of 2048 coordinates (whole buckets below that)
             // as 16 KB of bytes hold, less three that the first float4 group may begin before the first of them; fewer where
             // that would leave less than a thousand waves (1 M coordinates: 14.3 us with eight blocks each, 8.0 with one).

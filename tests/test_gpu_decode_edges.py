@@ -239,3 +239,28 @@ def test_tiles_of_few_groups(g, n, K, d, update):
     np.testing.assert_array_equal(w.cpu().numpy()[d:], w0[d:])
     np.testing.assert_array_equal(y.cpu().numpy()[d:], y0[d:])
     assert nuq.nuq_last_error_flags() == 0
+
+
+@pytest.mark.parametrize("n,S,s,d", [(8192, 256, 3, (1 << 21) - 1), (8192, 256, 3, 1 << 21), (8192, 256, 4, 1 << 21), (8193, 256, 4, 1 << 21),
+                                     (1000, 256, 2, 3_000_001), (512, 256, 2, 3_000_001), (4096, 64, 5, (1 << 22) - 1),
+                                     (4096, 64, 5, 1 << 22), (513, 128, 7, 1_000_003), (700, 128, 7, 1_000_003), (2049, 256, 7, 1_000_003),
+                                     (3000, 256, 7, 1_000_003), (600, 1024, 7, 1_000_003), (8192, 256, 1, (1 << 26) - 1),
+                                     (8192, 256, 1, 1 << 26), (513, 128, 1, (1 << 26) + 5)])
+def test_one_message_written_and_added(g, n, S, s, d):
+    """Both sides of every line between the two decoders of a single written message: what it writes is what a zero vector holds
+    after the message was added to it, which always takes the scattering decoder."""
+    nuq = g.nuq
+    gen = torch.Generator(device=g.DEV).manual_seed(n + s)
+    q = torch.randint(1, s + 2, (d,), generator=gen, device=g.DEV, dtype=torch.uint8)
+    q |= torch.randint(0, 2, (d,), generator=gen, device=g.DEV, dtype=torch.uint8) << 7
+    q *= torch.rand(d, generator=gen, device=g.DEV) < 0.1
+    nb = -(-d // n)
+    m = nuq.Message(torch.rand(nb, generator=gen, device=g.DEV), torch.empty(nb + 1, dtype=torch.int64, device=g.DEV),
+                    torch.zeros(d // 8 + 2 * nb + 64, dtype=torch.int32, device=g.DEV),
+                    torch.empty(nb * nuq.nuq_num_sync(n, S), dtype=torch.int32, device=g.DEV))
+    nuq.nuq_encode(q, n, s, S, m.bit_off, m.words, m.sync, g.workspace(d, n, s))
+    written, added = torch.full((d,), 7.0, device=g.DEV), torch.zeros(d, device=g.DEV)
+    nuq.nuq_decode_accumulate([m], d, n, s, S, 0.3, False, written)
+    nuq.nuq_decode_accumulate([m], d, n, s, S, 0.3, True, added)
+    assert nuq.nuq_last_error_flags() == 0
+    assert torch.equal(written, added) and int((written != 0).sum()) == int((q != 0).sum())
