@@ -881,12 +881,13 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     // give the 64 parsing lanes at most 32 units: parts of large buckets of few workers.  The parse is bound by
     // instruction issue, so one full wave per SIMD gets through more records than two half-empty ones.
     // Small buckets: only where they fill the tile, 2048 coordinates have at most 16 units (4 x 16.8 M coordinates in buckets
-    // of 512 at stride 512 84 -> 78 us, two messages at 256 48 -> 44; with 32 units 50 -> 52) and there is a tile for every CU
-    // (0.3 M coordinates, exponential levels at s = 7, both directions 65.8 -> 69.5 with tiles of 4096).
-    const bool big = nsync && (bucket >= kTileCoordsBig ? (K << P.pieces_shift) <= 32u
-                                                        : kTileCoordsBig % bucket == 0 && kTileCoordsBig / bucket * K <= kMaxStreams &&
-                                                              d >= 256ull * kTileCoordsBig &&
-                                                              (kTileCoords / bucket * K << P.pieces_shift) <= 16u);
+    // of 512 at stride 512 84 -> 78 us, two messages at 256 48 -> 44; with 32 units 50 -> 52), there is a tile for every CU
+    // (0.3 M coordinates, exponential levels at s = 7, both directions 65.8 -> 69.5 with tiles of 4096) and the result is
+    // written: what the other updates read takes registers for twice the coordinates, which leaves a wave per SIMD (17 M
+    // coordinates of two messages in buckets of 512, momentum 52 -> 67 us; 10 M of one in buckets of 1024 28 -> 34).
+    const bool small_big = kTileCoordsBig % bucket == 0 && kTileCoordsBig / bucket * K <= kMaxStreams && !accumulate && !momentum &&
+                           d >= 256ull * kTileCoordsBig && (kTileCoords / bucket * K << P.pieces_shift) <= 16u;
+    const bool big = nsync && (bucket >= kTileCoordsBig ? (K << P.pieces_shift) <= 32u : small_big);
     const uint32_t tile_coords = big ? kTileCoordsBig : kTileCoords;
     const uint32_t variant = 2u * ((levels ? 3u : 0u) + (momentum ? (uint32_t)kUpdateMomentum
                                                                   : accumulate ? (uint32_t)kUpdateAdd
