@@ -14,10 +14,20 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libnuq.so")
 
+_BUILD = ("run `python -c 'import __graft_entry__ as g; g.build()'` (or `python paper_1908_06077_amd/build.py`) first; "
+          "there is no fallback path")
+
 if not os.path.exists(_LIB_PATH):
-    raise ImportError(
-        "libnuq.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
-        "(or `python paper_1908_06077_amd/build.py`) first; there is no fallback path")
+    raise ImportError("libnuq.so is not built: " + _BUILD)
+
+
+def _check_built(calls_key: int, library_key: int, calls_torch: str, torch_version: str) -> None:
+    """_nuq_calls calls the library by its addresses and reads torch's tensors, so it has to be built for both."""
+    if calls_key != library_key:
+        raise ImportError("_nuq_calls and libnuq.so are built from different versions of nuq.h: " + _BUILD)
+    if calls_torch != torch_version:
+        raise ImportError("_nuq_calls is built for torch %s, this is %s: " % (calls_torch, torch_version) + _BUILD)
+
 
 _lib = ctypes.CDLL(_LIB_PATH)
 
@@ -80,9 +90,12 @@ for _name, (_res, _args) in _SIGNATURES.items():
     _fn.argtypes = _args
 
 
-if not os.path.exists(os.path.join(_HERE, "_nuq_calls.so")):
-    raise ImportError("_nuq_calls.so is not built: see libnuq.so above")
-from . import _nuq_calls as _calls  # noqa: E402
+try:
+    from . import _nuq_calls as _calls  # noqa: E402
+except ImportError as e:
+    raise ImportError("_nuq_calls is not built for this Python and torch (%s): " % e + _BUILD) from e
+_check_built(_calls.header_key, ctypes.c_uint64.in_dll(_lib, "nuq_header_key").value, _calls.torch_version,
+             torch.__version__)
 
 _calls.bind(tuple(ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value for n in _calls.names()),
             torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)

@@ -586,6 +586,13 @@ uint32_t decode_resident_workgroups(uint32_t variant, bool wave)
 
 extern "C" {
 
+// Which nuq.h this library is built from (see build.py); 0: not said.
+#ifndef NUQ_HEADER_KEY
+#define NUQ_HEADER_KEY 0ull
+#endif
+extern const uint64_t nuq_header_key;
+const uint64_t nuq_header_key = NUQ_HEADER_KEY;
+
 uint64_t nuq_num_buckets(uint64_t d, uint32_t bucket)
 {
     return bucket ? (d + bucket - 1) / bucket : 0;

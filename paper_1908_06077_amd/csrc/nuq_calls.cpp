@@ -455,5 +455,9 @@ PyMODINIT_FUNC PyInit__nuq_calls()
     g_sync = PyUnicode_InternFromString("sync");
     if (!g_norms || !g_bit_off || !g_words || !g_sync)
         return nullptr;
-    return PyModule_Create(&g_module);
+    PyObject *m = PyModule_Create(&g_module);
+    if (m && (PyModule_AddObject(m, "header_key", PyLong_FromUnsignedLongLong(NUQ_HEADER_KEY)) ||      // see build.py
+              PyModule_AddStringConstant(m, "torch_version", NUQ_TORCH_VERSION)))
+        Py_CLEAR(m);
+    return m;
 }

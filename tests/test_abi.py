@@ -197,3 +197,25 @@ def test_huffman_lengths_on_the_host(nuq):
                 2 ** rng.integers(0, 45, size=s + 2), np.zeros(s + 2, dtype=np.int64)][t % 4]
         assert nuq.nuq_huffman_lengths([int(x) for x in hist], s) == \
             [int(x) for x in oracle.huffman_lengths(np.asarray(hist, dtype=np.uint64), s)]
+
+
+def test_files_built_apart_are_refused(nuq):
+    from paper_1908_06077_amd import binding
+    binding._check_built(5, 5, "2.10.0", "2.10.0")
+    with pytest.raises(ImportError, match="nuq.h"):
+        binding._check_built(5, 6, "2.10.0", "2.10.0")
+    with pytest.raises(ImportError, match="torch"):
+        binding._check_built(5, 5, "2.9.0", "2.10.0")
+
+
+def test_build_without_a_compiler_starts_nothing(nuq, monkeypatch, tmp_path):
+    from paper_1908_06077_amd import build
+    started = tmp_path / "started"
+    hipcc = tmp_path / "hipcc"
+    hipcc.write_text("#!/bin/sh\ntouch %s\n" % started)
+    hipcc.chmod(0o755)
+    monkeypatch.setenv("HIPCC", str(hipcc))
+    monkeypatch.setenv("CXX", str(tmp_path / "none"))
+    with pytest.raises(RuntimeError, match="g\\+\\+"):
+        build.build()
+    assert not started.exists()
