@@ -272,6 +272,13 @@ bool narrow_teams(uint64_t nb, uint32_t K, uint32_t bucket, uint32_t s, bool lin
     }
 }
 
+// float4 rows of a bucket per thread.  Their TEAM words each are where team_norm's partial sums go before the bytes do.
+template <int TEAM>
+uint32_t team_rows(uint32_t bucket)
+{
+    return std::max<uint32_t>(TEAM > kWave ? kNormParts<TEAM> : 1, (bucket + 4 * TEAM - 1) / (4 * TEAM));
+}
+
 int check_launch()
 {
     return hipGetLastError() == hipSuccess ? NUQ_OK : NUQ_EHIP;
@@ -391,7 +398,7 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     int rc = dispatch_team<kUse>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
-        P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
+        P.rows = team_rows<TEAM>(bucket);
         P.rec_cap = team_rec_cap(bucket);
         P.out_cap = team_out_cap(slot_words);
         const TeamLdsMap map = team_lds_map(P.rows, TEAM, P.rec_cap, P.out_cap, nsync, P.nblk);
@@ -464,7 +471,7 @@ int pack_fixed_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t buc
     return dispatch_team<kUse>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
-        P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
+        P.rows = team_rows<TEAM>(bucket);
         if (b == 4 || b == 8) {             // codes go from registers to memory
             dim3 grid;
             if (!bucket_grid<TEAM>(P.nb, K, grid))
@@ -672,7 +679,7 @@ int nuq_quantize(const float *v, uint64_t d, uint32_t bucket, uint32_t s, uint64
     const bool narrow = narrow_teams<TeamUse::kStore>(P.nb, 1, bucket, 0);
     return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
-        P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
+        P.rows = team_rows<TEAM>(bucket);
         dim3 grid;
         if (!bucket_grid<TEAM>(P.nb, 1, grid))
             return (int)NUQ_EINVAL;
@@ -729,7 +736,7 @@ int nuq_quantize_table(const float *v, uint64_t d, uint32_t bucket, uint32_t s, 
     const bool narrow = narrow_teams<TeamUse::kStore>(P.nb, 1, bucket, 0);
     return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
-        P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
+        P.rows = team_rows<TEAM>(bucket);
         dim3 grid;
         if (!bucket_grid<TEAM>(P.nb, 1, grid))
             return (int)NUQ_EINVAL;
@@ -1280,7 +1287,7 @@ int nuq_encode_huffman(const uint8_t *q, uint64_t d, uint32_t bucket, uint32_t s
     return dispatch_team<TeamUse::kStore>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
-        P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
+        P.rows = team_rows<TEAM>(bucket);
         P.lds_words = huffman_lds_words(P.rows, TEAM, bucket, nsync);
         const size_t lds_bytes = (size_t)P.lds_words * 4 * G::kTeamsPerWG;
         if (lds_bytes > 160 * 1024)
@@ -1372,7 +1379,7 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
     int rc = dispatch_team<TeamUse::kHuffman>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
-        P.rows = (bucket + 4 * TEAM - 1) / (4 * TEAM);
+        P.rows = team_rows<TEAM>(bucket);
         P.lds_words = ((P.rows * TEAM + P.out_cap + nsync + 3u) & ~3u) + 64u;       // 16-byte aligned teams and fields
         const size_t lds_bytes = (size_t)P.lds_words * 4 * G::kTeamsPerWG;
         if (lds_bytes > 160 * 1024)

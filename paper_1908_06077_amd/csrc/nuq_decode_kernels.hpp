@@ -1469,9 +1469,9 @@ __global__ __launch_bounds__(kSingleWG) void k_decode_single(DecodeParams P)
 // The write mode for buckets of 512 coordinates or more.  A wave takes up to 64 pieces, 8 blocks of 2048 coordinates (or as
 // many whole small buckets), as bytes in 16 KB of LDS: the parser stores a record's level and sign, and the blocks are then
 // written out in order, each byte looked up in a table of its bucket's 32 values, fp32(scale * value).  Every line of the
-// result is written once.  Against clearing it first and scattering into it (k_decode_single, which smaller buckets and the
-// add keep): 200 M coordinates in buckets of 8192 260 -> 153 us, of 512 374 -> 261; 16.8 M at s = 7 in buckets of 4096 123 ->
-// 55; 1 M 11.1 -> 8.0.
+// result is written once.  Against clearing it first and scattering into it (k_decode_single, which smaller buckets, the add
+// and, by the rule in decode_accumulate_any, sparse messages keep): 200 M coordinates in buckets of 8192 260 -> 153 us, of 512
+// 374 -> 261; 16.8 M at s = 7 in buckets of 4096 123 -> 55; 1 M 11.1 -> 8.0.
 constexpr uint32_t kOneCoords = 16384;
 constexpr uint32_t kOneMinBucket = 512;
 

@@ -1095,8 +1095,8 @@ __host__ __device__ inline TeamLdsMap team_lds_map(uint32_t rows, uint32_t team,
 
 // Front of the fused kernels: the bucket's coordinates into registers (v is read once), its norm (written to
 // norms_out), the quantizer; put(i, word) takes the bytes (format F) of the thread's row i < P.rows (coordinates
-// 4 * (i * TEAM + tid) .. + 3), rows in ascending order; issued() is called once the loads are under way.  lds: TEAM words
-// per team that put may be the next to write.
+// 4 * (i * TEAM + tid) .. + 3), rows in ascending order; issued() is called once the loads are under way.  lds:
+// kNormParts x TEAM words per team (teams of several waves) that put may be the next to write.
 template <int TEAM, int VPT, class F, class Put, class Issued>
 __device__ __forceinline__ void front_quantize(const EncodeParams &P, const EncodeWorker &W, uint64_t b, bool active,
                                                uint64_t base, uint32_t nbk, uint32_t tid, uint32_t *lds,
@@ -1264,7 +1264,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
     extern __shared__ __align__(16) uint32_t smem[];
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
-    const uint32_t team = team_uniform_u32<TEAM>(threadIdx.x / TEAM);   // a scalar unless a wave holds four teams
+    const uint32_t team = team_uniform_u32<TEAM>(threadIdx.x / TEAM);   // a scalar unless a wave holds several teams
     const TeamLdsMap map = team_lds_map(P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk);
     uint32_t *const lds = smem + team * map.words;
     uint32_t *const tables = smem + TeamGeom<TEAM>::kTeamsPerWG * map.words;
@@ -1300,7 +1300,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
 // workgroup owns FB consecutive buckets of one worker, sums the words before them, writes their offsets and copies their
 // staging slots to their place in `words`.
 //
-// The encoder leaves len_b in bit_off[b+1] and, per workgroup of its own (1, 4 or 16 buckets: a unit), the words of its
+// The encoder leaves len_b in bit_off[b+1] and, per workgroup of its own (1, 4, 8 or 16 buckets: a unit), the words of its
 // buckets in `units`: the words before a group are a sum over units, taken directly or, for more than 8192 units, from
 // per-chunk prefix sums.
 
