@@ -102,6 +102,24 @@ struct OldValues {
     }
 };
 
+// One float4 group of the output: v applied to the old values w and yv.
+template <int UPDATE>
+__device__ __forceinline__ void put_group(const DecodeParams &P, float4 *o, float4 *y, const float4 &v, float4 w, float4 yv)
+{
+    if constexpr (UPDATE == kUpdateWrite) {
+        store_once4(o, v);                                          // written once, not read here again
+    } else if constexpr (UPDATE == kUpdateAdd) {
+        *o = float4{v.x + w.x, v.y + w.y, v.z + w.z, v.w + w.w};
+    } else {
+        momentum_one(w.x, yv.x, v.x, P.alpha, P.la, P.mu);
+        momentum_one(w.y, yv.y, v.y, P.alpha, P.la, P.mu);
+        momentum_one(w.z, yv.z, v.z, P.alpha, P.la, P.mu);
+        momentum_one(w.w, yv.w, v.w, P.alpha, P.la, P.mu);
+        *o = w;
+        *y = yv;
+    }
+}
+
 // A full tile's output.  kHave: `old` holds what request() loads; else it is loaded here, two groups at a time, with the
 // loads issued before the LDS reads so that their latencies overlap.
 // kPart: a tile of n4 < TC / 4 groups (1 or more); the others' loads are of the last one, their stores left out.  (As a loop
@@ -117,7 +135,7 @@ __device__ __forceinline__ void apply_full_tile(const DecodeParams &P, double *t
     for (uint32_t r0 = 0; r0 < kFull; r0 += 2u) {
         if (kPart && r0 == 2u && n4 <= 2u * WG)                       // (tiles of tiny buckets: a few groups in all)
             break;
-        float4 w[2], yv[2];
+        float4 w[2] = {}, yv[2] = {};                                 // (a written tile has none)
         double2 a[2], c[2];
 #pragma unroll
         for (uint32_t r = 0; r < 2u; ++r) {
@@ -143,18 +161,7 @@ __device__ __forceinline__ void apply_full_tile(const DecodeParams &P, double *t
             const float4 v{(float)(sc * a[r].x), (float)(sc * a[r].y), (float)(sc * c[r].x), (float)(sc * c[r].y)};
             if (kPart && i >= n4)
                 continue;
-            if constexpr (UPDATE == kUpdateWrite) {
-                store_once4(reinterpret_cast<float4 *>(o) + i, v);     // written once, not read here again
-            } else if constexpr (UPDATE == kUpdateAdd) {
-                reinterpret_cast<float4 *>(o)[i] = float4{v.x + w[r].x, v.y + w[r].y, v.z + w[r].z, v.w + w[r].w};
-            } else {
-                momentum_one(w[r].x, yv[r].x, v.x, P.alpha, P.la, P.mu);
-                momentum_one(w[r].y, yv[r].y, v.y, P.alpha, P.la, P.mu);
-                momentum_one(w[r].z, yv[r].z, v.z, P.alpha, P.la, P.mu);
-                momentum_one(w[r].w, yv[r].w, v.w, P.alpha, P.la, P.mu);
-                reinterpret_cast<float4 *>(o)[i] = w[r];
-                reinterpret_cast<float4 *>(y)[i] = yv[r];
-            }
+            put_group<UPDATE>(P, reinterpret_cast<float4 *>(o) + i, reinterpret_cast<float4 *>(y) + i, v, w[r], yv[r]);
         }
     }
 }
@@ -178,14 +185,28 @@ __device__ __forceinline__ void tile_output(const DecodeParams &P, double *tile,
                                             const OldValues<UPDATE, TC, WG> *old = nullptr)
 {
     float *o = P.out + c_lo, *y = update_yl<UPDATE>(P, c_lo);
+    const double sc = (double)P.scale;
     const uint32_t n4 = tile_groups<UPDATE>(P, c_lo, span);
     if (n4 == TC / 4u) {
         apply_full_tile<UPDATE, TC, WG, kHave>(P, tile, o, y, tid, old);
+    } else if constexpr (UPDATE == kUpdateMomentum && WG > (uint32_t)kWave) {
+        // The two-wave kernel spills with a second instance of the above (52 bytes instead of 44), which costs its full tiles
+        // more than parts gain: momentum step on 8.9 M coordinates of six messages in buckets of 8192 at stride 128 38.8 -> 36.7
+        // us, on 13.8 M in buckets of 1000 56.3 -> 54.2.  (Adding and writing gain 5 to 6 % on such parts and lose 1 elsewhere.)
+        for (uint32_t i = tid; i < n4; i += WG) {
+            double2 *src = reinterpret_cast<double2 *>(tile) + 2u * i;
+            const double2 a = src[0], c = src[1];
+            src[0] = double2{0.0, 0.0};
+            src[1] = double2{0.0, 0.0};
+            const float4 v{(float)(sc * a.x), (float)(sc * a.y), (float)(sc * c.x), (float)(sc * c.y)};
+            float4 *dst = reinterpret_cast<float4 *>(o) + i, *ydst = reinterpret_cast<float4 *>(y) + i;
+            put_group<UPDATE>(P, dst, ydst, v, *dst, *ydst);
+        }
     } else if (n4) {
         apply_full_tile<UPDATE, TC, WG, false, true>(P, tile, o, y, tid, nullptr, n4);
     }
     for (uint32_t i = (n4 << 2) + tid; i < span; i += WG) {      // (n4 = 0 without 16-byte alignment)
-        const float r = (float)((double)P.scale * tile[i]);
+        const float r = (float)(sc * tile[i]);
         tile[i] = 0.0;
         if constexpr (UPDATE == kUpdateMomentum)
             momentum_one(o[i], y[i], r, P.alpha, P.la, P.mu);
