@@ -960,6 +960,20 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
     // ntiles mod grid of them get one tile more than the rest: those are the workgroups that arrive first on their
     // CUs, whose parsing waves are the oldest on their SIMDs and run faster than the later ones.
     const uint32_t grid = P.ntiles < resident ? P.ntiles : resident;
+    // Pieces of more words than a row of decode_wave, one lane each: row after row, the wave waits at the end of each for the
+    // lane with most records, and pays a round trip; from global memory it does not, as long as the pieces of the waves on a CU
+    // (256 of them) stay in its cache of 32 KB, of which 24 are counted on.  With 64 words and more to a piece a line per lane
+    // is what counts, hence no bound on the piece then.  Rows and global memory in turn, written: 4 x 2.7 M coordinates in buckets
+    // of 8192 at s = 5, stride 256 (13 words) 16.3 and 15.0 us, 4 x 7.6 M at s = 6 (19) 39.1 and 37.3, 5 x 0.2 M at s = 10, stride
+    // 512 (103 words, a wave per CU) 58.1 and 54.9; beyond the bound 4 x 14.7 M in buckets of 4096 at s = 7 (30) 103 and 111, 8 x
+    // 12.3 M at s = 10 (105) 177 and 301.  Where several lanes load a piece's longer row, and in small buckets, rows are faster
+    // throughout (4 x 0.4 M at s = 7, stride 512 51.4 and 53.3; 7 x 0.8 M in buckets of 256 16.9 and 18.0).
+    if (wave && !P.parts_shift && bucket > 512u) {
+        constexpr uint32_t kDirectWords = 24u * 1024u / 4u;
+        P.direct_words = kDirectWords / (max_streams * P.segs_per_tile * ((grid + 255u) / 256u));
+        if (P.direct_words >= 64u)
+            P.direct_words = ~0u;
+    }
     ScopedTiming timing(NUQ_T_DECODE, static_cast<hipStream_t>(stream));
     if (levels)
         for (uint32_t j = 0; j < s + 2u; ++j)

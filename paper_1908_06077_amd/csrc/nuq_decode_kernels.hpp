@@ -60,6 +60,7 @@ struct DecodeParams {
     uint32_t stream_cap;        // words the lanes of a stream carry = kWordsPerLane << lanes_shift
     uint32_t stream_stride;     // LDS words per stream: stream_cap, or stream_cap - 1 (odd) for tiles of many streams
     uint32_t parts_shift;       // one-wave decoder: log2 of the lanes that load a piece's words
+    uint32_t direct_words;      // k_decode_wave: pieces longer than a row and of so many words at most are read from global memory
     float scale;
     float *yl;                  // kUpdateMomentum: y^l of the previous step, replaced by this step's
     double alpha, la, mu;       // kUpdateMomentum: step size, l * step size, momentum parameter
@@ -1056,6 +1057,7 @@ struct WaveMeta {           // what a lane loads for its stream (bucket, worker)
 // The paper's ENCODE (App. A): records ERC(gap) | sign | ERC(level index), pieces of equal record count.
 template <bool kTable>
 struct ErcCodec {
+    static constexpr bool kDirect = true;
     static constexpr uint32_t kRowWords = 13, kFewWords = 8;
     uint16_t *lut;          // LDS: 128 entries (gap_table_entry)
     uint8_t *lut_level;     // LDS: 128 entries (level_table_entry)
@@ -1107,7 +1109,8 @@ struct ErcCodec {
     {
         return Parser{lut, lut_level, lev, sink, (double)norm * (kTable ? 1.0 : ldexp(1.0, -1 - (int)s))};
     }
-    __device__ __forceinline__ void start(Parser &U, const StagedWords &words, const Range &R) const
+    template <class Words>
+    __device__ __forceinline__ void start(Parser &U, const Words &words, const Range &R) const
     {
         U.start(words, R.bit_lo & 31u, R.bit_hi - (R.bit_lo & ~31u), (int)R.forced, R.idx_hi);
     }
@@ -1115,6 +1118,7 @@ struct ErcCodec {
 };
 
 // The kernel's body is written once for every code of the level indices.  A Codec supplies
+//   kDirect                          pieces of more words than a row may be read from global memory instead (P.direct_words)
 //   kRowWords, kFewWords             words of a lane's piece that are staged at a time; where no lane has more than the latter
 //   init(P, lane)                    its tables, into LDS that the kernel handed it
 //   entries(sy, g, P, e_lo, e_hi)    the index entries that bound piece g of a bucket (sy = the bucket's entries)
@@ -1127,7 +1131,9 @@ struct ErcCodec {
 // Words reach the parser through LDS, a row per lane: kRowWords words of the lane's piece at a time.  The first row of the
 // next tile's pieces is in flight while a tile is parsed; a piece with more words than a row (dense gradients, level tables
 // that leave most coordinates nonzero) gets the next row, also requested while the one before is parsed, until no lane of
-// the wave has words left.  A record may straddle two rows: a row's last word is the next one's first.  Copied stream by
+// the wave has words left.  A record may straddle two rows: a row's last word is the next one's first.  The lanes wait for
+// one another at the end of every row, so where the lines that all pieces in flight on a CU stand in fit its cache, pieces
+// longer than a row are read from there record by record instead (direct_words).  Copied stream by
 // stream into a fixed share of the staging area, as they were, a piece of more than eight words was read from global memory
 // record by record, which is what buckets of 256, eight workers' buckets of 512 or 1000 and dense level tables have: decode
 // of 4 x 16.8 M coordinates in buckets of 256 66 -> 44 us at stride 128, 113 -> 66 at 256, of 8 x 16.8 M in buckets of 1000
@@ -1138,6 +1144,7 @@ template <class Codec, int UPDATE, uint32_t TC>
 __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &codec)
 {
     constexpr uint32_t kRowWords = Codec::kRowWords, kFewWords = Codec::kFewWords;
+    constexpr bool kDirect = Codec::kDirect && UPDATE != kUpdateMomentum;      // (that kernel has no register left for it)
     __shared__ __align__(16) double tile[TC];
     // rows of kRowWords words per lane that loads for a piece, one more (odd: they then start in different banks) where that
     // is even; the parser may read one word before a row and three behind it
@@ -1300,6 +1307,17 @@ __device__ __forceinline__ void decode_wave(const DecodeParams &P, const Codec &
                     parser.run(words, parser.end);
                     parser.finish(bad);
                 }
+            } else if (kDirect && __popcll(__ballot(U0.words > P.direct_words)) <= kWave / 2) {
+                // (see direct_words; half of the pieces or more have no more words than that, so on average all of them)
+                if constexpr (kDirect) {
+                    if (work) {
+                        const GlobalWords direct{(const uint32_t *)U0.src, U0.words - 1u};
+                        codec.start(parser, direct, U0.R);
+                        parser.run(direct, parser.end);
+                        parser.finish(bad);
+                    }
+                }
+                __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0), as below
             } else {
                 // a record needs its position's word and the next one: the last position that a row serves
                 const uint32_t step = row_words - 1u;                 // words by which a row moves on

@@ -911,6 +911,7 @@ __global__ __launch_bounds__(kHuffmanDirectWG) void k_huffman_decode_direct(Huff
 // zero bits, followed by one nonzero symbol when its codeword and sign still fit the 32-bit window: about as many
 // steps as the ERC parse has records.  With any other code a step is one symbol.
 struct HuffmanWaveCodec {
+    static constexpr bool kDirect = false;
     static constexpr uint32_t kRowWords = 13, kFewWords = 11;      // gradient data: about ten words per piece of 256 coordinates; 13: eight workgroups per CU
     // LDS, 256 entries: symbol | length << 4 of the codeword the eight bits start with, 0 where that is "0" for symbol 0,
     // kNoCodeword where it has nine bits or more (the code is complete, the host has seen to that: every prefix is of some

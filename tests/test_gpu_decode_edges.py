@@ -264,3 +264,34 @@ def test_one_message_written_and_added(g, n, S, s, d):
     nuq.nuq_decode_accumulate([m], d, n, s, S, 0.3, True, added)
     assert nuq.nuq_last_error_flags() == 0
     assert torch.equal(written, added) and int((written != 0).sum()) == int((q != 0).sum())
+
+
+@pytest.mark.parametrize("n,S,K,s,d", [(512, 128, 4, 7, 512 * 7300 + 100), (8192, 256, 8, 10, 8192 * 280 + 5), (1000, 256, 6, 10, 1000 * 1400),
+                                       (4096, 256, 4, 14, 4096 * 1200), (2048, 128, 4, 10, 2048 * 1900)])
+@pytest.mark.parametrize("update", [False, True])
+def test_pieces_row_by_row_and_from_global_memory(g, n, S, K, s, d, update):
+    """Pieces longer than a row on a full chip (row by row) and bucket range by bucket range (a wave per CU: from global memory)."""
+    nuq = g.nuq
+    gen = torch.Generator(device=g.DEV).manual_seed(d)
+    B, nsync = nuq.nuq_num_buckets(d, n), nuq.nuq_num_sync(n, S)
+    ws = torch.empty(nuq.nuq_encode_workspace_bytes(1, d, n, s), dtype=torch.uint8, device=g.DEV)
+    msgs = []
+    for k in range(K):
+        v = torch.randn(d, generator=gen, device=g.DEV) * torch.rand(d, generator=gen, device=g.DEV) ** 4
+        m = nuq.Message(torch.empty(B, device=g.DEV), torch.empty(B + 1, dtype=torch.int64, device=g.DEV),
+                        torch.empty(nuq.nuq_max_words(d, n, s), dtype=torch.int32, device=g.DEV),
+                        torch.empty(B * nsync, dtype=torch.int32, device=g.DEV))
+        nuq.nuq_quantize_encode(v, n, s, k, S, m.norms, m.bit_off, m.words, m.sync, ws)
+        msgs.append(m)
+    assert float(msgs[0].bit_off[-1]) / 32 / (B * nsync) > 13              # words per piece
+    prior = torch.randn(d, generator=gen, device=g.DEV)
+    out, parts = prior.clone(), prior.clone()
+    nuq.nuq_decode_accumulate(msgs, d, n, s, S, 1.0 / K, update, out)
+    step = max(1, 200 * 2048 // n)
+    for b in range(0, B, step):
+        e = min(B, b + step)
+        some = [nuq.Message(m.norms[b:e], m.bit_off[b:e + 1], m.words, m.sync[b * nsync:e * nsync]) for m in msgs]
+        lo, hi = b * n, min(d, e * n)
+        nuq.nuq_decode_accumulate(some, hi - lo, n, s, S, 1.0 / K, update, parts[lo:hi])
+    assert torch.equal(out, parts)
+    assert nuq.nuq_last_error_flags() == 0
