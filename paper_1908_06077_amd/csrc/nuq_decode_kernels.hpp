@@ -1057,7 +1057,7 @@ struct WaveMeta {           // what a lane loads for its stream (bucket, worker)
 // The paper's ENCODE (App. A): records ERC(gap) | sign | ERC(level index), pieces of equal record count.
 template <bool kTable>
 struct ErcCodec {
-    static constexpr bool kDirect = true;
+    static constexpr bool kDirect = !kTable;
     static constexpr uint32_t kRowWords = 13, kFewWords = 8;
     uint16_t *lut;          // LDS: 128 entries (gap_table_entry)
     uint8_t *lut_level;     // LDS: 128 entries (level_table_entry)
