@@ -94,7 +94,7 @@ def main():
              and args.update == "none" and not args.graph and not args.per_worker_calls)
     if plain and not args.no_per_config:
         # the other four workloads of the benchmark spec in the same process (fewer steps, a smaller oracle sample), and
-        # what a launch costs at the least: the floor under the small one-worker workloads
+        # what a call that launches a kernel costs at the least
         result["launch_floor_ms"] = launch_floor(torch)
         result["per_config"] = {}
         for cfg in (1, 2, 3, 4, 5):
@@ -110,17 +110,17 @@ def main():
 
 
 def launch_floor(torch):
-    """Milliseconds per launch of the library's smallest kernel (norm of one coordinate), 200 back to back."""
+    """Milliseconds per call of the smallest one that launches a kernel (moments of one coordinate), 200 back to back."""
     import paper_1908_06077_amd as nuq
     dev = torch.device("cuda:0")
     v = torch.ones(1, dtype=torch.float32, device=dev)
-    out = torch.empty(1, dtype=torch.float32, device=dev)
+    sums = [torch.zeros(1, dtype=torch.float64, device=dev) for _ in range(2)]
     for _ in range(10):
-        nuq.nuq_bucket_norms(v, 1, out)
+        nuq.nuq_moments_accumulate(v, *sums)
     a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     a.record()
     for _ in range(200):
-        nuq.nuq_bucket_norms(v, 1, out)
+        nuq.nuq_moments_accumulate(v, *sums)
     b.record()
     torch.cuda.synchronize()
     return round(a.elapsed_time(b) / 200, 5)

@@ -864,8 +864,10 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
                                                (d < (1ull << 21) || bucket <= (32ull << (2u * s))));
         if (!accumulate && nsync && bucket >= kOneMinBucket && one) {
             // One message, written: up to 64 pieces per wave, as many blocks of 2048 coordinates (whole buckets below that)
-            // as 16 KB of bytes hold, less three that the first float4 group may begin before the first of them; fewer where
-            // that would leave less than a thousand waves (1 M coordinates: 14.3 us with eight blocks each, 8.0 with one).
+            // as 16 KB of bytes hold, less three that the first float4 group may begin before the first of them; no more than one
+            // and another for every 1024 blocks that there are, which leaves 512 waves or more to a message of that many (1 M
+            // coordinates: 14.3 us with eight blocks each, 8.0 with one).  One for every whole 1024, hence 1024 waves, is slower
+            // where pieces are long: 1 M at s = 7 in buckets of 512 49.0 and 72.5 us, 3.8 M at s = 5 in 4096 16.8 and 30.3.
             constexpr uint64_t kOneWaves = 1024;
             const uint32_t span = std::min(bucket, 1u << kSyncBlockShift);
             const uint64_t nblocks = P.nb * (P.nseg >> P.pieces_shift);
