@@ -272,6 +272,16 @@ bool narrow_teams(uint64_t nb, uint32_t K, uint32_t bucket, uint32_t s, bool lin
     }
 }
 
+// Whether teams of less than a wave load gradients in buckets above 256 non-temporally.  Four workers, buckets of 512, 12 M
+// coordinates 55.1 -> 51.4 us to encode and 117 -> 107 a step with momentum, whose parameters and strings stay in the last-level
+// cache; packing them at 4 bits 61 -> 57; 20 M in buckets of 1024 a step 169 -> 157;
+// 60 M 231 -> 228, 40 M in a step 303 -> 279; 400 M 1506 and 1506.  From about 2 G coordinates in all it costs: 2 x 1.56 G 2913
+// and 3025 us, 4 x 0.8 G 3040 and 3098.  (Buckets of 256: 4 x 5 M 32.9 and 33.8; 4 x 20 M, a step 207 and 213.)
+uint32_t stream_loads(uint64_t d, uint32_t K)
+{
+    return d <= (1ull << 31) / K ? 1u : 0u;
+}
+
 // float4 rows of a bucket per thread.  Their TEAM words each are where team_norm's partial sums go before the bytes do.
 template <int TEAM>
 uint32_t team_rows(uint32_t bucket)
@@ -301,8 +311,11 @@ int launch_finish_as(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, c
                      uint32_t groups, uint32_t unit_shift, hipStream_t st)
 {
     const uint64_t span = (uint64_t)FB * groups;
-    hipLaunchKernelGGL((k_finish<FB, WG>), dim3((uint32_t)((P.nb + span - 1) / span), K), dim3(WG), 0, st, P, Wk, prefix,
-                       nchunks, groups, unit_shift);
+    const dim3 grid((uint32_t)((P.nb + span - 1) / span), K);
+    if (unit_shift)
+        hipLaunchKernelGGL((k_finish<FB, WG, true>), grid, dim3(WG), 0, st, P, Wk, prefix, nchunks, groups, unit_shift);
+    else if constexpr (FB <= 16)                 // (groups of 64 buckets are of small ones)
+        hipLaunchKernelGGL((k_finish<FB, WG, false>), grid, dim3(WG), 0, st, P, Wk, prefix, nchunks, groups, 0u);
     return check_launch();
 }
 
@@ -392,6 +405,7 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     P.staging = w.staging;
     P.flags = flags;
     P.norm_linf = norm_kind == NUQ_NORM_LINF ? 1u : 0u;
+    P.stream = stream_loads(d, K);
     constexpr TeamUse kUse = MODE == 0 ? TeamUse::kErc : TeamUse::kErcOther;
     const double l1 = MODE == 2 ? (double)levels[1] : std::ldexp(1.0, -(int)s);
     const bool narrow = narrow_teams<kUse>(nb, K, bucket, s, P.norm_linf, l1);
@@ -399,9 +413,9 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
         P.rows = team_rows<TEAM>(bucket);
-        P.rec_cap = team_rec_cap(bucket);
-        P.out_cap = team_out_cap(slot_words);
-        const TeamLdsMap map = team_lds_map(P.rows, TEAM, P.rec_cap, P.out_cap, nsync, P.nblk);
+        P.rec_cap = team_rec_cap(bucket, TEAM);
+        P.out_cap = team_out_cap(slot_words, P.rows, TEAM);
+        const TeamLdsMap map = team_lds_map(bucket, P.rows, TEAM, P.rec_cap, P.out_cap, nsync, P.nblk);
         const size_t lds_bytes = ((size_t)map.words * G::kTeamsPerWG + 512) * 4;            // + the code tables
         if (lds_bytes > 160 * 1024)
             return (int)NUQ_EINVAL;
@@ -463,6 +477,7 @@ int pack_fixed_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t buc
     P.s = s;
     P.flags = flags;
     P.norm_linf = norm_kind == NUQ_NORM_LINF ? 1u : 0u;
+    P.stream = stream_loads(d, K);
     FixedParams F{};
     F.b = b;
     F.wpb = (bucket * b + 31u) / 32u;
@@ -1391,6 +1406,7 @@ int nuq_quantize_encode_huffman_batch(uint32_t K, const float *const *v, const u
     P.units = w.units;
     P.staging = w.staging;
     P.flags = flags;
+    P.stream = stream_loads(d, K);
     const bool narrow = narrow_teams<TeamUse::kHuffman>(nb, K, bucket, s);
     int rc = dispatch_team<TeamUse::kHuffman>(bucket, narrow, [&](auto team_c, auto vpt_c) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;

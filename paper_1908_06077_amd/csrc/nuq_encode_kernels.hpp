@@ -56,6 +56,7 @@ struct EncodeParams {
     uint32_t *staging;     // [K * nb * slot_words]
     uint32_t *flags;
     uint32_t norm_linf;    // level-table mode: 0 = Euclidean norm, 1 = maximum norm
+    uint32_t stream;       // teams of less than a wave: gradients are loaded non-temporally too (see load_rows)
 };
 
 template <int TEAM>
@@ -97,8 +98,8 @@ __device__ __forceinline__ float4 load_vec4(const float *vb, uint32_t vi, uint32
 
 // A bucket's rows into registers.  Gradients are read once, so teams of a wave or more load them non-temporally: the
 // stream then does not push the staged bit strings, lengths and messages, which the next kernel reads, out of the caches
-// (172 -> 164 us on 8192-coordinate buckets, 3 % on 16384); quarter-wave teams, whose loads are 256-byte pieces, lose 5 %
-// with that and keep plain loads.  wg_base: the workgroup's first bucket (uniform), lane_off: coordinates from there to
+// (172 -> 164 us on 8192-coordinate buckets, 3 % on 16384).  Smaller teams, whose loads are 256- or 512-byte pieces, do
+// so for buckets above 256 (`stream`, stream_loads).  wg_base: the workgroup's first bucket (uniform), lane_off: coordinates from there to
 // the team's bucket.  The addresses of a full bucket are a uniform base per row (scalar registers; the empty asm keeps
 // the compiler from folding the row into the lanes' 64-bit addresses, two instructions per row and lane) plus one 32-bit
 // lane offset (in the global address space by type: behind the asm the compiler would have to assume a generic pointer).
@@ -106,21 +107,33 @@ typedef const __attribute__((address_space(1))) char *GlobalBytes;
 typedef const __attribute__((address_space(1))) f32x4_any *GlobalFloat4;
 template <int TEAM, int VPT>
 __device__ __forceinline__ void load_rows(float4 (&x)[VPT], const float *wg_base, uint32_t lane_off, uint32_t nbk,
-                                          uint32_t rows, uint32_t tid)
+                                          uint32_t rows, uint32_t tid, bool stream)
 {
     if (__all(nbk == (uint32_t)VPT * TEAM * 4u)) {       // full buckets that fill every row
         const uint32_t off = 4u * (lane_off + 4u * tid);                           // bytes, below 2^18
+        auto load = [&](auto once) {
 #pragma unroll
-        for (int i = 0; i < VPT; ++i) {
-            GlobalBytes row = (GlobalBytes)wg_base + i * (16 * TEAM);
-            if constexpr (TEAM >= 64) {
-                asm("" : "+s"(row));
-                const f32x4_any r = __builtin_nontemporal_load((GlobalFloat4)(row + off));
-                x[i] = float4{r.x, r.y, r.z, r.w};
-            } else {
-                const f32x4_any r = *(GlobalFloat4)(row + off);
+            for (int i = 0; i < VPT; ++i) {
+                GlobalBytes row = (GlobalBytes)wg_base + i * (16 * TEAM);
+                f32x4_any r;
+                if constexpr (decltype(once)::value) {
+                    asm("" : "+s"(row));        // (also keeps the two kinds of loads from being merged into the plain one)
+                    r = __builtin_nontemporal_load((GlobalFloat4)(row + off));
+                } else {
+                    r = *(GlobalFloat4)(row + off);
+                }
                 x[i] = float4{r.x, r.y, r.z, r.w};
             }
+        };
+        if constexpr (TEAM >= 64) {
+            load(std::true_type{});
+        } else if constexpr (VPT == 8) {
+            if (stream)
+                load(std::true_type{});
+            else
+                load(std::false_type{});
+        } else {
+            load(std::false_type{});
         }
     } else if (__all(nbk >= 4u)) {
         // Buckets that do not fill every row (their size, or the vector's end): addresses clamped to the last four
@@ -425,7 +438,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
 // nonzeros and `out_cap` words, sized for the usual case, and a bucket that exceeds one of them takes a slower way:
 //   nonzeros fit, bits fit  : as above
 //   nonzeros fit, bits don't: the same, but records are OR-ed into the (zeroed) staging slot in global memory
-//   nonzeros don't fit      : code_unlisted
+//   nonzeros don't fit      : Unlisted
 //
 // The kernel is bound by vector issue, so what counts here is instructions per record and per coordinate.
 
@@ -483,6 +496,7 @@ __device__ const CodeTables kCodeTables = make_code_tables();
 
 template <int TEAM>
 constexpr bool kSmallTeam = TEAM <= kWave;
+constexpr uint32_t kUsualRecords = 12, kKeptRecords = 2 * kUsualRecords;     // per thread of a small team (code_small)
 
 // The byte format of the coding phase for the level count s.
 template <int TEAM>
@@ -642,6 +656,25 @@ struct TeamLds {
     const uint32_t *tables;
 };
 
+// Where the coding phase puts its results: pointers out of the kernel's arguments, fetched before the gradient is waited for.
+// (Fetched where they are used, a scalar load each in the last dependent steps of a workgroup's life, they cost 2 to 3 % of 8 x
+// 25.6 M coordinates in buckets of 8192.)
+struct EncodeOut {
+    uint32_t *unit;        // staging area of the workgroup's buckets
+    uint32_t *unit_words;  // words of their strings together
+    uint64_t *bit_off;
+    uint32_t *sync;
+};
+template <int TEAM>
+__device__ __forceinline__ EncodeOut encode_out(const EncodeParams &P, const EncodeWorker &W)
+{
+    const uint64_t first = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG;
+    EncodeOut O{P.staging + ((uint64_t)blockIdx.y * P.nb + first) * P.slot_words,
+                P.units + (uint64_t)blockIdx.y * P.nb_stride + blockIdx.x, W.bit_off, W.sync};
+    asm volatile("" : "+s"(O.unit), "+s"(O.unit_words), "+s"(O.bit_off), "+s"(O.sync));
+    return O;
+}
+
 // What a thread knows of its bucket after step (1).
 struct Chunk {
     uint64_t nz;           // mask of its chunk's nonzeros
@@ -650,36 +683,80 @@ struct Chunk {
     uint32_t nnz;          // records of the bucket
 };
 
-// The bit string from LDS (zero up to a multiple of four words) to the bucket's slot, with 16-byte stores.
+// The bit string from LDS to its place in the staging area, with 16-byte stores.  Teams of several waves: the slot and the
+// LDS words behind the string up to a multiple of four are the bucket's own.  Others: the next bucket's string follows at once,
+// so the last piece ends with the string and takes words again that another piece has too.
 template <int TEAM>
 __device__ __forceinline__ void store_bucket(uint32_t *slot, const uint32_t *out, uint32_t nwords, uint32_t tid)
 {
-    for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
-        *reinterpret_cast<uint4 *>(slot + i) = *reinterpret_cast<const uint4 *>(out + i);
+    if constexpr (TeamGeom<TEAM>::kTeamsPerWG == 1) {
+        for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
+            *reinterpret_cast<uint4 *>(slot + i) = *reinterpret_cast<const uint4 *>(out + i);
+    } else if (nwords >= 4u) {
+        typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+        for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM) {
+            const uint32_t at = min(i, nwords - 4u);
+            *reinterpret_cast<u32x4_any *>(slot + at) = u32x4_any{out[at], out[at + 1u], out[at + 2u], out[at + 3u]};
+        }
+    } else if (tid < nwords) {
+        slot[tid] = out[tid];
+    }
 }
 
-// What k_finish needs to know of an encoder's workgroup: every bucket's bit length, left in the place of its offset, and
-// the words of all its buckets.  Called by all threads; total: bit length of the team's bucket.
-template <int TEAM>
-__device__ __forceinline__ void report_lengths(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
-                                               uint32_t total)
+// Where a bucket's string of `total` bits goes: the strings of a workgroup's buckets (a unit) stand in its first bucket's slot
+// and on, each from the next word.  Leaves what k_finish needs to know: every bucket's bit length, in the place of its offset,
+// and the words of all of them.  Called by all threads of the workgroup.  kCaller: levels that the caller has no business to
+// use may make strings longer than slots are; what would leave the unit is not stored.
+// Each in a slot of its own, as they were, 27 words in 128 at 512 coordinates, left half-written lines and k_finish a bisection
+// over buckets for every four words: k_finish of 4 x 1.56 G coordinates 703 -> 560 us.
+struct Place {
+    uint32_t *slot;
+    bool store;
+};
+template <int TEAM, bool kCaller>
+__device__ __forceinline__ Place place_bucket(const EncodeParams &P, const EncodeOut &O, bool active, uint64_t b, uint32_t total)
 {
+    constexpr uint32_t N = TeamGeom<TEAM>::kTeamsPerWG;
     const uint32_t tid = threadIdx.x % TEAM;
+    const uint32_t words = active ? (total + 31u) >> 5 : 0u;
+    static_assert(N > 1u && N <= (uint32_t)kRow, "one row of lanes scans the word counts");
+    __shared__ uint32_t team_words[N];
+    const uint32_t team = threadIdx.x / TEAM, row = threadIdx.x & (kWave - 1u) & ~(uint32_t)(kRow - 1);
+    if (tid == 0)
+        team_words[team] = words;
+    __syncthreads();
+    uint32_t inc = team_words[threadIdx.x & (N - 1u)];
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xf, 0xf, true);   // row_shr:1
+    inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xf, 0xf, true);   // row_shr:2
+    if constexpr (N > 4u)
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x114, 0xf, 0xf, true);   // row_shr:4
+    if constexpr (N > 8u)
+        inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xf, 0xf, true);   // row_shr:8
+    // (the first N lanes of a row hold the sums; N < 16: those behind start from them)
     if (active && tid == 0)
-        W.bit_off[b + 1] = total;
-    uint32_t words = active ? (total + 31u) >> 5 : 0u;
-    if constexpr (TeamGeom<TEAM>::kTeamsPerWG > 1) {
-        __shared__ uint32_t team_words[TeamGeom<TEAM>::kTeamsPerWG];
-        if (tid == 0)
-            team_words[threadIdx.x / TEAM] = words;
-        __syncthreads();
-        words = 0;
-#pragma unroll
-        for (int i = 0; i < TeamGeom<TEAM>::kTeamsPerWG; ++i)
-            words += team_words[i];
+        O.bit_off[b + 1] = total;
+    if (threadIdx.x == N - 1u)
+        *O.unit_words = inc;
+    const uint32_t end = (uint32_t)__shfl((int)inc, (int)(row | team), kWave);
+    bool store = active;
+    if constexpr (kCaller)
+        store = active && end <= (uint32_t)min((uint64_t)N, P.nb - (uint64_t)blockIdx.x * N) * P.slot_words;
+    return Place{O.unit + (end - words), store};
+}
+
+// The same for a workgroup of one bucket, whose slot is its unit.  The lengths are left at the end: a store ahead of the
+// barriers of the coding phase would be waited for there.
+template <bool kCaller>
+__device__ __forceinline__ bool fits_slot(const EncodeParams &P, uint32_t total)
+{
+    return !kCaller || (total + 31u) >> 5 <= P.slot_words;
+}
+__device__ __forceinline__ void report_length(const EncodeOut &O, uint64_t b, uint32_t total, uint32_t tid)
+{
+    if (tid == 0) {
+        O.bit_off[b + 1] = total;
+        *O.unit_words = (total + 31u) >> 5;
     }
-    if (threadIdx.x == 0)
-        P.units[(uint64_t)blockIdx.y * P.nb_stride + blockIdx.x] = words;
 }
 
 // Buckets with more nonzeros than the list holds: every thread codes the records of its own chunk, in two passes; the bit
@@ -688,112 +765,124 @@ __device__ __forceinline__ void report_lengths(const EncodeParams &P, const Enco
 // second window over the same words.  OR-ed into the slot in global memory, as it was, the atomics were the whole time: 4 x 8 M
 // coordinates at 9 bits each, buckets of 3000 1103 -> 142 us, of 8192 540 -> 139, of 32768 605 -> 206.
 template <int TEAM, bool kCaller>
-__device__ __forceinline__ uint32_t code_unlisted(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
-                                              const TeamLds &L, const Chunk &C, uint32_t *slot)
-{
-    const uint32_t tid = threadIdx.x % TEAM;
-    const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
-    const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
-    const int last = C.nz ? (int)C.base + 63 - __clzll((long long)C.nz) : -1;
-    const int before = team_exclusive_max<TEAM>(last, -1, reinterpret_cast<int *>(L.scratch + 16));
-    auto for_my_records = [&](auto &&f) {
+struct Unlisted {
+    const EncodeParams &P;
+    const TeamLds &L;
+    const Chunk &C;
+    int before;             // index of the last nonzero ahead of the thread's chunk
+    uint32_t bits;          // of the chunk's records
+
+    template <class F>
+    __device__ __forceinline__ void for_my_records(F &&f) const
+    {
+        const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
+        const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
         int p = before;
         uint64_t m = C.nz;
         while (m) {
             const int e = (int)C.base + __ffsll((unsigned long long)m) - 1;
             m &= m - 1;
             uint32_t len;
-            const uint32_t bits = record((uint32_t)(e - p), (uint32_t)qbytes[e], len);
-            f(e, bits, len);
+            const uint32_t rbits = record((uint32_t)(e - p), (uint32_t)qbytes[e], len);
+            f(e, rbits, len);
             p = e;
         }
-    };
-    uint32_t bits = 0;
-    for_my_records([&](int, uint32_t, uint32_t len) { bits += len; });
-    uint32_t total;
-    const uint32_t off0 = team_exclusive_sum<TEAM>(bits, L.scratch + 32, total);
-    const uint32_t nwords = (total + 31u) >> 5;
-    uint32_t *const obuf = reinterpret_cast<uint32_t *>(L.rec);
-    const uint32_t cap = (uint32_t)(L.out - obuf) + P.out_cap;      // a multiple of four (small teams: nwords <= cap)
-    auto clear = [&](uint32_t n) {
-        for (uint32_t i = 4u * tid; i < n; i += 4u * TEAM)
-            *reinterpret_cast<uint4 *>(obuf + i) = uint4{0u, 0u, 0u, 0u};
-    };
-    clear(kSmallTeam<TEAM> ? nwords : min(nwords, cap));
-    // index entries: their record numbers go to LDS (bit 31: a block without records), an entry past the last record is the
-    // bucket's length, and whoever emits such a record writes the entry
-    uint32_t *const sg = W.sync + (active ? b : 0) * P.nsync;
-    const uint32_t pmask = (1u << P.pieces_shift) - 1u;
-    for (uint32_t i = tid; i < P.nsync; i += TEAM) {
-        const uint32_t f = L.blk[i >> P.pieces_shift], n = L.blk[(i >> P.pieces_shift) + 1u] - f;
-        const uint32_t r = f + (((i & pmask) * n) >> P.pieces_shift);
-        if (r >= C.nnz && active)
-            sg[i] = total;
-        L.sync_l[i] = r | (n ? 0u : 0x80000000u);
     }
-    team_barrier<TEAM>();
-    auto emit_first = [&](uint32_t last_word) {
-        uint32_t t = off0, rno = C.rank0, cur = 0, hi = P.nsync;
-        while (cur < hi) {                       // first entry at or after this thread's first record (they are sorted)
-            const uint32_t mid = (cur + hi) >> 1;
-            if ((L.sync_l[mid] & 0x7fffffffu) < rno)
-                cur = mid + 1u;
-            else
-                hi = mid;
+    __device__ __forceinline__ void count()
+    {
+        const int last = C.nz ? (int)C.base + 63 - __clzll((long long)C.nz) : -1;
+        before = team_exclusive_max<TEAM>(last, -1, reinterpret_cast<int *>(L.scratch + 16));
+        bits = 0;
+        for_my_records([&](int, uint32_t, uint32_t len) { bits += len; });
+    }
+    // off0: the chunk's first bit, total: of the bucket
+    __device__ __forceinline__ void emit(const EncodeOut &O, bool active, uint64_t b, uint32_t off0, uint32_t total,
+                                         const Place &at) const
+    {
+        const uint32_t tid = threadIdx.x % TEAM;
+        const uint32_t nwords = (total + 31u) >> 5;
+        uint32_t *const obuf = reinterpret_cast<uint32_t *>(L.rec);
+        const uint32_t cap = kSmallTeam<TEAM> ? ~0u : (uint32_t)(L.out - obuf) + P.out_cap;      // a multiple of four (small teams: all of it fits)
+        auto clear = [&](uint32_t n) {
+            for (uint32_t i = 4u * tid; i < n; i += 4u * TEAM)
+                *reinterpret_cast<uint4 *>(obuf + i) = uint4{0u, 0u, 0u, 0u};
+        };
+        clear(min(nwords, cap));
+        // index entries: their record numbers go to LDS (bit 31: a block without records), an entry past the last record is
+        // the bucket's length, and whoever emits such a record writes the entry
+        uint32_t *const sg = O.sync + (active ? b : 0) * P.nsync;
+        const uint32_t pmask = (1u << P.pieces_shift) - 1u;
+        for (uint32_t i = tid; i < P.nsync; i += TEAM) {
+            const uint32_t f = L.blk[i >> P.pieces_shift], n = L.blk[(i >> P.pieces_shift) + 1u] - f;
+            const uint32_t r = f + (((i & pmask) * n) >> P.pieces_shift);
+            if (r >= C.nnz && active)
+                sg[i] = total;
+            L.sync_l[i] = r | (n ? 0u : 0x80000000u);
         }
-        BitWriter w(off0);
-        for_my_records([&](int e, uint32_t rbits, uint32_t len) {
-            while (cur < P.nsync) {
-                const uint32_t tg = L.sync_l[cur];
-                if ((tg & 0x7fffffffu) != rno)
-                    break;
-                const uint32_t rel = (tg >> 31) ? 0u : (uint32_t)e - ((cur >> P.pieces_shift) << kSyncBlockShift);
-                if (active)
-                    sg[cur] = t | (rel << 21);
-                ++cur;
-            }
-            ++rno;
-            t += len;
-            w.put(obuf, rbits, len, last_word);
-        });
-        if (C.nz)
-            w.flush(obuf, last_word);
-    };
-    if (kSmallTeam<TEAM> || nwords <= cap) {                                     // uniform over the team
-        emit_first(~0u);
         team_barrier<TEAM>();
-        if (active)
-            store_bucket<TEAM>(slot, obuf, nwords, tid);
-    } else {
-        emit_first(cap - 1u);
-        team_barrier<TEAM>();
-        if (active)
-            store_bucket<TEAM>(slot, obuf, cap, tid);
-        for (uint32_t lo = cap; lo < nwords; lo += cap) {
-            team_barrier<TEAM>();
-            clear(min(nwords - lo, cap));
-            team_barrier<TEAM>();
-            if (C.nz && (off0 + bits + 31u) >> 5 > lo) {
-                BitWriter w(off0);
-                w.wi -= lo;
-                for_my_records([&](int, uint32_t rbits, uint32_t len) { w.put(obuf, rbits, len, cap - 1u); });
-                w.flush(obuf, cap - 1u);
+        auto emit_first = [&](uint32_t last_word) {
+            uint32_t t = off0, rno = C.rank0, cur = 0, hi = P.nsync;
+            while (cur < hi) {                       // first entry at or after this thread's first record (they are sorted)
+                const uint32_t mid = (cur + hi) >> 1;
+                if ((L.sync_l[mid] & 0x7fffffffu) < rno)
+                    cur = mid + 1u;
+                else
+                    hi = mid;
             }
+            BitWriter w(off0);
+            for_my_records([&](int e, uint32_t rbits, uint32_t len) {
+                while (cur < P.nsync) {
+                    const uint32_t tg = L.sync_l[cur];
+                    if ((tg & 0x7fffffffu) != rno)
+                        break;
+                    const uint32_t rel = (tg >> 31) ? 0u : (uint32_t)e - ((cur >> P.pieces_shift) << kSyncBlockShift);
+                    if (active)
+                        sg[cur] = t | (rel << 21);
+                    ++cur;
+                }
+                ++rno;
+                t += len;
+                w.put(obuf, rbits, len, last_word);
+            });
+            if (C.nz)
+                w.flush(obuf, last_word);
+        };
+        if (kSmallTeam<TEAM> || nwords <= cap) {                                     // uniform over the team
+            emit_first(~0u);
             team_barrier<TEAM>();
-            if (active)
-                store_bucket<TEAM>(slot + lo, obuf, min(nwords - lo, cap), tid);
+            if (at.store)
+                store_bucket<TEAM>(at.slot, obuf, nwords, tid);
+        } else {
+            emit_first(cap - 1u);
+            team_barrier<TEAM>();
+            if (at.store)
+                store_bucket<TEAM>(at.slot, obuf, cap, tid);
+            for (uint32_t lo = cap; lo < nwords; lo += cap) {
+                team_barrier<TEAM>();
+                clear(min(nwords - lo, cap));
+                team_barrier<TEAM>();
+                if (C.nz && (off0 + bits + 31u) >> 5 > lo) {
+                    BitWriter w(off0);
+                    w.wi -= lo;
+                    for_my_records([&](int, uint32_t rbits, uint32_t len) { w.put(obuf, rbits, len, cap - 1u); });
+                    w.flush(obuf, cap - 1u);
+                }
+                team_barrier<TEAM>();
+                if (at.store)
+                    store_bucket<TEAM>(at.slot + lo, obuf, min(nwords - lo, cap), tid);
+            }
         }
     }
-    return total;
-}
+};
 
 // Steps (2) and (3), teams of several waves: two or three records per thread.  The records' table entries, four of them
 // kept; the index entries are looked up from the entry's side (the run that holds the record starts at run_off[owner]; the
 // lengths of the records before it in that run are looked up again).
-template <int TEAM>
-__device__ __forceinline__ uint32_t code_listed_large(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
-                                                  const TeamLds &L, uint32_t nnz, uint32_t *slot)
+template <int TEAM, bool kCaller>
+__device__ __forceinline__ void code_listed_large(const EncodeParams &P, const EncodeOut &O, bool active, uint64_t b,
+                                              const TeamLds &L, uint32_t nnz)
 {
+    uint32_t *const slot = O.unit;
     const uint32_t tid = threadIdx.x % TEAM;
     const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
     const LargeRecords record{L.tables};
@@ -825,10 +914,11 @@ __device__ __forceinline__ uint32_t code_listed_large(const EncodeParams &P, con
     const uint32_t off0 = team_exclusive_sum<TEAM, false>(bits, L.scratch + 16, total);
     const uint32_t nwords = (total + 31u) >> 5;
     const bool in_lds = nwords <= P.out_cap;                     // uniform over the team (the buffer was cleared before)
+    const bool store = active && fits_slot<kCaller>(P, total);
     if (P.nsync)
         L.run_off[tid] = off0;
     if (!in_lds) {
-        if (active) {
+        if (store) {
             for (uint32_t i = tid; i < nwords; i += TEAM)
                 slot[i] = 0u;
             __threadfence();   // the zeros are in place before any record is OR-ed over them
@@ -854,10 +944,10 @@ __device__ __forceinline__ uint32_t code_listed_large(const EncodeParams &P, con
     };
     if (in_lds)
         emit_all(L.out);
-    else if (active)
+    else if (store)
         emit_all(slot);
     team_barrier<TEAM>();
-    uint32_t *const sg = W.sync + (active ? b : 0) * P.nsync;
+    uint32_t *const sg = O.sync + (active ? b : 0) * P.nsync;
     const uint32_t pmask = (1u << P.pieces_shift) - 1u;
     for (uint32_t i = tid; i < P.nsync; i += TEAM) {
         const uint32_t t = i >> P.pieces_shift;
@@ -880,64 +970,71 @@ __device__ __forceinline__ uint32_t code_listed_large(const EncodeParams &P, con
         if (active)
             sg[i] = entry;
     }
-    if (active && in_lds)
+    if (store && in_lds)
         store_bucket<TEAM>(slot, L.out, nwords, tid);
-    return total;
+    report_length(O, b, total, tid);
 }
 
 // Steps (2) and (3), teams of a wave or less: around ten records per thread, each looked up once and kept as one word.
 // A bucket is one block of the index and has at most one entry per thread.  While records are emitted, a record's place in
 // the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 27 bits), so the thread
 // of entry i reads its record's index before and its offset after.
+// A wave may hold teams whose bucket is listed and others whose is not; the workgroup's place in the staging area is worked
+// out where they are together.
 template <int TEAM, bool kCaller>
-__device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
-                                                  const TeamLds &L, uint32_t nnz, uint32_t *slot)
+__device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOut &O, bool active, uint64_t b,
+                                       const TeamLds &L, const Chunk &C, bool listed)
 {
     const uint32_t tid = threadIdx.x % TEAM;
+    const uint32_t nnz = C.nnz;
     const uint8_t *qbytes = reinterpret_cast<const uint8_t *>(L.qb32);
-    const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
     const uint32_t per = (nnz + TEAM - 1u) / TEAM;
-    const uint32_t r0 = min(tid * per, nnz), r1 = min(r0 + per, nnz);
-    // The first twelve are what gradients have; twelve more are kept where some lane of the wave has them (up to 32 where
-    // most coordinates are nonzero; looked up again for the emission they cost twice), the rest looked up again.
-    constexpr uint32_t kUsual = 12, kKept = 2 * kUsual;
-    uint32_t kept[kKept] = {}, bits = 0;
+    const uint32_t r0 = min(tid * per, nnz), n = min(r0 + per, nnz) - r0;
+    // The first twelve are what gradients have; twelve more are kept where some lane of the wave has them (looked up again
+    // for the emission they cost twice); more there are not (team_rec_cap).
+    uint32_t kept[kKeptRecords] = {}, bits = 0;
     uint16_t *const run = L.rec + r0;
-    const uint32_t n = r1 - r0;
-    const bool many = __any(n > kUsual);
-    int p = r0 ? (int)run[-1] : -1;
-    auto look_up = [&](uint32_t i) {
-        if (i < n) {
-            const int e = (int)run[i];
-            kept[i] = record.packed((uint32_t)(e - p), (uint32_t)qbytes[e]);
-            bits += kept[i] >> 27;
-            p = e;
-        }
-    };
+    const bool many = __any(listed && n > kUsualRecords);
+    Unlisted<TEAM, kCaller> U{P, L, C, -1, 0u};
+    if (listed) {
+        const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
+        int p = r0 ? (int)run[-1] : -1;
+        auto look_up = [&](uint32_t i) {
+            if (i < n) {
+                const int e = (int)run[i];
+                kept[i] = record.packed((uint32_t)(e - p), (uint32_t)qbytes[e]);
+                bits += kept[i] >> 27;
+                p = e;
+            }
+        };
 #pragma unroll
-    for (uint32_t i = 0; i < kUsual; ++i)
-        look_up(i);
-    if (many)
-#pragma unroll
-        for (uint32_t i = kUsual; i < kKept; ++i)
+        for (uint32_t i = 0; i < kUsualRecords; ++i)
             look_up(i);
-    const int p_kept = p;
-    for (uint32_t i = kKept; i < n; ++i) {
-        const int e = (int)run[i];
-        bits += record.packed((uint32_t)(e - p), (uint32_t)qbytes[e]) >> 27;
-        p = e;
+        if (many)
+#pragma unroll
+            for (uint32_t i = kUsualRecords; i < kKeptRecords; ++i)
+                look_up(i);
+    } else {
+        U.count();
+        bits = U.bits;
     }
     uint32_t total;
     const uint32_t off0 = team_exclusive_sum<TEAM>(bits, nullptr, total);
+    const Place at = place_bucket<TEAM, kCaller>(P, O, active, b, total);
+    uint32_t *const slot = at.slot;
+    if (!listed) {
+        U.emit(O, active, b, off0, total, at);
+        return;
+    }
     const uint32_t nwords = (total + 31u) >> 5;
     const bool in_lds = nwords <= P.out_cap;                     // uniform over the team
     const bool entry = tid < P.nsync && nnz;
     const uint32_t r_entry = (tid * nnz) >> P.pieces_shift;      // < nnz for an entry
     const uint32_t e_entry = entry ? (uint32_t)L.rec[r_entry] : 0u;
-    if (in_lds) {
+    if (in_lds) {                                                // (the bytes have been read to the end: their place is free)
         for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
             *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
-    } else if (active) {
+    } else if (at.store) {
         for (uint32_t i = tid; i < nwords; i += TEAM)
             slot[i] = 0u;
         __threadfence();       // the zeros are in place before any record is OR-ed over them
@@ -955,43 +1052,32 @@ __device__ __forceinline__ uint32_t code_listed_small(const EncodeParams &P, con
             }
         };
 #pragma unroll
-        for (uint32_t i = 0; i < kUsual; ++i)
+        for (uint32_t i = 0; i < kUsualRecords; ++i)
             emit(i);
         if (many)
 #pragma unroll
-            for (uint32_t i = kUsual; i < kKept; ++i)
+            for (uint32_t i = kUsualRecords; i < kKeptRecords; ++i)
                 emit(i);
-        int q = p_kept;
-        for (uint32_t i = kKept; i < n; ++i) {
-            const int e = (int)run[i];
-            uint32_t len;
-            const uint32_t rb = record((uint32_t)(e - q), (uint32_t)qbytes[e], len);
-            run[i] = (uint16_t)t;
-            t += len;
-            w.put(dst, rb, len);
-            q = e;
-        }
         if (n)
             w.flush(dst);
     };
     if (in_lds)
         emit_all(L.out);
-    else if (active)
+    else if (at.store)
         emit_all(slot);
     team_barrier<TEAM>();
     if (active) {
         if (tid < P.nsync)
-            W.sync[b * P.nsync + tid] = entry ? (uint32_t)L.rec[r_entry] | (e_entry << 21) : 0u;
-        if (in_lds)
+            O.sync[b * P.nsync + tid] = entry ? (uint32_t)L.rec[r_entry] | (e_entry << 21) : 0u;
+        if (in_lds && at.store)
             store_bucket<TEAM>(slot, L.out, nwords, tid);
     }
-    return total;
 }
 
-// Returns the bucket's bit length.  kCaller: the bytes are flag_caller_bytes'.
+// kCaller: the bytes are flag_caller_bytes'.
 template <int TEAM, int VPT, bool kCaller>
-__device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const EncodeWorker &W, bool active, uint64_t b,
-                                                const TeamLds &L)
+__device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const EncodeOut &O, bool active, uint64_t b,
+                                            const TeamLds &L)
 {
     const uint32_t tid = threadIdx.x % TEAM;
     const uint32_t rows = P.rows;
@@ -1029,8 +1115,6 @@ __device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const
         if (tid == 0)
             L.blk[P.nblk] = C.nnz;
     }
-    const uint64_t gb = (uint64_t)blockIdx.y * P.nb + b;         // bucket index over the whole batch
-    uint32_t *const slot = P.staging + (active ? gb : 0) * P.slot_words;
     if (listed) {
         uint16_t *r = L.rec + C.rank0;
         auto list = [&](uint32_t m, uint32_t at) {
@@ -1045,32 +1129,45 @@ __device__ __forceinline__ uint32_t encode_from_lds(const EncodeParams &P, const
         if constexpr (!kSmallTeam<TEAM>)
             for (uint32_t i = 4u * tid; i < P.out_cap; i += 4u * TEAM)
                 *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
-        team_barrier<TEAM>();
-        if constexpr (kSmallTeam<TEAM>)
-            return code_listed_small<TEAM, kCaller>(P, W, active, b, L, C.nnz, slot);
-        else
-            return code_listed_large<TEAM>(P, W, active, b, L, C.nnz, slot);
+    }
+    team_barrier<TEAM>();
+    if constexpr (kSmallTeam<TEAM>) {
+        code_small<TEAM, kCaller>(P, O, active, b, L, C, listed);
+    } else if (listed) {
+        code_listed_large<TEAM, kCaller>(P, O, active, b, L, C.nnz);
     } else {
-        team_barrier<TEAM>();
-        return code_unlisted<TEAM, kCaller>(P, W, active, b, L, C, slot);
+        Unlisted<TEAM, kCaller> U{P, L, C, -1, 0u};
+        U.count();
+        uint32_t total;
+        const uint32_t off0 = team_exclusive_sum<TEAM>(U.bits, L.scratch + 32, total);
+        U.emit(O, active, b, off0, total, Place{O.unit, fits_slot<kCaller>(P, total)});
+        report_length(O, b, total, threadIdx.x);
     }
 }
 
-// What a team's LDS holds of a bucket's nonzero list and bit string.  Large buckets: a quarter of the worst case (about
-// four times what a Gaussian gradient produces).  257 to 512 coordinates: five nonzeros in eight (gradients: one in four),
-// which lets five workgroups of 16 buckets share a CU.  Up to 256: all of them, since eight workgroups, as many as there are
-// waves for, fit beside that (at most 272 words per team), and the smaller a bucket, the denser it is.  30 M coordinates, list
-// of five in eight -> whole list, s = 3: buckets of 64 141 -> 101 us, of 100 91 -> 84.
-__host__ __device__ inline uint32_t team_rec_cap(uint32_t bucket)
+// What a team's LDS holds of a bucket's nonzero list and bit string.  Teams of several waves: a quarter of the worst case
+// (about four times what a Gaussian gradient produces).
+//
+// Teams of a wave or less keep every record of a listed bucket in registers before the first bit is written, so the string
+// takes the place of the bytes it was made from.  257 to 512 coordinates: the list holds 37 nonzeros in 64 (gradients: one in
+// four), with which eight workgroups of 16 buckets share a CU, as many as there are waves for.  Up to 256: all of them, since
+// eight workgroups fit beside that, and the smaller a bucket, the denser it is.  With the string in LDS of its own five fitted:
+// encode of 4 x 1.56 G coordinates 6.65 -> 6.00 ms, of 8 x 10 M in buckets of 1000 (half a wave each: four, now seven)
+// 92.8 -> 79.3 us.
+__host__ __device__ inline uint32_t team_rec_cap(uint32_t bucket, uint32_t team)
 {
     const uint32_t quarter = bucket / 4u;
-    if (bucket <= 1024u)
-        return bucket > 256u && bucket <= 512u ? (bucket * 5u / 8u + 7u) & ~7u : bucket;
-    return quarter > 1024u ? quarter : 1024u;
+    const uint32_t cap = bucket <= 256u    ? bucket
+                         : bucket <= 512u  ? (bucket * 37u / 64u + 7u) & ~7u
+                         : bucket <= 1024u ? bucket
+                                           : (quarter > 1024u ? quarter : 1024u);
+    return team <= (uint32_t)kWave && cap > team * kKeptRecords ? team * kKeptRecords : cap;
 }
-__host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words)       // a multiple of 4, like slot_words
+__host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words, uint32_t rows, uint32_t team)   // a multiple of 4, like slot_words
 {
-    const uint32_t quarter = (slot_words / 4u + 3u) & ~3u;
+    const uint32_t quarter = (slot_words / 4u + 3u) & ~3u, bytes = rows * team;
+    if (team <= (uint32_t)kWave)
+        return slot_words < bytes ? slot_words : bytes;
     return slot_words <= 256u ? slot_words : (quarter > 256u ? quarter : 256u);
 }
 
@@ -1079,17 +1176,22 @@ __host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words)       // a
 struct TeamLdsMap {
     uint32_t rec, out, sync, blk, run_off, scratch, words;
 };
-__host__ __device__ inline TeamLdsMap team_lds_map(uint32_t rows, uint32_t team, uint32_t rec_cap, uint32_t out_cap,
-                                                   uint32_t nsync, uint32_t nblk)
+__host__ __device__ inline TeamLdsMap team_lds_map(uint32_t bucket, uint32_t rows, uint32_t team, uint32_t rec_cap,
+                                                   uint32_t out_cap, uint32_t nsync, uint32_t nblk)
 {
+    const bool small = team <= (uint32_t)kWave;
+    // a bucket of a small team whose nonzeros do not fit the list assembles its string in the list's place: at most nine bits
+    // per coordinate (sign, level code of seven bits, one bit of gap each)
+    const uint32_t list = (rec_cap + 1u) / 2u, dense = small ? (bucket * 9u + 31u) / 32u : 0u;
     TeamLdsMap m;
     m.rec = rows * team;
-    m.out = m.rec + (((rec_cap + 1u) / 2u + 3u) & ~3u);
-    m.sync = m.out + out_cap;
+    const uint32_t behind = m.rec + (((list > dense ? list : dense) + 3u) & ~3u);
+    m.out = small ? 0u : behind;
+    m.sync = behind + (small ? 0u : out_cap);
     m.blk = m.sync + nsync;
     m.run_off = m.blk + nblk + 1u;
-    m.scratch = (m.run_off + (team > (uint32_t)kWave ? team : 0u) + 1u) & ~1u;      // 8-byte aligned
-    m.words = (m.scratch + (team > (uint32_t)kWave ? 64u : 0u) + 3u) & ~3u;         // small teams need no scratch
+    m.scratch = (m.run_off + (small ? 0u : team) + 1u) & ~1u;      // 8-byte aligned
+    m.words = (m.scratch + (small ? 0u : 64u) + 3u) & ~3u;         // small teams need no scratch
     return m;
 }
 
@@ -1104,7 +1206,7 @@ __device__ __forceinline__ void front_quantize(const EncodeParams &P, const Enco
 {
     float4 x[VPT];
     const uint64_t wg_base = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG * P.bucket;
-    load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid);
+    load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid, P.stream != 0u);
     issued();
     auto row = [&](int i) { return x[i]; };
     const float nrm = team_uniform_f32<TEAM>(
@@ -1192,7 +1294,7 @@ __device__ __forceinline__ void front_quantize_table(const EncodeParams &P, cons
     const float *vb = W.v + base;
     float4 x[VPT];
     const uint64_t wg_base = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG * P.bucket;
-    load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid);
+    load_rows<TEAM, VPT>(x, W.v + wg_base, active ? (uint32_t)(base - wg_base) : 0u, nbk, P.rows, tid, P.stream != 0u);
     issued();
     float nrm;
     if (P.norm_linf) {
@@ -1258,19 +1360,23 @@ __device__ __forceinline__ void front_quantize_table_to_lds(const EncodeParams &
 
 // MODE 0: fused norms + quantize + encode from v.  MODE 1: encode from level/sign bytes.  MODE 2: as 0 for the level
 // table T and the norm P.norm_linf selects (T is ignored in the other modes).
+// (Small teams: eight waves per SIMD, as many as their LDS allows.)
 template <int TEAM, int VPT, int MODE>
-__global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, EncodeBatch Wk, LevelTable T)
+__global__ __launch_bounds__(TeamGeom<TEAM>::kWG, kSmallTeam<TEAM> && MODE == 0 ? 8 : 1) void k_encode(EncodeParams P,
+                                                                                                      EncodeBatch Wk,
+                                                                                                      LevelTable T)
 {
     extern __shared__ __align__(16) uint32_t smem[];
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
     const uint32_t team = team_uniform_u32<TEAM>(threadIdx.x / TEAM);   // a scalar unless a wave holds several teams
-    const TeamLdsMap map = team_lds_map(P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk);
+    const TeamLdsMap map = team_lds_map(P.bucket, P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk);
     uint32_t *const lds = smem + team * map.words;
     uint32_t *const tables = smem + TeamGeom<TEAM>::kTeamsPerWG * map.words;
     const TeamLds L{lds, reinterpret_cast<uint16_t *>(lds + map.rec), lds + map.out, lds + map.sync, lds + map.blk,
                     lds + map.run_off, lds + map.scratch, tables};
     const TableCopy<TEAM> copy(P.s);
+    const EncodeOut O = encode_out<TEAM>(P, W);
 
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + team;
     const bool active = b < P.nb;
@@ -1290,7 +1396,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_encode(EncodeParams P, 
         });
     }
     __syncthreads();
-    report_lengths<TEAM>(P, W, active, b, encode_from_lds<TEAM, VPT, MODE == 1>(P, W, active, b, L));
+    encode_from_lds<TEAM, VPT, MODE == 1>(P, O, active, b, L);
 }
 
 // ------------------------------------------------- offsets and gather of the slots
@@ -1376,18 +1482,21 @@ __global__ __launch_bounds__(256) void k_chunk_scan(uint64_t *chunk_sums, uint64
 //
 // What bounds it is latency: a chain of dependent loads (lengths, then the strings they locate, and the units before the
 // group), each a round trip, in a kernel of a few microseconds.  So the lengths and the units are requested together, the
-// strings as soon as the lengths are there (their place in the slots does not depend on the sum), and everything moves in
-// pieces of four words (a bucket's last piece may be shorter; any 4-byte aligned address takes a 16-byte store), each
+// strings as soon as the lengths are there (their place in the staging area does not depend on the sum), and everything moves
+// in pieces of four words (a unit's last piece may be shorter; any 4-byte aligned address takes a 16-byte store), each
 // found by one bisection.
-template <uint32_t FB, uint32_t WG>
+// kUnits: units of several buckets.
+template <uint32_t FB, uint32_t WG, bool kUnits>
 __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, const uint64_t *chunk_prefix,
-                                                uint64_t nchunks, uint32_t groups, uint32_t unit_shift)
+                                                uint64_t nchunks, uint32_t groups, uint32_t shift)
 {
+    const uint32_t unit_shift = kUnits ? shift : 0u;
     static_assert(FB == 4 || FB == 16 || FB == 64, "one wave scans the group's word counts");
     static_assert(WG == 64 || WG == 256, "block_sum_u64 adds four waves");
     __shared__ uint64_t scratch[4];
     __shared__ uint32_t wstart[FB + 1];   // first word of each bucket, relative to the group's first
-    __shared__ uint32_t pstart[FB + 1];   // first piece of each bucket
+    __shared__ uint32_t pstart[FB + 1];   // first piece of each unit
+    const uint32_t nunits = FB >> unit_shift;                     // per group
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t *__restrict__ units = P.units + (uint64_t)blockIdx.y * P.nb_stride;
     const uint32_t tid = threadIdx.x;
@@ -1422,8 +1531,15 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
 
     for (uint32_t g = 0; g < groups && b_first < P.nb; ++g, b_first += FB) {
         if (tid < kWave) {                      // the first wave: inclusive scans of the word and piece counts
-            const uint32_t words = (my_len + 31u) >> 5;
-            const uint32_t wi = wave_inclusive_sum(words), pi = wave_inclusive_sum((words + 3u) >> 2);
+            uint32_t words = (my_len + 31u) >> 5;
+            const uint32_t wi = wave_inclusive_sum(words);
+            if constexpr (kUnits) {                 // words of unit tid
+                const uint32_t last = ((tid + 1u) << unit_shift) - 1u;
+                const uint32_t end = (uint32_t)__shfl((int)wi, (int)(last & (kWave - 1u)), kWave);
+                const uint32_t begin = (uint32_t)__shfl_up((int)end, 1, kWave);
+                words = tid < nunits ? end - (tid ? begin : 0u) : 0u;
+            }
+            const uint32_t pi = wave_inclusive_sum((words + 3u) >> 2);
             if (tid < FB) {
                 wstart[tid + 1] = wi;
                 pstart[tid + 1] = pi;
@@ -1437,6 +1553,9 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
             my_len = load_len(b_first + FB);
         const uint32_t total = pstart[FB];
         const uint32_t *__restrict__ staging = P.staging + ((uint64_t)blockIdx.y * P.nb + b_first) * P.slot_words;
+        // words that a unit has room for (see place_bucket's kCaller)
+        const uint32_t here = (uint32_t)min((uint64_t)FB, P.nb - b_first);
+        auto room = [&](uint32_t j) { return kUnits ? (here - min(j, here)) * P.slot_words : P.slot_words; };
         constexpr uint32_t kFlight = 4;         // pieces per thread under way at once
         for (uint32_t p0 = tid; !summed || p0 < total; p0 += kFlight * WG) {
             uint4 x[kFlight];
@@ -1447,11 +1566,12 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
                 uint32_t j = 0;
 #pragma unroll
                 for (uint32_t step = FB / 2; step >= 1; step >>= 1)
-                    j += (pstart[j + step] <= p) ? step : 0u;
-                bkt[q] = j;
+                    if (!kUnits || step < nunits)
+                        j += (pstart[j + step] <= p) ? step : 0u;
+                bkt[q] = j << unit_shift;
                 at[q] = 4u * (p - pstart[j]);
-                if (p < total)
-                    x[q] = *reinterpret_cast<const uint4 *>(staging + (uint64_t)j * P.slot_words + at[q]);
+                if (p < total && at[q] < room(bkt[q]))
+                    x[q] = *reinterpret_cast<const uint4 *>(staging + (uint64_t)bkt[q] * P.slot_words + at[q]);
             }
             if (!summed) {                      // (once, with the first pieces under way)
                 if constexpr (WG == 64u) {
@@ -1465,10 +1585,25 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
                 }
                 summed = true;
             }
+            // a bucket's words are written if all of them fit
+            uint32_t fit = wstart[FB];
+            if (kUnits && base + fit > W.words_cap) {
+                fit = 0;
+                for (uint32_t i = 1; i < FB && base + wstart[i] <= W.words_cap; ++i)
+                    fit = wstart[i];
+            }
 #pragma unroll
             for (uint32_t q = 0; q < kFlight; ++q) {
-                const uint32_t end = wstart[bkt[q] + 1u], w = wstart[bkt[q]] + at[q];
-                if (p0 + q * WG < total && base + end <= W.words_cap) {
+                const uint32_t w = wstart[bkt[q]] + at[q];
+                uint32_t end = wstart[bkt[q] + (1u << unit_shift)];
+                bool put = p0 + q * WG < total;
+                if constexpr (kUnits) {
+                    end = min(end, fit);
+                    put = put && w < end;
+                } else {
+                    put = put && base + end <= W.words_cap;
+                }
+                if (put) {
                     uint32_t *dst = W.words + base + w;
                     typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
                     if (w + 4u <= end) {

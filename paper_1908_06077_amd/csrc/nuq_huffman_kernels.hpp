@@ -327,7 +327,7 @@ __device__ __forceinline__ uint32_t huffman_pairs_from_lds(const EncodeParams &P
 }
 
 // Norms + quantizer + Huffman coding of one bucket per team, v read once, all workers in one launch (blockIdx.y): the
-// bit string goes to the bucket's staging slot and its length where k_finish looks for it (report_lengths); that kernel
+// bit string goes to the staging area and its length where k_finish looks for it (place_bucket); that kernel
 // turns them into bit_off and words as for the ERC strings.  kPairs: s <= 6.
 template <int TEAM, int VPT, bool kPairs>
 __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodeParams P, EncodeBatch Wk, HuffmanCode H)
@@ -341,6 +341,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
     uint32_t *field = qb32 + P.rows * TEAM;
     uint32_t *sync_l = field + P.out_cap;
     uint32_t *scratch = lds + P.lds_words - 64u;
+    const EncodeOut O = encode_out<TEAM>(P, W);
     const uint64_t b = (uint64_t)blockIdx.x * TeamGeom<TEAM>::kTeamsPerWG + team;
     const bool active = b < P.nb;
     const uint64_t base = active ? b * P.bucket : 0;
@@ -360,13 +361,17 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
         total = huffman_from_lds<TEAM>(P, enc, qb32, field, sync_l, scratch, nbk, tid);
     }
     team_barrier<TEAM>();
+    uint32_t *slot = O.unit;
+    if constexpr (TeamGeom<TEAM>::kTeamsPerWG > 1)
+        slot = place_bucket<TEAM, false>(P, O, active, b, total).slot;
     if (active) {
-        store_bucket<TEAM>(P.staging + ((uint64_t)blockIdx.y * P.nb + b) * P.slot_words, field, (total + 31u) >> 5, tid);
-        uint32_t *sg = W.sync + b * P.nsync;
+        store_bucket<TEAM>(slot, field, (total + 31u) >> 5, tid);
+        uint32_t *sg = O.sync + b * P.nsync;
         for (uint32_t i = tid; i < P.nsync; i += TEAM)
             sg[i] = sync_l[i];
     }
-    report_lengths<TEAM>(P, W, active, b, total);
+    if constexpr (TeamGeom<TEAM>::kTeamsPerWG == 1)
+        report_length(O, b, total, tid);
 }
 
 template <int TEAM, int VPT>
