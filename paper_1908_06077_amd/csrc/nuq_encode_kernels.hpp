@@ -649,9 +649,9 @@ struct TeamLds {
     uint32_t *qb32;        // rows * TEAM: bytes
     uint16_t *rec;         // rec_cap indices ...
     uint32_t *out;         // ... then out_cap words of bit string; 16-byte aligned
-    uint32_t *sync_l;      // nsync
+    uint32_t *sync_l;      // nsync (buckets that are not listed) ...
     uint32_t *blk;         // nblk + 1: records before each block of the index
-    uint32_t *run_off;     // TEAM (large teams): bit offset of every thread's run
+    uint32_t *run_off;     // ... or TEAM (large teams, listed buckets): bit offset of every thread's run
     uint32_t *scratch;     // 64
     const uint32_t *tables;
 };
@@ -1146,7 +1146,8 @@ __device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const Enc
 }
 
 // What a team's LDS holds of a bucket's nonzero list and bit string.  Teams of several waves: a quarter of the worst case
-// (about four times what a Gaussian gradient produces).
+// (about four times what a Gaussian gradient produces), but no more than 3584 nonzeros of buckets of up to 16384, of which five
+// then share a CU instead of four: heavy tails, 4 x 134 M coordinates in buckets of 16384, both directions 605 -> 578 us.
 //
 // Teams of a wave or less keep every record of a listed bucket in registers before the first bit is written, so the string
 // takes the place of the bytes it was made from.  257 to 512 coordinates: the list holds 37 nonzeros in 64 (gradients: one in
@@ -1160,7 +1161,9 @@ __host__ __device__ inline uint32_t team_rec_cap(uint32_t bucket, uint32_t team)
     const uint32_t cap = bucket <= 256u    ? bucket
                          : bucket <= 512u  ? (bucket * 37u / 64u + 7u) & ~7u
                          : bucket <= 1024u ? bucket
-                                           : (quarter > 1024u ? quarter : 1024u);
+                         : bucket <= 4096u ? 1024u
+                         : bucket <= 16384u && quarter > 3584u ? 3584u
+                                           : quarter;
     return team <= (uint32_t)kWave && cap > team * kKeptRecords ? team * kKeptRecords : cap;
 }
 __host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words, uint32_t rows, uint32_t team)   // a multiple of 4, like slot_words
@@ -1188,9 +1191,9 @@ __host__ __device__ inline TeamLdsMap team_lds_map(uint32_t bucket, uint32_t row
     const uint32_t behind = m.rec + (((list > dense ? list : dense) + 3u) & ~3u);
     m.out = small ? 0u : behind;
     m.sync = behind + (small ? 0u : out_cap);
-    m.blk = m.sync + nsync;
-    m.run_off = m.blk + nblk + 1u;
-    m.scratch = (m.run_off + (small ? 0u : team) + 1u) & ~1u;      // 8-byte aligned
+    m.run_off = m.sync;
+    m.blk = m.sync + (small || nsync > team ? nsync : team);
+    m.scratch = (m.blk + nblk + 2u) & ~1u;                         // 8-byte aligned
     m.words = (m.scratch + (small ? 0u : 64u) + 3u) & ~3u;         // small teams need no scratch
     return m;
 }

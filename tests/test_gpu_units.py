@@ -33,11 +33,12 @@ def crafted(rng, n, counts, tail, s):
 
 
 @pytest.mark.parametrize("s", [3, 8])
-@pytest.mark.parametrize("n,S", [(3, 64), (257, 64), (320, 128), (511, 256), (512, 64), (1024, 128), (1025, 64), (2048, 256)])
+@pytest.mark.parametrize("n,S", [(3, 64), (257, 64), (320, 128), (511, 256), (512, 64), (1024, 128), (1025, 64), (2048, 256),
+                                 (5000, 64), (14400, 64), (16384, 128)])
 def test_list_edges(g, n, S, s):
     """One nonzero fewer than the list holds, as many, one more, in buckets side by side; the last unit partly filled."""
     rng = np.random.default_rng(n + s)
-    cap = n if n <= 256 else (n * 37 // 64 + 7) & ~7 if n <= 512 else min(n, 1024)
+    cap = n if n <= 256 else (n * 37 // 64 + 7) & ~7 if n <= 512 else min(n, 1024) if n <= 4096 else min(n // 4, 3584)
     counts = [n // 4, cap - 1, cap, min(n, cap + 1), 0, n, cap, n // 4, min(n, cap + 1), 1, n // 3] * 3
     q = crafted(rng, n, counts, 1 if n > 1 else 0, s)
     m = coded(g, q, n, s, S)
