@@ -67,7 +67,8 @@ enum {
 enum {
     NUQ_FLAG_CAPACITY = 1,  /* encoded words did not fit words_cap; words is incomplete */
     NUQ_FLAG_NONFINITE = 2, /* a bucket norm was Inf/NaN; that bucket was encoded empty */
-    NUQ_FLAG_MALFORMED = 4  /* a decoded stream broke the format; output is incomplete  */
+    NUQ_FLAG_MALFORMED = 4  /* a decoded stream broke the format, or nuq_encode refused a bucket; output is
+                               incomplete */
 };
 
 /* A bucket's coordinates stay in the registers of one workgroup between the norm and the quantizer, so
@@ -129,7 +130,10 @@ int nuq_quantize(const float *v, uint64_t d, uint32_t bucket, uint32_t s, uint64
  * workspace: at least nuq_encode_workspace_bytes(1, d, bucket, s) bytes, 16-byte aligned;
  * contents are scratch.  If the encoded size exceeds words_cap the device flag
  * NUQ_FLAG_CAPACITY is raised, bit_off is still complete and words holds the buckets
- * that fit.  A level index above s+1 in q is a caller error (undefined bits). */
+ * that fit.  A level index above s+1 in q is a caller error: it is coded modulo 16 (a multiple of 16 as
+ * 1).  A bucket whose string such levels make longer than levels up to s+1 can (by more than the words its
+ * place in the workspace is rounded up by) is refused: it becomes one word of ones, which no decoder takes,
+ * its index entries are 0, NUQ_FLAG_MALFORMED is raised, and no other bucket changes. */
 int nuq_encode(const uint8_t *q, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride,
                uint64_t *bit_off, uint32_t *words, uint64_t words_cap, uint32_t *sync,
                void *workspace, uint64_t workspace_bytes, nuq_stream_t stream);

@@ -705,16 +705,11 @@ __device__ __forceinline__ void store_bucket(uint32_t *slot, const uint32_t *out
 
 // Where a bucket's string of `total` bits goes: the strings of a workgroup's buckets (a unit) stand in its first bucket's slot
 // and on, each from the next word.  Leaves what k_finish needs to know: every bucket's bit length, in the place of its offset,
-// and the words of all of them.  Called by all threads of the workgroup.  kCaller: levels that the caller has no business to
-// use may make strings longer than slots are; what would leave the unit is not stored.
+// and the words of all of them.  Called by all threads of the workgroup.
 // Each in a slot of its own, as they were, 27 words in 128 at 512 coordinates, left half-written lines and k_finish a bisection
 // over buckets for every four words: k_finish of 4 x 1.56 G coordinates 703 -> 560 us.
-struct Place {
-    uint32_t *slot;
-    bool store;
-};
-template <int TEAM, bool kCaller>
-__device__ __forceinline__ Place place_bucket(const EncodeParams &P, const EncodeOut &O, bool active, uint64_t b, uint32_t total)
+template <int TEAM>
+__device__ __forceinline__ uint32_t *place_bucket(const EncodeOut &O, bool active, uint64_t b, uint32_t total)
 {
     constexpr uint32_t N = TeamGeom<TEAM>::kTeamsPerWG;
     const uint32_t tid = threadIdx.x % TEAM;
@@ -738,24 +733,37 @@ __device__ __forceinline__ Place place_bucket(const EncodeParams &P, const Encod
     if (threadIdx.x == N - 1u)
         *O.unit_words = inc;
     const uint32_t end = (uint32_t)__shfl((int)inc, (int)(row | team), kWave);
-    bool store = active;
-    if constexpr (kCaller)
-        store = active && end <= (uint32_t)min((uint64_t)N, P.nb - (uint64_t)blockIdx.x * N) * P.slot_words;
-    return Place{O.unit + (end - words), store};
+    return O.unit + (end - words);
 }
 
 // The same for a workgroup of one bucket, whose slot is its unit.  The lengths are left at the end: a store ahead of the
 // barriers of the coding phase would be waited for there.
-template <bool kCaller>
-__device__ __forceinline__ bool fits_slot(const EncodeParams &P, uint32_t total)
-{
-    return !kCaller || (total + 31u) >> 5 <= P.slot_words;
-}
 __device__ __forceinline__ void report_length(const EncodeOut &O, uint64_t b, uint32_t total, uint32_t tid)
 {
     if (tid == 0) {
         O.bit_off[b + 1] = total;
         *O.unit_words = (total + 31u) >> 5;
+    }
+}
+
+// Slots have room for the longest string of levels up to s + 1.  Levels above that (nuq_encode's caller's error: kCaller) can
+// make a longer one; such a bucket is refused as a whole, whatever its neighbours hold: one word of ones in place of its
+// string, which no decoder takes (its level code does not end), index entries of 0, and the flag.
+constexpr uint32_t kRefusedBits = 32u;
+template <bool kCaller>
+__device__ __forceinline__ bool refused(const EncodeParams &P, uint32_t total)
+{
+    return kCaller && __builtin_expect((total + 31u) >> 5 > P.slot_words, 0);
+}
+template <int TEAM>
+__device__ __forceinline__ void refuse_bucket(const EncodeParams &P, const EncodeOut &O, uint64_t b, uint32_t *slot)
+{
+    const uint32_t tid = threadIdx.x % TEAM;
+    for (uint32_t i = tid; i < P.nsync; i += TEAM)
+        O.sync[b * P.nsync + i] = 0u;
+    if (tid == 0) {
+        slot[0] = ~0u;
+        atomicOr(P.flags, kFlagMalformed);
     }
 }
 
@@ -797,7 +805,7 @@ struct Unlisted {
     }
     // off0: the chunk's first bit, total: of the bucket
     __device__ __forceinline__ void emit(const EncodeOut &O, bool active, uint64_t b, uint32_t off0, uint32_t total,
-                                         const Place &at) const
+                                         uint32_t *slot) const
     {
         const uint32_t tid = threadIdx.x % TEAM;
         const uint32_t nwords = (total + 31u) >> 5;
@@ -850,13 +858,13 @@ struct Unlisted {
         if (kSmallTeam<TEAM> || nwords <= cap) {                                     // uniform over the team
             emit_first(~0u);
             team_barrier<TEAM>();
-            if (at.store)
-                store_bucket<TEAM>(at.slot, obuf, nwords, tid);
+            if (active)
+                store_bucket<TEAM>(slot, obuf, nwords, tid);
         } else {
             emit_first(cap - 1u);
             team_barrier<TEAM>();
-            if (at.store)
-                store_bucket<TEAM>(at.slot, obuf, cap, tid);
+            if (active)
+                store_bucket<TEAM>(slot, obuf, cap, tid);
             for (uint32_t lo = cap; lo < nwords; lo += cap) {
                 team_barrier<TEAM>();
                 clear(min(nwords - lo, cap));
@@ -868,8 +876,8 @@ struct Unlisted {
                     w.flush(obuf, cap - 1u);
                 }
                 team_barrier<TEAM>();
-                if (at.store)
-                    store_bucket<TEAM>(at.slot + lo, obuf, min(nwords - lo, cap), tid);
+                if (active)
+                    store_bucket<TEAM>(slot + lo, obuf, min(nwords - lo, cap), tid);
             }
         }
     }
@@ -914,11 +922,15 @@ __device__ __forceinline__ void code_listed_large(const EncodeParams &P, const E
     const uint32_t off0 = team_exclusive_sum<TEAM, false>(bits, L.scratch + 16, total);
     const uint32_t nwords = (total + 31u) >> 5;
     const bool in_lds = nwords <= P.out_cap;                     // uniform over the team (the buffer was cleared before)
-    const bool store = active && fits_slot<kCaller>(P, total);
+    if (refused<kCaller>(P, total)) {                            // (so is this)
+        refuse_bucket<TEAM>(P, O, b, slot);
+        report_length(O, b, kRefusedBits, tid);
+        return;
+    }
     if (P.nsync)
         L.run_off[tid] = off0;
     if (!in_lds) {
-        if (store) {
+        if (active) {
             for (uint32_t i = tid; i < nwords; i += TEAM)
                 slot[i] = 0u;
             __threadfence();   // the zeros are in place before any record is OR-ed over them
@@ -944,7 +956,7 @@ __device__ __forceinline__ void code_listed_large(const EncodeParams &P, const E
     };
     if (in_lds)
         emit_all(L.out);
-    else if (store)
+    else if (active)
         emit_all(slot);
     team_barrier<TEAM>();
     uint32_t *const sg = O.sync + (active ? b : 0) * P.nsync;
@@ -970,7 +982,7 @@ __device__ __forceinline__ void code_listed_large(const EncodeParams &P, const E
         if (active)
             sg[i] = entry;
     }
-    if (store && in_lds)
+    if (active && in_lds)
         store_bucket<TEAM>(slot, L.out, nwords, tid);
     report_length(O, b, total, tid);
 }
@@ -1020,10 +1032,14 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
     }
     uint32_t total;
     const uint32_t off0 = team_exclusive_sum<TEAM>(bits, nullptr, total);
-    const Place at = place_bucket<TEAM, kCaller>(P, O, active, b, total);
-    uint32_t *const slot = at.slot;
+    const bool refuse = refused<kCaller>(P, total);              // uniform over the team; not where the team has no bucket
+    uint32_t *const slot = place_bucket<TEAM>(O, active, b, refuse ? kRefusedBits : total);
+    if (refuse) {
+        refuse_bucket<TEAM>(P, O, b, slot);
+        return;
+    }
     if (!listed) {
-        U.emit(O, active, b, off0, total, at);
+        U.emit(O, active, b, off0, total, slot);
         return;
     }
     const uint32_t nwords = (total + 31u) >> 5;
@@ -1034,7 +1050,7 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
     if (in_lds) {                                                // (the bytes have been read to the end: their place is free)
         for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
             *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
-    } else if (at.store) {
+    } else if (active) {
         for (uint32_t i = tid; i < nwords; i += TEAM)
             slot[i] = 0u;
         __threadfence();       // the zeros are in place before any record is OR-ed over them
@@ -1063,13 +1079,13 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
     };
     if (in_lds)
         emit_all(L.out);
-    else if (at.store)
+    else if (active)
         emit_all(slot);
     team_barrier<TEAM>();
     if (active) {
         if (tid < P.nsync)
             O.sync[b * P.nsync + tid] = entry ? (uint32_t)L.rec[r_entry] | (e_entry << 21) : 0u;
-        if (in_lds && at.store)
+        if (in_lds)
             store_bucket<TEAM>(slot, L.out, nwords, tid);
     }
 }
@@ -1140,8 +1156,12 @@ __device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const Enc
         U.count();
         uint32_t total;
         const uint32_t off0 = team_exclusive_sum<TEAM>(U.bits, L.scratch + 32, total);
-        U.emit(O, active, b, off0, total, Place{O.unit, fits_slot<kCaller>(P, total)});
-        report_length(O, b, total, threadIdx.x);
+        const bool refuse = refused<kCaller>(P, total);
+        if (refuse)
+            refuse_bucket<TEAM>(P, O, b, O.unit);
+        else
+            U.emit(O, active, b, off0, total, O.unit);
+        report_length(O, b, refuse ? kRefusedBits : total, threadIdx.x);
     }
 }
 
@@ -1556,9 +1576,6 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
             my_len = load_len(b_first + FB);
         const uint32_t total = pstart[FB];
         const uint32_t *__restrict__ staging = P.staging + ((uint64_t)blockIdx.y * P.nb + b_first) * P.slot_words;
-        // words that a unit has room for (see place_bucket's kCaller)
-        const uint32_t here = (uint32_t)min((uint64_t)FB, P.nb - b_first);
-        auto room = [&](uint32_t j) { return kUnits ? (here - min(j, here)) * P.slot_words : P.slot_words; };
         constexpr uint32_t kFlight = 4;         // pieces per thread under way at once
         for (uint32_t p0 = tid; !summed || p0 < total; p0 += kFlight * WG) {
             uint4 x[kFlight];
@@ -1573,7 +1590,7 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
                         j += (pstart[j + step] <= p) ? step : 0u;
                 bkt[q] = j << unit_shift;
                 at[q] = 4u * (p - pstart[j]);
-                if (p < total && at[q] < room(bkt[q]))
+                if (p < total)
                     x[q] = *reinterpret_cast<const uint4 *>(staging + (uint64_t)bkt[q] * P.slot_words + at[q]);
             }
             if (!summed) {                      // (once, with the first pieces under way)

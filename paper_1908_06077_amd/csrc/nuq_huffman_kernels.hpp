@@ -363,7 +363,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
     team_barrier<TEAM>();
     uint32_t *slot = O.unit;
     if constexpr (TeamGeom<TEAM>::kTeamsPerWG > 1)
-        slot = place_bucket<TEAM, false>(P, O, active, b, total).slot;
+        slot = place_bucket<TEAM>(O, active, b, total);
     if (active) {
         store_bucket<TEAM>(slot, field, (total + 31u) >> 5, tid);
         uint32_t *sg = O.sync + b * P.nsync;

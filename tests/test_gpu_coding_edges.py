@@ -106,3 +106,56 @@ def test_strings_of_one_window_and_of_two(g, n, S):
     np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
     if S:
         np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)
+
+
+@pytest.mark.parametrize("s", [1, 3])
+@pytest.mark.parametrize("n,S", [(64, 64), (200, 0), (300, 64), (512, 128), (1000, 256), (1024, 0), (2000, 64), (2049, 512),
+                                 (3000, 0), (8192, 256), (16384, 128), (20001, 512), (32768, 1024)])
+def test_strings_longer_than_slots(g, n, S, s):
+    """Levels above s + 1 can make a string longer than any of levels up to it: of exactly a slot's words it is coded like any
+    other, a word longer it is refused.  The bucket is one word of ones, the flag is raised, decoders refuse it, and no other
+    bucket changes, in the same workgroup or not."""
+    nuq = g.nuq
+    rng = np.random.default_rng(n + s)
+    slot = ((n * (5 if s == 1 else 8) + 31) // 32 + 3) & ~3
+    x = (32 * slot - 3 * n) // 6                            # records of 9 bits (level 15), the others take 3 (level 1)
+
+    def full(high):
+        b = np.ones(n, dtype=np.uint8)
+        b[rng.permutation(n)[:high]] = 15
+        return b | (rng.integers(0, 2, n) << 7).astype(np.uint8)
+
+    def ordinary():
+        return np.where(rng.random(n) < 0.2, rng.integers(1, s + 2, n) | (rng.integers(0, 2, n) << 7), 0).astype(np.uint8)
+    every_other = np.where(np.arange(n) % 2 == 0, 15, 0).astype(np.uint8)
+    buckets = [ordinary(), full(x + 1), ordinary(), full(x), np.zeros(n, dtype=np.uint8), full(n), full(n), every_other, ordinary(),
+               ordinary()] + ([ordinary() for _ in range(9)] + [full(x + 1), ordinary()[: n // 2]])
+    q = np.concatenate(buckets)
+    d = q.size
+    bit_off, words, sync, kept = [0], [], [], []
+    for b in buckets:
+        bo, w, sy = oracle.encode(b, n, 14, S)
+        kept.append(w.size <= slot)
+        bits, w, sy = (int(bo[1]), w, sy) if kept[-1] else (32, np.array([0xFFFFFFFF], dtype=np.uint32), np.zeros_like(sy))
+        bit_off.append(32 * sum(v.size for v in words) + bits)
+        words.append(w)
+        sync.append(sy)
+    assert kept[:7] == [True, False, True, True, True, False, False] and not kept[-2] and words[3].size == slot
+    m = g.alloc_message(d, n, 14, S)
+    nuq.nuq_encode(torch.from_numpy(q).to(g.DEV), n, s, S, m.bit_off, m.words, m.sync if S else None, g.workspace(d, n, s))
+    assert nuq.nuq_last_error_flags() == nuq.FLAG_MALFORMED
+    words = np.concatenate(words)
+    np.testing.assert_array_equal(g.u64(m.bit_off), np.array(bit_off, dtype=np.uint64))
+    np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
+    assert not g.u32(m.words)[words.size:].any()
+    if S:
+        np.testing.assert_array_equal(g.u32(m.sync), np.concatenate(sync))
+    m.norms.fill_(1.0)
+    legal = np.concatenate([np.full(b.size, k and (b & 127).max() <= s + 1) for k, b in zip(kept, buckets)])
+    level = (q & 127).astype(np.int64)
+    want = np.where(level > 0, np.ldexp(1.0, level - 1 - s), 0.0) * np.where(q >> 7, -1.0, 1.0)
+    out = torch.empty(d, dtype=torch.float32, device=g.DEV)
+    for msgs in ([m], [m, m]):
+        nuq.nuq_decode_accumulate(msgs, d, n, s, S, 1.0 / len(msgs), False, out)
+        assert nuq.nuq_last_error_flags() == nuq.FLAG_MALFORMED
+        np.testing.assert_array_equal(out.cpu().numpy()[legal], want[legal].astype(np.float32))
