@@ -1508,12 +1508,15 @@ __global__ __launch_bounds__(256) void k_chunk_scan(uint64_t *chunk_sums, uint64
 // strings as soon as the lengths are there (their place in the staging area does not depend on the sum), and everything moves
 // in pieces of four words (a unit's last piece may be shorter; any 4-byte aligned address takes a 16-byte store), each
 // found by one bisection.
-// kUnits: units of several buckets.
+// kUnits: units of several buckets (groups of four: one unit).  Their words are read from `units`, not worked out from the
+// lengths by shuffles between the two scans, and what is needed only where the message is full stays a loop (unrolled, its LDS
+// reads took 16 registers): at most 64 vector registers, hence eight waves per SIMD.  With 66 to 78 it took 6.8 us instead of
+// 5.2 for 1 x 12 M coordinates in buckets of 1500, whose 8000 waves are more than seven per SIMD.
 template <uint32_t FB, uint32_t WG, bool kUnits>
 __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, const uint64_t *chunk_prefix,
                                                 uint64_t nchunks, uint32_t groups, uint32_t shift)
 {
-    const uint32_t unit_shift = kUnits ? shift : 0u;
+    const uint32_t unit_shift = kUnits ? (FB == 4u ? 2u : shift) : 0u;
     static_assert(FB == 4 || FB == 16 || FB == 64, "one wave scans the group's word counts");
     static_assert(WG == 64 || WG == 256, "block_sum_u64 adds four waves");
     __shared__ uint64_t scratch[4];
@@ -1526,11 +1529,14 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
     auto load_len = [&](uint64_t b0) {
         return tid < FB && b0 + tid < P.nb ? (uint32_t)W.bit_off[b0 + tid + 1] : 0u;
     };
+    auto load_unit = [&](uint64_t b0) {
+        return kUnits && tid < nunits && b0 + ((uint64_t)tid << unit_shift) < P.nb ? units[(b0 >> unit_shift) + tid] : 0u;
+    };
 
     // A workgroup takes `groups` consecutive groups of FB buckets: the words before its first bucket are summed once
     // (from the chunk's start), after that the running total carries over from group to group.
     uint64_t b_first = (uint64_t)blockIdx.x * groups * FB;
-    uint32_t my_len = load_len(b_first);
+    uint32_t my_len = load_len(b_first), my_unit = load_unit(b_first);
     const uint64_t u_first = b_first >> unit_shift;
     uint64_t lo = 0, base = 0;
     if (chunk_prefix) {
@@ -1554,15 +1560,8 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
 
     for (uint32_t g = 0; g < groups && b_first < P.nb; ++g, b_first += FB) {
         if (tid < kWave) {                      // the first wave: inclusive scans of the word and piece counts
-            uint32_t words = (my_len + 31u) >> 5;
-            const uint32_t wi = wave_inclusive_sum(words);
-            if constexpr (kUnits) {                 // words of unit tid
-                const uint32_t last = ((tid + 1u) << unit_shift) - 1u;
-                const uint32_t end = (uint32_t)__shfl((int)wi, (int)(last & (kWave - 1u)), kWave);
-                const uint32_t begin = (uint32_t)__shfl_up((int)end, 1, kWave);
-                words = tid < nunits ? end - (tid ? begin : 0u) : 0u;
-            }
-            const uint32_t pi = wave_inclusive_sum((words + 3u) >> 2);
+            const uint32_t words = (my_len + 31u) >> 5;
+            const uint32_t wi = wave_inclusive_sum(words), pi = wave_inclusive_sum(((kUnits ? my_unit : words) + 3u) >> 2);
             if (tid < FB) {
                 wstart[tid + 1] = wi;
                 pstart[tid + 1] = pi;
@@ -1572,8 +1571,10 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
         }
         __syncthreads();
         const uint32_t len = my_len;
-        if (g + 1u < groups)
+        if (g + 1u < groups) {
             my_len = load_len(b_first + FB);
+            my_unit = load_unit(b_first + FB);
+        }
         const uint32_t total = pstart[FB];
         const uint32_t *__restrict__ staging = P.staging + ((uint64_t)blockIdx.y * P.nb + b_first) * P.slot_words;
         constexpr uint32_t kFlight = 4;         // pieces per thread under way at once
@@ -1603,12 +1604,14 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
                 } else {
                     base += block_sum_u64(part, scratch);
                 }
+                base = uniform_u64(base);
                 summed = true;
             }
             // a bucket's words are written if all of them fit
             uint32_t fit = wstart[FB];
             if (kUnits && base + fit > W.words_cap) {
                 fit = 0;
+#pragma unroll 1
                 for (uint32_t i = 1; i < FB && base + wstart[i] <= W.words_cap; ++i)
                     fit = wstart[i];
             }
