@@ -437,7 +437,8 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
 // level code) is four to ten times what gradients produce.  So the team's index list and bit-string buffer hold `rec_cap`
 // nonzeros and `out_cap` words, sized for the usual case, and a bucket that exceeds one of them takes a slower way:
 //   nonzeros fit, bits fit  : as above
-//   nonzeros fit, bits don't: the same, but records are OR-ed into the (zeroed) staging slot in global memory
+//   nonzeros fit, bits don't: teams of several waves: the same, but records are OR-ed into the (zeroed) staging slot in global
+//                             memory; others: Unlisted
 //   nonzeros don't fit      : Unlisted
 //
 // The kernel is bound by vector issue, so what counts here is instructions per record and per coordinate.
@@ -650,9 +651,9 @@ struct TeamLds {
     uint16_t *rec;         // rec_cap indices ...
     uint32_t *out;         // ... then out_cap words of bit string; 16-byte aligned
     uint32_t *sync_l;      // nsync (buckets that are not listed) ...
-    uint32_t *blk;         // nblk + 1: records before each block of the index
     uint32_t *run_off;     // ... or TEAM (large teams, listed buckets): bit offset of every thread's run
-    uint32_t *scratch;     // 64
+    uint32_t *blk;         // nblk + 1 (large teams): records before each block of the index
+    uint32_t *scratch;     // 64 (large teams)
     const uint32_t *tables;
 };
 
@@ -704,23 +705,29 @@ __device__ __forceinline__ void store_bucket(uint32_t *slot, const uint32_t *out
 }
 
 // Where a bucket's string of `total` bits goes: the strings of a workgroup's buckets (a unit) stand in its first bucket's slot
-// and on, each from the next word.  Leaves what k_finish needs to know: every bucket's bit length, in the place of its offset,
-// and the words of all of them.  Called by all threads of the workgroup.
+// and on, each from the next word.  In two steps, each called by all threads of the workgroup: its words are announced as soon
+// as they are known, the place is worked out when the string is complete, after a barrier of the workgroup; asked for before
+// the string was assembled it kept every team waiting for the workgroup's slowest in the middle of its life (8 x 0.3 M
+// coordinates in buckets of 1000 12.0 us, 11.6 so).  Leaves what k_finish needs to know: every bucket's bit length, in the place
+// of its offset, and the words of all of them.
 // Each in a slot of its own, as they were, 27 words in 128 at 512 coordinates, left half-written lines and k_finish a bisection
 // over buckets for every four words: k_finish of 4 x 1.56 G coordinates 703 -> 560 us.
 template <int TEAM>
-__device__ __forceinline__ uint32_t *place_bucket(const EncodeOut &O, bool active, uint64_t b, uint32_t total)
+using UnitWords = uint32_t[TeamGeom<TEAM>::kTeamsPerWG];       // in LDS
+template <int TEAM>
+__device__ __forceinline__ void announce_bucket(UnitWords<TEAM> &words, bool active, uint32_t total)
+{
+    if (threadIdx.x % TEAM == 0)
+        words[threadIdx.x / TEAM] = active ? (total + 31u) >> 5 : 0u;
+}
+template <int TEAM>
+__device__ __forceinline__ uint32_t *place_bucket(const UnitWords<TEAM> &words, const EncodeOut &O, bool active, uint64_t b,
+                                                  uint32_t total)
 {
     constexpr uint32_t N = TeamGeom<TEAM>::kTeamsPerWG;
-    const uint32_t tid = threadIdx.x % TEAM;
-    const uint32_t words = active ? (total + 31u) >> 5 : 0u;
     static_assert(N > 1u && N <= (uint32_t)kRow, "one row of lanes scans the word counts");
-    __shared__ uint32_t team_words[N];
     const uint32_t team = threadIdx.x / TEAM, row = threadIdx.x & (kWave - 1u) & ~(uint32_t)(kRow - 1);
-    if (tid == 0)
-        team_words[team] = words;
-    __syncthreads();
-    uint32_t inc = team_words[threadIdx.x & (N - 1u)];
+    uint32_t inc = words[threadIdx.x & (N - 1u)];
     inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x111, 0xf, 0xf, true);   // row_shr:1
     inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x112, 0xf, 0xf, true);   // row_shr:2
     if constexpr (N > 4u)
@@ -728,12 +735,12 @@ __device__ __forceinline__ uint32_t *place_bucket(const EncodeOut &O, bool activ
     if constexpr (N > 8u)
         inc += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)inc, 0x118, 0xf, 0xf, true);   // row_shr:8
     // (the first N lanes of a row hold the sums; N < 16: those behind start from them)
-    if (active && tid == 0)
+    if (active && threadIdx.x % TEAM == 0)
         O.bit_off[b + 1] = total;
     if (threadIdx.x == N - 1u)
         *O.unit_words = inc;
     const uint32_t end = (uint32_t)__shfl((int)inc, (int)(row | team), kWave);
-    return O.unit + (end - words);
+    return O.unit + (end - (active ? (total + 31u) >> 5 : 0u));
 }
 
 // The same for a workgroup of one bucket, whose slot is its unit.  The lengths are left at the end: a store ahead of the
@@ -803,14 +810,15 @@ struct Unlisted {
         bits = 0;
         for_my_records([&](int, uint32_t, uint32_t len) { bits += len; });
     }
-    // off0: the chunk's first bit, total: of the bucket
+    __device__ __forceinline__ uint32_t *string() const { return reinterpret_cast<uint32_t *>(L.rec); }
+    // off0: the chunk's first bit, total: of the bucket.  The string of a small team's bucket is left at string().
     __device__ __forceinline__ void emit(const EncodeOut &O, bool active, uint64_t b, uint32_t off0, uint32_t total,
-                                         uint32_t *slot) const
+                                         uint32_t *slot = nullptr) const
     {
         const uint32_t tid = threadIdx.x % TEAM;
         const uint32_t nwords = (total + 31u) >> 5;
-        uint32_t *const obuf = reinterpret_cast<uint32_t *>(L.rec);
-        const uint32_t cap = kSmallTeam<TEAM> ? ~0u : (uint32_t)(L.out - obuf) + P.out_cap;      // a multiple of four (small teams: all of it fits)
+        uint32_t *const obuf = string();
+        const uint32_t cap = kSmallTeam<TEAM> ? ~0u : (uint32_t)(L.out - obuf) + P.out_cap;   // a multiple of four
         auto clear = [&](uint32_t n) {
             for (uint32_t i = 4u * tid; i < n; i += 4u * TEAM)
                 *reinterpret_cast<uint4 *>(obuf + i) = uint4{0u, 0u, 0u, 0u};
@@ -821,7 +829,8 @@ struct Unlisted {
         uint32_t *const sg = O.sync + (active ? b : 0) * P.nsync;
         const uint32_t pmask = (1u << P.pieces_shift) - 1u;
         for (uint32_t i = tid; i < P.nsync; i += TEAM) {
-            const uint32_t f = L.blk[i >> P.pieces_shift], n = L.blk[(i >> P.pieces_shift) + 1u] - f;
+            const uint32_t f = kSmallTeam<TEAM> ? 0u : L.blk[i >> P.pieces_shift];       // (a small bucket is one block)
+            const uint32_t n = kSmallTeam<TEAM> ? C.nnz : L.blk[(i >> P.pieces_shift) + 1u] - f;
             const uint32_t r = f + (((i & pmask) * n) >> P.pieces_shift);
             if (r >= C.nnz && active)
                 sg[i] = total;
@@ -855,7 +864,9 @@ struct Unlisted {
             if (C.nz)
                 w.flush(obuf, last_word);
         };
-        if (kSmallTeam<TEAM> || nwords <= cap) {                                     // uniform over the team
+        if constexpr (kSmallTeam<TEAM>) {
+            emit_first(~0u);
+        } else if (nwords <= cap) {                                                  // uniform over the team
             emit_first(~0u);
             team_barrier<TEAM>();
             if (active)
@@ -991,8 +1002,9 @@ __device__ __forceinline__ void code_listed_large(const EncodeParams &P, const E
 // A bucket is one block of the index and has at most one entry per thread.  While records are emitted, a record's place in
 // the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 27 bits), so the thread
 // of entry i reads its record's index before and its offset after.
-// A wave may hold teams whose bucket is listed and others whose is not; the workgroup's place in the staging area is worked
-// out where they are together.
+// A wave may hold teams whose bucket is listed and others whose is not; they come together where the workgroup's strings are
+// placed.  A listed bucket whose string is longer than the bytes' place (levels of 8 and up, nearly every coordinate nonzero) is
+// coded like one that is not listed.
 template <int TEAM, bool kCaller>
 __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOut &O, bool active, uint64_t b,
                                        const TeamLds &L, const Chunk &C, bool listed)
@@ -1007,6 +1019,7 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
     uint32_t kept[kKeptRecords] = {}, bits = 0;
     uint16_t *const run = L.rec + r0;
     const bool many = __any(listed && n > kUsualRecords);
+    __shared__ UnitWords<TEAM> unit_words;
     Unlisted<TEAM, kCaller> U{P, L, C, -1, 0u};
     if (listed) {
         const auto record = make_records<TEAM, kCaller>(L.tables, P.s);
@@ -1031,32 +1044,27 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
         bits = U.bits;
     }
     uint32_t total;
-    const uint32_t off0 = team_exclusive_sum<TEAM>(bits, nullptr, total);
-    const bool refuse = refused<kCaller>(P, total);              // uniform over the team; not where the team has no bucket
-    uint32_t *const slot = place_bucket<TEAM>(O, active, b, refuse ? kRefusedBits : total);
-    if (refuse) {
-        refuse_bucket<TEAM>(P, O, b, slot);
-        return;
-    }
-    if (!listed) {
-        U.emit(O, active, b, off0, total, slot);
-        return;
-    }
+    uint32_t off0 = team_exclusive_sum<TEAM>(bits, nullptr, total);
     const uint32_t nwords = (total + 31u) >> 5;
-    const bool in_lds = nwords <= P.out_cap;                     // uniform over the team
-    const bool entry = tid < P.nsync && nnz;
+    const bool refuse = refused<kCaller>(P, total);              // uniform over the team, like what follows
+    const uint32_t sent = refuse ? kRefusedBits : total;
+    announce_bucket<TEAM>(unit_words, active, sent);
+    if (listed && nwords > P.out_cap) {                          // the bytes' place is too small
+        listed = false;
+        U.count();
+        uint32_t same;
+        off0 = team_exclusive_sum<TEAM>(U.bits, nullptr, same);
+    }
+    const bool entry = listed && tid < P.nsync && nnz;
     const uint32_t r_entry = (tid * nnz) >> P.pieces_shift;      // < nnz for an entry
     const uint32_t e_entry = entry ? (uint32_t)L.rec[r_entry] : 0u;
-    if (in_lds) {                                                // (the bytes have been read to the end: their place is free)
+    if (refuse) {
+    } else if (!listed) {
+        U.emit(O, active, b, off0, total);
+    } else {                                                     // (the bytes have been read to the end: their place is free)
         for (uint32_t i = 4u * tid; i < nwords; i += 4u * TEAM)
             *reinterpret_cast<uint4 *>(L.out + i) = uint4{0u, 0u, 0u, 0u};
-    } else if (active) {
-        for (uint32_t i = tid; i < nwords; i += TEAM)
-            slot[i] = 0u;
-        __threadfence();       // the zeros are in place before any record is OR-ed over them
-    }
-    team_barrier<TEAM>();
-    auto emit_all = [&](uint32_t *dst) {
+        team_barrier<TEAM>();
         BitWriter w(off0);
         uint32_t t = off0;
         auto emit = [&](uint32_t i) {
@@ -1064,7 +1072,7 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
                 run[i] = (uint16_t)t;
                 const uint32_t len = kept[i] >> 27;
                 t += len;
-                w.put(dst, kept[i] & 0x7ffffffu, len);
+                w.put(L.out, kept[i] & 0x7ffffffu, len);
             }
         };
 #pragma unroll
@@ -1075,19 +1083,19 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
             for (uint32_t i = kUsualRecords; i < kKeptRecords; ++i)
                 emit(i);
         if (n)
-            w.flush(dst);
-    };
-    if (in_lds)
-        emit_all(L.out);
-    else if (active)
-        emit_all(slot);
-    team_barrier<TEAM>();
-    if (active) {
-        if (tid < P.nsync)
-            O.sync[b * P.nsync + tid] = entry ? (uint32_t)L.rec[r_entry] | (e_entry << 21) : 0u;
-        if (in_lds)
-            store_bucket<TEAM>(slot, L.out, nwords, tid);
+            w.flush(L.out);
     }
+    __syncthreads();
+    uint32_t *const slot = place_bucket<TEAM>(unit_words, O, active, b, sent);
+    if (!active)
+        return;
+    if (refuse) {
+        refuse_bucket<TEAM>(P, O, b, slot);
+        return;
+    }
+    if (listed && tid < P.nsync)
+        O.sync[b * P.nsync + tid] = entry ? (uint32_t)L.rec[r_entry] | (e_entry << 21) : 0u;
+    store_bucket<TEAM>(slot, listed ? L.out : U.string(), nwords, tid);
 }
 
 // kCaller: the bytes are flag_caller_bytes'.
@@ -1117,7 +1125,7 @@ __device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const Enc
     C.nz = ((uint64_t)half[1] << 32) | half[0];
     C.rank0 = team_exclusive_sum<TEAM, false>((uint32_t)(__popc(half[0]) + __popc(half[1])), L.scratch, C.nnz);
     const bool listed = C.nnz <= P.rec_cap;        // uniform over the team
-    if (P.nsync && (!kSmallTeam<TEAM> || !listed)) {
+    if (P.nsync && !kSmallTeam<TEAM>) {
         // blk[t] = records before block t of the decoder index: the thread whose chunk holds the block's first
         // coordinate counts its own nonzeros below it (every block starts inside exactly one chunk)
         constexpr uint32_t kBlock = 1u << kSyncBlockShift;
@@ -1202,9 +1210,9 @@ struct TeamLdsMap {
 __host__ __device__ inline TeamLdsMap team_lds_map(uint32_t bucket, uint32_t rows, uint32_t team, uint32_t rec_cap,
                                                    uint32_t out_cap, uint32_t nsync, uint32_t nblk)
 {
-    const bool small = team <= (uint32_t)kWave;
     // a bucket of a small team whose nonzeros do not fit the list assembles its string in the list's place: at most nine bits
     // per coordinate (sign, level code of seven bits, one bit of gap each)
+    const bool small = team <= (uint32_t)kWave;
     const uint32_t list = (rec_cap + 1u) / 2u, dense = small ? (bucket * 9u + 31u) / 32u : 0u;
     TeamLdsMap m;
     m.rec = rows * team;
@@ -1214,7 +1222,7 @@ __host__ __device__ inline TeamLdsMap team_lds_map(uint32_t bucket, uint32_t row
     m.run_off = m.sync;
     m.blk = m.sync + (small || nsync > team ? nsync : team);
     m.scratch = (m.blk + nblk + 2u) & ~1u;                         // 8-byte aligned
-    m.words = (m.scratch + (small ? 0u : 64u) + 3u) & ~3u;         // small teams need no scratch
+    m.words = ((small ? m.blk : m.scratch + 64u) + 3u) & ~3u;      // small teams need neither block counts nor scratch
     return m;
 }
 
@@ -1396,8 +1404,8 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG, kSmallTeam<TEAM> && MODE == 0 
     const TeamLdsMap map = team_lds_map(P.bucket, P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk);
     uint32_t *const lds = smem + team * map.words;
     uint32_t *const tables = smem + TeamGeom<TEAM>::kTeamsPerWG * map.words;
-    const TeamLds L{lds, reinterpret_cast<uint16_t *>(lds + map.rec), lds + map.out, lds + map.sync, lds + map.blk,
-                    lds + map.run_off, lds + map.scratch, tables};
+    const TeamLds L{lds, reinterpret_cast<uint16_t *>(lds + map.rec), lds + map.out, lds + map.sync, lds + map.run_off,
+                    lds + map.blk, lds + map.scratch, tables};
     const TableCopy<TEAM> copy(P.s);
     const EncodeOut O = encode_out<TEAM>(P, W);
 

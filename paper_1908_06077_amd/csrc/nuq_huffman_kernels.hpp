@@ -360,10 +360,15 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_huffman_fused(EncodePar
         __syncthreads();
         total = huffman_from_lds<TEAM>(P, enc, qb32, field, sync_l, scratch, nbk, tid);
     }
-    team_barrier<TEAM>();
     uint32_t *slot = O.unit;
-    if constexpr (TeamGeom<TEAM>::kTeamsPerWG > 1)
-        slot = place_bucket<TEAM>(O, active, b, total);
+    if constexpr (TeamGeom<TEAM>::kTeamsPerWG > 1) {
+        __shared__ UnitWords<TEAM> unit_words;
+        announce_bucket<TEAM>(unit_words, active, total);
+        __syncthreads();
+        slot = place_bucket<TEAM>(unit_words, O, active, b, total);
+    } else {
+        team_barrier<TEAM>();
+    }
     if (active) {
         store_bucket<TEAM>(slot, field, (total + 31u) >> 5, tid);
         uint32_t *sg = O.sync + b * P.nsync;
