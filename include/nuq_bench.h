@@ -1,8 +1,9 @@
-/* Measurement aid of libnuq.so: per-launch kernel times for benchmarks.
+/* Measurement aids of libnuq.so: per-launch kernel times for benchmarks, launch shapes for tests.
  *
- * Not part of the method and not needed by a caller of include/nuq.h: bench.py uses it to bracket the
- * main kernel of each entry point with HIP events on the stream the kernel is launched on.  The
- * capture is process-global state: one capture at a time, not thread-safe.
+ * Not part of the method and not needed by a caller of include/nuq.h: bench.py brackets the main kernel
+ * of each entry point with HIP events on the stream the kernel is launched on (the capture is
+ * process-global state: one capture at a time, not thread-safe), and the tests ask where the lines of a
+ * launch rule lie, so that their inputs stay on both sides of them.
  */
 #ifndef NUQ_BENCH_H
 #define NUQ_BENCH_H
@@ -26,6 +27,14 @@ int nuq_timing_begin(uint32_t max_launches);
 /* Waits for the bracketed launches, writes up to `cap` durations (milliseconds) and entry-point
  * ids to the HOST arrays ms[] and entry[], the number written to *count, and ends the capture. */
 int nuq_timing_collect(float *ms, int32_t *entry, uint32_t cap, uint32_t *count);
+
+/* How the main kernel of the ERC encoders is laid out for a call of these sizes (host arithmetic).  mode 0:
+ * nuq_quantize_encode(_batch), 1: nuq_encode, 2: nuq_quantize_encode_table_batch (levels, norm_kind as
+ * there, HOST memory; ignored in the others).  shape (HOST, 4 values): threads per bucket; nonzeros that
+ * a bucket's list in LDS holds; words of its bit string that the string's buffer holds; words of the
+ * string of a bucket whose nonzeros do not fit the list that are put together at once. */
+int nuq_encode_shape(uint32_t mode, uint32_t K, uint64_t d, uint32_t bucket, uint32_t s,
+                     uint32_t sync_stride, const float *levels, uint32_t norm_kind, uint32_t *shape);
 
 #ifdef __cplusplus
 }

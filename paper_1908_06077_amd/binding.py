@@ -81,6 +81,7 @@ _SIGNATURES = {
     "nuq_moments_accumulate": (_i32, [_vp, _vp, _vp, _u64, _vp]),
     "nuq_normalized_variance": (_i32, [_vp, _vp, _u64, _u64, _vp, _u64, _vp, _vp]),
     "nuq_last_error_flags": (_i32, [_vp, _vp]),
+    "nuq_encode_shape": (_i32, [_u32, _u32, _u64, _u32, _u32, _u32, _vp, _u32, _vp]),
     "nuq_timing_begin": (_i32, [_u32]),
     "nuq_timing_collect": (_i32, [_vp, _vp, _u32, _vp]),
 }
@@ -604,6 +605,16 @@ def nuq_last_error_flags() -> int:
 # ------------------------------------------------------------ measurement aid
 
 T_NORMS, T_QUANTIZE, T_ENCODE, T_QUANTIZE_ENCODE, T_DECODE = 1, 2, 3, 4, 5
+
+
+def nuq_encode_shape(mode: int, K: int, d: int, bucket: int, s: int, sync_stride: int, levels=None,
+                     norm_kind: int = NORM_L2) -> tuple[int, int, int, int]:
+    """(threads per bucket, nonzeros its list holds, words of its string's buffer, words put together at once where the list
+    does not hold the nonzeros) of the ERC encoders' main kernel; mode 0: main levels, 1: nuq_encode, 2: a level table."""
+    shape = (_u32 * 4)()
+    table = (ctypes.c_float * (s + 2))(*levels) if mode == 2 else None
+    _check("nuq_encode_shape", _lib.nuq_encode_shape(mode, K, d, bucket, s, sync_stride, table, norm_kind, shape))
+    return tuple(shape)
 
 
 def nuq_timing_begin(max_launches: int) -> None:

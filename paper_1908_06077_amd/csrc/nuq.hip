@@ -282,6 +282,53 @@ uint32_t stream_loads(uint64_t d, uint32_t K)
     return d <= (1ull << 31) / K ? 1u : 0u;
 }
 
+// Nonzeros to be expected in a bucket of Gaussian coordinates whose first level is l1 of the norm: a coordinate of |z| standard
+// deviations is sent with probability min(1, |z| / z1), z1 of them being the first level.  (The largest |z| of 300 to 500 is 3.2.)
+double expected_nonzeros(uint32_t bucket, double l1, bool linf)
+{
+    const double z1 = l1 * (linf ? 3.2 : std::sqrt((double)bucket));
+    return bucket * (std::sqrt(2.0 / M_PI) / z1 * -std::expm1(-0.5 * z1 * z1) + std::erfc(z1 / M_SQRT2));
+}
+
+// Nonzeros that the LDS list of a team of the encoders holds (k_encode<TEAM, ., MODE>; l1, linf: its first level and norm).
+//
+// Teams of several waves: a quarter of the bucket (about four times what a Gaussian gradient produces), at least 1024; but no
+// more than 3584 of buckets of up to 16384, of which five then share a CU instead of four: heavy tails, 4 x 134 M coordinates in
+// buckets of 16384, both directions 605 -> 578 us.
+//
+// Teams of a wave or less: all of a bucket's coordinates up to 256, where eight workgroups, as many as there are waves for, share
+// a CU all the same, and above 512, but no more than kKeptRecords per thread.  257 to 512: what eight workgroups leave room for
+// (six with a level table, whose kernel has registers for no more), which is all of a bucket up to some 350 coordinates and 300
+// of 512.  A bucket that exceeds that costs half as much again, and where some do and others don't their waves go both ways.  So
+// where more than that are to be expected, but no more than kKeptRecords per thread, the list is as long as that, with seven
+// workgroups per CU (five); where still more are, it would be exceeded anyway.  4 x 12 M coordinates, 37 nonzeros in 64 for all ->
+// this: s = 4 in buckets of 300 127 -> 80 us, of 400 110 -> 74, of 512 75 -> 67; s = 5 in 450 122 -> 82; the whole list at s = 5 in
+// 512, 373 nonzeros of which it holds 384, would take 119 instead of 112.  QSGDinf at s = 3 in 300, both directions 227 -> 186.
+template <int TEAM, int MODE>
+uint32_t team_rec_cap(const EncodeParams &P, double l1)
+{
+    constexpr uint32_t kKept = TEAM * kKeptRecords, kTeams = TeamGeom<TEAM>::kTeamsPerWG;
+    const uint32_t bucket = P.bucket, quarter = bucket / 4u;
+    if constexpr (TEAM > kWave)
+        return bucket <= 4096u ? 1024u : bucket <= 16384u && quarter > 3584u ? 3584u : quarter;
+    if (TEAM > 16 || bucket <= 256u)
+        return std::min(kKept, bucket <= 1024u ? bucket : 1024u);
+    // LDS is given out in pieces of 1280 bytes; the list's words, a multiple of four, are what is free of a team's, or what the
+    // string of an unlisted bucket needs in their place
+    constexpr uint32_t kCU = 160u * 1024u, kPiece = 1280u, kStatic = kTeams * (4u + (MODE == 2 ? (uint32_t)sizeof(TableBins) : 0u));
+    const TeamLdsMap none = team_lds_map(P.slot_words, P.rows, TEAM, 0, P.out_cap, P.nsync, P.nblk);
+    auto room = [&](uint32_t groups) {
+        const uint32_t words = (kCU / groups / kPiece * kPiece - kStatic - 512u * 4u) / (4u * kTeams) & ~3u;
+        const uint32_t string = none.sync - none.rec;
+        return std::min(std::min(kKept, bucket), 2u * std::max(string, words - (none.words - string)));
+    };
+    constexpr uint32_t kGroups = MODE == 2 ? 6u : 8u;
+    const uint32_t usual = room(kGroups), most = room(kGroups - 1u);
+    const double mean = expected_nonzeros(bucket, l1, P.norm_linf), sd = std::sqrt(mean * (1.0 - mean / bucket));
+    const bool beyond = mean + 3.0 * sd + (P.norm_linf ? bucket / 16u : 0u) > usual;
+    return beyond && mean + 1.5 * sd <= most ? most : usual;
+}
+
 // float4 rows of a bucket per thread.  Their TEAM words each are where team_norm's partial sums go before the bytes do.
 template <int TEAM>
 uint32_t team_rows(uint32_t bucket)
@@ -354,6 +401,34 @@ int launch_finish(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, cons
                                      unit_shift, st);
 }
 
+// Sizes of k_encode<., ., MODE> for K workers' buckets (l1, linf: its first level and norm) into P, and what f(team, rows per
+// thread, LDS map) makes of them.
+template <int MODE, class F>
+int with_encode_shape(EncodeParams &P, uint32_t K, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride, double l1,
+                      bool linf, bool &narrow, F &&f)
+{
+    constexpr TeamUse kUse = MODE == 0 ? TeamUse::kErc : TeamUse::kErcOther;
+    P.d = d;
+    P.nb = nuq_num_buckets(d, bucket);
+    P.nb_stride = (P.nb + 3) & ~3ull;
+    P.bucket = bucket;
+    P.s = s;
+    P.nsync = nuq_num_sync(bucket, sync_stride);
+    P.pieces_shift = P.nsync ? sync_pieces_shift(bucket, sync_stride) : 0;
+    P.nblk = sync_blocks(bucket);
+    P.slot_words = slot_words_for(bucket, s);
+    P.norm_linf = linf ? 1u : 0u;
+    P.stream = stream_loads(d, K);
+    narrow = narrow_teams<kUse>(P.nb, K, bucket, s, linf, l1);
+    return dispatch_team<kUse>(bucket, narrow, [&](auto team_c, auto vpt_c) {
+        constexpr int TEAM = decltype(team_c)::value;
+        P.rows = team_rows<TEAM>(bucket);
+        P.out_cap = team_out_cap(P.slot_words, bucket, TEAM);
+        P.rec_cap = team_rec_cap<TEAM, MODE>(P, l1);
+        return f(team_c, vpt_c, team_lds_map(P.slot_words, P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk));
+    });
+}
+
 // MODE 0: fused norms + quantize + ENCODE from v.  MODE 1: ENCODE from level/sign bytes.  MODE 2: as 0 with the
 // level table `levels` (host memory, s + 2 values) and the norm `norm_kind` selects.
 template <int MODE>
@@ -382,8 +457,7 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
             return NUQ_EINVAL;
     }
     const uint64_t nb = nuq_num_buckets(d, bucket);
-    const uint32_t slot_words = slot_words_for(bucket, s);
-    const Workspace w = carve(workspace, K, nb, slot_words);
+    const Workspace w = carve(workspace, K, nb, slot_words_for(bucket, s));
     if (w.bytes > workspace_bytes)
         return NUQ_ECAPACITY;
     uint32_t *flags = flags_ptr();
@@ -392,30 +466,15 @@ int encode_batch(uint32_t K, const EncodeBatch &Wk, uint64_t d, uint32_t bucket,
     hipStream_t st = static_cast<hipStream_t>(stream);
 
     EncodeParams P{};
-    P.d = d;
-    P.nb = nb;
-    P.nb_stride = (nb + 3) & ~3ull;
-    P.bucket = bucket;
-    P.s = s;
-    P.nsync = nsync;
-    P.pieces_shift = nsync ? sync_pieces_shift(bucket, sync_stride) : 0;
-    P.nblk = sync_blocks(bucket);
-    P.slot_words = slot_words;
     P.units = w.units;
     P.staging = w.staging;
     P.flags = flags;
-    P.norm_linf = norm_kind == NUQ_NORM_LINF ? 1u : 0u;
-    P.stream = stream_loads(d, K);
-    constexpr TeamUse kUse = MODE == 0 ? TeamUse::kErc : TeamUse::kErcOther;
     const double l1 = MODE == 2 ? (double)levels[1] : std::ldexp(1.0, -(int)s);
-    const bool narrow = narrow_teams<kUse>(nb, K, bucket, s, P.norm_linf, l1);
-    int rc = dispatch_team<kUse>(bucket, narrow, [&](auto team_c, auto vpt_c) {
+    bool narrow = false;
+    int rc = with_encode_shape<MODE>(P, K, d, bucket, s, sync_stride, l1, norm_kind == NUQ_NORM_LINF, narrow,
+                                     [&](auto team_c, auto vpt_c, const TeamLdsMap &map) {
         constexpr int TEAM = decltype(team_c)::value, VPT = decltype(vpt_c)::value;
         using G = TeamGeom<TEAM>;
-        P.rows = team_rows<TEAM>(bucket);
-        P.rec_cap = team_rec_cap(bucket, TEAM);
-        P.out_cap = team_out_cap(slot_words, P.rows, TEAM);
-        const TeamLdsMap map = team_lds_map(bucket, P.rows, TEAM, P.rec_cap, P.out_cap, nsync, P.nblk);
         const size_t lds_bytes = ((size_t)map.words * G::kTeamsPerWG + 512) * 4;            // + the code tables
         if (lds_bytes > 160 * 1024)
             return (int)NUQ_EINVAL;
@@ -1731,6 +1790,29 @@ int nuq_last_error_flags(uint32_t *host_flags, nuq_stream_t stream)
     if (hipStreamSynchronize(st) != hipSuccess)
         return NUQ_EHIP;
     return NUQ_OK;
+}
+
+int nuq_encode_shape(uint32_t mode, uint32_t K, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride,
+                     const float *levels, uint32_t norm_kind, uint32_t *shape)
+{
+    if (mode > 2 || K < 1 || K > kMaxBatch || !valid_common(d, bucket, s) || !valid_sync(sync_stride) || !shape ||
+        (mode == 2 && (!levels || !valid_levels(levels, s))))
+        return NUQ_EINVAL;
+    EncodeParams P{};
+    bool narrow;
+    auto tell = [&](auto team_c, auto, const TeamLdsMap &map) {
+        constexpr int TEAM = decltype(team_c)::value;
+        shape[0] = TEAM;
+        shape[1] = P.rec_cap;
+        shape[2] = P.out_cap;
+        shape[3] = map.sync - map.rec;
+        return (int)NUQ_OK;
+    };
+    const double l1 = mode == 2 ? (double)levels[1] : std::ldexp(1.0, -(int)s);
+    const bool linf = mode == 2 && norm_kind == NUQ_NORM_LINF;
+    return mode == 0   ? with_encode_shape<0>(P, K, d, bucket, s, sync_stride, l1, linf, narrow, tell)
+           : mode == 1 ? with_encode_shape<1>(P, K, d, bucket, s, sync_stride, l1, linf, narrow, tell)
+                       : with_encode_shape<2>(P, K, d, bucket, s, sync_stride, l1, linf, narrow, tell);
 }
 
 int nuq_timing_begin(uint32_t max_launches)

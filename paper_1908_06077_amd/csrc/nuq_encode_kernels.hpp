@@ -437,8 +437,8 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
 // level code) is four to ten times what gradients produce.  So the team's index list and bit-string buffer hold `rec_cap`
 // nonzeros and `out_cap` words, sized for the usual case, and a bucket that exceeds one of them takes a slower way:
 //   nonzeros fit, bits fit  : as above
-//   nonzeros fit, bits don't: teams of several waves: the same, but records are OR-ed into the (zeroed) staging slot in global
-//                             memory; others: Unlisted
+//   nonzeros fit, bits don't: the same, but records are OR-ed into the (zeroed) staging slot in global memory (teams of several
+//                             waves; the others' buffer holds the longest string there is)
 //   nonzeros don't fit      : Unlisted
 //
 // The kernel is bound by vector issue, so what counts here is instructions per record and per coordinate.
@@ -647,9 +647,9 @@ __device__ __forceinline__ void team_barrier()
 
 // A team's LDS, in 32-bit words.
 struct TeamLds {
-    uint32_t *qb32;        // rows * TEAM: bytes
+    uint32_t *qb32;        // rows * TEAM: bytes (teams of a wave or less: then `out`)
     uint16_t *rec;         // rec_cap indices ...
-    uint32_t *out;         // ... then out_cap words of bit string; 16-byte aligned
+    uint32_t *out;         // ... then out_cap words of bit string (large teams); 16-byte aligned
     uint32_t *sync_l;      // nsync (buckets that are not listed) ...
     uint32_t *run_off;     // ... or TEAM (large teams, listed buckets): bit offset of every thread's run
     uint32_t *blk;         // nblk + 1 (large teams): records before each block of the index
@@ -1003,8 +1003,7 @@ __device__ __forceinline__ void code_listed_large(const EncodeParams &P, const E
 // the index list takes its bit offset instead (the list's 16 bits hold it: at most 2048 records of 27 bits), so the thread
 // of entry i reads its record's index before and its offset after.
 // A wave may hold teams whose bucket is listed and others whose is not; they come together where the workgroup's strings are
-// placed.  A listed bucket whose string is longer than the bytes' place (levels of 8 and up, nearly every coordinate nonzero) is
-// coded like one that is not listed.
+// placed.
 template <int TEAM, bool kCaller>
 __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOut &O, bool active, uint64_t b,
                                        const TeamLds &L, const Chunk &C, bool listed)
@@ -1044,17 +1043,11 @@ __device__ __forceinline__ void code_small(const EncodeParams &P, const EncodeOu
         bits = U.bits;
     }
     uint32_t total;
-    uint32_t off0 = team_exclusive_sum<TEAM>(bits, nullptr, total);
+    const uint32_t off0 = team_exclusive_sum<TEAM>(bits, nullptr, total);
     const uint32_t nwords = (total + 31u) >> 5;
-    const bool refuse = refused<kCaller>(P, total);              // uniform over the team, like what follows
+    const bool refuse = refused<kCaller>(P, total);              // uniform over the team
     const uint32_t sent = refuse ? kRefusedBits : total;
     announce_bucket<TEAM>(unit_words, active, sent);
-    if (listed && nwords > P.out_cap) {                          // the bytes' place is too small
-        listed = false;
-        U.count();
-        uint32_t same;
-        off0 = team_exclusive_sum<TEAM>(U.bits, nullptr, same);
-    }
     const bool entry = listed && tid < P.nsync && nnz;
     const uint32_t r_entry = (tid * nnz) >> P.pieces_shift;      // < nnz for an entry
     const uint32_t e_entry = entry ? (uint32_t)L.rec[r_entry] : 0u;
@@ -1173,33 +1166,21 @@ __device__ __forceinline__ void encode_from_lds(const EncodeParams &P, const Enc
     }
 }
 
-// What a team's LDS holds of a bucket's nonzero list and bit string.  Teams of several waves: a quarter of the worst case
-// (about four times what a Gaussian gradient produces), but no more than 3584 nonzeros of buckets of up to 16384, of which five
-// then share a CU instead of four: heavy tails, 4 x 134 M coordinates in buckets of 16384, both directions 605 -> 578 us.
-//
-// Teams of a wave or less keep every record of a listed bucket in registers before the first bit is written, so the string
-// takes the place of the bytes it was made from.  257 to 512 coordinates: the list holds 37 nonzeros in 64 (gradients: one in
-// four), with which eight workgroups of 16 buckets share a CU, as many as there are waves for.  Up to 256: all of them, since
-// eight workgroups fit beside that, and the smaller a bucket, the denser it is.  With the string in LDS of its own five fitted:
-// encode of 4 x 1.56 G coordinates 6.65 -> 6.00 ms, of 8 x 10 M in buckets of 1000 (half a wave each: four, now seven)
-// 92.8 -> 79.3 us.
-__host__ __device__ inline uint32_t team_rec_cap(uint32_t bucket, uint32_t team)
+// Words of a team's bit-string buffer, a multiple of four like the slot's.  Teams of several waves: a quarter of the worst case.
+// Teams of a wave or less keep every record of a listed bucket in registers before the first bit is written, so the string takes
+// the place of the bytes it was made from, and more than that where it can be longer, which it can from s = 7 on (nine bits to a
+// coordinate): the longest string of as many records as there may be is eight bits each for sign and level, and less than
+// 1.5 bits of gap code to a coordinate (ERC(2) takes 3 bits, ERC(4) 6, others less for what they skip).  (For longer ones than the
+// bytes' place records went to the slot in global memory one by one: 4 x 12 M coordinates at s = 14 in buckets of 64 4.84 ms, of 256
+// 1.83, of 600 1.62, where 0.17, 0.10 and 0.11 do.)
+__host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words, uint32_t bucket, uint32_t team)
 {
-    const uint32_t quarter = bucket / 4u;
-    const uint32_t cap = bucket <= 256u    ? bucket
-                         : bucket <= 512u  ? (bucket * 37u / 64u + 7u) & ~7u
-                         : bucket <= 1024u ? bucket
-                         : bucket <= 4096u ? 1024u
-                         : bucket <= 16384u && quarter > 3584u ? 3584u
-                                           : quarter;
-    return team <= (uint32_t)kWave && cap > team * kKeptRecords ? team * kKeptRecords : cap;
-}
-__host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words, uint32_t rows, uint32_t team)   // a multiple of 4, like slot_words
-{
-    const uint32_t quarter = (slot_words / 4u + 3u) & ~3u, bytes = rows * team;
-    if (team <= (uint32_t)kWave)
-        return slot_words < bytes ? slot_words : bytes;
-    return slot_words <= 256u ? slot_words : (quarter > 256u ? quarter : 256u);
+    const uint32_t quarter = (slot_words / 4u + 3u) & ~3u;
+    if (team > (uint32_t)kWave)
+        return slot_words <= 256u ? slot_words : quarter > 256u ? quarter : 256u;
+    const uint32_t records = bucket < team * kKeptRecords ? bucket : team * kKeptRecords;
+    const uint32_t longest = ((records * 8u + bucket + bucket / 2u + 31u) / 32u + 3u) & ~3u;
+    return slot_words < longest ? slot_words : longest;
 }
 
 // Offsets of a team's LDS regions (see TeamLds), in words; `words` in all, a multiple of 4.  The workgroup's code tables
@@ -1207,15 +1188,14 @@ __host__ __device__ inline uint32_t team_out_cap(uint32_t slot_words, uint32_t r
 struct TeamLdsMap {
     uint32_t rec, out, sync, blk, run_off, scratch, words;
 };
-__host__ __device__ inline TeamLdsMap team_lds_map(uint32_t bucket, uint32_t rows, uint32_t team, uint32_t rec_cap,
+__host__ __device__ inline TeamLdsMap team_lds_map(uint32_t slot_words, uint32_t rows, uint32_t team, uint32_t rec_cap,
                                                    uint32_t out_cap, uint32_t nsync, uint32_t nblk)
 {
-    // a bucket of a small team whose nonzeros do not fit the list assembles its string in the list's place: at most nine bits
-    // per coordinate (sign, level code of seven bits, one bit of gap each)
+    // (a bucket of a small team whose nonzeros do not fit the list assembles its string, a slot's words at most, in its place)
     const bool small = team <= (uint32_t)kWave;
-    const uint32_t list = (rec_cap + 1u) / 2u, dense = small ? (bucket * 9u + 31u) / 32u : 0u;
+    const uint32_t list = (rec_cap + 1u) / 2u, dense = small ? slot_words : 0u, bytes = rows * team;
     TeamLdsMap m;
-    m.rec = rows * team;
+    m.rec = small && out_cap > bytes ? out_cap : bytes;
     const uint32_t behind = m.rec + (((list > dense ? list : dense) + 3u) & ~3u);
     m.out = small ? 0u : behind;
     m.sync = behind + (small ? 0u : out_cap);
@@ -1401,7 +1381,7 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG, kSmallTeam<TEAM> && MODE == 0 
     const EncodeWorker &W = Wk.w[blockIdx.y];
     const uint32_t tid = threadIdx.x % TEAM;
     const uint32_t team = team_uniform_u32<TEAM>(threadIdx.x / TEAM);   // a scalar unless a wave holds several teams
-    const TeamLdsMap map = team_lds_map(P.bucket, P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk);
+    const TeamLdsMap map = team_lds_map(P.slot_words, P.rows, TEAM, P.rec_cap, P.out_cap, P.nsync, P.nblk);
     uint32_t *const lds = smem + team * map.words;
     uint32_t *const tables = smem + TeamGeom<TEAM>::kTeamsPerWG * map.words;
     const TeamLds L{lds, reinterpret_cast<uint16_t *>(lds + map.rec), lds + map.out, lds + map.sync, lds + map.run_off,

@@ -1,0 +1,45 @@
+"""Capacities of the ERC encoders' LDS, asked of the library (no GPU): the lists of small buckets hold what buckets have, their
+buffers the longest string of what is listed."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_1908_06077_amd as nuq
+
+
+def erc_bits(x):
+    return 1 if x == 1 else erc_bits(x.bit_length() - 1) + x.bit_length()
+
+
+@pytest.mark.parametrize("n", [1, 3, 17, 64, 200, 256, 257, 300, 350, 400, 450, 512, 513, 600, 768, 769, 1000, 1024, 1025, 1500, 2048])
+def test_longest_string_of_a_listed_bucket(n):
+    """Every record at the longest level code, gaps spread so that their codes are longest: pairs first (ERC(2) takes 3 bits for two
+    coordinates), what is left over single."""
+    for mode in (0, 1):
+        for s in range(1, 15):
+            for nb in (1, 20_000):
+                _, listed, buffer, whole = nuq.nuq_encode_shape(mode, 1, nb * n, n, s, 64)
+                level = 7 if mode == 1 else max(erc_bits(j) for j in range(1, s + 2))
+                slot = (n * (2 + max(erc_bits(j) for j in range(1, s + 2))) + 31) // 32
+                pairs = min(listed, n - listed)
+                longest = (listed * (1 + level) + 3 * pairs + (listed - pairs) + 31) // 32
+                assert buffer >= min(longest, slot) and whole >= slot
+
+
+@pytest.mark.parametrize("law", ["gauss", "heavy"])
+@pytest.mark.parametrize("n,levels", [(260, range(1, 15)), (300, range(1, 15)), (350, range(1, 15)), (400, range(1, 6)), (450, range(1, 6)),
+                                      (500, range(1, 5)), (512, range(1, 5)), (768, range(1, 15)), (1000, range(1, 15))])
+def test_lists_hold_what_buckets_have(n, levels, law):
+    rng = np.random.default_rng(n)
+    rows = 200
+    v = rng.standard_normal((rows, n))
+    if law == "heavy":
+        v = v / np.sqrt(rng.chisquare(3, v.shape) / 3.0)
+    v = v.astype(np.float32).ravel()
+    norms = oracle.bucket_norms(v, n).astype(np.float32)
+    for s in levels:
+        nonzeros = np.count_nonzero(oracle.quantize(v, n, s, 1, norms).reshape(rows, n), axis=1)
+        for mode in (0, 1):
+            for S in (64, 128, 512):
+                listed = nuq.nuq_encode_shape(mode, 4, 4_000_000, n, s, S)[1]
+                assert np.mean(nonzeros <= listed) > 0.97, (s, mode, S, listed, nonzeros.mean())

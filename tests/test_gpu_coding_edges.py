@@ -24,7 +24,7 @@ def g():
 def test_crafted_bytes(g, n, S, s):
     nuq = g.nuq
     rng = np.random.default_rng(n * 16 + s)
-    cap = (n * 5 // 8 + 7) & ~7 if n <= 512 else n if n <= 1024 else max(n // 4, 1024)     # indices the list holds
+    cap = nuq.nuq_encode_shape(1, 1, 10 * n, n, s, S)[1]                                   # indices the list holds
     counts = [n, min(n, cap), min(n, cap + 1), max(n // 4, 1), max(n // 15, 1), max(n // 40, 1), 1, 0, n // 2, n]
     d = len(counts) * n - min(5, n - 1)
     q = np.zeros(d, dtype=np.uint8)
@@ -83,13 +83,11 @@ def test_levels_above_the_top(g, n, S, s, density):
 
 @pytest.mark.parametrize("n,S", [(3000, 0), (3000, 64), (8192, 256), (16384, 128), (20000, 512), (32768, 1024)])
 def test_strings_of_one_window_and_of_two(g, n, S):
-    """Buckets without a zero, a string of exactly the words that the list's and the buffer's LDS hold, a word more, and the
-    longest."""
+    """Buckets without a zero, a string of exactly the words that are put together at once, a word more, and the longest."""
     nuq, s = g.nuq, 14
     rng = np.random.default_rng(n)
-    up4 = lambda x: (x + 3) & ~3
-    slot = up4((9 * n + 31) // 32)
-    cap = up4((max(n // 4, 1024) + 1) // 2) + max(up4(slot // 4), 256)
+    _, listed, _, cap = nuq.nuq_encode_shape(1, 1, 6 * n, n, s, S)
+    assert listed < n
     x = (32 * cap - 3 * n) // 6                                # records of 9 bits (level 15), the others take 3 (level 1)
     d = 6 * n
     q = np.ones(d, dtype=np.uint8)
@@ -101,7 +99,7 @@ def test_strings_of_one_window_and_of_two(g, n, S):
     assert nuq.nuq_last_error_flags() == 0
     bo, words, sync = oracle.encode(q, n, s, S)
     lens = (bo[1:].astype(np.int64) - (bo[:-1].astype(np.int64) + 31) // 32 * 32 + 31) // 32
-    assert lens[0] == cap and lens[1] == cap + 1
+    assert lens[0] == cap and lens[1] == cap + 1 and lens[2] > cap
     np.testing.assert_array_equal(g.u64(m.bit_off), bo)
     np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
     if S:
@@ -159,3 +157,38 @@ def test_strings_longer_than_slots(g, n, S, s):
         nuq.nuq_decode_accumulate(msgs, d, n, s, S, 1.0 / len(msgs), False, out)
         assert nuq.nuq_last_error_flags() == nuq.FLAG_MALFORMED
         np.testing.assert_array_equal(out.cpu().numpy()[legal], want[legal].astype(np.float32))
+
+
+@pytest.mark.parametrize("s", [6, 7, 8, 14])
+@pytest.mark.parametrize("n,nb,S", [(17, 40, 0), (64, 19, 64), (200, 21, 64), (256, 33, 128), (300, 18, 64), (400, 19, 256), (512, 21, 64),
+                                    (600, 9, 128), (600, 5200, 128), (768, 5200, 256), (1000, 7, 64), (1000, 5200, 256), (1024, 6, 1024),
+                                    (2000, 7, 64)])
+def test_longest_strings(g, n, nb, S, s):
+    """Several buckets per workgroup, strings up to the longest there are: no zero and the top level (longer than the bytes they
+    are made from, where levels need seven bits), every other coordinate, as many nonzeros as the list holds at the longest
+    level code, beside ordinary and empty buckets and in a unit that is not full."""
+    nuq = g.nuq
+    rng = np.random.default_rng(n + nb + s)
+    d = nb * n - n // 3
+    _, listed, buffer, _ = nuq.nuq_encode_shape(1, 1, d, n, s, S)
+    q = np.zeros(nb * n, dtype=np.uint8)
+    top = min(s + 1, 15)
+    for b in list(range(min(nb, 40))) + list(range(max(nb - 7, 0), nb)):
+        at = [np.arange(n), np.flatnonzero(rng.random(n) < 0.2), np.arange(0, n, 2), np.arange(n),
+              np.sort(rng.choice(n, min(listed, n), replace=False)), np.arange(0)][b % 6]
+        lev = rng.integers(1, s + 2, at.size) if b % 6 == 1 else np.full(at.size, top)
+        q[b * n + at] = lev
+    q = np.where(q, q | (rng.integers(0, 2, q.size) << 7), 0).astype(np.uint8)[:d]
+    m = g.alloc_message(d, n, s, S)
+    nuq.nuq_encode(torch.from_numpy(q).to(g.DEV), n, s, S, m.bit_off, m.words, m.sync if S else None, g.workspace(d, n, s))
+    assert nuq.nuq_last_error_flags() == 0
+    bo, words, sync = oracle.encode(q, n, s, S)
+    first = int(bo[1] + 31) // 32
+    assert first == (n * (9 if s >= 7 else 8) + 31) // 32
+    if listed == n:
+        assert buffer >= first and (s < 7 or 32 * buffer > 8 * n)
+    np.testing.assert_array_equal(g.u64(m.bit_off), bo)
+    np.testing.assert_array_equal(g.u32(m.words)[: words.size], words)
+    assert not g.u32(m.words)[words.size:].any()
+    if sync.size:
+        np.testing.assert_array_equal(g.u32(m.sync)[: sync.size], sync)

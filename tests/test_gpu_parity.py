@@ -286,8 +286,8 @@ def test_encode_of_dense_buckets(g, n, s, S):
         q[lo:hi] = np.where(m, lev | sign, 0)
     fill(0, 1.0, True)       # every coordinate at the top level: the worst case
     fill(1, 0.05, False)     # ordinary
-    fill(2, 0.26, True)      # a few more nonzeros than the list holds (large buckets)
-    fill(3, 0.24, True)      # the list holds them, the bit string is too long for the buffer
+    fill(2, 0.26, True)      # a few more nonzeros than the list holds (buckets above 4096)
+    fill(3, 0.24, True)      # the list holds them, the bit string is too long for the buffer (buckets above 4096)
     fill(4, 0.0, False)      # empty
     fill(5, 0.6, False)
     fill(6, 1.0, False)      # short last bucket, full

@@ -38,7 +38,7 @@ def crafted(rng, n, counts, tail, s):
 def test_list_edges(g, n, S, s):
     """One nonzero fewer than the list holds, as many, one more, in buckets side by side; the last unit partly filled."""
     rng = np.random.default_rng(n + s)
-    cap = n if n <= 256 else (n * 37 // 64 + 7) & ~7 if n <= 512 else min(n, 1024) if n <= 4096 else min(n // 4, 3584)
+    cap = g.nuq.nuq_encode_shape(1, 1, 33 * n, n, s, S)[1]
     counts = [n // 4, cap - 1, cap, min(n, cap + 1), 0, n, cap, n // 4, min(n, cap + 1), 1, n // 3] * 3
     q = crafted(rng, n, counts, 1 if n > 1 else 0, s)
     m = coded(g, q, n, s, S)
@@ -55,6 +55,7 @@ def test_list_edges_of_half_a_wave(g):
     n, s, S = 1000, 3, 256
     rng = np.random.default_rng(5)
     counts = [40] * 5124
+    assert g.nuq.nuq_encode_shape(1, 1, len(counts) * n - 3, n, s, S)[:2] == (32, 768)
     counts[7:12] = counts[5118:5123] = [767, 768, 769, 1000, 768]
     q = crafted(rng, n, counts, 3, s)
     m = coded(g, q, n, s, S)
