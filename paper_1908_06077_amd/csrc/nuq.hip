@@ -229,6 +229,15 @@ int dispatch_team(uint32_t bucket, bool narrow, F &&f)
     return narrow ? dispatch_team_as<kUse, true>(bucket, f) : dispatch_team_as<kUse, false>(bucket, f);
 }
 
+// Nonzeros to be expected in a bucket of Gaussian coordinates whose first level is l1 of the norm: a coordinate of |z| standard
+// deviations is sent with probability min(1, |z| / z1), z1 of them being the first level.  (The largest |z| of 300 to 800 is
+// 3.2.)
+double expected_nonzeros(uint32_t bucket, double l1, bool linf)
+{
+    const double z1 = l1 * (linf ? 3.2 : std::sqrt((double)bucket));
+    return bucket * (std::sqrt(2.0 / M_PI) / z1 * -std::expm1(-0.5 * z1 * z1) + std::erfc(z1 / M_SQRT2));
+}
+
 // Whether nb buckets of each of K workers take the narrow shapes.  A team's fixed work (norm reduction, scale, key, scans,
 // barriers) costs the fused encoders as much as a thousand coordinates per wave, so with half the waves per bucket a full chip
 // gets through more buckets; a chip that is not full waits for a single bucket instead, which then takes longer.  The line is a
@@ -242,7 +251,8 @@ int dispatch_team(uint32_t bucket, bool narrow, F &&f)
 //   513 to 1024: from 5120 buckets (8937 of 600 coordinates 18.6 -> 14.9 us, 5916 14.9 -> 13.0, 4222 of 513 15.4 and 17.4),
 //     where half a wave's rows waste less of a bucket (up to 832 coordinates: 28 % on 131 k buckets of 513) or levels are
 //     sparse (13 k of 1000 22.5 -> 20.4; dense, 95 k of 1024 at s = 5, 9 % slower), but not with many levels from a table or
-//     from bytes (55 k of 600, s = 14, 79 and 87); Huffman of more than 832 from 8192 (11 k of 1000 21.5 -> 20.9; 6.2 k of 1024
+//     from bytes (55 k of 600, s = 14, 79 and 87), nor with more nonzeros than half a wave lists, 768 (58 k of 832 at s = 7 123
+//     and 101, 62 k of 780 at s = 10 159 and 111); Huffman of more than 832 from 8192 (11 k of 1000 21.5 -> 20.9; 6.2 k of 1024
 //     6 % slower).  All others, memory-bound: up to 640 coordinates, five rows where a wave loads 768, from 8192 buckets (packing
 //     at 4 or 8 bits 15 % less on 50 k and more), up to 832 from 32768 (56 k of 700 9 % less, 17 k of 800 2 % more).
 // What these shapes cost where the chip is not full: nuq_quantize on 0.2 M coordinates in buckets of 1000 3.8 us with a wave, 6.0
@@ -256,8 +266,11 @@ bool narrow_teams(uint64_t nb, uint32_t K, uint32_t bucket, uint32_t s, bool lin
     const uint64_t teams = nb * K;
     const bool sparse = !linf && l1 * l1 * bucket >= 9.0;
     if constexpr (kUse == TeamUse::kErc || kUse == TeamUse::kErcOther) {
-        if (bucket <= 1024u)
-            return teams >= 5120u && (bucket <= 832u || sparse) && (kUse == TeamUse::kErc || s <= 5u);
+        if (bucket <= 1024u) {
+            const bool fit = bucket <= 32u * kKeptRecords || sparse ||
+                             (bucket <= 832u && expected_nonzeros(bucket, l1, linf) + 24.0 <= 32.0 * kKeptRecords);
+            return teams >= 5120u && fit && (kUse == TeamUse::kErc || s <= 5u);
+        }
         if (bucket <= 4096u)
             return teams >= (sparse ? 2048u : linf ? 8192u : 4096u);
         return teams > 256u;
@@ -280,14 +293,6 @@ bool narrow_teams(uint64_t nb, uint32_t K, uint32_t bucket, uint32_t s, bool lin
 uint32_t stream_loads(uint64_t d, uint32_t K)
 {
     return d <= (1ull << 31) / K ? 1u : 0u;
-}
-
-// Nonzeros to be expected in a bucket of Gaussian coordinates whose first level is l1 of the norm: a coordinate of |z| standard
-// deviations is sent with probability min(1, |z| / z1), z1 of them being the first level.  (The largest |z| of 300 to 500 is 3.2.)
-double expected_nonzeros(uint32_t bucket, double l1, bool linf)
-{
-    const double z1 = l1 * (linf ? 3.2 : std::sqrt((double)bucket));
-    return bucket * (std::sqrt(2.0 / M_PI) / z1 * -std::expm1(-0.5 * z1 * z1) + std::erfc(z1 / M_SQRT2));
 }
 
 // Nonzeros that the LDS list of a team of the encoders holds (k_encode<TEAM, ., MODE>; l1, linf: its first level and norm).

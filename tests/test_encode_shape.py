@@ -28,7 +28,8 @@ def test_longest_string_of_a_listed_bucket(n):
 
 @pytest.mark.parametrize("law", ["gauss", "heavy"])
 @pytest.mark.parametrize("n,levels", [(260, range(1, 15)), (300, range(1, 15)), (350, range(1, 15)), (400, range(1, 6)), (450, range(1, 6)),
-                                      (500, range(1, 5)), (512, range(1, 5)), (768, range(1, 15)), (1000, range(1, 15))])
+                                      (500, range(1, 5)), (512, range(1, 5)), (768, range(1, 15)), (780, range(1, 15)),
+                                      (832, range(1, 15)), (1000, range(1, 15))])
 def test_lists_hold_what_buckets_have(n, levels, law):
     rng = np.random.default_rng(n)
     rows = 200
