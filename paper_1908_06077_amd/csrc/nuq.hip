@@ -297,9 +297,13 @@ uint32_t stream_loads(uint64_t d, uint32_t K)
 
 // Nonzeros that the LDS list of a team of the encoders holds (k_encode<TEAM, ., MODE>; l1, linf: its first level and norm).
 //
-// Teams of several waves: a quarter of the bucket (about four times what a Gaussian gradient produces), at least 1024; but no
-// more than 3584 of buckets of up to 16384, of which five then share a CU instead of four: heavy tails, 4 x 134 M coordinates in
-// buckets of 16384, both directions 605 -> 578 us.
+// Teams of several waves: a quarter of the bucket (about four times what a Gaussian gradient produces), at least 1024; but of
+// buckets of 12289 to 16384 no more than what five of them leave room for on a CU, as many as there are registers for (4 x 134 M
+// heavy-tailed coordinates in buckets of 16384, both directions 605 us with four, 578 with five): 4076 of 16384 up to s = 6, 3820
+// above, a quarter up to some 15300.  With 3584 for all, buckets of 15000 and 16384 with 0.23 to 0.245 of their coordinates nonzero
+// took 183 and 190 us instead of 166 and 161 (4 x 30 M).  Level tables keep to 3584: their records are longer, so that what more is
+// listed overflows the string's buffer (0.23 nonzero, exponential levels at s = 7, both directions 334 us, with 4096 951).  Encoding
+// bytes gains nothing from a fifth workgroup (30 M, a tenth nonzero, 34.8 and 34.9 us, 0.23 46 with a quarter, 56 with 3584).
 //
 // Teams of a wave or less: all of a bucket's coordinates up to 256, where eight workgroups, as many as there are waves for, share
 // a CU all the same, and above 512, but no more than kKeptRecords per thread.  257 to 512: what eight workgroups leave room for
@@ -313,22 +317,27 @@ template <int TEAM, int MODE>
 uint32_t team_rec_cap(const EncodeParams &P, double l1)
 {
     constexpr uint32_t kKept = TEAM * kKeptRecords, kTeams = TeamGeom<TEAM>::kTeamsPerWG;
-    const uint32_t bucket = P.bucket, quarter = bucket / 4u;
-    if constexpr (TEAM > kWave)
-        return bucket <= 4096u ? 1024u : bucket <= 16384u && quarter > 3584u ? 3584u : quarter;
-    if (TEAM > 16 || bucket <= 256u)
-        return std::min(kKept, bucket <= 1024u ? bucket : 1024u);
+    const uint32_t bucket = P.bucket;
     // LDS is given out in pieces of 1280 bytes; the list's words, a multiple of four, are what is free of a team's, or what the
-    // string of an unlisted bucket needs in their place
-    constexpr uint32_t kCU = 160u * 1024u, kPiece = 1280u, kStatic = kTeams * (4u + (MODE == 2 ? (uint32_t)sizeof(TableBins) : 0u));
+    // string of a small team's unlisted bucket needs in their place
+    constexpr uint32_t kCU = 160u * 1024u, kPiece = 1280u, kTables = MODE == 2 ? (uint32_t)sizeof(TableBins) : 0u,
+                       kStatic = kTeams * (kTables + (kTeams > 1u ? 4u : 0u));
     const TeamLdsMap none = team_lds_map(P.slot_words, P.rows, TEAM, 0, P.out_cap, P.nsync, P.nblk);
+    const uint32_t string = TEAM > kWave ? 0u : none.sync - none.rec;
     auto room = [&](uint32_t groups) {
         const uint32_t words = (kCU / groups / kPiece * kPiece - kStatic - 512u * 4u) / (4u * kTeams) & ~3u;
-        const uint32_t string = none.sync - none.rec;
-        return std::min(std::min(kKept, bucket), 2u * std::max(string, words - (none.words - string)));
+        return 2u * std::max(string, words - (none.words - string));
     };
+    if constexpr (TEAM > kWave) {
+        const uint32_t quarter = std::max(bucket / 4u, 1024u);
+        if (bucket <= 12288u || bucket > 16384u || MODE == 1)
+            return quarter;
+        return std::min(quarter, MODE == 2 ? 3584u : room(5u));
+    }
+    if (TEAM > 16 || bucket <= 256u)
+        return std::min(kKept, bucket <= 1024u ? bucket : 1024u);
     constexpr uint32_t kGroups = MODE == 2 ? 6u : 8u;
-    const uint32_t usual = room(kGroups), most = room(kGroups - 1u);
+    const uint32_t usual = std::min(std::min(kKept, bucket), room(kGroups)), most = std::min(std::min(kKept, bucket), room(kGroups - 1u));
     const double mean = expected_nonzeros(bucket, l1, P.norm_linf), sd = std::sqrt(mean * (1.0 - mean / bucket));
     const bool beyond = mean + 3.0 * sd + (P.norm_linf ? bucket / 16u : 0u) > usual;
     return beyond && mean + 1.5 * sd <= most ? most : usual;

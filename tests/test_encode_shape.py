@@ -44,3 +44,15 @@ def test_lists_hold_what_buckets_have(n, levels, law):
             for S in (64, 128, 512):
                 listed = nuq.nuq_encode_shape(mode, 4, 4_000_000, n, s, S)[1]
                 assert np.mean(nonzeros <= listed) > 0.97, (s, mode, S, listed, nonzeros.mean())
+
+
+@pytest.mark.parametrize("n", [12288, 12289, 14336, 15000, 16000, 16384, 20000])
+def test_lists_of_large_buckets(n):
+    """A quarter of the bucket where nonzeros are anyone's guess (bytes) or five workgroups leave room for it, little less elsewhere."""
+    for s in range(1, 15):
+        for S in (0, 64, 256):
+            assert nuq.nuq_encode_shape(1, 1, 9 * n, n, s, S)[1] == n // 4
+            listed, buffer = nuq.nuq_encode_shape(0, 1, 9 * n, n, s, S)[1:3]
+            assert listed == n // 4 or (n > 15000 and n // 4 - 290 < listed < n // 4)
+            words = ((n + 1023) // 1024) * 256 + (listed + 1) // 2 + buffer + max(256, nuq.nuq_num_sync(n, S)) - (-n // 2048) + 66 + 512
+            assert n <= 12288 or n > 16384 or 5 * (-(-4 * words // 1280)) <= 128                   # of 128 pieces of 1280 bytes

@@ -291,6 +291,10 @@ def test_encode_of_dense_buckets(g, n, s, S):
     fill(4, 0.0, False)      # empty
     fill(5, 0.6, False)
     fill(6, 1.0, False)      # short last bucket, full
+    if n > 4096:
+        _, listed, buffer, _ = nuq.nuq_encode_shape(1, 1, d, n, s, S)
+        bits = oracle.encode(q, n, s, S)[0].astype(np.int64)
+        assert np.count_nonzero(q[2 * n: 3 * n]) > listed >= np.count_nonzero(q[3 * n: 4 * n]) and bits[4] - bits[3] > 32 * buffer + 31
     qd = torch.from_numpy(q).to(g.DEV)
     m = g.alloc_message(d, n, s, S)
     nuq.nuq_encode(qd, n, s, S, m.bit_off, m.words, m.sync if nuq.nuq_num_sync(n, S) else None, g.workspace(d, n, s))
