@@ -285,14 +285,19 @@ bool narrow_teams(uint64_t nb, uint32_t K, uint32_t bucket, uint32_t s, bool lin
     }
 }
 
-// Whether teams of less than a wave load gradients in buckets above 256 non-temporally.  Four workers, buckets of 512, 12 M
-// coordinates 55.1 -> 51.4 us to encode and 117 -> 107 a step with momentum, whose parameters and strings stay in the last-level
-// cache; packing them at 4 bits 61 -> 57; 20 M in buckets of 1024 a step 169 -> 157;
-// 60 M 231 -> 228, 40 M in a step 303 -> 279; 400 M 1506 and 1506.  From about 2 G coordinates in all it costs: 2 x 1.56 G 2913
-// and 3025 us, 4 x 0.8 G 3040 and 3098.  (Buckets of 256: 4 x 5 M 32.9 and 33.8; 4 x 20 M, a step 207 and 213.)
+// Whether teams of less than a wave load full buckets of eight rows per thread, that is of exactly 512, or of 1024 in the narrow
+// shape, non-temporally (load_rows; others load from clamped addresses, where it brought nothing: buckets of 1000 30.7 and 31.4 us).
+// Four workers, buckets of 512, 12 M coordinates 55.1 -> 51.4 us to encode and 117 -> 107 a step with momentum, whose parameters and
+// strings stay in the last-level cache; packing them at 4 bits 61 -> 57; 20 M in buckets of 1024 a step 169 -> 157; 40 M in a step 303
+// -> 279; one encode of 200 M 200 -> 194, of 800 M 787 -> 755, of 1024 759 -> 713.  Beyond 1 G coordinates in all it no longer helps,
+// for a reason that no measurement here has shown (far more than any cache holds on either side): 1 x 1.5 G 1430 and 1456 us, 4 x 0.4
+// G 1540 and 1566, 4 x 0.8 G 3129 and 3253, in buckets of 1024 1320 and 1331, 1430 and 1427, 2847 and 2880.  Small calls are the same
+// either way (8 x 0.3 M 14.6 and 14.7), and so is one gradient encoded again and again, as the variance diagnostic does, though plain
+// loads may find it in the cache (12 M in buckets of 512 131.3 and 133.3 a draw, of 1024 116.7 and 115.6).
+// (Buckets of 256: 4 x 5 M 32.9 and 33.8; 4 x 20 M, a step 207 and 213.)
 uint32_t stream_loads(uint64_t d, uint32_t K)
 {
-    return d <= (1ull << 31) / K ? 1u : 0u;
+    return d <= (1ull << 30) / K ? 1u : 0u;
 }
 
 // Nonzeros that the LDS list of a team of the encoders holds (k_encode<TEAM, ., MODE>; l1, linf: its first level and norm).

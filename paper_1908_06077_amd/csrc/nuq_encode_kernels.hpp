@@ -56,7 +56,7 @@ struct EncodeParams {
     uint32_t *staging;     // [K * nb * slot_words]
     uint32_t *flags;
     uint32_t norm_linf;    // level-table mode: 0 = Euclidean norm, 1 = maximum norm
-    uint32_t stream;       // teams of less than a wave: gradients are loaded non-temporally too (see load_rows)
+    uint32_t stream;       // teams of less than a wave: full buckets of eight rows are loaded non-temporally too (load_rows)
 };
 
 template <int TEAM>
@@ -99,10 +99,11 @@ __device__ __forceinline__ float4 load_vec4(const float *vb, uint32_t vi, uint32
 // A bucket's rows into registers.  Gradients are read once, so teams of a wave or more load them non-temporally: the
 // stream then does not push the staged bit strings, lengths and messages, which the next kernel reads, out of the caches
 // (172 -> 164 us on 8192-coordinate buckets, 3 % on 16384).  Smaller teams, whose loads are 256- or 512-byte pieces, do
-// so for buckets above 256 (`stream`, stream_loads).  wg_base: the workgroup's first bucket (uniform), lane_off: coordinates from there to
-// the team's bucket.  The addresses of a full bucket are a uniform base per row (scalar registers; the empty asm keeps
-// the compiler from folding the row into the lanes' 64-bit addresses, two instructions per row and lane) plus one 32-bit
-// lane offset (in the global address space by type: behind the asm the compiler would have to assume a generic pointer).
+// so for full buckets of eight rows per thread (`stream`, stream_loads).  wg_base: the workgroup's first bucket (uniform),
+// lane_off: coordinates from there to the team's bucket.  The addresses of a full bucket are a uniform base per row (scalar
+// registers; the empty asm keeps the compiler from folding the row into the lanes' 64-bit addresses, two instructions per row
+// and lane) plus one 32-bit lane offset (in the global address space by type: behind the asm the compiler would have to assume
+// a generic pointer).
 typedef const __attribute__((address_space(1))) char *GlobalBytes;
 typedef const __attribute__((address_space(1))) f32x4_any *GlobalFloat4;
 template <int TEAM, int VPT>
