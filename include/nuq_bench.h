@@ -36,6 +36,11 @@ int nuq_timing_collect(float *ms, int32_t *entry, uint32_t cap, uint32_t *count)
 int nuq_encode_shape(uint32_t mode, uint32_t K, uint64_t d, uint32_t bucket, uint32_t s,
                      uint32_t sync_stride, const float *levels, uint32_t norm_kind, uint32_t *shape);
 
+/* Coordinates of a tile of the decoder for K messages of these sizes (where it works in tiles), 0 on invalid
+ * sizes.  table: levels from a table; update: 0 = the result is written, 1 = added, 2 = momentum rule. */
+uint32_t nuq_decode_tile(uint32_t K, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride, int table,
+                         uint32_t update);
+
 #ifdef __cplusplus
 }
 #endif

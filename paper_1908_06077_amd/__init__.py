@@ -18,5 +18,5 @@ from .binding import (  # noqa: F401
     nuq_quantize_pack_fixed_table_batch, nuq_unpack_accumulate_fixed_table,
     nuq_momentum_step, nuq_decode_momentum_step, nuq_moments_accumulate, nuq_normalized_variance, VARIANCE_WORKSPACE_BYTES,
     nuq_last_error_flags, library_path, exported_symbols,
-    nuq_encode_shape, nuq_timing_begin, nuq_timing_collect, T_NORMS, T_QUANTIZE, T_ENCODE, T_QUANTIZE_ENCODE, T_DECODE,
+    nuq_encode_shape, nuq_decode_tile, nuq_timing_begin, nuq_timing_collect, T_NORMS, T_QUANTIZE, T_ENCODE, T_QUANTIZE_ENCODE, T_DECODE,
 )

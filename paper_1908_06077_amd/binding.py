@@ -82,6 +82,7 @@ _SIGNATURES = {
     "nuq_normalized_variance": (_i32, [_vp, _vp, _u64, _u64, _vp, _u64, _vp, _vp]),
     "nuq_last_error_flags": (_i32, [_vp, _vp]),
     "nuq_encode_shape": (_i32, [_u32, _u32, _u64, _u32, _u32, _u32, _vp, _u32, _vp]),
+    "nuq_decode_tile": (_u32, [_u32, _u64, _u32, _u32, _u32, _i32, _u32]),
     "nuq_timing_begin": (_i32, [_u32]),
     "nuq_timing_collect": (_i32, [_vp, _vp, _u32, _vp]),
 }
@@ -615,6 +616,10 @@ def nuq_encode_shape(mode: int, K: int, d: int, bucket: int, s: int, sync_stride
     table = (ctypes.c_float * (s + 2))(*levels) if mode == 2 else None
     _check("nuq_encode_shape", _lib.nuq_encode_shape(mode, K, d, bucket, s, sync_stride, table, norm_kind, shape))
     return tuple(shape)
+
+
+def nuq_decode_tile(K: int, d: int, bucket: int, s: int, sync_stride: int, table: bool = False, update: int = 0) -> int:
+    return _lib.nuq_decode_tile(K, d, bucket, s, sync_stride, int(table), update)
 
 
 def nuq_timing_begin(max_launches: int) -> None:

@@ -903,6 +903,39 @@ int nuq_quantize_encode_batch(uint32_t K, const float *const *v, const uint64_t 
     return encode_batch<0>(K, Wk, d, bucket, s, sync_stride, workspace, workspace_bytes, stream);
 }
 
+// Coordinates of a tile of the decoders that have an index (update: what the output stage does with the sums, a kUpdate).
+//
+// Tiles of 4096 coordinates (32 KB of fp64, four workgroups per CU instead of eight) where the usual 2048 would
+// give the 64 parsing lanes at most 32 units: parts of large buckets of few workers whose pieces are long, or may be (level
+// tables).  The parse of long pieces is bound by instruction issue, so one full wave per SIMD gets through more records
+// than two half-empty ones (four messages in buckets of 8192 at s = 7, stride 512, 3 M coordinates 52.0 us, in tiles of 2048
+// 56.4; of 16384 at 256, 205 records to a piece, 27.2 and 30.1).  Up to about 128 records to a piece (with the main scheme
+// 0.8 x 2^s / sqrt(bucket) of the coordinates are nonzero on average, and never more than all) more waves and half the result for
+// each count for more: at s = 3, stride 256, 65 537 coordinates 7.98 -> 7.04 us with tiles of 2048, 6 M 13.9 -> 12.6, 60 M 69.1 ->
+// 65.6; two messages in buckets of 20000 at s = 7, stride 128, 3 M 16.9 -> 15.6, of 4096, 1 M 16.3 -> 14.7; 8192 at s = 5, stride 256,
+// 0.3 M 17.2 -> 15.7; momentum on one of 5000 at s = 8, 6 M 86.9 -> 72.2.  (Two dense messages at s = 14, stride 128, 1 M or less are
+// 10 % slower so: 18.3 and 20.7.)  With a full chip the line lies lower (58.4 and 59.2 us on 20 M of 8192 at s = 5, 72 records).
+// Small buckets: only where they fill the tile, 2048 coordinates have at most 16 units (4 x 16.8 M coordinates in buckets
+// of 512 at stride 512 84 -> 78 us, two messages at 256 48 -> 44; with 32 units 50 -> 52), there is a tile for every CU
+// (0.3 M coordinates, exponential levels at s = 7, both directions 65.8 -> 69.5 with tiles of 4096) and the result is
+// written: what the other updates read takes registers for twice the coordinates, which leaves a wave per SIMD (17 M
+// coordinates of two messages in buckets of 512, momentum 52 -> 67 us; 10 M of one in buckets of 1024 28 -> 34).
+static uint32_t decode_tile_coords(uint32_t K, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride, bool table, uint32_t update)
+{
+    if (!nuq_num_sync(bucket, sync_stride))
+        return kTileCoords;
+    const uint32_t pieces = 1u << sync_pieces_shift(bucket, sync_stride);       // per block of the index and message
+    if (bucket >= kTileCoordsBig) {
+        const double records = sync_stride * std::min(1.0, 0.8 * std::ldexp(1.0, (int)s) / std::sqrt((double)bucket));
+        const bool short_pieces = !table && records <= (d < (1ull << 24) ? 128.0 : 64.0);
+        return !short_pieces && K * pieces <= 32u ? kTileCoordsBig : kTileCoords;
+    }
+    return kTileCoordsBig % bucket == 0 && kTileCoordsBig / bucket * K <= kMaxStreams && update == kUpdateWrite &&
+                   d >= 256ull * kTileCoordsBig && kTileCoords / bucket * K * pieces <= 16u
+               ? kTileCoordsBig
+               : kTileCoords;
+}
+
 // levels: nullptr for the levels 2^(j-1-s), else the s + 2 values of a level table (host memory).
 static int decode_accumulate_any(uint32_t K, const float *const *norms, const uint64_t *const *bit_off,
                                  const uint32_t *const *words, const uint64_t *words_len,
@@ -986,29 +1019,9 @@ static int decode_accumulate_any(uint32_t K, const float *const *norms, const ui
                                static_cast<hipStream_t>(stream), P);
         return check_launch();
     }
-    // Tiles of 4096 coordinates (32 KB of fp64, four workgroups per CU instead of eight) where the usual 2048 would
-    // give the 64 parsing lanes at most 32 units: parts of large buckets of few workers whose pieces are long, or may be (level
-    // tables).  The parse of long pieces is bound by instruction issue, so one full wave per SIMD gets through more records
-    // than two half-empty ones (four messages in buckets of 8192 at s = 7, stride 512, 3 M coordinates 52.0 us, in tiles of 2048
-    // 56.4; of 16384 at 256, 205 records to a piece, 27.2 and 30.1).  Up to about 128 records to a piece (with the main scheme
-    // 0.8 x 2^s / sqrt(bucket) of the coordinates are nonzero on average) more waves and half the result for each count for more:
-    // at s = 3, stride 256, 65 537 coordinates 7.98 -> 7.04 us with tiles of 2048, 6 M 13.9 -> 12.6, 60 M 69.1 -> 65.6; two
-    // messages in buckets of 20000 at s = 7, stride 128, 3 M 16.9 -> 15.6; 8192 at s = 5, stride 256, 0.3 M
-    // 17.2 -> 15.7.  With a full chip the line lies lower (58.4 and 59.2 us on 20 M of the latter, 72 records).
-    // Small buckets: only where they fill the tile, 2048 coordinates have at most 16 units (4 x 16.8 M coordinates in buckets
-    // of 512 at stride 512 84 -> 78 us, two messages at 256 48 -> 44; with 32 units 50 -> 52), there is a tile for every CU
-    // (0.3 M coordinates, exponential levels at s = 7, both directions 65.8 -> 69.5 with tiles of 4096) and the result is
-    // written: what the other updates read takes registers for twice the coordinates, which leaves a wave per SIMD (17 M
-    // coordinates of two messages in buckets of 512, momentum 52 -> 67 us; 10 M of one in buckets of 1024 28 -> 34).
-    const double records = 0.8 * std::ldexp((double)sync_stride, (int)s) / std::sqrt((double)bucket);
-    const bool short_pieces = !levels && records <= (d < (1ull << 24) ? 128.0 : 64.0);
-    const bool small_big = kTileCoordsBig % bucket == 0 && kTileCoordsBig / bucket * K <= kMaxStreams && !accumulate && !momentum &&
-                           d >= 256ull * kTileCoordsBig && (kTileCoords / bucket * K << P.pieces_shift) <= 16u;
-    const bool big = nsync && (bucket >= kTileCoordsBig ? !short_pieces && (K << P.pieces_shift) <= 32u : small_big);
-    const uint32_t tile_coords = big ? kTileCoordsBig : kTileCoords;
-    const uint32_t variant = 2u * ((levels ? 3u : 0u) + (momentum ? (uint32_t)kUpdateMomentum
-                                                                  : accumulate ? (uint32_t)kUpdateAdd
-                                                                               : (uint32_t)kUpdateWrite)) + (big ? 1u : 0u);
+    const uint32_t update = momentum ? (uint32_t)kUpdateMomentum : accumulate ? (uint32_t)kUpdateAdd : (uint32_t)kUpdateWrite;
+    const uint32_t tile_coords = decode_tile_coords(K, d, bucket, s, sync_stride, levels != nullptr, update);
+    const uint32_t variant = 2u * ((levels ? 3u : 0u) + update) + (tile_coords == kTileCoordsBig ? 1u : 0u);
     if (momentum) {
         P.yl = momentum->yl;
         P.alpha = momentum->alpha;
@@ -1832,6 +1845,13 @@ int nuq_encode_shape(uint32_t mode, uint32_t K, uint64_t d, uint32_t bucket, uin
     return mode == 0   ? with_encode_shape<0>(P, K, d, bucket, s, sync_stride, l1, linf, narrow, tell)
            : mode == 1 ? with_encode_shape<1>(P, K, d, bucket, s, sync_stride, l1, linf, narrow, tell)
                        : with_encode_shape<2>(P, K, d, bucket, s, sync_stride, l1, linf, narrow, tell);
+}
+
+uint32_t nuq_decode_tile(uint32_t K, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride, int table, uint32_t update)
+{
+    if (K < 1 || K > NUQ_MAX_WORKERS || !valid_common(d, bucket, s) || !valid_sync(sync_stride))
+        return 0;
+    return decode_tile_coords(K, d, bucket, s, sync_stride, table != 0, update);
 }
 
 int nuq_timing_begin(uint32_t max_launches)

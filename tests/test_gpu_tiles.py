@@ -16,10 +16,12 @@ def g():
 
 
 @pytest.mark.parametrize("K", [2, 4])
-@pytest.mark.parametrize("n,s,S", [(8192, 3, 256), (8192, 5, 256), (8192, 6, 256), (4096, 3, 512), (4096, 7, 128), (20000, 7, 128),
-                                   (16384, 7, 256), (16384, 5, 512), (5000, 2, 1024)])
-def test_parts_of_large_buckets(g, n, s, S, K):
+@pytest.mark.parametrize("n,s,S,tile", [(8192, 3, 256, 2048), (8192, 5, 256, 2048), (8192, 6, 256, 4096), (4096, 3, 512, 2048),
+                                        (4096, 7, 128, 2048), (4096, 7, 256, 4096), (5000, 14, 256, 4096), (20000, 7, 128, 2048),
+                                        (16384, 7, 256, 4096), (16384, 5, 512, 2048), (16384, 6, 512, 4096), (5000, 2, 1024, 2048)])
+def test_parts_of_large_buckets(g, n, s, S, tile, K):
     nuq, d = g.nuq, 3 * n + 2049
+    assert nuq.nuq_decode_tile(K, d, n, s, S) == tile
     vs = [torch.randn(d, device=g.DEV, generator=torch.Generator(device=g.DEV).manual_seed(9 * n + k)) for k in range(K)]
     msgs = [g.fused_encode(v, n, s, 70 + k, S) for k, v in enumerate(vs)]
     host = [(m.norms.cpu().numpy(), g.u64(m.bit_off), g.u32(m.words)) for m in msgs]

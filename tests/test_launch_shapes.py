@@ -1,5 +1,5 @@
-"""Capacities of the ERC encoders' LDS, asked of the library (no GPU): the lists of small buckets hold what buckets have, their
-buffers the longest string of what is listed."""
+"""Launch shapes, asked of the library (no GPU): the LDS lists of the ERC encoders hold what buckets have, their buffers the longest
+string of what is listed; the decoder's tiles."""
 import numpy as np
 import pytest
 
@@ -56,3 +56,21 @@ def test_lists_of_large_buckets(n):
             assert listed == n // 4 or (n > 15000 and n // 4 - 290 < listed < n // 4)
             words = ((n + 1023) // 1024) * 256 + (listed + 1) // 2 + buffer + max(256, nuq.nuq_num_sync(n, S)) - (-n // 2048) + 66 + 512
             assert n <= 12288 or n > 16384 or 5 * (-(-4 * words // 1280)) <= 128                   # of 128 pieces of 1280 bytes
+
+
+def test_decode_tiles():
+    """Large buckets: 4096 coordinates where pieces may hold more than 128 records (64 in large messages), which no piece of fewer
+    coordinates does, and the lanes are at most half full; level tables, whose density nothing is known of, in any case."""
+    for n in (4096, 8192, 20000, 32768):
+        for s in range(1, 15):
+            for d, most in ((65_537, 128), (1 << 24, 64)):
+                for K in (1, 2, 4, 8):
+                    for S in (64, 128, 256, 512, 1024):
+                        dense = S * min(1.0, 0.8 * 2 ** s / n ** 0.5) > most
+                        few = K * 2048 // S <= 32
+                        for update in (0, 1, 2):
+                            assert nuq.nuq_decode_tile(K, d, n, s, S, False, update) == (4096 if few and dense else 2048)
+                        assert nuq.nuq_decode_tile(K, d, n, s, S, True) == (4096 if few else 2048)
+    assert nuq.nuq_decode_tile(4, 1 << 24, 512, 3, 512) == 4096 and nuq.nuq_decode_tile(4, 1 << 24, 512, 3, 512, update=2) == 2048
+    assert nuq.nuq_decode_tile(4, 1 << 18, 512, 3, 512) == 2048 and nuq.nuq_decode_tile(1, 1 << 24, 1000, 3, 512) == 2048
+    assert nuq.nuq_decode_tile(4, 1 << 24, 8192, 3, 0) == 2048 and nuq.nuq_decode_tile(0, 1 << 24, 8192, 3, 256) == 0
