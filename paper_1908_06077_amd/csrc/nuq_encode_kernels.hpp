@@ -1600,7 +1600,8 @@ __global__ __launch_bounds__(WG) void k_finish(EncodeParams P, EncodeBatch Wk, c
                 } else {
                     base += block_sum_u64(part, scratch);
                 }
-                base = uniform_u64(base);
+                if constexpr (kUnits)
+                    base = uniform_u64(base);
                 summed = true;
             }
             // a bucket's words are written if all of them fit
