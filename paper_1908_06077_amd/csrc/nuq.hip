@@ -342,7 +342,8 @@ uint32_t team_rec_cap(const EncodeParams &P, double l1)
     if (TEAM > 16 || bucket <= 256u)
         return std::min(kKept, bucket <= 1024u ? bucket : 1024u);
     constexpr uint32_t kGroups = MODE == 2 ? 6u : 8u;
-    const uint32_t usual = std::min(std::min(kKept, bucket), room(kGroups)), most = std::min(std::min(kKept, bucket), room(kGroups - 1u));
+    const uint32_t useful = std::min(kKept, bucket);
+    const uint32_t usual = std::min(useful, room(kGroups)), most = std::min(useful, room(kGroups - 1u));
     const double mean = expected_nonzeros(bucket, l1, P.norm_linf), sd = std::sqrt(mean * (1.0 - mean / bucket));
     const bool beyond = mean + 3.0 * sd + (P.norm_linf ? bucket / 16u : 0u) > usual;
     return beyond && mean + 1.5 * sd <= most ? most : usual;
@@ -371,7 +372,7 @@ bool bucket_grid(uint64_t nb, uint32_t K, dim3 &grid)
     return true;
 }
 
-// Offsets and gather: lengths and staging slots of K workers into their bit_off and words.
+// Offsets and gather: lengths and staged strings of K workers into their bit_off and words.
 template <uint32_t FB, uint32_t WG>
 int launch_finish_as(const EncodeParams &P, const EncodeBatch &Wk, uint32_t K, const uint64_t *prefix, uint64_t nchunks,
                      uint32_t groups, uint32_t unit_shift, hipStream_t st)
@@ -920,7 +921,8 @@ int nuq_quantize_encode_batch(uint32_t K, const float *const *v, const uint64_t 
 // (0.3 M coordinates, exponential levels at s = 7, both directions 65.8 -> 69.5 with tiles of 4096) and the result is
 // written: what the other updates read takes registers for twice the coordinates, which leaves a wave per SIMD (17 M
 // coordinates of two messages in buckets of 512, momentum 52 -> 67 us; 10 M of one in buckets of 1024 28 -> 34).
-static uint32_t decode_tile_coords(uint32_t K, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride, bool table, uint32_t update)
+static uint32_t decode_tile_coords(uint32_t K, uint64_t d, uint32_t bucket, uint32_t s, uint32_t sync_stride, bool table,
+                                   uint32_t update)
 {
     if (!nuq_num_sync(bucket, sync_stride))
         return kTileCoords;

@@ -426,8 +426,8 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
 // ----------------------------------------------------------------- coding phase
 //
 // On entry the team's bytes (FlagBytes) are in LDS (qb32, bytes at or beyond the bucket's length say "zero") and a
-// barrier has been passed.  Produces the bucket's bit string in LDS, copies it to the bucket's staging slot, writes its
-// index entries.  Every thread of the workgroup must call it (it contains barriers).
+// barrier has been passed.  Produces the bucket's bit string in LDS, copies it to the staging area, writes its index entries.
+// Every thread of the workgroup must call it (it contains barriers).
 //
 // Steps: (1) every thread finds the nonzeros of its contiguous chunk and the team compacts their indices into `rec` (a
 // prefix sum gives the ranks); (2) the records are dealt out evenly, a thread takes a contiguous run of them, looks up
@@ -439,10 +439,12 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG) void k_quantize(EncodeParams P
 // nonzeros and `out_cap` words, sized for the usual case, and a bucket that exceeds one of them takes a slower way:
 //   nonzeros fit, bits fit  : as above
 //   nonzeros fit, bits don't: the same, but records are OR-ed into the (zeroed) staging slot in global memory (teams of several
-//                             waves; the others' buffer holds the longest string there is)
+//                             waves; the others' buffer holds the longest string of as many records as are listed)
 //   nonzeros don't fit      : Unlisted
 //
-// The kernel is bound by vector issue, so what counts here is instructions per record and per coordinate.
+// What bounds the kernel is dependent chains with too few waves beside them, then vector issue: eight workgroups per CU instead of
+// five took 4 x 1.56 G coordinates in buckets of 512 from 6.65 to 6.00 ms, a quantizer of fewer and cheaper instructions nothing
+// (8 x 25.6 M in buckets of 8192 1.002 times as fast).
 
 // ERC of N (Alg. 2): groups binary(N), binary(bits(N) - 1), ... while the value is at least 2, last computed first, one 0.
 struct ErcWord {
@@ -777,9 +779,9 @@ __device__ __forceinline__ void refuse_bucket(const EncodeParams &P, const Encod
 
 // Buckets with more nonzeros than the list holds: every thread codes the records of its own chunk, in two passes; the bit
 // string is assembled over the list's and the buffer's words together (the two regions are adjacent: seven tenths of the
-// worst case for large buckets, more than all of it for small teams' buckets).  A string that does not fit there takes a
-// second window over the same words.  OR-ed into the slot in global memory, as it was, the atomics were the whole time: 4 x 8 M
-// coordinates at 9 bits each, buckets of 3000 1103 -> 142 us, of 8192 540 -> 139, of 32768 605 -> 206.
+// worst case), that of a small team's bucket in the list's place, which has room for a slot's words.  A string that does not fit
+// there takes a second window over the same words.  OR-ed into the slot in global memory, as it was, the atomics were the whole
+// time: 4 x 8 M coordinates at 9 bits each, buckets of 3000 1103 -> 142 us, of 8192 540 -> 139, of 32768 605 -> 206.
 template <int TEAM, bool kCaller>
 struct Unlisted {
     const EncodeParams &P;
@@ -1418,12 +1420,12 @@ __global__ __launch_bounds__(TeamGeom<TEAM>::kWG, kSmallTeam<TEAM> && MODE == 0 
     encode_from_lds<TEAM, VPT, MODE == 1>(P, O, active, b, L);
 }
 
-// ------------------------------------------------- offsets and gather of the slots
+// ------------------------------------------------- offsets and gather of the strings
 //
 // wc_b = ceil(len_b / 32) words per bucket; start word of bucket b = sum of wc over the worker's
 // earlier buckets; bit_off[b+1] = 32 * start_b + len_b.  One "finish" kernel per batch: a
 // workgroup owns FB consecutive buckets of one worker, sums the words before them, writes their offsets and copies their
-// staging slots to their place in `words`.
+// strings from the staging area to their place in `words`.
 //
 // The encoder leaves len_b in bit_off[b+1] and, per workgroup of its own (1, 4, 8 or 16 buckets: a unit), the words of its
 // buckets in `units`: the words before a group are a sum over units, taken directly or, for more than 8192 units, from

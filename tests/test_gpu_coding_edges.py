@@ -160,9 +160,9 @@ def test_strings_longer_than_slots(g, n, S, s):
 
 
 @pytest.mark.parametrize("s", [6, 7, 8, 14])
-@pytest.mark.parametrize("n,nb,S", [(17, 40, 0), (64, 19, 64), (200, 21, 64), (256, 33, 128), (300, 18, 64), (400, 19, 256), (512, 21, 64),
-                                    (600, 9, 128), (600, 5200, 128), (768, 5200, 256), (1000, 7, 64), (1000, 5200, 256), (1024, 6, 1024),
-                                    (2000, 7, 64)])
+@pytest.mark.parametrize("n,nb,S", [(17, 40, 0), (64, 19, 64), (200, 21, 64), (256, 33, 128), (300, 18, 64), (400, 19, 256),
+                                    (512, 21, 64), (600, 9, 128), (600, 5200, 128), (768, 5200, 256), (1000, 7, 64),
+                                    (1000, 5200, 256), (1024, 6, 1024), (2000, 7, 64)])
 def test_longest_strings(g, n, nb, S, s):
     """Several buckets per workgroup, strings up to the longest there are: no zero and the top level (longer than the bytes they
     are made from, where levels need seven bits), every other coordinate, as many nonzeros as the list holds at the longest

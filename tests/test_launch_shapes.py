@@ -27,8 +27,8 @@ def test_longest_string_of_a_listed_bucket(n):
 
 
 @pytest.mark.parametrize("law", ["gauss", "heavy"])
-@pytest.mark.parametrize("n,levels", [(260, range(1, 15)), (300, range(1, 15)), (350, range(1, 15)), (400, range(1, 6)), (450, range(1, 6)),
-                                      (500, range(1, 5)), (512, range(1, 5)), (768, range(1, 15)), (780, range(1, 15)),
+@pytest.mark.parametrize("n,levels", [(260, range(1, 15)), (300, range(1, 15)), (350, range(1, 15)), (400, range(1, 6)),
+                                      (450, range(1, 6)), (500, range(1, 5)), (512, range(1, 5)), (768, range(1, 15)), (780, range(1, 15)),
                                       (832, range(1, 15)), (1000, range(1, 15))])
 def test_lists_hold_what_buckets_have(n, levels, law):
     rng = np.random.default_rng(n)
@@ -48,13 +48,15 @@ def test_lists_hold_what_buckets_have(n, levels, law):
 
 @pytest.mark.parametrize("n", [12288, 12289, 14336, 15000, 16000, 16384, 20000])
 def test_lists_of_large_buckets(n):
-    """A quarter of the bucket where nonzeros are anyone's guess (bytes) or five workgroups leave room for it, little less elsewhere."""
+    """A quarter of the bucket where nonzeros are anyone's guess (bytes) or five workgroups leave room for it, little less
+    elsewhere."""
     for s in range(1, 15):
         for S in (0, 64, 256):
             assert nuq.nuq_encode_shape(1, 1, 9 * n, n, s, S)[1] == n // 4
             listed, buffer = nuq.nuq_encode_shape(0, 1, 9 * n, n, s, S)[1:3]
             assert listed == n // 4 or (n > 15000 and n // 4 - 290 < listed < n // 4)
-            words = ((n + 1023) // 1024) * 256 + (listed + 1) // 2 + buffer + max(256, nuq.nuq_num_sync(n, S)) - (-n // 2048) + 66 + 512
+            index = max(256, nuq.nuq_num_sync(n, S)) - (-n // 2048) + 2
+            words = ((n + 1023) // 1024) * 256 + (listed + 1) // 2 + buffer + index + 64 + 512
             assert n <= 12288 or n > 16384 or 5 * (-(-4 * words // 1280)) <= 128                   # of 128 pieces of 1280 bytes
 
 
