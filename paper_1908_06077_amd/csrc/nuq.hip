@@ -291,13 +291,16 @@ bool narrow_teams(uint64_t nb, uint32_t K, uint32_t bucket, uint32_t s, bool lin
 // strings stay in the last-level cache; packing them at 4 bits 61 -> 57; 20 M in buckets of 1024 a step 169 -> 157; 40 M in a step 303
 // -> 279; one encode of 200 M 200 -> 194, of 800 M 787 -> 755, of 1024 759 -> 713.  Beyond 1 G coordinates in all it no longer helps,
 // for a reason that no measurement here has shown (far more than any cache holds on either side): 1 x 1.5 G 1430 and 1456 us, 4 x 0.4
-// G 1540 and 1566, 4 x 0.8 G 3129 and 3253, in buckets of 1024 1320 and 1331, 1430 and 1427, 2847 and 2880.  Small calls are the same
-// either way (8 x 0.3 M 14.6 and 14.7), and so is one gradient encoded again and again, as the variance diagnostic does, though plain
-// loads may find it in the cache (12 M in buckets of 512 131.3 and 133.3 a draw, of 1024 116.7 and 115.6).
+// G 1540 and 1566, 4 x 0.8 G 3129 and 3253, in buckets of 1024 1320 and 1331, 1430 and 1427, 2847 and 2880.  Gradients of up to
+// 32 MB in all are found in the eight L2 caches where they have just been written or encoded before: 4 x 1.5 M in buckets of 512 15.1
+// and 16.0, of 1024 14.6 and 15.5, a step 29.3 and 30.2; at 8 M coordinates an encode alone still gains with plain loads (17.3 and
+// 17.8), a step, whose parameters go through these caches too, no longer (34.0 and 33.1), hence 7 M.  Beyond that one gradient
+// encoded again and again, as the variance diagnostic does, takes the same either way (12 M in buckets of 512 131.3 and 133.3 us a
+// draw, of 1024 116.7 and 115.6).
 // (Buckets of 256: 4 x 5 M 32.9 and 33.8; 4 x 20 M, a step 207 and 213.)
 uint32_t stream_loads(uint64_t d, uint32_t K)
 {
-    return d <= (1ull << 30) / K ? 1u : 0u;
+    return d > 7'000'000u / K && d <= (1ull << 30) / K ? 1u : 0u;
 }
 
 // Nonzeros that the LDS list of a team of the encoders holds (k_encode<TEAM, ., MODE>; l1, linf: its first level and norm).
